@@ -239,9 +239,11 @@ sq_status sq_quantize_act_geglu(const sq_layer* layer, const void* h, sq_dtype h
  *   y[m][n] = sum_ks seg_scale[ks][ns(n)] wscale[ks][n] ( s_pos[ks] acc_+ + s_neg[ks] acc_- ) + bias[n]
  * evaluated in fp32 and stored as fp32 or bf16 (round-half-to-even).  Activation and weight tiles
  * are read once and feed both accumulator sets.  Kernel selection: M <= 32 with K and the K-segment boundaries
- * multiples of 128 runs the weight-streaming (bandwidth-bound) kernel; M = 33..64 the MFMA tile kernel with 64-row
- * tiles (K and the boundaries multiples of 64), else the K-splitting skinny kernel; larger M the MFMA tile kernel;
- * shapes none of them takes (unaligned K or boundaries) a plain one-thread-per-output kernel.
+ * multiples of 128 runs the weight-streaming (bandwidth-bound) kernel; M > 32 with the same alignment, at most eight
+ * K-segments and no seg_scale, whose output one round of 64 x 64, 64 x 128 or 128 x 64 tiles covers, tiles whose waves split
+ * K; other M = 33..64 the MFMA tile kernel with 64-row tiles (K and the boundaries multiples of 64), else the K-splitting
+ * skinny kernel; larger M the MFMA tile kernel; shapes none of them takes (unaligned K or boundaries) a plain
+ * one-thread-per-output kernel.
  *   xq dev int8 [M][K] (from sq_quantize_act);  wq dev int8 [N][K];  wscale dev fp32 [S][N];
  *   bias dev fp32 [N] or NULL;  y dev [M][N] of y_dt.
  */

@@ -98,16 +98,20 @@ sq_status run_gemm(const sq_layer* L, const int8_t* xq, const int8_t* wq,
   if (path == 1 && !sq::mfma_supported(a, tb)) return SQ_ERR_UNSUPPORTED;
   if (path < 0) {
     // up to two 16-row tiles of tokens: the weight-stream kernel (measured 5.9 TB/s on wide layers); three or four
-    // tiles: the MFMA tile kernel with 64-row tiles is as fast or faster; the K-splitting skinny kernel serves
+    // tiles: tile kernels are as fast or faster; the K-splitting skinny kernel serves
     // the layers whose K-segments are only 64-aligned
+    // 33 rows and more: the K-splitting tiles where one round of them covers the output, else the tile kernel
     if (a.M <= 32 && sq::stream_supported(a, tb)) path = 3;
+    else if (a.M > 32 && g_gemm_variant < 0 && sq::ksplit_pick(a, tb) >= 0) path = 4;
     else if (a.M <= 64 && a.M > 32 && sq::mfma_supported(a, tb)) path = 1;
     else if (sq::skinny_supported(a, tb)) path = 2;
     else if (sq::mfma_supported(a, tb)) path = 1;
     else path = 0;
   }
   hipError_t e;
-  if (path == 3) {
+  if (path == 4) {
+    e = sq::launch_seglinear_ksplit(a, tb, mode, sq::ksplit_pick(a, tb), st);
+  } else if (path == 3) {
     e = sq::launch_seglinear_stream(a, tb, mode, sq::device_cus(), st);
   } else if (path == 2) {
     e = sq::launch_seglinear_skinny(a, tb, mode, st);
@@ -132,7 +136,7 @@ bool w4_layout_ok(const sq_layer* L) {
 }
 
 // Dynamic per-token steps: the weight-stream kernel (M <= 64, at most 8 K-segments: its step table is 4 KiB of LDS), the
-// MFMA tile kernel (8-bit weights, its alignment rules) or the one-thread-per-output kernel (any shape, 4-bit weights at
+// K-splitting tiles or the MFMA tile kernel (8-bit weights, its alignment rules) or the one-thread-per-output kernel (any shape, 4-bit weights at
 // large M).
 sq_status run_gemm_dynamic(const sq_layer* L, const int8_t* xq, const float* tok_steps, const void* wq, int w_bits,
                            const float* wscale, const float* bias, void* y, sq::OutMode mode, void* stream) {
@@ -159,6 +163,8 @@ sq_status run_gemm_dynamic(const sq_layer* L, const int8_t* xq, const float* tok
   if (g_force_path != 0 && g_force_path != 1 && stream_ok) {
     e = w_bits == 4 ? sq::launch_seglinear_stream_w4(a, tb, mode, sq::device_cus(), st)
                     : sq::launch_seglinear_stream(a, tb, mode, sq::device_cus(), st);
+  } else if (g_force_path < 0 && g_gemm_variant < 0 && w_bits == 8 && sq::ksplit_pick(a, tb) >= 0) {
+    e = sq::launch_seglinear_ksplit(a, tb, mode, sq::ksplit_pick(a, tb), st);
   } else if (g_force_path != 0 && mfma_ok) {           // large M, 8-bit weights: the MFMA tile kernel with per-row steps
     int v = g_gemm_variant >= 0 ? g_gemm_variant : sq::mfma_pick_variant(a, tb, mode);
     e = sq::launch_seglinear_mfma(a, tb, mode, v, st);

@@ -93,6 +93,12 @@ hipError_t launch_seglinear_mfma(GemmArgs a, const GemmTable& tb, OutMode mode, 
 int mfma_fp8_pick_variant(const GemmArgs& a, const GemmTable& tb);
 hipError_t launch_seglinear_mfma_fp8(GemmArgs a, const GemmTable& tb, OutMode mode, int variant, hipStream_t st);
 
+// seglinear_ksplit.hip : layers with few output tiles, the waves of a workgroup split K.  K and K-segment boundaries
+// % 128 == 0, at most eight K-segments, no seg_scale.
+// ksplit_pick: its tile for this layer, or -1 where the tile kernel is the faster one (or the only one).
+int ksplit_pick(const GemmArgs& a, const GemmTable& tb);
+hipError_t launch_seglinear_ksplit(GemmArgs a, const GemmTable& tb, OutMode mode, int tile, hipStream_t st);
+
 // seglinear_skinny.hip : M <= 64, weight-streaming kernel.  Same alignment needs as the MFMA kernel.
 bool skinny_supported(const GemmArgs& a, const GemmTable& tb);
 hipError_t launch_seglinear_skinny(const GemmArgs& a, const GemmTable& tb, OutMode mode, hipStream_t st);

@@ -1357,6 +1357,54 @@ DYNCASES = [
 ]
 
 
+# One round of small tiles (64 x 64, 64 x 128 where that is more than 256 of them, then 128 x 64), four waves splitting K: the
+# edges of the tiles, 1, 2, ring - 1, ring, ring + 1 and more stages of 128 bytes of K (the ring holds 9 or 6), odd and even
+# numbers of them, single and dual K-segments in either order, ragged and unaligned columns.
+KSPLIT = [
+    dict(M=33, K=128, N=1, kseg=[0, 128], dual=[1], dt="f32"),
+    dict(M=64, K=256, N=384, kseg=[0, 128, 256], dual=[1, 1], dt="f32"),
+    dict(M=65, K=1024, N=63, kseg=[0, 1024], dual=[0], dt="bf16"),
+    dict(M=128, K=1152, N=66, kseg=[0, 1152], dual=[1], dt="bf16"),
+    dict(M=129, K=1280, N=64, kseg=[0, 1280], dual=[1], dt="f32"),
+    dict(M=333, K=2816, N=320, kseg=[0, 384, 2816], dual=[0, 1], dt="bf16"),
+    dict(M=70, K=1792, N=100, kseg=[0, 1280, 1408, 1792], dual=[1, 0, 0], dt="f32"),
+    dict(M=100, K=3840, N=72, kseg=[0, 3840], dual=[0], dt="f32"),
+    dict(M=1100, K=128, N=1000, kseg=[0, 128], dual=[1], dt="bf16"),
+    dict(M=1090, K=768, N=1010, kseg=[0, 256, 768], dual=[1, 0], dt="bf16"),
+    dict(M=1089, K=896, N=996, kseg=[0, 896], dual=[0], dt="f32"),
+    dict(M=9000, K=384, N=130, kseg=[0, 384], dual=[1], dt="bf16"),
+    dict(M=8999, K=640, N=127, kseg=[0, 128, 640], dual=[0, 0], dt="f32"),
+]
+
+
+@pytest.mark.parametrize("case", KSPLIT, ids=lambda c: "%dx%dx%d_S%d" % (c["M"], c["K"], c["N"], len(c["dual"])))
+def test_seglinear_ksplit(oracle, case):
+    """The K-splitting tiles against the oracle: sums bit-exact, outputs within the fp32 tolerance, per-token steps too."""
+    import torch
+
+    g = _gpu()
+    M, K, N = case["M"], case["K"], case["N"]
+    w = wl.random_layer(M, K, N, case["kseg"], [0, N], case["dual"], seed=M + K + N, x_dtype="bf16", act="gelu", with_bias=M % 2 == 0)
+    gl = g.GpuLayer(w)
+    gl.quantize_weight()
+    gl.quantize_act()
+    r = oracle.seglinear(w.x, w.w, w.kseg_off, w.nseg_off, w.dual, w.s_pos, w.s_neg, None, w.bias)
+    tol = RTOL * float(np.abs(r.y32).max())
+    ap, an = gl.debug_acc()
+    assert np.array_equal(ap, r.acc_pos) and np.array_equal(an, r.acc_neg)
+    if case["dt"] == "f32":
+        assert float(np.abs(gl.seglinear("f32").astype(np.float64) - r.y32.astype(np.float64)).max()) <= tol
+    else:
+        g.check_bf16_against(gl.seglinear("bf16"), r.y32, wl.f32_to_bf16_bits(r.y32), tol)
+    if M > 64:
+        tok = torch.full((2, M, w.S), float("nan"), dtype=torch.float32, device=g.DEV)
+        sq.sq_quantize_act_dynamic(gl.layer, gl.x, gl.xq, tok)
+        y = torch.full((M, N), float("nan"), dtype=torch.float32, device=g.DEV)
+        sq.sq_seglinear_dynamic(gl.layer, gl.xq, tok, gl.wq, 8, gl.wscale, gl.bias, y)
+        rd = oracle.seglinear_dynamic(w.x, w.w, w.kseg_off, w.nseg_off, w.dual, None, w.bias, wbits=8)
+        assert float(np.abs(y.cpu().numpy().astype(np.float64) - rd.y32.astype(np.float64)).max()) <= RTOL * float(np.abs(rd.y32).max())
+
+
 @pytest.mark.parametrize("case", DYNCASES)
 def test_seglinear_dynamic(oracle, case):
     """Per-token steps: codes and steps bit-exact against the oracle, outputs within the fp32 tolerance, for 8-bit and
