@@ -50,6 +50,31 @@ def test_quantize_weight(oracle, shape, w_dtype):
     assert np.array_equal(wq, rq)
 
 
+@pytest.mark.parametrize("w_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("longest", [128, 1024, 1152, 2048, 2176, 4096, 4224, 8192, 8320, 16384, 16512, 32768, 32896])
+def test_quantize_weight_rows(oracle, longest, w_dtype):
+    """Row lengths around the limits of the register-resident quantizer (a wave or a workgroup per row segment, 4 / 8 / 16 loads
+    per thread; 16384 fp32 or 32768 bf16 columns, then the two-read kernel): 8- and 4-bit codes and steps, N not a multiple of 16."""
+    import torch
+
+    g = _gpu()
+    K, N = longest + 128, 19
+    w = wl.random_layer(2, K, N, [0, 128, K], [0, N], [1, 1], seed=longest, w_std=0.05)
+    w.w[3, :] = 0.0
+    w.w[5, 130] = -1e30
+    if w_dtype == "bf16":
+        w.w = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(w.w))
+    gl = g.GpuLayer(w, w_dtype=w_dtype)
+    wq, ws = gl.quantize_weight()
+    rq, rs = oracle.quantize_weight(w.w, w.kseg_off)
+    assert np.array_equal(ws.view(np.uint32), rs.view(np.uint32)) and np.array_equal(wq, rq)
+    w4 = torch.full((32 * K // 2,), 0x5A, dtype=torch.uint8, device=g.DEV)
+    sq.sq_quantize_weight_w4(gl.layer, gl.wt, w4, gl.wscale)
+    r4, rs4 = oracle.quantize_weight_w4(w.w, w.kseg_off)
+    assert np.array_equal(gl.wscale.cpu().numpy().view(np.uint32), rs4.view(np.uint32))
+    assert np.array_equal(w4.cpu().numpy(), oracle.pack_w4(r4))
+
+
 @pytest.mark.parametrize("case", [
     dict(M=9, K=64, kseg=[0, 64], dual=[1], x_dtype="bf16"),
     dict(M=70, K=512, kseg=[0, 128, 512], dual=[0, 1], x_dtype="bf16"),
@@ -553,6 +578,39 @@ def test_calibrate_act_percentile(oracle, case):
         torch.cuda.synchronize()
         assert np.array_equal(amax.cpu().numpy().view(np.uint32), np.stack([r2[2], r2[3]]).view(np.uint32)), (p, "second batch")
         assert np.array_equal(steps.cpu().numpy().view(np.uint32), np.stack([r2[0], r2[1]]).view(np.uint32))
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", [(1, [0, 8]), (128, [0, 8, 24, 64]), (1025, [0, 8]), (257, [0, 1000, 1032]), (1001, [0, 1024, 4096])],
+                         ids=lambda s: "%dx%s" % (s[0], "_".join(map(str, s[1][1:]))))
+def test_calibration_pass_shares(oracle, shape, dt):
+    """The aligned calibration passes deal 8-element chunks to workgroups of 1024 threads: fewer chunks than threads, one more
+    than a workgroup's, segments of one chunk next to wide ones, ragged ends; half the values zero or infinite in places."""
+    import torch
+
+    g = _gpu()
+    M, kseg = shape
+    K, S = kseg[-1], len(kseg) - 1
+    rng = np.random.default_rng(M + K)
+    x = (rng.standard_normal((M, K)) * np.exp(rng.uniform(-4, 4, size=(M, K)))).astype(np.float32)
+    x[rng.random((M, K)) < 0.5] = 0.0
+    x[M // 2, :] = -0.0
+    if M > 200:
+        x[3, K - 1] = np.inf
+    x = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(x)) if dt == "bf16" else x
+    dual = [(s + 1) % 2 for s in range(S)]
+    xd = torch.from_numpy(x).to(g.DEV)
+    xd = xd.to(torch.bfloat16) if dt == "bf16" else xd
+    layer = sq.Layer(M, K, 16, kseg, [0, 16], dual)
+    amax, steps = (torch.full((2, S), float("nan"), dtype=torch.float32, device=g.DEV) for _ in range(2))
+    sq.sq_calibrate_act(layer, xd, amax, steps)
+    r = oracle.calibrate_act(x, np.asarray(kseg, np.int32), np.asarray(dual, np.uint8))
+    assert np.array_equal(amax.cpu().numpy(), np.stack([r[2], r[3]])) and np.array_equal(steps.cpu().numpy(), np.stack([r[0], r[1]]))
+    ws = torch.full((sq.sq_calibrate_workspace_bytes(),), 0x5A, dtype=torch.uint8, device=g.DEV)
+    for p in (0.9999, 0.8, 0.3, 1.0):
+        sq.sq_calibrate_act_percentile(layer, xd, p, amax, steps, ws)
+        r = oracle.calibrate_act_percentile(x, np.asarray(kseg, np.int32), np.asarray(dual, np.uint8), p)
+        assert np.array_equal(amax.cpu().numpy(), np.stack([r[2], r[3]])), p
 
 
 WBLOCK = [
