@@ -533,40 +533,36 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_kernel(const void* _
   }
 }
 
-// The same for rows of 16-element chunks (K, the K-segment boundaries multiples of 16, 16-byte aligned pointers, K <=
-// 4096 NCH): a thread keeps its NCH chunks of the row in registers between the two passes, so the row is read once
-// (at large M the rows in flight on an XCD exceed its L2 and a second read goes back to memory), the loads are 16 bytes
-// wide and streaming, the quotient is the reciprocal product of round_quotient (bit-identical to the division) and the
-// codes leave as 16-byte stores.
-template <bool BF16, int NCH>
+// The same for aligned rows (K, the K-segment boundaries multiples of 16, 16-byte aligned pointers) of at most NCH loads of
+// 16 bytes per thread: TPR threads own a row and keep it in registers between the two passes, so the row is read once
+// (at large M the rows in flight on an XCD exceed its L2 and a second read goes back to memory), the loads are streaming and
+// the quotient is the reciprocal product of round_quotient (bit-identical to the division).  With a workgroup and 16
+// elements a thread for every row, a row of 1536 left 160 of 256 threads without work.
+template <bool BF16, int TPR, int NCH>
 __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const void* __restrict__ x, int8_t* __restrict__ xq,
                                                                         float* __restrict__ tok_steps, int M, int K,
                                                                         const ActTable tb, const float qmax) {
-  constexpr int NL = BF16 ? 2 : 4;                       // 16-byte loads per chunk
-  const int m = blockIdx.x;
+  constexpr int CE = BF16 ? 8 : 4;                       // elements of a 16-byte load
+  constexpr int RPW = 256 / TPR;                         // rows of the workgroup
+  const int t = threadIdx.x % TPR, wrow = threadIdx.x / TPR;
+  const int mr = blockIdx.x * RPW + wrow;
+  const int m = mr < M ? mr : M - 1;                     // rows beyond M do the last one again: same values, same places
   const size_t row = (size_t)m * K;
-  const int nch = K >> 4;
   __shared__ float red[2][4];
-  __shared__ float stp[SQ_MAX_SEGMENTS][4];              // s_+, s_-, and their reciprocals (NaN: always divide)
-  v4i raw[NCH][NL];
+  __shared__ float stp[RPW][SQ_MAX_SEGMENTS][4];         // s_+, s_-, and their reciprocals (NaN: always divide)
+  v4i raw[NCH];
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
-    const int c = threadIdx.x + 256 * j;
-#pragma unroll
-    for (int l = 0; l < NL; ++l) raw[j][l] = (v4i)(0);
-    if (c < nch) {
-      const v4i* src = BF16 ? reinterpret_cast<const v4i*>(reinterpret_cast<const uint16_t*>(x) + row + 16 * (size_t)c)
-                            : reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(x) + row + 16 * (size_t)c);
-#pragma unroll
-      for (int l = 0; l < NL; ++l) raw[j][l] = __builtin_nontemporal_load(src + l);
-    }
+    const int col = (t + TPR * j) * CE;
+    raw[j] = (v4i)(0);
+    if (col < K)
+      raw[j] = BF16 ? __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const uint16_t*>(x) + row + col))
+                    : __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(x) + row + col));
   }
-  auto value = [&](const int j, const int e) __attribute__((always_inline)) -> float {   // element e of chunk j (constants)
-    if (BF16) {
-      const uint32_t u = (uint32_t)raw[j][e >> 3][(e >> 1) & 3];
-      return __uint_as_float((e & 1) ? (u & 0xFFFF0000u) : (u << 16));
-    }
-    return __int_as_float(raw[j][BF16 ? 0 : (e >> 2)][e & 3]);
+  auto value = [&](const int j, const int e) __attribute__((always_inline)) -> float {   // element e of load j (constants)
+    if (!BF16) return __int_as_float(raw[j][e & 3]);
+    const uint32_t u = (uint32_t)raw[j][e >> 1];
+    return __uint_as_float((e & 1) ? (u & 0xFFFF0000u) : (u << 16));
   };
   for (int ks = 0; ks < tb.S; ++ks) {
     const int k0 = tb.kseg_off[ks], k1 = tb.kseg_off[ks + 1];
@@ -582,20 +578,18 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
       u16x2 hi_u = {0, 0};
 #pragma unroll
       for (int j = 0; j < NCH; ++j) {
-        const int col = (threadIdx.x + 256 * j) << 4;
+        const int col = (t + TPR * j) * CE;
         if (col < K && col >= k0 && col < k1) {
 #pragma unroll
-          for (int l = 0; l < 2; ++l)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              const int w = raw[j][BF16 ? l : 0][d];
-              if (dual) {
-                hi_s = __builtin_elementwise_max(hi_s, __builtin_bit_cast(s16x2, w));
-                hi_u = __builtin_elementwise_max(hi_u, __builtin_bit_cast(u16x2, w));
-              } else {
-                hi_u = __builtin_elementwise_max(hi_u, __builtin_bit_cast(u16x2, w & 0x7FFF7FFF));
-              }
+          for (int d = 0; d < 4; ++d) {
+            const int w = raw[j][d];
+            if (dual) {
+              hi_s = __builtin_elementwise_max(hi_s, __builtin_bit_cast(s16x2, w));
+              hi_u = __builtin_elementwise_max(hi_u, __builtin_bit_cast(u16x2, w));
+            } else {
+              hi_u = __builtin_elementwise_max(hi_u, __builtin_bit_cast(u16x2, w & 0x7FFF7FFF));
             }
+          }
         }
       }
       const uint32_t us = (uint32_t)(hi_s[0] > hi_s[1] ? hi_s[0] : hi_s[1]);
@@ -609,10 +603,10 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
     } else {
 #pragma unroll
       for (int j = 0; j < NCH; ++j) {
-        const int col = (threadIdx.x + 256 * j) << 4;
+        const int col = (t + TPR * j) * CE;
         if (col < K && col >= k0 && col < k1) {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
+          for (int e = 0; e < CE; ++e) {
             const float v = value(j, e);
             if (dual) {
               mp = __builtin_fmaxf(mp, v);
@@ -629,40 +623,45 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
       mp = __builtin_fmaxf(mp, __shfl_xor(mp, off, 64));
       mn = __builtin_fmaxf(mn, __shfl_xor(mn, off, 64));
     }
-    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = mp; red[1][threadIdx.x >> 6] = mn; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      mp = __builtin_fmaxf(__builtin_fmaxf(red[0][0], red[0][1]), __builtin_fmaxf(red[0][2], red[0][3]));
-      mn = __builtin_fmaxf(__builtin_fmaxf(red[1][0], red[1][1]), __builtin_fmaxf(red[1][2], red[1][3]));
+    if (TPR > 64) {
+      if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = mp; red[1][threadIdx.x >> 6] = mn; }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < TPR / 64; ++i) {
+        mp = __builtin_fmaxf(mp, red[0][wrow * (TPR / 64) + i]);
+        mn = __builtin_fmaxf(mn, red[1][wrow * (TPR / 64) + i]);
+      }
+    }
+    if (t == 0) {
       const float sp = (mp == 0.0f) ? 1.0f : mp / qmax, sn = (mn == 0.0f) ? 1.0f : mn / qmax;
-      stp[ks][0] = sp;
-      stp[ks][1] = sn;
-      stp[ks][2] = (sp >= 1e-30f && sp <= 1e30f) ? 1.0f / sp : __builtin_nanf("");
-      stp[ks][3] = (sn >= 1e-30f && sn <= 1e30f) ? 1.0f / sn : __builtin_nanf("");
+      stp[wrow][ks][0] = sp;
+      stp[wrow][ks][1] = sn;
+      stp[wrow][ks][2] = (sp >= 1e-30f && sp <= 1e30f) ? 1.0f / sp : __builtin_nanf("");
+      stp[wrow][ks][3] = (sn >= 1e-30f && sn <= 1e30f) ? 1.0f / sn : __builtin_nanf("");
       tok_steps[(size_t)m * tb.S + ks] = sp;
       tok_steps[((size_t)M + m) * tb.S + ks] = sn;
     }
-    __syncthreads();                                      // red is reused by the next segment; stp is complete after the last
+    if (TPR > 64) __syncthreads();                        // red is reused by the next segment; stp is complete after the last
 #pragma unroll
-    for (int j = 0; j < NCH; ++j)                         // keep the row as loaded: widened copies held across the passes
-#pragma unroll
-      for (int l = 0; l < NL; ++l) asm volatile("" : "+v"(raw[j][l]));   // would cost half the occupancy
+    for (int j = 0; j < NCH; ++j) asm volatile("" : "+v"(raw[j]));   // keep the row as loaded: widened copies held across the
+  }                                                                  // passes would cost half the occupancy
+  if (TPR == 64) {                                        // lane 0's steps, to this wave's other lanes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
-    const int c = threadIdx.x + 256 * j;
-    if (c >= nch) continue;
-    const int col = c << 4;
+    const int col = (t + TPR * j) * CE;
+    if (col >= K) continue;
     int ks = 0;
+    bool dual = tb.dual[0] != 0;
     for (int sg = 1; sg < tb.S; ++sg)
-      if (col >= tb.kseg_off[sg]) ks = sg;
-    bool dual = false;
-    for (int sg = 0; sg < tb.S; ++sg)
-      if (sg == ks) dual = tb.dual[sg] != 0;
-    const float sp = stp[ks][0], sn = stp[ks][1], ip = stp[ks][2], in = stp[ks][3];
-    v4i out;
+      if (col >= tb.kseg_off[sg]) { ks = sg; dual = tb.dual[sg] != 0; }
+    const float sp = stp[wrow][ks][0], sn = stp[wrow][ks][1], ip = stp[wrow][ks][2], in = stp[wrow][ks][3];
+    int out[2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < CE / 4; ++q) {
       int code[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -672,7 +671,8 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
       }
       out[q] = (int)pack4(code[0], code[1], code[2], code[3]);
     }
-    *reinterpret_cast<v4i*>(xq + row + col) = out;
+    if (BF16) *reinterpret_cast<v2i*>(xq + row + col) = (v2i){out[0], out[1]};
+    else *reinterpret_cast<int*>(xq + row + col) = out[0];
   }
 }
 
@@ -681,8 +681,19 @@ hipError_t launch_quantize_act_dynamic(const void* x, bool x_is_bf16, int8_t* xq
   bool fast = K % 16 == 0 && K <= 4096 * 8 && (reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(xq)) % 16 == 0;
   for (int s = 0; s <= tb.S; ++s) fast = fast && tb.kseg_off[s] % 16 == 0;
   if (fast) {
-#define SQ_D(B, N) hipLaunchKernelGGL((quantize_act_dynamic_fast_kernel<B, N>), dim3(M), dim3(256), 0, st, x, xq, tok_steps, M, K, tb, qmax)
-#define SQ_DN(B) do { if (K <= 4096) SQ_D(B, 1); else if (K <= 8192) SQ_D(B, 2); else if (K <= 16384) SQ_D(B, 4); else SQ_D(B, 8); } while (0)
+    // Threads per row: a workgroup and the fewest loads per thread that hold the row, except where that leaves a quarter of the
+    // threads or more without work and there are rows enough: up to 192 loads on a wave (8500 x 1536 bf16: 18.3 -> 13.6 us,
+    // fp32 on half a workgroup 22.3 -> 16.9), 257 - 384 on half a workgroup (4096 x 3072 bf16, two K-segments: 15.4 -> 14.2).
+    // Wider rows on fewer threads are slower (4096 x 4096 on a wave 18.5 us, on a workgroup 15.2), and few rows are a matter
+    // of latency (16 x 1152: a workgroup each 3.1 us, a wave each 4.6).
+    const int loads = K / (x_is_bf16 ? 8 : 4);
+#define SQ_D(B, T, N) hipLaunchKernelGGL((quantize_act_dynamic_fast_kernel<B, T, N>), dim3((M + 256 / T - 1) / (256 / T)), dim3(256), 0, st, x, xq, tok_steps, M, K, tb, qmax)
+#define SQ_DN(B) do { \
+    if (M >= 1024 && loads <= 192) SQ_D(B, 64, 3); \
+    else if (M >= 1024 && loads > 256 && loads <= 384) SQ_D(B, 128, 3); \
+    else if (loads <= 256) SQ_D(B, 256, 1); else if (loads <= 512) SQ_D(B, 256, 2); else if (loads <= 768) SQ_D(B, 256, 3); \
+    else if (loads <= 1024) SQ_D(B, 256, 4); else if (loads <= 1536) SQ_D(B, 256, 6); else if (loads <= 2048) SQ_D(B, 256, 8); \
+    else if (loads <= 4096) SQ_D(B, 256, 16); else SQ_D(B, 256, B ? 16 : 32); } while (0)
     if (x_is_bf16) SQ_DN(true); else SQ_DN(false);
 #undef SQ_DN
 #undef SQ_D

@@ -1415,6 +1415,33 @@ DYNCASES = [
 ]
 
 
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("M,loads", [(M, n) for M in (3, 1025) for n in (2, 64, 192, 196, 256, 260, 384, 388, 512, 516, 772, 1028, 1540, 2052, 4096)
+                                     if M == 3 or n < 600])
+def test_quantize_act_dynamic_rows(oracle, M, loads, dt):
+    """Row lengths around the limits of the thread counts per row (loads of 16 bytes) with few and with many, odd rows; two
+    K-segments, the last one short: codes and steps bit-exact."""
+    import torch
+
+    g = _gpu()
+    K = max(16, loads * (8 if dt == "bf16" else 4) // 16 * 16)
+    kseg, dual = ([0, K - 16, K], [1, 0]) if K > 16 else ([0, K], [1])
+    S = len(dual)
+    rng = np.random.default_rng(loads + M)
+    x = (rng.standard_normal((M, K)) * rng.uniform(0.1, 8.0, size=(M, 1))).astype(np.float32)
+    x[M // 2, :] = 0.0
+    if dt == "bf16":
+        x = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(x))
+    xd = torch.from_numpy(x).to(g.DEV)
+    xd = xd.to(torch.bfloat16) if dt == "bf16" else xd
+    xq = torch.full((M, K), 99, dtype=torch.int8, device=g.DEV)
+    tok = torch.full((2, M, S), float("nan"), dtype=torch.float32, device=g.DEV)
+    sq.sq_quantize_act_dynamic(sq.Layer(M, K, 16, kseg, [0, 16], dual), xd, xq, tok)
+    rp, rn, sp, sn = oracle.quantize_act_dynamic(x, np.asarray(kseg, np.int32), np.asarray(dual, np.uint8))
+    assert np.array_equal(xq.cpu().numpy().astype(np.int16), rp.astype(np.int16) + rn.astype(np.int16))
+    assert np.array_equal(tok.cpu().numpy().view(np.uint32), np.stack([sp, sn]).view(np.uint32))
+
+
 # One round of small tiles (64 x 64, 64 x 128 where that is more than 256 of them, then 128 x 64), four waves splitting K: the
 # edges of the tiles, 1, 2, ring - 1, ring, ring + 1 and more stages of 128 bytes of K (the ring holds 9 or 6), odd and even
 # numbers of them, single and dual K-segments in either order, ragged and unaligned columns.
