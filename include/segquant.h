@@ -202,12 +202,10 @@ sq_status sq_quantize_act(const sq_layer* layer, const void* x, sq_dtype x_dt, i
  *   h    dev, [M][K] of h_dt (pre-activation)                in
  *   act  host, int32 [S], SQ_ACT_* per K-segment             in
  *   xq   dev, int8 [M][K], polarity-merged codes             out
- *   workspace  dev or NULL.  With a workspace of at least sq_quantize_act_fused_workspace_bytes(layer) bytes
- *        (16-byte aligned, contents irrelevant on entry, owned by the caller, used only during the call; calls
- *        that share it must not overlap) a bf16 input with 16-aligned K-segments is served by table: the
- *        65536-entry map  bf16 pattern -> code  of every K-segment is filled first with the arithmetic above and
- *        the pass becomes one table read per element (same codes, HBM-bound instead of ALU-bound).  NULL, fp32
- *        input or unaligned segments: the arithmetic runs per element.
+ *   workspace  dev or NULL; where given, at least sq_quantize_act_fused_workspace_bytes(layer) bytes, 16-byte aligned.  It is
+ *        checked and otherwise unused: large bf16 inputs with 16-aligned K-segments are served by a table  bf16 pattern ->
+ *        code  that every workgroup fills on chip with the arithmetic above (same codes, HBM-bound instead of ALU-bound),
+ *        small ones, fp32 input and unaligned segments by the arithmetic per element.
  * SQ_ERR_INVALID_ARG for an unknown activation code or a workspace that is too small or misaligned; otherwise as
  * sq_quantize_act.
  */
@@ -438,8 +436,8 @@ sq_status sq_quantize_act_fp8(const sq_layer* layer, const void* x, sq_dtype x_d
 /* The same with the activation in front of the layer applied first (Sec. 4.3.1-4.3.2; App. B): xq = Q_dual(act(h)) on the
  * fp8 grid, act as for sq_quantize_act_fused (host, int32 [S], SQ_ACT_* per K-segment, must not be NULL; the fp32
  * operation sequence documented there).  workspace as for sq_quantize_act_fused (NULL, or
- * sq_quantize_act_fused_workspace_bytes(layer) device bytes, 16-byte aligned: bf16 inputs are then served by code tables,
- * same codes, two launches); SQ_ERR_INVALID_ARG for a workspace that is too small or misaligned. */
+ * sq_quantize_act_fused_workspace_bytes(layer) device bytes, 16-byte aligned; unused: code tables live on chip);
+ * SQ_ERR_INVALID_ARG for a workspace that is too small or misaligned. */
 sq_status sq_quantize_act_fp8_fused(const sq_layer* layer, const void* h, sq_dtype h_dt, const int32_t* act, uint8_t* xq,
                                     void* workspace, size_t workspace_bytes, void* stream);
 sq_status sq_seglinear_fp8(const sq_layer* layer, const uint8_t* xq, const uint8_t* wq, const float* wscale, const float* bias,

@@ -325,7 +325,7 @@ def sq_quantize_act_fp8(layer: Layer, x, xq, stream=None) -> None:
 
 def sq_quantize_act_fp8_fused(layer: Layer, h, act, xq, workspace=None, stream=None) -> None:
     """xq = Q_dual(act(h)) with E4M3 codes: h [M][K] fp32/bf16 pre-activation, act: SQ_ACT_* per K-segment (host sequence);
-    workspace: optional device byte tensor (bf16 inputs are then served by code tables)."""
+    workspace: optional device byte tensor (checked, unused: the code tables of bf16 inputs live on chip)."""
     if len(act) != layer.c.S:
         raise ValueError("one activation code per K-segment")
     codes = (C.c_int32 * max(len(act), 1))(*[int(a) for a in act])
@@ -350,13 +350,13 @@ SQ_ACT_NONE, SQ_ACT_SILU, SQ_ACT_GELU = 0, 1, 2
 
 
 def sq_quantize_act_fused_workspace_bytes(layer: Layer) -> int:
-    """Device bytes of the optional workspace of sq_quantize_act_fused (code tables, 64 KiB per K-segment)."""
+    """Device bytes that a workspace handed to sq_quantize_act_fused must have (64 KiB per K-segment)."""
     return int(load_library().sq_quantize_act_fused_workspace_bytes(C.byref(layer.c)))
 
 
 def sq_quantize_act_fused(layer: Layer, h, act, xq, workspace=None, stream=None) -> None:
     """xq = Q_dual(act(h)): h [M][K] fp32/bf16 pre-activation, act: SQ_ACT_* per K-segment (host sequence);
-    workspace: optional device byte tensor (bf16 inputs are then served by code tables)."""
+    workspace: optional device byte tensor (checked, unused: the code tables of bf16 inputs live on chip)."""
     codes = (C.c_int32 * max(len(act), 1))(*[int(a) for a in act])
     if len(act) != layer.c.S:
         raise ValueError("one activation code per K-segment")

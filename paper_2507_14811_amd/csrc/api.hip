@@ -317,14 +317,9 @@ static sq_status quantize_act_common(const sq_layer* layer, const void* x, sq_dt
   hipError_t e;
   if (geglu) {
     e = sq::launch_quantize_act_geglu(x, x_dt == SQ_BF16, xq, layer->M, layer->K, tb, sq::device_cus(), hs);
-  } else if (workspace != nullptr) {
-    if (workspace_bytes < sq::quantize_act_fused_workspace_bytes(layer->S) || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
-      return SQ_ERR_INVALID_ARG;
-    if (sq::quantize_act_lut_usable(x, x_dt == SQ_BF16, xq, layer->K, tb))
-      e = sq::launch_quantize_act_lut(x, xq, layer->M, layer->K, tb, workspace, sq::device_cus(), hs);
-    else
-      e = sq::launch_quantize_act(x, x_dt == SQ_BF16, xq, layer->M, layer->K, tb, hs);
   } else {
+    if (workspace != nullptr && (workspace_bytes < sq::quantize_act_fused_workspace_bytes(layer->S) || reinterpret_cast<uintptr_t>(workspace) % 16 != 0))
+      return SQ_ERR_INVALID_ARG;
     e = sq::launch_quantize_act(x, x_dt == SQ_BF16, xq, layer->M, layer->K, tb, hs);
   }
   return e == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
@@ -483,15 +478,10 @@ static sq_status quantize_act_fp8_common(const sq_layer* layer, const void* x, s
     }
   }
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
-  if (workspace != nullptr) {            // bf16 inputs by code table, as sq_quantize_act_fused
-    if (workspace_bytes < sq::quantize_act_fused_workspace_bytes(layer->S) || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
-      return SQ_ERR_INVALID_ARG;
-    if (sq::quantize_act_lut_usable(x, x_dt == SQ_BF16, reinterpret_cast<const int8_t*>(xq), layer->K, tb)) {
-      hipError_t el = sq::launch_quantize_act_lut(x, reinterpret_cast<int8_t*>(xq), layer->M, layer->K, tb, workspace,
-                                                  sq::device_cus(), hs, true);
-      return el == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
-    }
-  }
+  if (workspace != nullptr && (workspace_bytes < sq::quantize_act_fused_workspace_bytes(layer->S) || reinterpret_cast<uintptr_t>(workspace) % 16 != 0))
+    return SQ_ERR_INVALID_ARG;
+  if (sq::launch_quantize_act_table(x, x_dt == SQ_BF16, reinterpret_cast<int8_t*>(xq), layer->M, layer->K, tb, sq::device_cus(), hs, true))
+    return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
   hipError_t e = sq::launch_quantize_act_fp8(x, x_dt == SQ_BF16, xq, layer->M, layer->K, tb, hs);
   return e == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }

@@ -3,6 +3,8 @@
 // Both are single-pass, HBM-bandwidth-bound streams.
 #include "sq_kernels.hpp"
 
+#include <cmath>
+
 namespace sq {
 
 // ------------------------------------------------------------------------------------------------
@@ -139,111 +141,125 @@ static hipError_t launch_quantize_act_impl(const void* x, bool x_is_bf16, int8_t
 }
 
 // ------------------------------------------------------------------------------------------------
-// Fused activation + quantizer for bf16 inputs by table: a bf16 number has 65536 bit patterns, so per K-segment
-// the whole map  h -> code of Q_dual(act(h))  is a 64 KiB table.  A small kernel fills the tables with the very
-// arithmetic of the direct path (so the codes are the same to the bit); the streaming kernel keeps one segment's
-// table in LDS (two workgroups of 64 KiB per CU) and turns every element into one LDS byte read.  The direct path
-// costs ~45 ALU instructions per element and is ALU-bound at twice the HBM time; this one is a stream again.
+// Fused activation + quantizer for bf16 inputs by table.  A bf16 number has 65536 bit patterns, and the map
+// h -> code of Q_dual(act(h)) of a K-segment is a byte per pattern.  Most of it is constant: below 2^lo with 2^lo at most half
+// the smaller step (|act(x)| <= |x|: the quotient is below 1/2; fp8: 2^-10, half the smallest code) the code is 0.  So a workgroup
+// fills the patterns of [2^lo, 2^5) of its segment, 14 - 22 binades of 256, with the very arithmetic of the direct path (the
+// codes are the same to the bit), zeroes the rest, and then turns every element into one LDS byte read at the pattern
+// itself; a chunk with a magnitude of 32 or more goes through the arithmetic.  HBM-bound: the direct path costs ~50 ALU
+// instructions per element.  4608 x 15360 bf16, GELU on 12288 columns: 40.6 us in one launch (5.2 TB/s; 44 us with tables of
+// all 65536 patterns, filled by a launch of their own into a workspace and copied to LDS; direct path 66 us); 2048 x 4608:
+// 8.3 us (12.7).  One 1024-thread workgroup per compute unit; a second one, with a table of its own, changes nothing.
 // ------------------------------------------------------------------------------------------------
-constexpr int kLutBytes = 65536;
-constexpr int kLutThreads = 512;    // 256 and 1024 measured slower
+constexpr int kTabThreads = 1024;
+constexpr int kTabTop = (127 + 5) << 7;                  // first magnitude pattern beyond the table: 32.0
+constexpr int kTabBytes = 0x8000 + kTabTop;              // indexed by the 16-bit pattern, both signs
+constexpr int kTabBinades = 28;                          // widest table: beyond, the direct path
 
-// FP8: the table holds OCP E4M3 codes (nearest value of the IEEE quotient, clipped to +-448, zeros as +0) instead of int8 ones.
-template <bool FP8>
-__global__ __launch_bounds__(256) void act_lut_build_kernel(const ActTable tb, int8_t* __restrict__ lut) {
-  const int ks = blockIdx.y;
-  const uint32_t bits = blockIdx.x * 256u + threadIdx.x;                    // grid.x = 256
-  float sp = 1.0f, sn = 1.0f, ip = 1.0f, in = 1.0f;
-  bool dual = false;
-  int acode = SQ_ACT_NONE;
-  for (int s = 0; s < tb.S; ++s)
-    if (s == ks) { sp = tb.s_pos[s]; sn = tb.s_neg[s]; ip = tb.inv_pos[s]; in = tb.inv_neg[s]; dual = tb.dual[s] != 0; acode = tb.act[s]; }
-  const float v = activate(acode, __uint_as_float(bits << 16));
-  const bool ng = dual && (v < 0.0f);
-  if (FP8) lut[(size_t)ks * kLutBytes + bits] = (int8_t)fp8_encode(v / (ng ? sn : sp));
-  else lut[(size_t)ks * kLutBytes + bits] = (int8_t)clip_code(round_quotient(v, ng ? sn : sp, ng ? in : ip));
-}
-
-struct LutPlan {                         // workgroups [wg_begin[s], wg_begin[s+1]) stream K-segment s
-  int wg_begin[SQ_MAX_SEGMENTS + 1];
+struct TabPlan {
+  int wg_begin[SQ_MAX_SEGMENTS + 1];                     // workgroups [wg_begin[s], wg_begin[s+1]) stream K-segment s
+  int low[SQ_MAX_SEGMENTS];                              // first magnitude pattern with a code of its own
 };
 
-__global__ __launch_bounds__(kLutThreads) void quantize_act_lut_kernel(const uint16_t* __restrict__ h, int8_t* __restrict__ xq,
-                                                                       int M, int K, const ActTable tb, const LutPlan plan,
-                                                                       const int8_t* __restrict__ lut) {
-  __shared__ __attribute__((aligned(16))) uint8_t table[kLutBytes];
+template <bool FP8>
+__global__ __launch_bounds__(kTabThreads) void quantize_act_table_kernel(const uint16_t* __restrict__ h, int8_t* __restrict__ xq,
+                                                                         int M, int K, const ActTable tb, const TabPlan plan) {
+  __shared__ __attribute__((aligned(16))) uint8_t table[kTabBytes];
   int ks = 0;
   for (int s = 1; s < tb.S; ++s)
     if ((int)blockIdx.x >= plan.wg_begin[s]) ks = s;
-  int k0 = 0, k1 = 0, wg0 = 0, wg1 = 1;
-  for (int s = 0; s < tb.S; ++s)
-    if (s == ks) { k0 = tb.kseg_off[s]; k1 = tb.kseg_off[s + 1]; wg0 = plan.wg_begin[s]; wg1 = plan.wg_begin[s + 1]; }
-  {
-    const v4i* src = reinterpret_cast<const v4i*>(lut + (size_t)ks * kLutBytes);
-    for (int i = threadIdx.x; i < kLutBytes / 16; i += kLutThreads) reinterpret_cast<v4i*>(table)[i] = src[i];
+  const int k0 = tb.kseg_off[ks], wg0 = plan.wg_begin[ks], wg1 = plan.wg_begin[ks + 1], low = plan.low[ks];
+  const float sp = tb.s_pos[ks], sn = tb.s_neg[ks], ip = tb.inv_pos[ks], in = tb.inv_neg[ks];
+  const bool dual = tb.dual[ks] != 0;
+  const int acode = tb.act[ks];
+  auto code_of = [&](const float x) __attribute__((always_inline)) -> uint32_t {
+    const float v = activate(acode, x);
+    const bool ng = dual && (v < 0.0f);
+    if (FP8) return fp8_encode(v / (ng ? sn : sp));
+    return (uint32_t)clip_code(round_quotient(v, ng ? sn : sp, ng ? in : ip)) & 0xFFu;
+  };
+  // chunk c of this workgroup's share of the segment: 16 elements of one row
+  const uint32_t cps = (uint32_t)(tb.kseg_off[ks + 1] - k0) / kActChunk, nchunks = (uint32_t)M * cps;
+  const uint32_t stride = (uint32_t)(wg1 - wg0) * kTabThreads, dr = stride / cps, dc = stride - dr * cps;
+  uint32_t c = (uint32_t)((int)blockIdx.x - wg0) * kTabThreads + threadIdx.x, r = c / cps, cc = c - r * cps;
+  v4i raw[2] = {(v4i)(0), (v4i)(0)};
+  size_t at = 0;
+  auto fetch = [&]() __attribute__((always_inline)) {    // x is read once and dead afterwards: non-temporal
+    at = (size_t)r * K + k0 + (size_t)cc * kActChunk;
+    const v4i* p = reinterpret_cast<const v4i*>(h + at);
+    raw[0] = __builtin_nontemporal_load(p);
+    raw[1] = __builtin_nontemporal_load(p + 1);
+  };
+  if (c < nchunks) fetch();                              // under the fill of the table
+  for (int i = threadIdx.x; i < kTabBytes / 16; i += kTabThreads) reinterpret_cast<v4i*>(table)[i] = (v4i)(0);
+  __syncthreads();
+  for (int i = threadIdx.x; i < 2 * (kTabTop - low); i += kTabThreads) {
+    const uint32_t bits = (uint32_t)(low + (i >> 1)) | ((i & 1) ? 0x8000u : 0u);
+    table[bits] = (uint8_t)code_of(__uint_as_float(bits << 16));
   }
   __syncthreads();
-  const uint32_t cps = (uint32_t)(k1 - k0) / kActChunk;                    // 16-element chunks per row of the segment
-  const uint32_t nchunks = (uint32_t)M * cps;
-  const uint32_t stride = (uint32_t)(wg1 - wg0) * kLutThreads;
-  constexpr int U = 1;                                                // chunks in flight per thread: more only hurt (measured)
-  for (uint32_t c0 = (uint32_t)((int)blockIdx.x - wg0) * kLutThreads + threadIdx.x; c0 < nchunks; c0 += U * stride) {
-    v4i raw[U][2];
-    size_t eoff[U];
+  while (c < nchunks) {
+    const v4i cur[2] = {raw[0], raw[1]};
+    const size_t to = at;
+    c += stride;
+    r += dr;
+    cc += dc;
+    if (cc >= cps) { cc -= cps; ++r; }
+    if (c < nchunks) fetch();
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    u16x2 top = {0, 0};
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const uint32_t c = c0 + j * stride;
-      if (c < nchunks) {
-        const uint32_t r = c / cps, cc = c - r * cps;
-        eoff[j] = (size_t)r * K + k0 + (size_t)cc * kActChunk;
-        const v4i* p = reinterpret_cast<const v4i*>(h + eoff[j]);
-        raw[j][0] = __builtin_nontemporal_load(p);
-        raw[j][1] = __builtin_nontemporal_load(p + 1);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const uint32_t c = c0 + j * stride;
-      if (c >= nchunks) continue;
-      v4i out;
+    for (int d = 0; d < 8; ++d) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, (uint32_t)cur[d >> 2][d & 3] & 0x7FFF7FFFu));
+    v4i out;
+    if (top[0] < kTabTop && top[1] < kTabTop) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const uint32_t u0 = (uint32_t)raw[j][g / 2][(g % 2) * 2], u1 = (uint32_t)raw[j][g / 2][(g % 2) * 2 + 1];
+        const uint32_t u0 = (uint32_t)cur[g / 2][(g % 2) * 2], u1 = (uint32_t)cur[g / 2][(g % 2) * 2 + 1];
         const uint32_t b0 = table[u0 & 0xFFFFu], b1 = table[u0 >> 16], b2 = table[u1 & 0xFFFFu], b3 = table[u1 >> 16];
         out[g] = (int)(b0 | (b1 << 8) | (b2 << 16) | (b3 << 24));
       }
-      *reinterpret_cast<v4i*>(xq + eoff[j]) = out;
+    } else {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const uint32_t u0 = (uint32_t)cur[g / 2][(g % 2) * 2], u1 = (uint32_t)cur[g / 2][(g % 2) * 2 + 1];
+        out[g] = (int)(code_of(__uint_as_float(u0 << 16)) | (code_of(__uint_as_float(u0 & 0xFFFF0000u)) << 8) |
+                       (code_of(__uint_as_float(u1 << 16)) << 16) | (code_of(__uint_as_float(u1 & 0xFFFF0000u)) << 24));
+      }
     }
+    *reinterpret_cast<v4i*>(xq + to) = out;
   }
 }
 
-size_t quantize_act_fused_workspace_bytes(int S) { return (size_t)S * kLutBytes; }
+size_t quantize_act_fused_workspace_bytes(int S) { return (size_t)S * 65536; }
 
-bool quantize_act_lut_usable(const void* h, bool h_is_bf16, const int8_t* xq, int K, const ActTable& tb) {
+// The table kernel's launch, or false where the direct path serves: no activation, fp32 or unaligned input, steps so small that
+// the table would be wide, or a matrix too small for the fill (below 8192 elements per compute unit; 333 x 6144 bf16, the most
+// that goes direct: 6.2 us).
+bool launch_quantize_act_table(const void* h, bool h_is_bf16, int8_t* xq, int M, int K, const ActTable& tb, int cus, hipStream_t st,
+                               bool fp8) {
   bool ok = h_is_bf16 && (K % kActChunk == 0) && (reinterpret_cast<uintptr_t>(h) % 16 == 0) &&
-            (reinterpret_cast<uintptr_t>(xq) % 16 == 0);
-  for (int s = 0; s <= tb.S; ++s) ok = ok && (tb.kseg_off[s] % kActChunk == 0);
-  return ok;
-}
-
-hipError_t launch_quantize_act_lut(const void* h, int8_t* xq, int M, int K, const ActTable& tb, void* workspace, int cus,
-                                   hipStream_t st, bool fp8) {
-  int8_t* lut = reinterpret_cast<int8_t*>(workspace);
-  if (fp8) hipLaunchKernelGGL(act_lut_build_kernel<true>, dim3(256, tb.S), dim3(256), 0, st, tb, lut);
-  else hipLaunchKernelGGL(act_lut_build_kernel<false>, dim3(256, tb.S), dim3(256), 0, st, tb, lut);
-  // two workgroups per CU, dealt to the K-segments in proportion to their share of the matrix (at least one each)
-  const int total = 2 * cus > tb.S ? 2 * cus : tb.S;
-  LutPlan plan;
-  int given = 0;
+            (reinterpret_cast<uintptr_t>(xq) % 16 == 0) && (long long)M * K >= 8192ll * cus;
+  bool any = false;
+  TabPlan plan;
+  const int total = cus > tb.S ? cus : tb.S;             // dealt to the K-segments in proportion to their width, one at least
+  plan.wg_begin[0] = 0;
   for (int s = 0; s < tb.S; ++s) {
-    plan.wg_begin[s] = given;
-    const long long share = (long long)(total - tb.S) * (tb.kseg_off[s + 1] - tb.kseg_off[s]) / K;
-    given += 1 + (int)share;
+    ok = ok && tb.kseg_off[s] % kActChunk == 0;
+    any = any || tb.act[s] != SQ_ACT_NONE;
+    const float step = tb.dual[s] && tb.s_neg[s] < tb.s_pos[s] ? tb.s_neg[s] : tb.s_pos[s];
+    int e = 0;
+    (void)std::frexp(step, &e);                          // step in [2^(e-1), 2^e)
+    const int lo = e - 1 - (fp8 ? 10 : 1);               // 2^lo <= step / 2 (fp8: step / 2^10)
+    if (lo < 5 - kTabBinades || lo > 4) ok = false;
+    plan.low[s] = (127 + lo) << 7;
+    plan.wg_begin[s + 1] = plan.wg_begin[s] + 1 + (int)((long long)(total - tb.S) * (tb.kseg_off[s + 1] - tb.kseg_off[s]) / K);
   }
-  plan.wg_begin[tb.S] = given;
-  hipLaunchKernelGGL(quantize_act_lut_kernel, dim3(given), dim3(kLutThreads), 0, st, reinterpret_cast<const uint16_t*>(h), xq,
-                     M, K, tb, plan, lut);
-  return hipGetLastError();
+  if (!ok || !any) return false;
+  const dim3 grid(plan.wg_begin[tb.S]);
+  const uint16_t* src = reinterpret_cast<const uint16_t*>(h);
+  if (fp8) hipLaunchKernelGGL(quantize_act_table_kernel<true>, grid, dim3(kTabThreads), 0, st, src, xq, M, K, tb, plan);
+  else hipLaunchKernelGGL(quantize_act_table_kernel<false>, grid, dim3(kTabThreads), 0, st, src, xq, M, K, tb, plan);
+  return true;
 }
 
 // tb.act is read only when some K-segment has an activation fused in front of it (sq_quantize_act_fused)
@@ -251,6 +267,7 @@ hipError_t launch_quantize_act(const void* x, bool x_is_bf16, int8_t* xq, int M,
                                hipStream_t st) {
   bool any = false;
   for (int s = 0; s < tb.S; ++s) any = any || tb.act[s] != SQ_ACT_NONE;
+  if (any && launch_quantize_act_table(x, x_is_bf16, xq, M, K, tb, device_cus(), st, false)) return hipGetLastError();
   return any ? launch_quantize_act_impl<true>(x, x_is_bf16, xq, M, K, tb, st)
              : launch_quantize_act_impl<false>(x, x_is_bf16, xq, M, K, tb, st);
 }

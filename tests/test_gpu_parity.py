@@ -186,6 +186,45 @@ def test_quantize_act_fused(oracle, case, spread):
     assert torch.equal(xq, xq2)
 
 
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("steps", [(0.04, 0.0014), (0.002, 0.7), (3.0, 20.0), (1e-5, 1e-6)])
+def test_quantize_act_fused_table(oracle, steps, fp8):
+    """Matrices large enough for the code table: every finite bf16 pattern in every kind of segment (GELU and SiLU split by
+    polarity, none with one step, GELU with one step), chunks with and without magnitudes beyond the table, step pairs whose
+    tables start at different binades or are too wide to build: codes bit-exact."""
+    import torch
+
+    g = _gpu()
+    allbits = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    finite = allbits[(allbits & 0x7F80) != 0x7F80]
+    small = finite[np.abs(wl.bf16_bits_to_f32(finite)) < 32.0]
+    kseg, dual, act = [0, 4096, 4112, 8192, 12288], [1, 0, 1, 0], [2, 0, 1, 2]
+    M, K = 176, 12288                                          # 2.16 M elements: 8192 and more per compute unit
+    rng = np.random.default_rng(int(steps[0] * 1e6))
+    x = np.empty((M, K), np.uint16)
+    for a, b in zip(kseg[:-1], kseg[1:]):                      # shuffled, so that neighbouring chunks differ in kind
+        n = M * (b - a)
+        few = small[rng.integers(0, small.size, size=n // 2)]  # half the rows stay inside the table's magnitudes
+        rest = np.resize(rng.permutation(finite), n - few.size)
+        x[:, a:b] = np.concatenate([few, rest])[:n].reshape(M, b - a)
+    x32 = wl.bf16_bits_to_f32(x)
+    S = len(dual)
+    sp, sn = np.full(S, steps[0], np.float32), np.full(S, steps[1], np.float32)
+    layer = sq.Layer(M, K, 16, kseg, [0, 16], dual, sp, sn)
+    xd = torch.from_numpy(x.view(np.int16)).view(torch.bfloat16).to(g.DEV)
+    xq = torch.full((M, K), 99, dtype=torch.uint8 if fp8 else torch.int8, device=g.DEV)
+    if fp8:
+        sq.sq_quantize_act_fp8_fused(layer, xd, act, xq)
+        rp, rn = oracle.quantize_act_fp8_fused(x32, np.asarray(kseg, np.int32), np.asarray(dual, np.uint8), np.asarray(act, np.int32), sp, sn)
+        both = np.where(rn.view(np.uint8) & 0x7F, rn.view(np.uint8), rp.view(np.uint8))
+        both = np.where(both & 0x7F, both, 0).astype(np.uint8)
+    else:
+        sq.sq_quantize_act_fused(layer, xd, act, xq)
+        rp, rn = oracle.quantize_act_fused(x32, np.asarray(kseg, np.int32), np.asarray(dual, np.uint8), np.asarray(act, np.int32), sp, sn)
+        both = (rp.astype(np.int16) + rn.astype(np.int16)).astype(np.int8)
+    assert np.array_equal(xq.cpu().numpy(), both)
+
+
 @pytest.mark.parametrize("act", [1, 2])
 def test_quantize_act_fused_exhaustive_bf16_and_dense_f32(oracle, act):
     """Every finite bf16 value, and 4 M fp32 values spread over the magnitudes that matter, through the fused pass."""
