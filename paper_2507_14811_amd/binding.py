@@ -193,26 +193,43 @@ class Layer:
         return bool(self.dual.any())
 
 
-def _dptr(t) -> Optional[int]:
-    return None if t is None else C.c_void_p(t.data_ptr())
+# Host cost of a call: the small kernels take 3 - 8 us, so what a call costs in Python shows.  Addresses go to ctypes as
+# plain integers (the argtypes say pointer), the current stream comes as its raw handle (torch.cuda.current_stream() builds
+# an object for every call), and torch is looked up once.
+_torch = None
+_DTYPES: dict = {}
 
 
-def _stream(stream) -> C.c_void_p:
-    if stream is None:
+def _torch_module():
+    global _torch
+    if _torch is None:
         import torch
 
+        _DTYPES.update({torch.float32: SQ_F32, torch.bfloat16: SQ_BF16})
+        _torch = torch
+    return _torch
+
+
+def _dptr(t) -> Optional[int]:
+    return None if t is None else t.data_ptr()
+
+
+def _stream(stream):
+    if stream is None:
+        torch = _torch or _torch_module()
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
-    return C.c_void_p(getattr(stream, "cuda_stream", stream))
+    return getattr(stream, "cuda_stream", stream)
 
 
 def _dt(t) -> int:
-    import torch
-
-    if t.dtype == torch.float32:
-        return SQ_F32
-    if t.dtype == torch.bfloat16:
-        return SQ_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    if _torch is None:
+        _torch_module()
+    try:
+        return _DTYPES[t.dtype]
+    except KeyError:
+        raise TypeError(f"unsupported dtype {t.dtype}") from None
 
 
 def _check(st: int, what: str):
