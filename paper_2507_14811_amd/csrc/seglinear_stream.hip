@@ -20,6 +20,8 @@
 //     and biases come through the scalar cache, so no vmcnt(0) ever drains the ring.
 #include "seglinear_mfma_kernel.hpp"
 
+#include <cmath>
+
 namespace sq {
 
 // Waves per workgroup (one workgroup per CU).  With one or two 16-row token tiles a wave needs few registers and
@@ -185,6 +187,7 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
   constexpr int PRIME_LOADS = (RING - 1) * (W4 ? 1 : 2);           // direct loads of a fully primed ring
   static_assert(PRIME_LOADS <= 63, "the wait count is a 6-bit field");
   const int kq = a.K >> 2;                                         // items per row
+  const uint32_t kq_magic = 0xFFFFFFFFu / (uint32_t)kq + 1u;       // item / kq = umulhi(item, kq_magic): item, kq < 2^15
   const int nitem = a.x_raw ? a.M * kq : 0;
   uint64_t raw2[RAWPRE];                                           // bf16 items: 8 bytes
   v4i raw4[RAWPRE];                                                // fp32 items: 16 bytes
@@ -205,6 +208,24 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
 #pragma unroll 1
   while (issued_steps < RING - 1 && issued_steps < total) issue_step();
 
+  // bf16 activations of one K-segment: the codes come from a table of the magnitudes [2^lo, 2^hi) of both signs (below it every
+  // code is 0, above it the arithmetic runs), filled here with that arithmetic while the loads are on the way: 3840 evaluations
+  // per workgroup instead of one per element (16 x 1152: 18432; 12.8 -> 9.6 us for the layer of 6912 columns).
+  uint8_t* code_tab = reinterpret_cast<uint8_t*>(tok);             // [sign][kTabHalf]: entry 0 below the window, then the window
+  constexpr int kTabHalf = C::TOK / 2;
+  if (a.x_tab_n > 0) {
+    const float sp = tb.s_pos[0], sn = tb.s_neg[0], ip = tb.inv_pos[0], in = tb.inv_neg[0];
+    const bool dl = tb.dual[0] != 0;
+    for (int i = threadIdx.x; i < 2 * (a.x_tab_n + 1); i += NT) {
+      const int sgn = i & 1, e = i >> 1;
+      const float av = activate(tb.act[0], __uint_as_float((uint32_t)(a.x_tab_low - 1 + e) << 16 | (uint32_t)sgn << 31));
+      const bool ng = dl && (av < 0.0f);
+      const int code = clip_code(round_quotient(av, ng ? sn : sp, ng ? in : ip));
+      code_tab[sgn * kTabHalf + e] = e == 0 ? (uint8_t)0 : (uint8_t)code;
+    }
+    lds_barrier();
+  }
+
   if (a.x_raw) {
 #define SQ_RAW_OPERANDS "+v"(raw2[0]), "+v"(raw2[1]), "+v"(raw2[2]), "+v"(raw2[3]), "+v"(raw2[4]), \
                         "+v"(raw4[0]), "+v"(raw4[1]), "+v"(raw4[2]), "+v"(raw4[3]), "+v"(raw4[4])
@@ -223,7 +244,7 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
   if (a.x_raw != nullptr) {
     const int rowb = a.K + 16;
     auto quantize_item = [&](const int c, const uint32_t (&w)[4]) __attribute__((always_inline)) {
-      const int r = c / kq, col = (c - r * kq) << 2;
+      const int r = (int)__umulhi((uint32_t)c, kq_magic), col = (c - r * kq) << 2;
       float sp = 1.0f, sn = 1.0f, ip = 1.0f, in = 1.0f;
       bool dl = false;
       int acode = SQ_ACT_NONE;
@@ -273,7 +294,7 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
       for (int i = threadIdx.x; i < ntab; i += NT) amax[i] = 0u;
       lds_barrier();
       auto scan_item = [&](const int c, const uint32_t (&w)[4], float (&av)[4]) __attribute__((always_inline)) {
-        const int r = c / kq, col = (c - r * kq) << 2;
+        const int r = (int)__umulhi((uint32_t)c, kq_magic), col = (c - r * kq) << 2;
         int ks = 0, acode = SQ_ACT_NONE;
         bool dl = false;
         for (int sg = 0; sg < tb.S; ++sg)
@@ -320,7 +341,7 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
       }
       lds_barrier();
       auto code_item = [&](const int c, const float (&av)[4]) __attribute__((always_inline)) {
-        const int r = c / kq, col = (c - r * kq) << 2;
+        const int r = (int)__umulhi((uint32_t)c, kq_magic), col = (c - r * kq) << 2;
         int ks = 0;
         bool dl = false;
         for (int sg = 0; sg < tb.S; ++sg)
@@ -354,7 +375,7 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
         uint32_t w[4];
         float av[4];
         load_item(c, w);
-        const int r = c / kq, col = (c - r * kq) << 2;
+        const int r = (int)__umulhi((uint32_t)c, kq_magic), col = (c - r * kq) << 2;
         int acode = SQ_ACT_NONE;
         for (int sg = 0; sg < tb.S; ++sg)
           if (col >= tb.kseg_off[sg]) acode = tb.act[sg];
@@ -366,6 +387,43 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
           av[i] = activate(acode, xv);
         }
         code_item(c, av);
+      }
+    } else if (a.x_tab_n > 0) {
+      const uint32_t below = (uint32_t)a.x_tab_low - 1u, top = (uint32_t)(a.x_tab_low + a.x_tab_n);
+      const bool dl = tb.dual[0] != 0;
+      auto table_item = [&](const int c, const uint32_t (&w)[4]) __attribute__((always_inline)) {
+        uint32_t pk = 0;
+        bool beyond = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t p = (w[i >> 1] >> (16 * (i & 1))) & 0xFFFFu, mag = p & 0x7FFFu;
+          const uint32_t at = mag < below ? below : mag > top ? top : mag;
+          beyond = beyond || at == top;
+          pk |= (uint32_t)code_tab[(p >> 15) * kTabHalf + (at - below)] << (8 * i);    // (at == top: unused)
+        }
+        if (beyond) {
+          quantize_item(c, w);
+          return;
+        }
+        const int r = (int)__umulhi((uint32_t)c, kq_magic), col = (c - r * kq) << 2;
+        int pos = (int)pk, neg = 0;
+        if (PS) {
+          if (dl) split_polarity((int)pk, pos, neg);
+          *reinterpret_cast<int*>(smem + plane + r * rowb + col) = neg;
+        }
+        *reinterpret_cast<int*>(smem + r * rowb + col) = pos;
+      };
+#pragma unroll
+      for (int j = 0; j < RAWPRE; ++j) {
+        const int c = threadIdx.x + j * NT;
+        const uint32_t w[4] = {(uint32_t)raw2[j], (uint32_t)(raw2[j] >> 32), 0u, 0u};
+        if (c < nitem) table_item(c, w);
+      }
+#pragma unroll 1
+      for (int c = threadIdx.x + RAWPRE * NT; c < nitem; c += NT) {
+        uint32_t w[4];
+        load_item(c, w);
+        table_item(c, w);
       }
     } else {
 #pragma unroll
@@ -688,6 +746,21 @@ bool stream_supported(const GemmArgs& a, const GemmTable& tb) {
 }
 #endif
 
+// Window of the code table for raw bf16 activations (one K-segment, an activation in front, static steps): from 2^lo, at most
+// half the smaller step (|act(x)| <= |x|, so below it every code is 0), over at most 15 binades, 1920 of the 2047 entries a sign
+// has, and at most to 32.  None where fewer elements than twice the table's evaluations are to be quantized.
+template <class TB> static void set_code_table(GemmArgs& a, const TB& tb) {
+  a.x_tab_low = a.x_tab_n = 0;
+  if (a.x_raw == nullptr || !a.x_raw_bf16 || a.x_raw_dynamic || tb.S != 1 || tb.act[0] == SQ_ACT_NONE || (long)a.M * a.K < 8192) return;
+  const float step = tb.dual[0] && tb.s_neg[0] < tb.s_pos[0] ? tb.s_neg[0] : tb.s_pos[0];
+  int e = 0;
+  (void)std::frexp(step, &e);                                      // step in [2^(e-1), 2^e)
+  const int lo = e - 2, hi = lo + 15 < 5 ? lo + 15 : 5;
+  if (lo < -100 || hi < 3 || lo >= hi) return;
+  a.x_tab_low = (127 + lo) << 7;
+  a.x_tab_n = (hi - lo) << 7;
+}
+
 template <int MT, int SLAB_KB, bool W4, bool FP8>
 static hipError_t launch_stream_ms(const GemmArgs& a, const GemmTable& tb, int mode, bool dual, bool ps, int grid, hipStream_t st) {
 #define SQ_K(D, P) hipLaunchKernelGGL((seglinear_stream_kernel<MT, D, SLAB_KB, GemmTable, NoGroups, W4, P, FP8>), dim3(grid), dim3(stream_waves(MT) * 64), 0, st, a, tb, NoGroups{}, mode)
@@ -701,7 +774,8 @@ static hipError_t launch_stream_ms(const GemmArgs& a, const GemmTable& tb, int m
 }
 
 template <bool W4, bool FP8>
-static hipError_t launch_stream_impl(const GemmArgs& a, const GemmTable& tb, OutMode mode, int cus, hipStream_t st) {
+static hipError_t launch_stream_impl(GemmArgs a, const GemmTable& tb, OutMode mode, int cus, hipStream_t st) {
+  set_code_table(a, tb);
   const bool dual = any_dual(tb.dual, tb.S);
   const int mt = (a.M + 15) / 16;
   const int ngroups = (a.N + 15) / 16;
@@ -759,8 +833,9 @@ static hipError_t launch_grouped_ms(const GemmArgs& a, const GroupSegTable& tb, 
 }
 
 template <bool W4, bool FP8>
-static hipError_t launch_grouped_impl(const GemmArgs& a, const GroupSegTable& tb, const GroupTable& gt, OutMode mode, int cus,
+static hipError_t launch_grouped_impl(GemmArgs a, const GroupSegTable& tb, const GroupTable& gt, OutMode mode, int cus,
                                       hipStream_t st) {
+  set_code_table(a, tb);
   const bool dual = any_dual(tb.dual, tb.S);
   const int mt = (a.M + 15) / 16;
   const long ngroups = (long)((a.N + 15) / 16) * gt.L;

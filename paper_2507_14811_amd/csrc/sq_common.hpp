@@ -88,6 +88,7 @@ struct GemmArgs {
   int x_raw_bf16;                  // table's activation) into the LDS slab by the kernel itself; nullptr: xq holds codes
   int x_raw_dynamic;               // with x_raw: per-token steps found by the kernel (min/max rule per row and K-segment)
   float act_qmax;                  //   largest activation code of those steps (127, or 7 for 4-bit activation codes)
+  int x_tab_low, x_tab_n;          // with x_raw, static steps: code table of the magnitude patterns [low, low + n); n = 0: none
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }

@@ -1680,6 +1680,38 @@ def test_seglinear_fused(oracle, case):
         compare(items[l][3], w, b, f"grouped layer {l}")
 
 
+@pytest.mark.parametrize("M,K,steps,act", [(16, 1152, (0.04, 0.0022), 1), (7, 2048, (0.04, 0.0013), 2), (17, 512, (2.0, 9.0), 1),
+                                           (32, 1152, (0.03, 3e-5), 1), (4, 2048, (0.04, 0.0022), 2), (16, 640, (0.01, None), 1)])
+def test_seglinear_fused_code_table(M, K, steps, act):
+    """The weight-stream kernel's code table for raw bf16 activations (8192 elements and more, one K-segment): every kind of
+    pattern below, inside and beyond its window, windows cut at 15 binades or at 32, one layer too small for it; equal bit for
+    bit to the quantizer's codes through the same kernel."""
+    import torch
+
+    g = _gpu()
+    rng = np.random.default_rng(M + K)
+    bits = rng.integers(0, 65536, size=(M, K)).astype(np.uint16)
+    bits[(bits & 0x7F80) == 0x7F80] = 0x8000
+    half = (rng.standard_normal((M, K)) * 2.0).astype(np.float32)
+    bits = np.where(rng.random((M, K)) < 0.5, bits, wl.f32_to_bf16_bits(half)).astype(np.uint16)
+    bits[0, :8] = [0x0000, 0x8000, 0x0001, 0x8001, 0x41FF, 0x4200, 0xC1FF, 0xC200]
+    x = torch.from_numpy(bits.view(np.int16)).view(torch.bfloat16).to(g.DEV)
+    N = 80
+    layer = sq.Layer(M, K, N, [0, K], [0, N], [0 if steps[1] is None else 1], [steps[0]], [steps[1] or 1.0])
+    wq = torch.from_numpy(rng.integers(-127, 128, size=(N, K)).astype(np.int8)).to(g.DEV)
+    ws = torch.from_numpy(rng.uniform(0.1, 1.0, size=(1, N)).astype(np.float32)).to(g.DEV)
+    xq = torch.full((M, K), 99, dtype=torch.int8, device=g.DEV)
+    y0, y1, y2 = (torch.full((M, N), float("nan"), device=g.DEV) for _ in range(3))
+    sq.sq_quantize_act_fused(layer, x, [act], xq)
+    sq.sq_tuning_set("force_path", 3)
+    sq.sq_seglinear(layer, xq, wq, ws, None, y0)
+    sq.sq_tuning_set("force_path", -1)
+    sq.sq_seglinear_fused(layer, x, [act], wq, ws, None, y1)
+    sq.sq_seglinear_grouped_fused(layer, x, [act], [(wq, ws, None, y2)])
+    torch.cuda.synchronize()
+    assert torch.equal(y0, y1) and torch.equal(y0, y2)
+
+
 def test_seglinear_fused_rejects_what_the_stream_kernel_cannot_run():
     import torch
 
