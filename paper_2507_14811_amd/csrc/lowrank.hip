@@ -20,6 +20,13 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 constexpr int kLrRowsPerWg = 256;     // down projection: 4 waves x 64 token rows
 constexpr int kLrMaxSplit = 32;
 constexpr int kLrUpCols = 128;        // up projection: output columns per wave (32 token rows)
+// Outputs from which the up projection fetches ahead (52 MB of y_q): beyond that the GEMM's y_q is no longer near, and what
+// counts is bytes in flight and keeping y_q, read once, out of the caches; below it the loads are short and the wave per SIMD
+// that the second block's registers cost is worth more.  Per-token GEMM and branch together, three sets of buffers in turn, bf16
+// output, form without / with fetching ahead: rank 64 2048 x 1152 x 3456 (28 MB) 50.4 / 52.3 us, 4096 x 1024 x 3072 (50 MB) 65.0 /
+// 67.4, 1500 x 3072 x 9216 (55 MB) 107.7 / 100.6, 4096 x 1536 x 4608 (75 MB) 108.2 / 99.7, 8500 x 1536 x 4608 (157 MB) 203.7 /
+// 187.7; rank 32 61.1 / 62.9 at 50 MB, 101.6 / 94.4 at 55 MB.  The call alone, 9000 x 512 x 1536: 32.8 / 36.3 us.
+constexpr long long kLrAheadOutputs = 13000000;
 
 int lowrank_splits(int M, int K, int cus) {
   const int row_blocks = (M + kLrRowsPerWg - 1) / kLrRowsPerWg;
@@ -288,7 +295,7 @@ __global__ __launch_bounds__(256) void lowrank_sum_kernel(const float* __restric
 // block for rank 64 where the fp32 instruction v_mfma_f32_32x32x2_f32 needs 32 of twice the length).  The matrix
 // instruction pairs lane half h of both operands, so half h takes the features [h R/2, (h + 1) R/2) of T and Lu: every lane
 // reads one contiguous run of each.  T is the "A" operand: a half-wave then holds 32 consecutive columns of one row.
-template <bool YBF16, int R>
+template <bool YBF16, int R, bool AHEAD>
 __global__ __launch_bounds__(256) void lowrank_up_kernel(const float* __restrict__ tsum, const uint16_t* __restrict__ lu,
                                                          const float* y_in, void* y_out, int M, int N) {
   constexpr int KH = R / 2;
@@ -325,9 +332,10 @@ __global__ __launch_bounds__(256) void lowrank_up_kernel(const float* __restrict
   }
   const int mb = blockIdx.y * 32;
   const bool pair_ok = (N % 2 == 0) && (reinterpret_cast<uintptr_t>(y_out) % 4 == 0);     // two bf16 columns per store
-  // y_q and the Lu rows of a block column, requested one block column ahead of their use: every wave then keeps two blocks'
-  // loads in flight, and the stores of one run under the loads of the next (8500 x 1536 x 4608: 72 -> 66 us, 235 MB of y_q and y;
-  // 256 columns per wave instead of 128 69 us)
+  // AHEAD: y_q and the Lu rows of a block column are requested one block column ahead of their use, so that every wave keeps two
+  // blocks' loads in flight and the stores of one run under the loads of the next, at 215 instead of 140 vector registers (rank
+  // 64; two waves per SIMD instead of three); y_q is then read past the caches (8500 x 1536 x 4608: 72 -> 66 us, 235 MB of y_q
+  // and y; 256 columns per wave instead of 128 69 us).
   struct Block { v8bf lf[KH / 8]; float yq[16]; };
   auto load_block = [&](const int nb) __attribute__((always_inline)) {
     Block b;
@@ -338,19 +346,26 @@ __global__ __launch_bounds__(256) void lowrank_up_kernel(const float* __restrict
     for (int c = 0; c < KH / 8; ++c) b.lf[c] = *reinterpret_cast<const v8bf*>(lsrc + 8 * c);
     // Element v of the block in lane l: token row mb + 8 (v >> 2) + 4 (l >> 5) + (v & 3), output column nb + (l & 31): the 32
     // lanes of a half-wave hold 32 consecutive columns of one row, so every access covers whole 128-byte (fp32) or 64-byte
-    // (bf16) row pieces.  Rows beyond M re-read the last one.
+    // (bf16) row pieces.  AHEAD: rows beyond M re-read the last one.
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int mv = mb + 8 * (v >> 2) + 4 * h + (v & 3);
-      b.yq[v] = y_in != nullptr ? __builtin_nontemporal_load(y_in + (size_t)(mv < M ? mv : M - 1) * N + na) : 0.0f;
+      if (AHEAD) b.yq[v] = y_in != nullptr ? __builtin_nontemporal_load(y_in + (size_t)(mv < M ? mv : M - 1) * N + na) : 0.0f;
+      else b.yq[v] = (y_in != nullptr && n < N && mv < M) ? y_in[(size_t)mv * N + n] : 0.0f;
     }
     return b;
   };
-  Block cur = load_block(n_begin);
+  Block next;
+  if (AHEAD) next = load_block(n_begin);
 #pragma unroll 1
   for (int nb = n_begin; nb < n_end; nb += 32) {
-    Block next = cur;
-    if (nb + 32 < n_end) next = load_block(nb + 32);
+    Block cur;
+    if (AHEAD) {
+      cur = next;
+      if (nb + 32 < n_end) next = load_block(nb + 32);
+    } else {
+      cur = load_block(nb);
+    }
     const v8bf* lf = cur.lf;
     const float* yq = cur.yq;
     const int n = nb + (lane & 31);
@@ -387,7 +402,6 @@ __global__ __launch_bounds__(256) void lowrank_up_kernel(const float* __restrict
         }
       }
     }
-    cur = next;
   }
 }
 
@@ -422,9 +436,12 @@ hipError_t launch_lowrank_add(const void* x, bool x_is_bf16, const uint16_t* ld,
     tsum = dst;
   }
   dim3 gu((N + 4 * kLrUpCols - 1) / (4 * kLrUpCols), (M + 31) / 32);
-#define SQ_UP(B, R) hipLaunchKernelGGL((lowrank_up_kernel<B, R>), gu, dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
-  if (rank == 64) { if (y_is_bf16) SQ_UP(true, 64); else SQ_UP(false, 64); }
-  else            { if (y_is_bf16) SQ_UP(true, 32); else SQ_UP(false, 32); }
+  const bool ahead = (long long)M * N >= kLrAheadOutputs;
+#define SQ_UP(B, R) \
+  if (ahead) hipLaunchKernelGGL((lowrank_up_kernel<B, R, true>), gu, dim3(256), 0, st, tsum, lu, y_in, y_out, M, N); \
+  else hipLaunchKernelGGL((lowrank_up_kernel<B, R, false>), gu, dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
+  if (rank == 64) { if (y_is_bf16) { SQ_UP(true, 64); } else { SQ_UP(false, 64); } }
+  else            { if (y_is_bf16) { SQ_UP(true, 32); } else { SQ_UP(false, 32); } }
 #undef SQ_UP
   return hipGetLastError();
 }

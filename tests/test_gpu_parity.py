@@ -840,6 +840,40 @@ def test_lowrank_add(oracle, case):
         assert torch.equal(y1, y2)
 
 
+@pytest.mark.parametrize("rank,yq", [(64, True), (32, True), (64, False)])
+@pytest.mark.parametrize("M,N", [(201, 65002), (203, 64999), (4130, 3200)])
+def test_lowrank_add_large(M, N, rank, yq):
+    """From 13 M outputs the up projection fetches y_q and Lu one block column ahead: ragged rows, ragged and odd columns, bit for bit
+    the result of the same rows in calls below that size (K = 256: one K slice in all of them, so the same T)."""
+    import torch
+
+    g = _gpu()
+    K = 256
+    gen = torch.Generator(device=g.DEV)
+    gen.manual_seed(M + rank)
+    x, ld, lu, y0 = (torch.randn(s, generator=gen, device=g.DEV) for s in ((M, K), (rank, K), (N, rank), (M, N)))
+    x, ld, lu = x.to(torch.bfloat16), (ld / 16).to(torch.bfloat16), (lu * 0.1).to(torch.bfloat16)
+    y0 = y0 if yq else None
+
+    def call(r0, r1, dt):
+        layer = sq.Layer(r1 - r0, K, N, [0, K], [0, N], [0])
+        ws = torch.full((sq.sq_lowrank_workspace_bytes(layer, rank),), 0xFF, dtype=torch.uint8, device=g.DEV)
+        y = torch.full((r1 - r0, N), float("nan"), dtype=dt, device=g.DEV)
+        sq.sq_lowrank_add(layer, x[r0:r1], ld, lu, None if y0 is None else y0[r0:r1], y, ws)
+        return y
+
+    step = (M + 1) // 2
+    for dt in (torch.float32, torch.bfloat16):
+        parts = torch.cat([call(r, min(r + step, M), dt) for r in range(0, M, step)])
+        assert torch.equal(call(0, M, dt), parts)
+    if yq:                                                # in place
+        layer = sq.Layer(M, K, N, [0, K], [0, N], [0])
+        ws = torch.empty((sq.sq_lowrank_workspace_bytes(layer, rank),), dtype=torch.uint8, device=g.DEV)
+        want, y1 = call(0, M, torch.float32), y0.clone()
+        sq.sq_lowrank_add(layer, x, ld, lu, y1, y1, ws)
+        assert torch.equal(y1, want)
+
+
 @pytest.mark.parametrize("M", [16, 300])
 def test_w4_layer_with_lowrank_branch(oracle, M):
     """The 4-bit setting end to end: W = Lu Ld + R (numpy's SVD, rank 64), R through the 4-bit weight quantizer and the
