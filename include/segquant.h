@@ -238,10 +238,10 @@ sq_status sq_quantize_act_geglu(const sq_layer* layer, const void* h, sq_dtype h
  * evaluated in fp32 and stored as fp32 or bf16 (round-half-to-even).  Activation and weight tiles
  * are read once and feed both accumulator sets.  Kernel selection: M <= 32 with K and the K-segment boundaries
  * multiples of 128 runs the weight-streaming (bandwidth-bound) kernel; M > 32 with the same alignment, at most eight
- * K-segments and no seg_scale, whose output one round of 64 x 64, 64 x 128 or 128 x 64 tiles covers, tiles whose waves split
- * K; other M = 33..64 the MFMA tile kernel with 64-row tiles (K and the boundaries multiples of 64), else the K-splitting
- * skinny kernel; larger M the MFMA tile kernel; shapes none of them takes (unaligned K or boundaries) a plain
- * one-thread-per-output kernel.
+ * K-segments and no seg_scale, whose output one round of 64 x 64, 64 x 128 or 128 x 64 tiles covers and whose K-segments are long
+ * enough for them, tiles whose waves split K; other M = 33..64 the MFMA tile kernel with 64-row tiles (K and the boundaries
+ * multiples of 64), else the K-splitting skinny kernel; larger M the MFMA tile kernel; shapes none of them takes (unaligned K or
+ * boundaries) a plain one-thread-per-output kernel.
  *   xq dev int8 [M][K] (from sq_quantize_act);  wq dev int8 [N][K];  wscale dev fp32 [S][N];
  *   bias dev fp32 [N] or NULL;  y dev [M][N] of y_dt.
  */
@@ -459,7 +459,8 @@ int sq_version(void);
  * Diagnostics hook for benchmarks and tests: process-wide override of kernel selection.
  *   key "gemm_variant": -1 = automatic (default), otherwise the index of a tile configuration
  *   key "force_path":   -1 = automatic, 0 = generic kernel, 1 = MFMA tile kernel, 2 = skinny kernel,
- *                       3 = skinny weight-stream kernel
+ *                       3 = skinny weight-stream kernel, 4 = K-splitting tiles (sq_seglinear, its raw-sum form and
+ *                       sq_seglinear_dynamic; "gemm_variant" 0 / 1 / 2: tiles of 64 x 64, 64 x 128, 128 x 64; -1: 64 x 64)
  * Returns SQ_ERR_INVALID_ARG for an unknown key or value.  Not thread-safe against running calls.
  */
 sq_status sq_tuning_set(const char* key, int value);

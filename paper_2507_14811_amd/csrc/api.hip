@@ -8,7 +8,7 @@
 namespace {
 
 int g_gemm_variant = -1;   // sq_tuning_set("gemm_variant", v)
-int g_force_path = -1;     // sq_tuning_set("force_path", p): 0 generic, 1 MFMA tiles, 2 skinny, 3 skinny weight stream
+int g_force_path = -1;     // sq_tuning_set("force_path", p): 0 generic, 1 MFMA tiles, 2 skinny, 3 skinny weight stream, 4 K-splitting tiles
 
 bool offsets_ok(int n, int cnt, const int32_t* off) {
   if (cnt < 1 || cnt > SQ_MAX_SEGMENTS || off == nullptr) return false;
@@ -75,6 +75,12 @@ void fill_gemm_table(const sq_layer* L, sq::GemmTable& tb) {
   if (L->seg_scale) std::memcpy(tb.seg_scale, L->seg_scale, sizeof(float) * L->S * L->T);
 }
 
+// sq_tuning_set("force_path", 4): the tile that "gemm_variant" names (automatic: 64 x 64), -1 where it cannot run
+int forced_ksplit_tile(const sq::GemmArgs& a, const sq::GemmTable& tb) {
+  const int tile = g_gemm_variant < 0 ? 0 : g_gemm_variant;
+  return tile < 3 && sq::ksplit_supported(a, tb) ? tile : -1;
+}
+
 sq_status run_gemm(const sq_layer* L, const int8_t* xq, const int8_t* wq,
                    const float* wscale, const float* bias, void* y, int32_t* acc_pos, int32_t* acc_neg,
                    sq::OutMode mode, void* stream) {
@@ -96,13 +102,15 @@ sq_status run_gemm(const sq_layer* L, const int8_t* xq, const int8_t* wq,
   if (path == 3 && !sq::stream_supported(a, tb)) return SQ_ERR_UNSUPPORTED;
   if (path == 2 && !sq::skinny_supported(a, tb)) return SQ_ERR_UNSUPPORTED;
   if (path == 1 && !sq::mfma_supported(a, tb)) return SQ_ERR_UNSUPPORTED;
+  int ktile = path == 4 ? forced_ksplit_tile(a, tb) : -1;
+  if (path == 4 && ktile < 0) return SQ_ERR_UNSUPPORTED;
   if (path < 0) {
-    // up to two 16-row tiles of tokens: the weight-stream kernel (measured 5.9 TB/s on wide layers); three or four
-    // tiles: tile kernels are as fast or faster; the K-splitting skinny kernel serves
-    // the layers whose K-segments are only 64-aligned
-    // 33 rows and more: the K-splitting tiles where one round of them covers the output, else the tile kernel
+    // up to two 16-row tiles of tokens: the weight-stream kernel (measured 5.9 TB/s on wide layers); more rows: the
+    // K-splitting tiles where ksplit_pick() finds them the faster ones, else the tile kernel; the skinny kernel serves the
+    // layers of up to 64 rows that neither takes
+    if (a.M > 32 && g_gemm_variant < 0) ktile = sq::ksplit_pick(a, tb);
     if (a.M <= 32 && sq::stream_supported(a, tb)) path = 3;
-    else if (a.M > 32 && g_gemm_variant < 0 && sq::ksplit_pick(a, tb) >= 0) path = 4;
+    else if (ktile >= 0) path = 4;
     else if (a.M <= 64 && a.M > 32 && sq::mfma_supported(a, tb)) path = 1;
     else if (sq::skinny_supported(a, tb)) path = 2;
     else if (sq::mfma_supported(a, tb)) path = 1;
@@ -110,7 +118,7 @@ sq_status run_gemm(const sq_layer* L, const int8_t* xq, const int8_t* wq,
   }
   hipError_t e;
   if (path == 4) {
-    e = sq::launch_seglinear_ksplit(a, tb, mode, sq::ksplit_pick(a, tb), st);
+    e = sq::launch_seglinear_ksplit(a, tb, mode, ktile, st);
   } else if (path == 3) {
     e = sq::launch_seglinear_stream(a, tb, mode, sq::device_cus(), st);
   } else if (path == 2) {
@@ -159,12 +167,16 @@ sq_status run_gemm_dynamic(const sq_layer* L, const int8_t* xq, const float* tok
   const bool mfma_ok = w_bits == 8 && sq::mfma_supported(a, tb) && sq::mfma_pick_variant(a, tb, mode) >= 0;
   if (g_force_path == 3 && !stream_ok) return SQ_ERR_UNSUPPORTED;
   if (g_force_path == 1 && !mfma_ok) return SQ_ERR_UNSUPPORTED;
+  int ktile = -1;
+  if (w_bits == 8 && g_force_path == 4) ktile = forced_ksplit_tile(a, tb);
+  else if (w_bits == 8 && g_force_path < 0 && g_gemm_variant < 0 && !stream_ok) ktile = sq::ksplit_pick(a, tb);
+  if (g_force_path == 4 && ktile < 0) return SQ_ERR_UNSUPPORTED;
   hipError_t e;
-  if (g_force_path != 0 && g_force_path != 1 && stream_ok) {
+  if (g_force_path != 0 && g_force_path != 1 && g_force_path != 4 && stream_ok) {
     e = w_bits == 4 ? sq::launch_seglinear_stream_w4(a, tb, mode, sq::device_cus(), st)
                     : sq::launch_seglinear_stream(a, tb, mode, sq::device_cus(), st);
-  } else if (g_force_path < 0 && g_gemm_variant < 0 && w_bits == 8 && sq::ksplit_pick(a, tb) >= 0) {
-    e = sq::launch_seglinear_ksplit(a, tb, mode, sq::ksplit_pick(a, tb), st);
+  } else if (ktile >= 0) {
+    e = sq::launch_seglinear_ksplit(a, tb, mode, ktile, st);
   } else if (g_force_path != 0 && mfma_ok) {           // large M, 8-bit weights: the MFMA tile kernel with per-row steps
     int v = g_gemm_variant >= 0 ? g_gemm_variant : sq::mfma_pick_variant(a, tb, mode);
     e = sq::launch_seglinear_mfma(a, tb, mode, v, st);
@@ -812,7 +824,7 @@ sq_status sq_tuning_set(const char* key, int value) {
     return SQ_OK;
   }
   if (std::strcmp(key, "force_path") == 0) {
-    if (value < -1 || value > 3) return SQ_ERR_INVALID_ARG;
+    if (value < -1 || value > 4) return SQ_ERR_INVALID_ARG;
     g_force_path = value;
     return SQ_OK;
   }

@@ -447,23 +447,40 @@ static long tile_count(const GemmArgs& a, int t) {
   return (long)((a.M + kTiles[t].BM - 1) / kTiles[t].BM) * ((a.N + kTiles[t].BN - 1) / kTiles[t].BN);
 }
 
-static bool ksplit_supported(const GemmArgs& a, const GemmTable& tb) {
+bool ksplit_supported(const GemmArgs& a, const GemmTable& tb) {
   if (tb.S > kKsplitSegments || tb.has_seg_scale) return false;
   for (int s = 0; s <= tb.S; ++s)
     if (tb.kseg_off[s] % 128 != 0) return false;
   return (reinterpret_cast<uintptr_t>(a.xq) | reinterpret_cast<uintptr_t>(a.wq)) % 16 == 0;
 }
 
-// The tile, or -1: the layer has more tiles than there are compute units.  One round of tiles is where this kernel is the
-// faster one: of 101 random layers (33 - 4000 rows, K 512 - 19840, N 512 - 11847, one and both polarities, one and two
-// K-segments) all 85 with one round of 64 x 64 tiles, or else of 64 x 128 or 128 x 64, ran 1.09 - 3.2 times as fast as on the
-// tile kernel (median 1.6).  A second round repeats the exposed start and exchange (3 - 7 us; the tile kernel fetches across
-// tiles) and made it slower than the tile kernel on all but one of the others (1296 x 8192 x 2048: 61 against 55 us).
+// The tile, or -1 where the tile kernel serves: the layer has more tiles than there are compute units, or its K-segments are too
+// short for it.  A second round of tiles repeats the exposed start and exchange (3 - 7 us; the tile kernel fetches across tiles)
+// and made this kernel the slower one on all but one of 16 layers (1296 x 8192 x 2048: 61 against 55 us).  A K-segment costs a
+// start, a drain and an exchange (0.3 - 0.5 us on the tiles with 64 columns, 2 us on 64 x 128), which its stages of 128 columns have
+// to earn back: about 0.2 us each where both polarity paths run, 0.07 where one does (64 x 128: 0.09 and 0.02).  2145 layers of
+// 1 - 8 equal segments of 128 - 12288 columns, 33 - 20000 rows, every mix of paths: of the 1040 that the lines below take none was
+// slower than on the tile kernel by more than 1.5 %, the median took 0.82 of its time; of all with one round of tiles, those of
+// many short segments took up to 1.8 times as long (1024 x 1024 x 1920, eight segments: 21.1 us on the tile kernel, 36.8 here).
 int ksplit_pick(const GemmArgs& a, const GemmTable& tb) {
   if (!ksplit_supported(a, tb)) return -1;
-  for (int t = 0; t < 3; ++t)
-    if (tile_count(a, t) <= device_cus()) return t;
-  return -1;
+  int tile = 0;
+  while (tile < 3 && tile_count(a, tile) > device_cus()) ++tile;
+  if (tile == 3) return -1;
+  const int S = tb.S;
+  int both = 0, one = 0;                                           // stages in segments with two paths / with one
+  for (int s = 0; s < S; ++s) (tb.dual[s] ? both : one) += (tb.kseg_off[s + 1] - tb.kseg_off[s]) >> 7;
+  bool earns;
+  if (tile == 1) {
+    earns = both > 0 ? 6 * both + one >= 128 * S + 16 : S == 1 && one >= 24;
+  } else if (both == 0) {
+    earns = tile == 2 ? S <= 2 : (S <= 3 || one >= 24 * S);
+  } else if (one == 0) {
+    earns = S <= 4 || both >= 2 * S;
+  } else {
+    earns = both + one >= 2 * S && 5 * both >= 2 * one + 12;
+  }
+  return earns ? tile : -1;
 }
 
 hipError_t launch_seglinear_ksplit(GemmArgs a, const GemmTable& tb, OutMode mode, int tile, hipStream_t st) {

@@ -95,7 +95,9 @@ hipError_t launch_seglinear_mfma_fp8(GemmArgs a, const GemmTable& tb, OutMode mo
 
 // seglinear_ksplit.hip : layers with few output tiles, the waves of a workgroup split K.  K and K-segment boundaries
 // % 128 == 0, at most eight K-segments, no seg_scale.
-// ksplit_pick: its tile for this layer, or -1 where the tile kernel is the faster one (or the only one).
+// ksplit_pick: its tile for this layer (0: 64 x 64, 1: 64 x 128, 2: 128 x 64), or -1 where the tile kernel is the faster one (or
+// the only one).
+bool ksplit_supported(const GemmArgs& a, const GemmTable& tb);
 int ksplit_pick(const GemmArgs& a, const GemmTable& tb);
 hipError_t launch_seglinear_ksplit(GemmArgs a, const GemmTable& tb, OutMode mode, int tile, hipStream_t st);
 

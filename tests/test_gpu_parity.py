@@ -1563,6 +1563,61 @@ def test_seglinear_ksplit(oracle, case):
         assert float(np.abs(y.cpu().numpy().astype(np.float64) - rd.y32.astype(np.float64)).max()) <= RTOL * float(np.abs(rd.y32).max())
 
 
+# Every K-splitting tile, forced: segments of 1, 9, 10, 13, 21 and more stages of 128 columns (the rings hold 9 and 6, the steady
+# state begins behind them), up to eight K-segments of either kind, ragged and odd edges, more tiles than compute units.
+KSPLIT_TILES = [
+    dict(M=1, N=1, seg=[128], dual=[1]),
+    dict(M=70, N=130, seg=[1152], dual=[1]),
+    dict(M=65, N=66, seg=[1280], dual=[0]),
+    dict(M=129, N=190, seg=[1664, 2688], dual=[1, 0]),
+    dict(M=33, N=8, seg=[128, 1152, 1152], dual=[0, 1, 1]),
+    dict(M=100, N=72, seg=[2944, 3840], dual=[0, 0]),
+    dict(M=200, N=257, seg=[128, 256, 128, 384, 1152, 128, 128, 1280], dual=[1, 0, 1, 1, 0, 0, 1, 1]),
+    dict(M=700, N=4100, seg=[256, 1408], dual=[1, 1]),
+]
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("case", KSPLIT_TILES, ids=lambda c: "%dx%dx%d_S%d" % (c["M"], sum(c["seg"]), c["N"], len(c["seg"])))
+def test_seglinear_ksplit_tiles(oracle, case, tile):
+    import torch
+
+    g = _gpu()
+    M, N, K = case["M"], case["N"], sum(case["seg"])
+    w = wl.random_layer(M, K, N, [0] + list(np.cumsum(case["seg"])), [0, N], case["dual"], seed=M + K + N + tile, x_dtype="bf16",
+                        act="gelu", with_bias=tile != 1)
+    _check_layer(oracle, g, w, 4, tile)
+    gl = g.GpuLayer(w)
+    gl.quantize_weight()
+    tok = torch.full((2, M, w.S), float("nan"), dtype=torch.float32, device=g.DEV)
+    sq.sq_quantize_act_dynamic(gl.layer, gl.x, gl.xq, tok)
+    y = torch.full((M, N), float("nan"), dtype=torch.float32, device=g.DEV)
+    sq.sq_tuning_set("force_path", 4)
+    sq.sq_tuning_set("gemm_variant", tile)
+    sq.sq_seglinear_dynamic(gl.layer, gl.xq, tok, gl.wq, 8, gl.wscale, gl.bias, y)
+    r = oracle.seglinear_dynamic(w.x, w.w, w.kseg_off, w.nseg_off, w.dual, None, w.bias, wbits=8)
+    assert float(np.abs(y.cpu().numpy().astype(np.float64) - r.y32.astype(np.float64)).max()) <= RTOL * float(np.abs(r.y32).max())
+
+
+def test_seglinear_ksplit_forced_elsewhere_is_refused():
+    """Nine K-segments, a 64-aligned segment, seg_scale: the forced call must not fall back to another kernel."""
+    import torch
+
+    g = _gpu()
+    for K, kseg, scale in ((1152, list(range(0, 1153, 128)), None), (256, [0, 64, 256], None), (256, [0, 256], [1.5])):
+        S = len(kseg) - 1
+        layer = sq.Layer(64, K, 64, kseg, [0, 64], [0] * S, [0.1] * S, [0.1] * S, scale)
+        q = torch.zeros((64, K), dtype=torch.int8, device=g.DEV)
+        ws, y = torch.ones((S, 64), device=g.DEV), torch.zeros((64, 64), device=g.DEV)
+        tok = torch.ones((2, 64, S), device=g.DEV)
+        sq.sq_seglinear(layer, q, q, ws, None, y)
+        sq.sq_tuning_set("force_path", 4)
+        for call in (lambda: sq.sq_seglinear(layer, q, q, ws, None, y), lambda: sq.sq_seglinear_dynamic(layer, q, tok, q, 8, ws, None, y)):
+            with pytest.raises(sq.SqError):
+                call()
+        sq.sq_tuning_set("force_path", -1)
+
+
 @pytest.mark.parametrize("case", DYNCASES)
 def test_seglinear_dynamic(oracle, case):
     """Per-token steps: codes and steps bit-exact against the oracle, outputs within the fp32 tolerance, for 8-bit and
