@@ -550,35 +550,41 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_kernel(const void* _
   }
 }
 
-// The same for aligned rows (K, the K-segment boundaries multiples of 16, 16-byte aligned pointers) of at most NCH loads of
-// 16 bytes per thread: TPR threads own a row and keep it in registers between the two passes, so the row is read once
+// The same for aligned rows (K, the K-segment boundaries multiples of 16, 16-byte aligned pointers) of at most NCH chunks of G
+// 16-byte loads per thread: TPR threads own a row and keep it in registers between the two passes, so the row is read once
 // (at large M the rows in flight on an XCD exceed its L2 and a second read goes back to memory), the loads are streaming and
-// the quotient is the reciprocal product of round_quotient (bit-identical to the division).  With a workgroup and 16
-// elements a thread for every row, a row of 1536 left 160 of 256 threads without work.
-template <bool BF16, int TPR, int NCH>
+// the quotient is the reciprocal product of round_quotient (bit-identical to the division).  G: 1, or a chunk of 16 elements, whose
+// segment tests, step reads and store are shared by its loads.
+template <bool BF16, int TPR, int NCH, int G>
 __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const void* __restrict__ x, int8_t* __restrict__ xq,
                                                                         float* __restrict__ tok_steps, int M, int K,
                                                                         const ActTable tb, const float qmax) {
   constexpr int CE = BF16 ? 8 : 4;                       // elements of a 16-byte load
+  constexpr int CC = G * CE;                             // elements of a chunk
   constexpr int RPW = 256 / TPR;                         // rows of the workgroup
+  static_assert(CC <= 16, "K and the boundaries are multiples of 16 only");
   const int t = threadIdx.x % TPR, wrow = threadIdx.x / TPR;
   const int mr = blockIdx.x * RPW + wrow;
   const int m = mr < M ? mr : M - 1;                     // rows beyond M do the last one again: same values, same places
   const size_t row = (size_t)m * K;
   __shared__ float red[2][4];
   __shared__ float stp[RPW][SQ_MAX_SEGMENTS][4];         // s_+, s_-, and their reciprocals (NaN: always divide)
-  v4i raw[NCH];
+  v4i raw[NCH][G];
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
-    const int col = (t + TPR * j) * CE;
-    raw[j] = (v4i)(0);
-    if (col < K)
-      raw[j] = BF16 ? __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const uint16_t*>(x) + row + col))
-                    : __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(x) + row + col));
+    const int col = (t + TPR * j) * CC;
+#pragma unroll
+    for (int l = 0; l < G; ++l) raw[j][l] = (v4i)(0);
+    if (col < K) {
+#pragma unroll
+      for (int l = 0; l < G; ++l)
+        raw[j][l] = BF16 ? __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const uint16_t*>(x) + row + col) + l)
+                         : __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(x) + row + col) + l);
+    }
   }
-  auto value = [&](const int j, const int e) __attribute__((always_inline)) -> float {   // element e of load j (constants)
-    if (!BF16) return __int_as_float(raw[j][e & 3]);
-    const uint32_t u = (uint32_t)raw[j][e >> 1];
+  auto value = [&](const int j, const int e) __attribute__((always_inline)) -> float {   // element e of chunk j (constants)
+    if (!BF16) return __int_as_float(raw[j][(e >> 2) % G][e & 3]);
+    const uint32_t u = (uint32_t)raw[j][(e >> 3) % G][(e >> 1) & 3];
     return __uint_as_float((e & 1) ? (u & 0xFFFF0000u) : (u << 16));
   };
   for (int ks = 0; ks < tb.S; ++ks) {
@@ -595,11 +601,11 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
       u16x2 hi_u = {0, 0};
 #pragma unroll
       for (int j = 0; j < NCH; ++j) {
-        const int col = (t + TPR * j) * CE;
+        const int col = (t + TPR * j) * CC;
         if (col < K && col >= k0 && col < k1) {
 #pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            const int w = raw[j][d];
+          for (int d = 0; d < 4 * G; ++d) {
+            const int w = raw[j][d / 4][d % 4];
             if (dual) {
               hi_s = __builtin_elementwise_max(hi_s, __builtin_bit_cast(s16x2, w));
               hi_u = __builtin_elementwise_max(hi_u, __builtin_bit_cast(u16x2, w));
@@ -620,10 +626,10 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
     } else {
 #pragma unroll
       for (int j = 0; j < NCH; ++j) {
-        const int col = (t + TPR * j) * CE;
+        const int col = (t + TPR * j) * CC;
         if (col < K && col >= k0 && col < k1) {
 #pragma unroll
-          for (int e = 0; e < CE; ++e) {
+          for (int e = 0; e < CC; ++e) {
             const float v = value(j, e);
             if (dual) {
               mp = __builtin_fmaxf(mp, v);
@@ -660,8 +666,10 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
     }
     if (TPR > 64) __syncthreads();                        // red is reused by the next segment; stp is complete after the last
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) asm volatile("" : "+v"(raw[j]));   // keep the row as loaded: widened copies held across the
-  }                                                                  // passes would cost half the occupancy
+    for (int j = 0; j < NCH; ++j)
+#pragma unroll
+      for (int l = 0; l < G; ++l) asm volatile("" : "+v"(raw[j][l]));   // keep the row as loaded: widened copies held across the
+  }                                                                     // passes would cost half the occupancy
   if (TPR == 64) {                                        // lane 0's steps, to this wave's other lanes
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -669,16 +677,16 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
   }
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
-    const int col = (t + TPR * j) * CE;
+    const int col = (t + TPR * j) * CC;
     if (col >= K) continue;
     int ks = 0;
     bool dual = tb.dual[0] != 0;
     for (int sg = 1; sg < tb.S; ++sg)
       if (col >= tb.kseg_off[sg]) { ks = sg; dual = tb.dual[sg] != 0; }
     const float sp = stp[wrow][ks][0], sn = stp[wrow][ks][1], ip = stp[wrow][ks][2], in = stp[wrow][ks][3];
-    int out[2];
+    int out[4];
 #pragma unroll
-    for (int q = 0; q < CE / 4; ++q) {
+    for (int q = 0; q < CC / 4; ++q) {
       int code[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -688,7 +696,8 @@ __global__ __launch_bounds__(256) void quantize_act_dynamic_fast_kernel(const vo
       }
       out[q] = (int)pack4(code[0], code[1], code[2], code[3]);
     }
-    if (BF16) *reinterpret_cast<v2i*>(xq + row + col) = (v2i){out[0], out[1]};
+    if (CC == 16) *reinterpret_cast<v4i*>(xq + row + col) = (v4i){out[0], out[1], out[2], out[3]};
+    else if (CC == 8) *reinterpret_cast<v2i*>(xq + row + col) = (v2i){out[0], out[1]};
     else *reinterpret_cast<int*>(xq + row + col) = out[0];
   }
 }
@@ -701,16 +710,27 @@ hipError_t launch_quantize_act_dynamic(const void* x, bool x_is_bf16, int8_t* xq
     // Threads per row: a workgroup and the fewest loads per thread that hold the row, except where that leaves a quarter of the
     // threads or more without work and there are rows enough: up to 192 loads on a wave (8500 x 1536 bf16: 18.3 -> 13.6 us,
     // fp32 on half a workgroup 22.3 -> 16.9), 257 - 384 on half a workgroup (4096 x 3072 bf16, two K-segments: 15.4 -> 14.2).
-    // Wider rows on fewer threads are slower (4096 x 4096 on a wave 18.5 us, on a workgroup 15.2), and few rows are a matter
-    // of latency (16 x 1152: a workgroup each 3.1 us, a wave each 4.6).
+    // Wider rows on fewer threads are slower (4096 x 4096 on a wave 18.5 us, on a workgroup 15.2), few rows are a matter
+    // of latency (a workgroup each and a wave each: 16 x 1152 3.1 and 4.6 us, 1024 x 1536 4.4 and 5.8, 1500 x 1024 4.8 and 4.8,
+    // 2048 x 512 4.9 and 4.1).
     const int loads = K / (x_is_bf16 ? 8 : 4);
-#define SQ_D(B, T, N) hipLaunchKernelGGL((quantize_act_dynamic_fast_kernel<B, T, N>), dim3((M + 256 / T - 1) / (256 / T)), dim3(256), 0, st, x, xq, tok_steps, M, K, tb, qmax)
+    // Chunks of 16 elements instead of single loads: a workgroup's chunks fit such a row as well (up to 4096 columns and the
+    // lengths beyond 6144; between them a second, nearly empty chunk per thread), and with about a row per compute unit or fewer the work
+    // on each load shows (fp32 16 x 12288: 7.6 us, by single loads 9.7; 64 x 4096 4.6 and 5.1), as it does for the lengths that
+    // one chunk per thread covers (bf16 2048 x 4096 8.4 and 8.8) and where 32 single loads cost the occupancy (fp32 4096 x 30720
+    // 181 and 198).
+    const bool chunks = K > 2048 && ((M <= device_cus() * 5 / 4 && (K <= 4096 || K > 6144)) || (x_is_bf16 ? K > 3072 && K <= 4096 : K > 16384));
+#define SQ_D(B, T, N, G) hipLaunchKernelGGL((quantize_act_dynamic_fast_kernel<B, T, N, G>), dim3((M + 256 / T - 1) / (256 / T)), dim3(256), 0, st, x, xq, tok_steps, M, K, tb, qmax)
 #define SQ_DN(B) do { \
-    if (M >= 1024 && loads <= 192) SQ_D(B, 64, 3); \
-    else if (M >= 1024 && loads > 256 && loads <= 384) SQ_D(B, 128, 3); \
-    else if (loads <= 256) SQ_D(B, 256, 1); else if (loads <= 512) SQ_D(B, 256, 2); else if (loads <= 768) SQ_D(B, 256, 3); \
-    else if (loads <= 1024) SQ_D(B, 256, 4); else if (loads <= 1536) SQ_D(B, 256, 6); else if (loads <= 2048) SQ_D(B, 256, 8); \
-    else if (loads <= 4096) SQ_D(B, 256, 16); else SQ_D(B, 256, B ? 16 : 32); } while (0)
+    constexpr int C16 = B ? 2 : 4; \
+    if (chunks) { \
+      if (K <= 4096) SQ_D(B, 256, 1, C16); else if (K <= 8192) SQ_D(B, 256, 2, C16); else if (K <= 16384) SQ_D(B, 256, 4, C16); \
+      else SQ_D(B, 256, 8, C16); \
+    } else if (M >= (loads <= 64 ? 1024 : loads <= 128 ? 1536 : 2048) && loads <= 192) SQ_D(B, 64, 3, 1); \
+    else if (M >= 2048 && loads > 256 && loads <= 384) SQ_D(B, 128, 3, 1); \
+    else if (loads <= 256) SQ_D(B, 256, 1, 1); else if (loads <= 512) SQ_D(B, 256, 2, 1); else if (loads <= 768) SQ_D(B, 256, 3, 1); \
+    else if (loads <= 1024) SQ_D(B, 256, 4, 1); else if (loads <= 1536) SQ_D(B, 256, 6, 1); else if (loads <= 2048) SQ_D(B, 256, 8, 1); \
+    else SQ_D(B, 256, 16, 1); } while (0)
     if (x_is_bf16) SQ_DN(true); else SQ_DN(false);
 #undef SQ_DN
 #undef SQ_D
