@@ -430,8 +430,14 @@ __global__ __launch_bounds__(256) void quantize_weight_row_kernel(const void* __
   }
 }
 
-// Threads and loads per row segment by the longest segment: a wave for up to 1024 fp32 (2048 bf16) columns, a workgroup
-// beyond; longer rows than a workgroup's registers hold (16384 / 32768 columns) and unaligned ones keep the two-read kernels.
+// Threads and loads per row segment by the longest segment: a wave for up to 2048 fp32 (4096 bf16) columns, a workgroup beyond
+// 1024 (2048) where there are too few segments to give every compute unit eight waves, and always beyond 2048 (4096); longer
+// rows than a workgroup's registers hold (16384 / 32768 columns) and unaligned ones keep the two-read kernels.  So do short
+// segments that leave most of a wave without work (to the left this kernel, to the right the two-read one: bf16 13824 rows of
+// 256, 8 bit 7.8 / 6.8 us, 384, 4 bit 10.1 / 9.2, 512, 4 bit 10.6 / 11.7; fp32 13824 rows of 128, 4 bit 7.1 / 6.6).  A wave
+// against a workgroup: fp32 6912 x 1152, 8 bit 8.6 / 12.5 us (two-read 10.7), 384 x 1152 4.1 / 3.8.  One long segment among
+// many short ones, each of which would get as many threads, goes there too (fp32 3072 x 3200, 2176 columns and eight times 128,
+// 8 bit 31.0 / 19.8; 1024 x 16384, 16000 columns and three times 128, 42 / 46).
 template <int BITS>
 static bool launch_weight_rows(const void* w, bool w_is_bf16, uint8_t* out, float* wscale, int N, int K, const KsegTable& tb,
                                hipStream_t st) {
@@ -443,11 +449,14 @@ static bool launch_weight_rows(const void* w, bool w_is_bf16, uint8_t* out, floa
     longest = L > longest ? L : longest;
     ok = ok && tb.off[s] % ce == 0;
   }
-  if (!ok || longest > 256 * 16 * ce) return false;
+  const int shortest = w_is_bf16 ? (BITS == 8 ? 257 : 385) : (BITS == 8 ? 1 : 129);
+  if (!ok || longest > 256 * 16 * ce || longest < shortest) return false;
+  if (longest > 64 * 4 * ce && (BITS == 8 ? 4ll : 6ll) * K < (long long)tb.S * longest) return false;
   const long items = (long)(BITS == 4 ? (N + 15) & ~15 : N) * tb.S;
 #define SQ_ROWS(B, T, C) hipLaunchKernelGGL((quantize_weight_row_kernel<B, BITS, T, C>), dim3((unsigned)((items + 256 / T - 1) / (256 / T))), dim3(256), 0, st, w, out, wscale, N, K, tb)
 #define SQ_PICK(B) \
   if (longest <= 64 * 4 * ce) SQ_ROWS(B, 64, 4); \
+  else if (longest <= 64 * 8 * ce && items >= 2048) SQ_ROWS(B, 64, 8); \
   else if (longest <= 256 * 4 * ce) SQ_ROWS(B, 256, 4); \
   else if (longest <= 256 * 8 * ce) SQ_ROWS(B, 256, 8); \
   else SQ_ROWS(B, 256, 16)

@@ -652,6 +652,33 @@ def test_calibration_pass_shares(oracle, shape, dt):
         assert np.array_equal(amax.cpu().numpy(), np.stack([r[2], r[3]])), p
 
 
+@pytest.mark.parametrize("w_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,kseg", [(2051, [0, 1152]), (2051, [0, 2048]), (1030, [0, 2176, 4352]), (2051, [0, 4096]), (3001, [0, 256]), (3001, [0, 384]),
+                                    (517, [0, 512]), (70, [0, 2176] + [2176 + 128 * i for i in range(1, 9)]), (300, [0, 128, 256, 384, 8448])],
+                         ids=lambda v: str(v) if isinstance(v, int) else "%d_S%d" % (v[-1], len(v) - 1))
+def test_quantize_weight_row_shares(oracle, N, kseg, w_dtype):
+    """The choice between a wave, a workgroup and the two-read kernel: many and few rows on either side of its lines, short
+    segments, one long segment among short ones; 8- and 4-bit codes and steps, N not a multiple of 16."""
+    import torch
+
+    g = _gpu()
+    K = kseg[-1]
+    w = wl.random_layer(2, K, N, kseg, [0, N], [1] * (len(kseg) - 1), seed=N + K, w_std=0.05)
+    w.w[N - 1, : kseg[1]] = 0.0
+    w.w[7, K - 1] = 3.0
+    if w_dtype == "bf16":
+        w.w = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(w.w))
+    gl = g.GpuLayer(w, w_dtype=w_dtype)
+    wq, ws = gl.quantize_weight()
+    rq, rs = oracle.quantize_weight(w.w, w.kseg_off)
+    assert np.array_equal(ws.view(np.uint32), rs.view(np.uint32)) and np.array_equal(wq, rq)
+    w4 = torch.full(((N + 15) // 16 * 16 * K // 2,), 0x5A, dtype=torch.uint8, device=g.DEV)
+    sq.sq_quantize_weight_w4(gl.layer, gl.wt, w4, gl.wscale)
+    r4, rs4 = oracle.quantize_weight_w4(w.w, w.kseg_off)
+    assert np.array_equal(gl.wscale.cpu().numpy().view(np.uint32), rs4.view(np.uint32))
+    assert np.array_equal(w4.cpu().numpy(), oracle.pack_w4(r4))
+
+
 WBLOCK = [
     dict(N=384, K=256, kseg=[0, 128, 256], nseg=[0, 128, 256, 384], w_dtype="f32"),
     dict(N=70, K=100, kseg=[0, 37, 100], nseg=[0, 5, 70], w_dtype="f32"),           # unaligned
