@@ -154,7 +154,9 @@ static hipError_t launch_quantize_act_impl(const void* x, bool x_is_bf16, int8_t
 constexpr int kTabThreads = 1024;
 constexpr int kTabTop = (127 + 5) << 7;                  // first magnitude pattern beyond the table: 32.0
 constexpr int kTabBytes = 0x8000 + kTabTop;              // indexed by the 16-bit pattern, both signs
-constexpr int kTabBinades = 28;                          // widest table: beyond, the direct path
+constexpr int kTabUnit = 8192;                           // elements per compute unit for which a table of kTabBinades pays ...
+constexpr int kTabBinades = 28;
+constexpr int kTabMoreBinades = 12;                      // ... and what another kTabUnit pays for
 
 struct TabPlan {
   int wg_begin[SQ_MAX_SEGMENTS + 1];                     // workgroups [wg_begin[s], wg_begin[s+1]) stream K-segment s
@@ -232,13 +234,17 @@ __global__ __launch_bounds__(kTabThreads) void quantize_act_table_kernel(const u
 
 size_t quantize_act_fused_workspace_bytes(int S) { return (size_t)S * 65536; }
 
-// The table kernel's launch, or false where the direct path serves: no activation, fp32 or unaligned input, steps so small that
-// the table would be wide, or a matrix too small for the fill (below 8192 elements per compute unit; 333 x 6144 bf16, the most
-// that goes direct: 6.2 us).
+// The table kernel's launch, or false where the direct path serves: no activation, fp32 or unaligned input, or a matrix too small
+// for the fill.  A binade of both signs costs a workgroup 0.08 - 0.1 us, an element 0.4 ns of a compute unit's time less than the
+// direct path.  Table / direct in us, int8 and fp8: 348 x 6144 (8352 elements per compute unit), 13 - 27 binades 5.5 - 6.8 / 6.1 -
+// 6.6, 46 binades 8.6 / 6.4; 683 x 6144, 33 binades 7.5 / 8.3, 47 binades 8.9 / 8.4; 2048 x 4608, 65 binades 12.9 / 13.4, 125
+// binades 18.9 / 13.4 (fp8 steps of 2^-50, 2^-110); 4608 x 15360, 29 binades 41.3 / 73.1 (fp8 step 2^-14).
 bool launch_quantize_act_table(const void* h, bool h_is_bf16, int8_t* xq, int M, int K, const ActTable& tb, int cus, hipStream_t st,
                                bool fp8) {
   bool ok = h_is_bf16 && (K % kActChunk == 0) && (reinterpret_cast<uintptr_t>(h) % 16 == 0) &&
-            (reinterpret_cast<uintptr_t>(xq) % 16 == 0) && (long long)M * K >= 8192ll * cus;
+            (reinterpret_cast<uintptr_t>(xq) % 16 == 0) && (long long)M * K >= (long long)kTabUnit * cus;
+  const long long more = (long long)kTabMoreBinades * M * K / ((long long)kTabUnit * cus) - kTabMoreBinades;
+  const int lowest = more > 126 ? -126 : 5 - kTabBinades - (int)more < -126 ? -126 : 5 - kTabBinades - (int)more;
   bool any = false;
   TabPlan plan;
   const int total = cus > tb.S ? cus : tb.S;             // dealt to the K-segments in proportion to their width, one at least
@@ -250,7 +256,7 @@ bool launch_quantize_act_table(const void* h, bool h_is_bf16, int8_t* xq, int M,
     int e = 0;
     (void)std::frexp(step, &e);                          // step in [2^(e-1), 2^e)
     const int lo = e - 1 - (fp8 ? 10 : 1);               // 2^lo <= step / 2 (fp8: step / 2^10)
-    if (lo < 5 - kTabBinades || lo > 4) ok = false;
+    if (lo < lowest || lo > 4) ok = false;
     plan.low[s] = (127 + lo) << 7;
     plan.wg_begin[s + 1] = plan.wg_begin[s] + 1 + (int)((long long)(total - tb.S) * (tb.kseg_off[s + 1] - tb.kseg_off[s]) / K);
   }

@@ -225,6 +225,38 @@ def test_quantize_act_fused_table(oracle, steps, fp8):
     assert np.array_equal(xq.cpu().numpy(), both)
 
 
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("steps", [(0.04, 0.0014), (0.02, 6e-5), (1e-9, 3e-4)])
+def test_quantize_act_fused_table_many_chunks(steps, fp8):
+    """Several chunks per thread, ragged rows and segment widths, tables of up to 40 binades, every bf16 pattern: the whole matrix
+    bit for bit what the same rows give in calls too small for the table, which take the arithmetic per element."""
+    import torch
+
+    g = _gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    kseg, dual, act = [0, 1040, 1056, 4112, 6160], [1, 0, 1, 0], [2, 1, 1, 0]
+    K = kseg[-1]
+    M = 40000 * cus // K + 1                                   # 2.4 chunks of 16 per thread of the table kernel
+    gen = torch.Generator(device=g.DEV)
+    gen.manual_seed(int(steps[1] * 1e7))
+    x = (torch.randn((M, K), generator=gen, device=g.DEV) * 3.0).to(torch.bfloat16)
+    some = torch.rand((M, K // 16), generator=gen, device=g.DEV) < 0.2
+    bits = torch.randint(-32768, 32768, (M, K), generator=gen, device=g.DEV, dtype=torch.int32).to(torch.int16)
+    bits = torch.where((bits & 0x7F80) == 0x7F80, torch.zeros_like(bits), bits)
+    x = torch.where(some.repeat_interleave(16, dim=1), bits.view(torch.bfloat16), x)
+    sp, sn = [steps[0]] * 4, [steps[1]] * 4
+    dt, call = (torch.uint8, sq.sq_quantize_act_fp8_fused) if fp8 else (torch.int8, sq.sq_quantize_act_fused)
+
+    def codes(r0, r1):
+        xq = torch.full((r1 - r0, K), 99, dtype=dt, device=g.DEV)
+        call(sq.Layer(r1 - r0, K, 16, kseg, [0, 16], dual, sp, sn), x[r0:r1], act, xq)
+        return xq
+
+    step = 8192 * cus // K - 1                                 # below 8192 elements per compute unit
+    parts = torch.cat([codes(r, min(r + step, M)) for r in range(0, M, step)])
+    assert torch.equal(codes(0, M), parts)
+
+
 @pytest.mark.parametrize("act", [1, 2])
 def test_quantize_act_fused_exhaustive_bf16_and_dense_f32(oracle, act):
     """Every finite bf16 value, and 4 M fp32 values spread over the magnitudes that matter, through the fused pass."""
