@@ -47,15 +47,14 @@ struct KsplitCfg {
   static constexpr int IM = BM / WM / 32, JN = BN / WN / 32;       // 32x32 blocks of a wave
   static constexpr int STAGE = (BM + BN) * 128;
   static constexpr int GA = BM / 8 / NW;                           // direct loads of a wave and stage: X^ rows ...
-  static constexpr int GBT = BN / 8;                               // ... W^ rows: load g of the stage goes to wave g % NW
-  static constexpr int GB = (GBT + NW - 1) / NW;
+  static constexpr int GB = BN / 8 / NW;                           // ... and W^ rows
   static constexpr int NU = 2 * IM * JN, UPW = NU / KW;            // half-blocks of a wave's part, and of its owner's share
   static constexpr int POL = DUAL ? 2 : 1;
   static constexpr int XPHASE = NW * KW * POL * 2048;              // exchange: one half-block per owner, all waves
   static constexpr int RAW = 144 * 1024 / STAGE;
   static constexpr int NS = RAW > 9 ? 9 : RAW;
   static constexpr int LDS = NS * STAGE > XPHASE ? NS * STAGE : XPHASE;
-  static_assert(BM % (8 * NW) == 0 && BN % 32 == 0 && NU % KW == 0, "tile");
+  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && NU % KW == 0, "tile");
   static_assert(NS >= 3 && LDS <= 160 * 1024, "LDS budget");
 };
 
@@ -69,18 +68,19 @@ __global__ __launch_bounds__(WM * WN * 256, 2) void seglinear_ksplit_kernel(cons
   const int kw = wave & 3, part = wave >> 2;
   const int wm = part / WN, wn = part % WN;
 
-  // tiles of this workgroup: each XCD (workgroup ids are dealt round-robin) walks a contiguous run of the list, ordered in
-  // panels of group_m row tiles, so that the tiles in flight on an XCD share operand rows in its L2
+  // the workgroup's tile (one each, the grid is the tile list): each XCD (workgroup ids are dealt round-robin) takes a contiguous run
+  // of the list, ordered in panels of group_m row tiles, so that the tiles on an XCD share operand rows in its L2
   const int ntiles = a.tiles_m * a.tiles_n;
-  const int xcd = blockIdx.x & 7, xlocal = blockIdx.x >> 3;
-  const int xper = ntiles >> 3, xrem = ntiles & 7;
-  const int xstart = xcd < xrem ? xcd * (xper + 1) : xrem * (xper + 1) + (xcd - xrem) * xper;
-  const int xcnt = xper + (xcd < xrem ? 1 : 0);
-  const int xwg = (int)(gridDim.x >> 3) + (xcd < (int)(gridDim.x & 7) ? 1 : 0);
+  const int xcd = blockIdx.x & 7, xper = ntiles >> 3, xrem = ntiles & 7;
+  const int logical = (xcd < xrem ? xcd * (xper + 1) : xrem * (xper + 1) + (xcd - xrem) * xper) + (blockIdx.x >> 3);
+  const int gsz = a.group_m * a.tiles_n, g = logical / gsz, in = logical - g * gsz, first = g * a.group_m;
+  const int gm = (a.tiles_m - first) < a.group_m ? (a.tiles_m - first) : a.group_m;
+  const int tn = in / gm;
+  const int m0 = (first + (in - tn * gm)) * BM, n0 = tn * BN;
 
   const uint32_t lds0 = (uint32_t)(uintptr_t)SQ_LDS(smem);
   const int lrow = lane >> 3, lslot = lane & 7;
-  const int lw = GA + C::GBT / NW + (wave < C::GBT % NW ? 1 : 0);  // direct loads of this wave per stage
+  constexpr int NL = GA + GB;                                      // direct loads of a wave per stage
   const int frow = lane & 31;
   const int foff = frow * 128 + (((2 * kw + (lane >> 5)) ^ row_swizzle<128>(frow)) << 4);
   const char* fragA = smem + wm * (IM * 32 * 128) + foff;
@@ -89,346 +89,333 @@ __global__ __launch_bounds__(WM * WN * 256, 2) void seglinear_ksplit_kernel(cons
                                         reinterpret_cast<uintptr_t>(a.bias) | reinterpret_cast<uintptr_t>(a.acc_pos) |
                                         reinterpret_cast<uintptr_t>(a.acc_neg)) % 16 == 0);
 
-#pragma unroll 1
-  for (int t = xlocal; t < xcnt; t += xwg) {
-    const int logical = xstart + t;
-    const int gsz = a.group_m * a.tiles_n, g = logical / gsz, in = logical - g * gsz, first = g * a.group_m;
-    const int gm = (a.tiles_m - first) < a.group_m ? (a.tiles_m - first) : a.group_m;
-    const int tn = in / gm;
-    const int m0 = (first + (in - tn * gm)) * BM, n0 = tn * BN;
+  uint32_t voffA[GA], voffB[GB];
+#pragma unroll
+  for (int e = 0; e < GA; ++e) {
+    const int rt = (e * NW + wave) * 8 + lrow;
+    int r = m0 + rt;
+    r = r < a.M ? r : a.M - 1;                                   // ragged tail: re-read the last row, masked at the store
+    voffA[e] = (uint32_t)r * (uint32_t)a.K + (uint32_t)((lslot ^ row_swizzle<128>(rt)) << 4);
+  }
+#pragma unroll
+  for (int e = 0; e < GB; ++e) {
+    const int rt = (e * NW + wave) * 8 + lrow;
+    int r = n0 + rt;
+    r = r < a.N ? r : a.N - 1;
+    voffB[e] = (uint32_t)r * (uint32_t)a.K + (uint32_t)((lslot ^ row_swizzle<128>(rt)) << 4);
+  }
 
-    uint32_t voffA[GA], voffB[GB];
+  v8f fsum[MULTI ? UPW : 1];
 #pragma unroll
-    for (int e = 0; e < GA; ++e) {
-      const int rt = (e * NW + wave) * 8 + lrow;
-      int r = m0 + rt;
-      r = r < a.M ? r : a.M - 1;                                   // ragged tail: re-read the last row, masked at the store
-      voffA[e] = (uint32_t)r * (uint32_t)a.K + (uint32_t)((lslot ^ row_swizzle<128>(rt)) << 4);
-    }
-#pragma unroll
-    for (int e = 0; e < GB; ++e) {
-      const int rt = (e * NW + wave) * 8 + lrow;
-      int r = n0 + rt;
-      r = r < a.N ? r : a.N - 1;
-      voffB[e] = (uint32_t)r * (uint32_t)a.K + (uint32_t)((lslot ^ row_swizzle<128>(rt)) << 4);
-    }
-
-    v8f fsum[MULTI ? UPW : 1];
-#pragma unroll
-    for (int u = 0; u < (MULTI ? UPW : 1); ++u) fsum[u] = (v8f)(0.0f);
+  for (int u = 0; u < (MULTI ? UPW : 1); ++u) fsum[u] = (v8f)(0.0f);
 
 #pragma unroll 1
-    for (int ks = 0; ks < (MULTI ? tb.S : 1); ++ks) {
-      const int kbeg = MULTI ? tb.kseg_off[ks] : 0, n = ((MULTI ? tb.kseg_off[ks + 1] : a.K) - kbeg) >> 7;   // stages of the segment
-      const bool dl = DUAL && (!MULTI || tb.dual[ks] != 0);
-      const int8_t* xbase = a.xq + kbeg;
-      const int8_t* wbase = a.wq + kbeg;
-      auto uniform_ptr = [](const int8_t* p) __attribute__((always_inline)) {
-        const uint64_t u = reinterpret_cast<uint64_t>(p);
-        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-        return reinterpret_cast<const int8_t*>(((uint64_t)hi << 32) | lo);
-      };
-      int islot = 0, rslot = 0;                                    // ring slots of the next stage to fetch / to read
-      const int8_t *pa = xbase, *pb = wbase;                       // operand bases of the next stage to fetch
-      uint32_t so = 0;
-      auto issue_begin = [&]() __attribute__((always_inline)) {
-        so = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)islot * (uint32_t)STAGE + (uint32_t)wave * 1024u);
-        pa = uniform_ptr(pa);
-        pb = uniform_ptr(pb);
-      };
-      auto issue_load = [&](const int e) __attribute__((always_inline)) {   // e is a compile-time constant after unrolling
-        if (e < GA) {
-          glds16(pa, voffA[e < GA ? e : 0], so + (uint32_t)(e * NW) * 1024u);
-        } else {
-          const int g = e - GA;
-          if ((g + 1) * NW <= C::GBT || g * NW + wave < C::GBT) glds16(pb, voffB[g >= 0 ? g : 0], so + (uint32_t)(BM / 8 + g * NW) * 1024u);
-        }
-      };
-      auto issue_end = [&]() __attribute__((always_inline)) {
-        islot = (islot + 1 == NS) ? 0 : islot + 1;
-        pa += 128;
-        pb += 128;
-      };
-      // all loads of this wave up to a stage have landed when at most `after` later stages are outstanding
-      auto wait_after = [&](const int after) __attribute__((always_inline)) {
-        const int left = after * lw;
-        if (left >= 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-        else if (left >= 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-        else if (left >= 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-        else if (left >= 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      };
+  for (int ks = 0; ks < (MULTI ? tb.S : 1); ++ks) {
+    const int kbeg = MULTI ? tb.kseg_off[ks] : 0, n = ((MULTI ? tb.kseg_off[ks + 1] : a.K) - kbeg) >> 7;   // stages of the segment
+    const bool dl = DUAL && (!MULTI || tb.dual[ks] != 0);
+    const int8_t* xbase = a.xq + kbeg;
+    const int8_t* wbase = a.wq + kbeg;
+    auto uniform_ptr = [](const int8_t* p) __attribute__((always_inline)) {
+      const uint64_t u = reinterpret_cast<uint64_t>(p);
+      const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+      return reinterpret_cast<const int8_t*>(((uint64_t)hi << 32) | lo);
+    };
+    int islot = 0, rslot = 0;                                    // ring slots of the next stage to fetch / to read
+    const int8_t *pa = xbase, *pb = wbase;                       // operand bases of the next stage to fetch
+    uint32_t so = 0;
+    auto issue_begin = [&]() __attribute__((always_inline)) {
+      so = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)islot * (uint32_t)STAGE + (uint32_t)wave * 1024u);
+      pa = uniform_ptr(pa);
+      pb = uniform_ptr(pb);
+    };
+    auto issue_load = [&](const int e) __attribute__((always_inline)) {   // e is a compile-time constant after unrolling
+      if (e < GA) {
+        glds16(pa, voffA[e < GA ? e : 0], so + (uint32_t)(e * NW) * 1024u);
+      } else {
+        const int g = e - GA;
+        glds16(pb, voffB[g >= 0 ? g : 0], so + (uint32_t)(BM / 8 + g * NW) * 1024u);
+      }
+    };
+    auto issue_end = [&]() __attribute__((always_inline)) {
+      islot = (islot + 1 == NS) ? 0 : islot + 1;
+      pa += 128;
+      pb += 128;
+    };
+    // all loads of this wave up to a stage have landed when at most `after` later stages are outstanding
+    auto wait_after = [&](const int after) __attribute__((always_inline)) {
+      const int left = after * NL;
+      if (left >= 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+      else if (left >= 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+      else if (left >= 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+      else if (left >= 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
 
-      v16i accp[IM][JN], accn[DUAL ? IM : 1][DUAL ? JN : 1];
+    v16i accp[IM][JN], accn[DUAL ? IM : 1][DUAL ? JN : 1];
 #pragma unroll
-      for (int i = 0; i < IM; ++i)
+    for (int i = 0; i < IM; ++i)
 #pragma unroll
-        for (int j = 0; j < JN; ++j) {
-          accp[i][j] = (v16i)(0);
-          if (DUAL) accn[i][j] = (v16i)(0);
-        }
-      v4i ap[2][IM], an[2][DUAL ? IM : 1], bf[JN - 1], bl[2];     // bl: the last block column, two sets
+      for (int j = 0; j < JN; ++j) {
+        accp[i][j] = (v16i)(0);
+        if (DUAL) accn[i][j] = (v16i)(0);
+      }
+    v4i ap[2][IM], an[2][DUAL ? IM : 1], bf[JN - 1], bl[2];     // bl: the last block column, two sets
 
-      // The MFMAs of one stage (set c), one per slot, interleaved with the fragment reads of the next stage, (DL) their
-      // polarity separation and the direct loads of stage s + NS.  Block column by block column, so that a column's W^
-      // fragment register is refilled right behind its last use; the last column has two sets, so that no read is young at
-      // the barrier.
-      auto iter = [&](auto dl_tag, auto c_tag, auto pf_tag, auto more_tag, const int s) __attribute__((always_inline)) {
-        constexpr bool DL = decltype(dl_tag)::value;
-        constexpr bool PF = decltype(pf_tag)::value;
-        constexpr int c = decltype(c_tag)::value, NP = DL ? 2 : 1, NM = IM * JN * NP, NL = GA + GB;
-        constexpr int QV_RAW = IM + 2, QV0 = QV_RAW < NM - 1 ? QV_RAW : NM - 1;        // first slot with separation work
-        constexpr int ND = DL ? IM * 4 : 0, DPS = ND ? (ND + NM - QV0 - 1) / (NM - QV0) : 0;
-        constexpr bool ALWAYS = decltype(more_tag)::value;         // there are stages left to fetch: the steady state
-        const bool more = PF && (ALWAYS || s + NS < n);
-        if (PF) {
-          if (ALWAYS) {                                            // a constant, two of them where the W^ loads are uneven
-            if (C::GBT % NW == 0 || lw == NL) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NL) : "memory");
-            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * (NL - 1)) : "memory");
-          } else {
-            wait_after((s + NS < n ? s + NS : n) - (s + 2));
-          }
-          __syncthreads();                                         // stage s + 1 is published, stage s is read by everybody
-          rslot = (rslot + 1 == NS) ? 0 : rslot + 1;
-          issue_begin();
-        }
-        const char* fa = fragA + rslot * STAGE;
-        const char* fb = fragB + rslot * STAGE;
+    // The MFMAs of one stage (set c), one per slot, interleaved with the fragment reads of the next stage, (DL) their
+    // polarity separation and the direct loads of stage s + NS.  Block column by block column, so that a column's W^
+    // fragment register is refilled right behind its last use; the last column has two sets, so that no read is young at
+    // the barrier.
+    auto iter = [&](auto dl_tag, auto c_tag, auto pf_tag, auto more_tag, const int s) __attribute__((always_inline)) {
+      constexpr bool DL = decltype(dl_tag)::value;
+      constexpr bool PF = decltype(pf_tag)::value;
+      constexpr int c = decltype(c_tag)::value, NP = DL ? 2 : 1, NM = IM * JN * NP;
+      constexpr int QV_RAW = IM + 2, QV0 = QV_RAW < NM - 1 ? QV_RAW : NM - 1;        // first slot with separation work
+      constexpr int ND = DL ? IM * 4 : 0, DPS = ND ? (ND + NM - QV0 - 1) / (NM - QV0) : 0;
+      constexpr bool ALWAYS = decltype(more_tag)::value;         // there are stages left to fetch: the steady state
+      const bool more = PF && (ALWAYS || s + NS < n);
+      if (PF) {
+        if (ALWAYS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NL) : "memory");
+        else wait_after((s + NS < n ? s + NS : n) - (s + 2));
+        __syncthreads();                                         // stage s + 1 is published, stage s is read by everybody
+        rslot = (rslot + 1 == NS) ? 0 : rslot + 1;
+        issue_begin();
+      }
+      const char* fa = fragA + rslot * STAGE;
+      const char* fb = fragB + rslot * STAGE;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < NM; ++q) {
+        const int j = q / (IM * NP), i = (q / NP) % IM;
+        const v4i bv = j + 1 < JN ? bf[j + 1 < JN ? j : 0] : bl[c];
+        if (NP == 1 || q % NP == 0) accp[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bv, ap[c][i], accp[i][j], 0, 0, 0);
+        else accn[DUAL ? i : 0][DUAL ? j : 0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bv, an[c][DUAL ? i : 0], accn[DUAL ? i : 0][DUAL ? j : 0], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
+        if (PF) {
+          if (q < IM) ap[c ^ 1][q < IM ? q : 0] = *reinterpret_cast<const v4i*>(fa + (q < IM ? q : 0) * (32 * 128));
+          if (q == (IM < NM ? IM - 1 : 0)) bl[c ^ 1] = *reinterpret_cast<const v4i*>(fb + (JN - 1) * (32 * 128));
+          if (j + 1 < JN && q % (IM * NP) == IM * NP - 1) bf[j + 1 < JN ? j : 0] = *reinterpret_cast<const v4i*>(fb + j * (32 * 128));
+          if (ND && q >= QV0) {
 #pragma unroll
-        for (int q = 0; q < NM; ++q) {
-          const int j = q / (IM * NP), i = (q / NP) % IM;
-          const v4i bv = j + 1 < JN ? bf[j + 1 < JN ? j : 0] : bl[c];
-          if (NP == 1 || q % NP == 0) accp[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bv, ap[c][i], accp[i][j], 0, 0, 0);
-          else accn[DUAL ? i : 0][DUAL ? j : 0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bv, an[c][DUAL ? i : 0], accn[DUAL ? i : 0][DUAL ? j : 0], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-          if (PF) {
-            if (q < IM) ap[c ^ 1][q < IM ? q : 0] = *reinterpret_cast<const v4i*>(fa + (q < IM ? q : 0) * (32 * 128));
-            if (q == (IM < NM ? IM - 1 : 0)) bl[c ^ 1] = *reinterpret_cast<const v4i*>(fb + (JN - 1) * (32 * 128));
-            if (j + 1 < JN && q % (IM * NP) == IM * NP - 1) bf[j + 1 < JN ? j : 0] = *reinterpret_cast<const v4i*>(fb + j * (32 * 128));
-            if (ND && q >= QV0) {
-#pragma unroll
-              for (int d = 0; d < DPS; ++d) {
-                const int w = (q - QV0) * DPS + d;
-                if (w < ND) {
-                  int neg = negative_codes(ap[c ^ 1][w / 4][w % 4]);
-                  asm volatile("" : "+v"(neg));                    // done here, not sunk behind the next barrier
-                  an[c ^ 1][DUAL ? w / 4 : 0][w % 4] = neg;
-                }
+            for (int d = 0; d < DPS; ++d) {
+              const int w = (q - QV0) * DPS + d;
+              if (w < ND) {
+                int neg = negative_codes(ap[c ^ 1][w / 4][w % 4]);
+                asm volatile("" : "+v"(neg));                    // done here, not sunk behind the next barrier
+                an[c ^ 1][DUAL ? w / 4 : 0][w % 4] = neg;
               }
             }
-#pragma unroll
-            for (int e = 0; e < NL; ++e) {                         // spread over the slots behind the X^ reads
-              constexpr int Q0 = IM < NM ? IM : NM - 1;
-              if (Q0 + e * (NM - Q0) / NL == q && more) issue_load(e);
-            }
           }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (more) issue_end();
-      };
-      auto k_loop = [&](auto dl_tag) __attribute__((always_inline)) {
-        constexpr bool DL = decltype(dl_tag)::value;
-        std::integral_constant<int, 0> c0;
-        std::integral_constant<int, 1> c1;
-        const int np = n < NS ? n : NS;
-#pragma unroll 1
-        for (int s = 0; s < np; ++s) {
-          issue_begin();
 #pragma unroll
-          for (int e = 0; e < GA + GB; ++e) issue_load(e);
-          issue_end();
-        }
-        wait_after(np - 1);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < IM; ++i) ap[0][i] = *reinterpret_cast<const v4i*>(fragA + i * (32 * 128));
-#pragma unroll
-        for (int j = 0; j + 1 < JN; ++j) bf[j] = *reinterpret_cast<const v4i*>(fragB + j * (32 * 128));
-        bl[0] = *reinterpret_cast<const v4i*>(fragB + (JN - 1) * (32 * 128));
-        if (DL) {
-#pragma unroll
-          for (int i = 0; i < IM; ++i)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) an[0][DUAL ? i : 0][d] = negative_codes(ap[0][i][d]);
-        }
-        std::true_type yes;
-        std::false_type no;
-        int s = 0;
-        // an odd number of stages is left for the loops below, so that every K loop ends on one copy of the last iteration
-        // (two copies that meet behind the loop cost the register allocator a second accumulator set)
-        if ((n & 1) == 0) {
-          iter(dl_tag, c0, yes, no, 0);
-#pragma unroll
-          for (int i = 0; i < IM; ++i) {
-            ap[0][i] = ap[1][i];
-            if (DL) an[0][DUAL ? i : 0] = an[1][DUAL ? i : 0];
+          for (int e = 0; e < NL; ++e) {                         // spread over the slots behind the X^ reads
+            constexpr int Q0 = IM < NM ? IM : NM - 1;
+            if (Q0 + e * (NM - Q0) / NL == q && more) issue_load(e);
           }
-          bl[0] = bl[1];
-          s = 1;
         }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (more) issue_end();
+    };
+    auto k_loop = [&](auto dl_tag) __attribute__((always_inline)) {
+      constexpr bool DL = decltype(dl_tag)::value;
+      std::integral_constant<int, 0> c0;
+      std::integral_constant<int, 1> c1;
+      const int np = n < NS ? n : NS;
 #pragma unroll 1
-        for (; s + 1 + NS < n; s += 2) {
-          iter(dl_tag, c0, yes, yes, s);
-          iter(dl_tag, c1, yes, yes, s + 1);
+      for (int s = 0; s < np; ++s) {
+        issue_begin();
+#pragma unroll
+        for (int e = 0; e < GA + GB; ++e) issue_load(e);
+        issue_end();
+      }
+      wait_after(np - 1);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < IM; ++i) ap[0][i] = *reinterpret_cast<const v4i*>(fragA + i * (32 * 128));
+#pragma unroll
+      for (int j = 0; j + 1 < JN; ++j) bf[j] = *reinterpret_cast<const v4i*>(fragB + j * (32 * 128));
+      bl[0] = *reinterpret_cast<const v4i*>(fragB + (JN - 1) * (32 * 128));
+      if (DL) {
+#pragma unroll
+        for (int i = 0; i < IM; ++i)
+#pragma unroll
+          for (int d = 0; d < 4; ++d) an[0][DUAL ? i : 0][d] = negative_codes(ap[0][i][d]);
+      }
+      std::true_type yes;
+      std::false_type no;
+      int s = 0;
+      // an odd number of stages is left for the loops below, so that every K loop ends on one copy of the last iteration
+      // (two copies that meet behind the loop cost the register allocator a second accumulator set)
+      if ((n & 1) == 0) {
+        iter(dl_tag, c0, yes, no, 0);
+#pragma unroll
+        for (int i = 0; i < IM; ++i) {
+          ap[0][i] = ap[1][i];
+          if (DL) an[0][DUAL ? i : 0] = an[1][DUAL ? i : 0];
         }
+        bl[0] = bl[1];
+        s = 1;
+      }
 #pragma unroll 1
-        for (; s + 1 < n; s += 2) {
-          iter(dl_tag, c0, yes, no, s);
-          iter(dl_tag, c1, yes, no, s + 1);
-        }
-        iter(dl_tag, c0, no, no, s);
-      };
-      if (dl) k_loop(std::integral_constant<bool, DUAL>{});
-      else k_loop(std::false_type{});
+      for (; s + 1 + NS < n; s += 2) {
+        iter(dl_tag, c0, yes, yes, s);
+        iter(dl_tag, c1, yes, yes, s + 1);
+      }
+#pragma unroll 1
+      for (; s + 1 < n; s += 2) {
+        iter(dl_tag, c0, yes, no, s);
+        iter(dl_tag, c1, yes, no, s + 1);
+      }
+      iter(dl_tag, c0, no, no, s);
+    };
+    if (dl) k_loop(std::integral_constant<bool, DUAL>{});
+    else k_loop(std::false_type{});
 
-      // ---- exchange and flush: in phase w the waves of a part hand half-block w of every owner over, who adds, scales and
-      // (last K-segment) stores.  One body for all phases: unrolled, the owners' sums of several phases are live next to the
-      // accumulators.
-      const bool last = !MULTI || ks + 1 == tb.S;
+    // ---- exchange and flush: in phase w the waves of a part hand half-block w of every owner over, who adds, scales and
+    // (last K-segment) stores.  One body for all phases: unrolled, the owners' sums of several phases are live next to the
+    // accumulators.
+    const bool last = !MULTI || ks + 1 == tb.S;
 #pragma unroll 1
-      for (int w = 0; w < UPW; ++w) {
-        const int u = kw * UPW + w, b = u >> 1, p = u & 1, i = b / JN, j = b - i * JN;
-        const int nb = n0 + (wn * JN + j) * 32 + 16 * p;           // the half-block's 16 columns
-        const int m = m0 + (wm * IM + i) * 32 + frow;
-        const int nc = nb + 4 * (lane >> 5);                       // this lane's columns: nc .. nc + 3 and nc + 8 .. nc + 11
-        const bool in_m = m < a.M;
-        const bool inside = vec4 && nb + 15 < a.N;                 // uniform: whole, aligned row pieces
-        // the constants are requested in front of the exchange, which covers their latency (the raw-sum mode has none: its
-        // caller passes no wscale)
-        float sp = tb.s_pos[MULTI ? ks : 0], sn = dl ? tb.s_neg[MULTI ? ks : 0] : 0.0f;
-        if (a.tok_steps) {                                         // dynamic per-token steps of this lane's row
-          const int mr = in_m ? m : a.M - 1;
-          sp = a.tok_steps[(size_t)mr * tb.S + ks];
-          sn = dl ? a.tok_steps[((size_t)a.M + mr) * tb.S + ks] : 0.0f;
-        }
-        const bool add_bias = last && a.bias != nullptr;
-        float cw[8] = {}, bs[8] = {};
-        if (mode != OUT_DEBUG_ACC) {
-          const float* ws = a.wscale + (size_t)ks * a.N;           // rows of wscale keep 16-byte alignment where vec4
-          const float* bias = add_bias ? a.bias : ws;
-          if (inside) {
+    for (int w = 0; w < UPW; ++w) {
+      const int u = kw * UPW + w, b = u >> 1, p = u & 1, i = b / JN, j = b - i * JN;
+      const int nb = n0 + (wn * JN + j) * 32 + 16 * p;           // the half-block's 16 columns
+      const int m = m0 + (wm * IM + i) * 32 + frow;
+      const int nc = nb + 4 * (lane >> 5);                       // this lane's columns: nc .. nc + 3 and nc + 8 .. nc + 11
+      const bool in_m = m < a.M;
+      const bool inside = vec4 && nb + 15 < a.N;                 // uniform: whole, aligned row pieces
+      // the constants are requested in front of the exchange, which covers their latency (the raw-sum mode has none: its
+      // caller passes no wscale)
+      float sp = tb.s_pos[MULTI ? ks : 0], sn = dl ? tb.s_neg[MULTI ? ks : 0] : 0.0f;
+      if (a.tok_steps) {                                         // dynamic per-token steps of this lane's row
+        const int mr = in_m ? m : a.M - 1;
+        sp = a.tok_steps[(size_t)mr * tb.S + ks];
+        sn = dl ? a.tok_steps[((size_t)a.M + mr) * tb.S + ks] : 0.0f;
+      }
+      const bool add_bias = last && a.bias != nullptr;
+      float cw[8] = {}, bs[8] = {};
+      if (mode != OUT_DEBUG_ACC) {
+        const float* ws = a.wscale + (size_t)ks * a.N;           // rows of wscale keep 16-byte alignment where vec4
+        const float* bias = add_bias ? a.bias : ws;
+        if (inside) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const v4f w4 = *reinterpret_cast<const v4f*>(ws + nc + 8 * h), b4 = *reinterpret_cast<const v4f*>(bias + nc + 8 * h);
+          for (int h = 0; h < 2; ++h) {
+            const v4f w4 = *reinterpret_cast<const v4f*>(ws + nc + 8 * h), b4 = *reinterpret_cast<const v4f*>(bias + nc + 8 * h);
 #pragma unroll
-              for (int r = 0; r < 4; ++r) { cw[4 * h + r] = w4[r]; bs[4 * h + r] = b4[r]; }
-            }
-          } else {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-              const int n = nc + (r & 3) + 8 * (r >> 2), nv = n < a.N ? n : a.N - 1;
-              cw[r] = ws[nv];
-              bs[r] = bias[nv];
-            }
+            for (int r = 0; r < 4; ++r) { cw[4 * h + r] = w4[r]; bs[4 * h + r] = b4[r]; }
           }
-        }
-        __syncthreads();                                           // the ring (or the previous phase) has been read
-        char* to = smem + wave * (C::KW * C::POL * 2048) + lane * 16;
+        } else {
 #pragma unroll
-        for (int ws_ = 0; ws_ < UPW; ++ws_)
-          if (w == ws_) {
-#pragma unroll
-            for (int o = 0; o < C::KW; ++o) {
-              const int uo = o * UPW + ws_, io = (uo >> 1) / JN, jo = (uo >> 1) % JN, po = uo & 1;
-#pragma unroll
-              for (int h = 0; h < C::POL; ++h) {
-                v16i& v = h == 0 ? accp[io][jo] : accn[DUAL ? io : 0][DUAL ? jo : 0];
-                *reinterpret_cast<v4i*>(to + (o * C::POL + h) * 2048) = (v4i){v[8 * po], v[8 * po + 1], v[8 * po + 2], v[8 * po + 3]};
-                *reinterpret_cast<v4i*>(to + (o * C::POL + h) * 2048 + 1024) = (v4i){v[8 * po + 4], v[8 * po + 5], v[8 * po + 6], v[8 * po + 7]};
-              }
-            }
-          }
-        __syncthreads();
-        v8i sum[C::POL];                                           // X^ W^ (and X^_- W^) of the whole segment
-#pragma unroll
-        for (int src = 0; src < C::KW; ++src)
-#pragma unroll
-          for (int h = 0; h < C::POL; ++h) {
-            const char* from = smem + (part * C::KW + src) * (C::KW * C::POL * 2048) + (kw * C::POL + h) * 2048 + lane * 16;
-            const v4i lo = *reinterpret_cast<const v4i*>(from), hi = *reinterpret_cast<const v4i*>(from + 1024);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              sum[h][d] = src == 0 ? lo[d] : sum[h][d] + lo[d];
-              sum[h][4 + d] = src == 0 ? hi[d] : sum[h][4 + d] + hi[d];
-            }
-          }
-        if (DUAL && dl) sum[0] -= sum[C::POL - 1];                 // X^_+ W^ = X^ W^ - X^_- W^, exactly
-        if (mode == OUT_DEBUG_ACC) {
-          if (in_m) {
-            const size_t o = ((size_t)ks * a.M + m) * a.N + nc;
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-              const int cc = (r & 3) + 8 * (r >> 2);
-              if (nc + cc < a.N) {
-                a.acc_pos[o + cc] = sum[0][r];
-                a.acc_neg[o + cc] = dl ? sum[C::POL - 1][r] : 0;
-              }
-            }
-          }
-          continue;
-        }
-        v8f fs = fsum[0];                                          // running sum of the earlier K-segments
-#pragma unroll
-        for (int q = 1; q < (MULTI ? UPW : 1); ++q) fs = w == q ? fsum[MULTI ? q : 0] : fs;
-        float tv[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          float v = (cw[r] * sp) * (float)sum[0][r];
-          if (DUAL) v += (cw[r] * sn) * (dl ? (float)sum[C::POL - 1][r] : 0.0f);
-          if (MULTI) v += fs[r];
-          tv[r] = v;
-        }
-        if (!last) {
-#pragma unroll
-          for (int q = 0; q < UPW; ++q)
-            if (w == q)
-#pragma unroll
-              for (int r = 0; r < 8; ++r) fsum[MULTI ? q : 0][r] = tv[r];
-          continue;
-        }
-#pragma unroll
-        for (int r = 0; r < 8; ++r) tv[r] += add_bias ? bs[r] : 0.0f;
-        const size_t o = (size_t)m * a.N + nc;
-        if (mode == OUT_BF16) {
-          uint16_t* y = reinterpret_cast<uint16_t*>(a.y);
-          const uint32_t a0 = f32x2_to_bf16x2(tv[0], tv[1]), a1 = f32x2_to_bf16x2(tv[2], tv[3]);
-          const uint32_t b0 = f32x2_to_bf16x2(tv[4], tv[5]), b1 = f32x2_to_bf16x2(tv[6], tv[7]);
-          if (inside && a.N % 8 == 0) {
-            // lanes 32..63 of the first operand <-> lanes 0..31 of the second: eight consecutive columns per lane
-            const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
-            const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-            if (in_m) *reinterpret_cast<v4i*>(y + o + 4 * (lane >> 5)) = (v4i){(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]};
-          } else if (in_m) {
-            if (inside) {
-              *reinterpret_cast<v2i*>(y + o) = (v2i){(int)a0, (int)a1};
-              *reinterpret_cast<v2i*>(y + o + 8) = (v2i){(int)b0, (int)b1};
-            } else {
-#pragma unroll
-              for (int r = 0; r < 8; ++r) {
-                const int cc = (r & 3) + 8 * (r >> 2);
-                if (nc + cc < a.N) y[o + cc] = f32_to_bf16(tv[r]);
-              }
-            }
-          }
-        } else if (in_m) {
-          float* y = reinterpret_cast<float*>(a.y);
-          if (inside) {
-            *reinterpret_cast<v4f*>(y + o) = (v4f){tv[0], tv[1], tv[2], tv[3]};
-            *reinterpret_cast<v4f*>(y + o + 8) = (v4f){tv[4], tv[5], tv[6], tv[7]};
-          } else {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-              const int cc = (r & 3) + 8 * (r >> 2);
-              if (nc + cc < a.N) y[o + cc] = tv[r];
-            }
+          for (int r = 0; r < 8; ++r) {
+            const int n = nc + (r & 3) + 8 * (r >> 2), nv = n < a.N ? n : a.N - 1;
+            cw[r] = ws[nv];
+            bs[r] = bias[nv];
           }
         }
       }
-      // the next segment or tile counts its direct loads from zero and overwrites the exchange area
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();                                           // the ring (or the previous phase) has been read
+      char* to = smem + wave * (C::KW * C::POL * 2048) + lane * 16;
+#pragma unroll
+      for (int ws_ = 0; ws_ < UPW; ++ws_)
+        if (w == ws_) {
+#pragma unroll
+          for (int o = 0; o < C::KW; ++o) {
+            const int uo = o * UPW + ws_, io = (uo >> 1) / JN, jo = (uo >> 1) % JN, po = uo & 1;
+#pragma unroll
+            for (int h = 0; h < C::POL; ++h) {
+              v16i& v = h == 0 ? accp[io][jo] : accn[DUAL ? io : 0][DUAL ? jo : 0];
+              *reinterpret_cast<v4i*>(to + (o * C::POL + h) * 2048) = (v4i){v[8 * po], v[8 * po + 1], v[8 * po + 2], v[8 * po + 3]};
+              *reinterpret_cast<v4i*>(to + (o * C::POL + h) * 2048 + 1024) = (v4i){v[8 * po + 4], v[8 * po + 5], v[8 * po + 6], v[8 * po + 7]};
+            }
+          }
+        }
       __syncthreads();
+      v8i sum[C::POL];                                           // X^ W^ (and X^_- W^) of the whole segment
+#pragma unroll
+      for (int src = 0; src < C::KW; ++src)
+#pragma unroll
+        for (int h = 0; h < C::POL; ++h) {
+          const char* from = smem + (part * C::KW + src) * (C::KW * C::POL * 2048) + (kw * C::POL + h) * 2048 + lane * 16;
+          const v4i lo = *reinterpret_cast<const v4i*>(from), hi = *reinterpret_cast<const v4i*>(from + 1024);
+#pragma unroll
+          for (int d = 0; d < 4; ++d) {
+            sum[h][d] = src == 0 ? lo[d] : sum[h][d] + lo[d];
+            sum[h][4 + d] = src == 0 ? hi[d] : sum[h][4 + d] + hi[d];
+          }
+        }
+      if (DUAL && dl) sum[0] -= sum[C::POL - 1];                 // X^_+ W^ = X^ W^ - X^_- W^, exactly
+      if (mode == OUT_DEBUG_ACC) {
+        if (in_m) {
+          const size_t o = ((size_t)ks * a.M + m) * a.N + nc;
+#pragma unroll
+          for (int r = 0; r < 8; ++r) {
+            const int cc = (r & 3) + 8 * (r >> 2);
+            if (nc + cc < a.N) {
+              a.acc_pos[o + cc] = sum[0][r];
+              a.acc_neg[o + cc] = dl ? sum[C::POL - 1][r] : 0;
+            }
+          }
+        }
+        continue;
+      }
+      v8f fs = fsum[0];                                          // running sum of the earlier K-segments
+#pragma unroll
+      for (int q = 1; q < (MULTI ? UPW : 1); ++q) fs = w == q ? fsum[MULTI ? q : 0] : fs;
+      float tv[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        float v = (cw[r] * sp) * (float)sum[0][r];
+        if (DUAL) v += (cw[r] * sn) * (dl ? (float)sum[C::POL - 1][r] : 0.0f);
+        if (MULTI) v += fs[r];
+        tv[r] = v;
+      }
+      if (!last) {
+#pragma unroll
+        for (int q = 0; q < UPW; ++q)
+          if (w == q)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) fsum[MULTI ? q : 0][r] = tv[r];
+        continue;
+      }
+#pragma unroll
+      for (int r = 0; r < 8; ++r) tv[r] += add_bias ? bs[r] : 0.0f;
+      const size_t o = (size_t)m * a.N + nc;
+      if (mode == OUT_BF16) {
+        uint16_t* y = reinterpret_cast<uint16_t*>(a.y);
+        const uint32_t a0 = f32x2_to_bf16x2(tv[0], tv[1]), a1 = f32x2_to_bf16x2(tv[2], tv[3]);
+        const uint32_t b0 = f32x2_to_bf16x2(tv[4], tv[5]), b1 = f32x2_to_bf16x2(tv[6], tv[7]);
+        if (inside && a.N % 8 == 0) {
+          // lanes 32..63 of the first operand <-> lanes 0..31 of the second: eight consecutive columns per lane
+          const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+          if (in_m) *reinterpret_cast<v4i*>(y + o + 4 * (lane >> 5)) = (v4i){(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]};
+        } else if (in_m) {
+          if (inside) {
+            *reinterpret_cast<v2i*>(y + o) = (v2i){(int)a0, (int)a1};
+            *reinterpret_cast<v2i*>(y + o + 8) = (v2i){(int)b0, (int)b1};
+          } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+              const int cc = (r & 3) + 8 * (r >> 2);
+              if (nc + cc < a.N) y[o + cc] = f32_to_bf16(tv[r]);
+            }
+          }
+        }
+      } else if (in_m) {
+        float* y = reinterpret_cast<float*>(a.y);
+        if (inside) {
+          *reinterpret_cast<v4f*>(y + o) = (v4f){tv[0], tv[1], tv[2], tv[3]};
+          *reinterpret_cast<v4f*>(y + o + 8) = (v4f){tv[4], tv[5], tv[6], tv[7]};
+        } else {
+#pragma unroll
+          for (int r = 0; r < 8; ++r) {
+            const int cc = (r & 3) + 8 * (r >> 2);
+            if (nc + cc < a.N) y[o + cc] = tv[r];
+          }
+        }
+      }
     }
+    // the next segment counts its direct loads from zero and overwrites the exchange area
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
   }
 }
 
@@ -498,7 +485,7 @@ hipError_t launch_seglinear_ksplit(GemmArgs a, const GemmTable& tb, OutMode mode
   a.tiles_m = (a.M + kTiles[tile].BM - 1) / kTiles[tile].BM;
   a.tiles_n = (a.N + kTiles[tile].BN - 1) / kTiles[tile].BN;
   a.group_m = a.tiles_m < 8 ? a.tiles_m : 8;
-  const int grid = a.tiles_m * a.tiles_n < device_cus() ? a.tiles_m * a.tiles_n : device_cus();
+  const int grid = a.tiles_m * a.tiles_n;
   if (tile == 0) return launch_cfg<64, 64, 2, 1>(a, kt, mode, dual, grid, st);
   if (tile == 1) return launch_cfg<64, 128, 1, 2>(a, kt, mode, dual, grid, st);
   return launch_cfg<128, 64, 2, 1>(a, kt, mode, dual, grid, st);
