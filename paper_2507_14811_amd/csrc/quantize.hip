@@ -835,9 +835,11 @@ __global__ __launch_bounds__(256) void quantize_act_geglu_kernel(const void* __r
 // workgroup with activate(), i.e. the very bits the arithmetic path produces) sit in LDS, and a gate costs one ds_read_b32
 // instead of the ~35-instruction sequence.  An item with a gate outside the window (tiny, huge, non-finite: seen on the
 // packed extremes of its magnitudes) goes through the sequence, in a block of its own so that the common path stays free of
-// it.  HBM-bound, 5 bytes per output: 4096 x 5120 20.7 us (5.1 TB/s), 25.7 with items of sixteen that left 2.5 rounds to a
-// thread, loads that waited for the previous item, and a window test per element.  Persistent workgroups (two per CU) so
-// that filling the table is a small part of their work.
+// it.  HBM-bound, 5 bytes per output: 4096 x 5120 20.9 us (5.0 TB/s).  Each by itself: window test on packed extremes instead of
+// per element 24.7 -> 23.5 us, items of eight instead of sixteen (which left 2.5 rounds to a thread) 23.5 -> 21.4, the next
+// item's loads ahead 21.4 -> 20.9.  With the 4096 x 5120 x 1280 product behind it in a long run, where the chip's power budget is
+// shared, 79.9 -> 79.6 us on one card and 78.0 -> 75.4 on another.  Persistent workgroups (two per CU) so that filling the table
+// is a small part of their work.
 constexpr int kGegluExpLo = 113, kGegluExps = 17;        // biased exponents 113 ... 129: 2^-14 <= |gate| < 2^3
 constexpr int kGegluThreads = 1024;
 __global__ __launch_bounds__(kGegluThreads, 8) void quantize_act_geglu_tab_kernel(const uint16_t* __restrict__ h,
@@ -924,7 +926,9 @@ hipError_t launch_quantize_act_geglu(const void* h, bool h_is_bf16, int8_t* xq, 
   for (int s = 0; s <= tb.S; ++s) vec = vec && tb.kseg_off[s] % 16 == 0;
   const size_t nitem = (size_t)M * (size_t)(vec ? K / 16 : K);
   if (nitem == 0) return hipSuccess;
-  if (vec && h_is_bf16 && nitem >= (size_t)cus * 2 * kGegluThreads) {      // enough chunks to pay for the tables
+  // 32768 outputs per compute unit pay for the tables.  Table / direct in us: 820 x 5120 (16400 per compute unit) 8.1 / 7.7, 1024 x
+  // 5120 8.7 / 8.4, 1229 x 5120 9.2 / 9.9, 1638 x 5120 (32760, the most that goes direct) 11.1 / 12.3, 2048 x 5120 12.7 / 15.4.
+  if (vec && h_is_bf16 && nitem >= (size_t)cus * 2 * kGegluThreads) {
     hipLaunchKernelGGL(quantize_act_geglu_tab_kernel, dim3((unsigned)cus * 2), dim3(kGegluThreads), 0, st,
                        reinterpret_cast<const uint16_t*>(h), xq, M, K, tb);
     return hipGetLastError();

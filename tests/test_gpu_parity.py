@@ -1879,12 +1879,12 @@ def test_seglinear_fused_rejects_what_the_stream_kernel_cannot_run():
 
 GEGLU = [
     dict(M=70, K=512, kseg=[0, 128, 512], dual=[0, 1], h_dtype="bf16"),
-    dict(M=1100, K=1280, kseg=[0, 1280], dual=[1], h_dtype="bf16"),            # many chunks per workgroup
+    dict(M=1100, K=1280, kseg=[0, 1280], dual=[1], h_dtype="bf16"),            # many workgroups
     dict(M=129, K=1024, kseg=[0, 16, 48, 1024], dual=[1, 0, 1], h_dtype="f32"),
     dict(M=13, K=100, kseg=[0, 37, 100], dual=[1, 1], h_dtype="bf16"),         # unaligned: one output per thread
     dict(M=5, K=24, kseg=[0, 24], dual=[1], h_dtype="f32"),
     dict(M=1, K=16, kseg=[0, 16], dual=[0], h_dtype="bf16"),
-    dict(M=2100, K=2560, kseg=[0, 512, 2560], dual=[1, 0], h_dtype="bf16"),    # more chunks than threads in flight
+    dict(M=2100, K=2560, kseg=[0, 512, 2560], dual=[1, 0], h_dtype="bf16"),    # two segments, many workgroups
     dict(M=4096, K=1024, kseg=[0, 1024], dual=[1], h_dtype="bf16"),
 ]
 
@@ -1921,6 +1921,37 @@ def test_quantize_act_geglu(oracle, case, spread):
     bad = np.argwhere(got != want)
     assert bad.size == 0, (len(bad), bad[:5], got[tuple(bad[0])], want[tuple(bad[0])])
     assert np.abs(want).max() == 127
+
+
+@pytest.mark.parametrize("K,kseg,dual", [(2064, [0, 16, 2064], [0, 1]), (5120, [0, 1024, 1040, 5120], [1, 0, 1]), (8208, [0, 8208], [1])])
+def test_quantize_act_geglu_table(oracle, K, kseg, dual):
+    """From 32768 outputs per compute unit on bf16 gates go through the table of GELU results: ragged item counts, several items per
+    thread, K-segments of one item, gates on either side of both window ends in the first, middle and last items."""
+    import torch
+
+    g = _gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    M = -(-32768 * cus // K) + 3
+    rng = np.random.default_rng(K)
+    h = rng.standard_normal((M, 2 * K), dtype=np.float32) * rng.uniform(0.01, 6.0, size=(M, 1)).astype(np.float32)
+    edges = np.array([2.0 ** -14, 2.0 ** -14 * (1 - 2.0 ** -8), 7.96875, 8.0, 0.0, 2.0 ** -15, 95.0, 1e30], np.float32)
+    for m, c in ((0, 0), (0, 8), (1, K - 16), (M // 2, K // 2 // 16 * 16), (M // 2 + 1, 16), (M - 1, 0), (M - 1, K - 16)):
+        h[m, K + c:K + c + 16] = np.concatenate([edges, -edges])
+    for m, v in ((2, 2.0 ** -14), (3, 7.96875), (4, 8.0), (5, -(2.0 ** -14)), (M - 2, -7.96875), (M - 3, -8.0)):
+        h[m, K:] = v                                       # whole items of one edge
+    bits = wl.f32_to_bf16_bits(h)
+    h = wl.bf16_bits_to_f32(bits)
+    hd = torch.from_numpy(bits.view(np.int16)).view(torch.bfloat16).to(g.DEV)
+    S = len(dual)
+    sp, sn = np.full(S, 0.04, np.float32), np.full(S, 0.011, np.float32)
+    xq = torch.full((M, K), 99, dtype=torch.int8, device=g.DEV)
+    sq.sq_quantize_act_geglu(sq.Layer(M, K, 4, kseg, [0, 4], dual, sp, sn), hd, xq)
+    got = xq.cpu().numpy()
+    for r in range(0, M, 512):                             # the oracle in row blocks: bounded memory
+        rp, rn = oracle.quantize_act_geglu(h[r:r + 512], np.asarray(kseg, np.int32), np.asarray(dual, np.uint8), sp, sn)
+        want = (rp.astype(np.int16) + rn.astype(np.int16)).astype(np.int8)
+        bad = np.argwhere(got[r:r + 512] != want)
+        assert bad.size == 0, (r, len(bad), bad[:5])
 
 
 FUSEDDYN = [
