@@ -179,13 +179,12 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
     }
   };
   // ---- raw activations (a.x_raw): the activation in front of the layer and Q_dual (Sec. 4.3.2) happen on the way into
-  // the slab, in items of four elements.  Every workgroup quantizes the whole of X for itself (M <= 64 rows).  Each
-  // thread's first RAWPRE items are requested before the ring is primed, with loads the compiler does not track, and
-  // waited for with a count that leaves the ring's direct loads in flight (vector memory loads complete in order), so
-  // that the latency of X, the latency of the first weights and the arithmetic overlap.
+  // the slab, in items of four elements.  Every workgroup quantizes the whole of X for itself (M <= 64 rows).  Each thread's
+  // first RAWPRE items are requested at once, the code table (below) is filled while they are on the way, and the ring is primed
+  // when they have landed: the wait that the compiler puts in front of a use then drains nothing of the ring, whose loads it
+  // does not know.  The arithmetic on X overlaps with the latency of the first weights.  (Priming the ring first, behind loads
+  // of X that the compiler did not know either, measured the same: 16 x 1152 x 6912 11.3 us, 28 such layers in one launch 43.1.)
   constexpr int RAWPRE = 5, NT = NW * 64;
-  constexpr int PRIME_LOADS = (RING - 1) * (W4 ? 1 : 2);           // direct loads of a fully primed ring
-  static_assert(PRIME_LOADS <= 63, "the wait count is a 6-bit field");
   const int kq = a.K >> 2;                                         // items per row
   const uint32_t kq_magic = 0xFFFFFFFFu / (uint32_t)kq + 1u;       // item / kq = umulhi(item, kq_magic): item, kq < 2^15
   const int nitem = a.x_raw ? a.M * kq : 0;
@@ -197,20 +196,14 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
     raw2[j] = 0;
     raw4[j] = (v4i)(0);
     if (c < nitem) {
-      if (a.x_raw_bf16)
-        asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(raw2[j]) : "v"(reinterpret_cast<const uint16_t*>(a.x_raw) + (size_t)c * 4) : "memory");
-      else
-        asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(raw4[j]) : "v"(reinterpret_cast<const float*>(a.x_raw) + (size_t)c * 4) : "memory");
+      if (a.x_raw_bf16) raw2[j] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const uint16_t*>(a.x_raw) + (size_t)c * 4);
+      else raw4[j] = *reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(a.x_raw) + (size_t)c * 4);
     }
   }
 
-  if (g_cnt > 0) set_issue_group(0);
-#pragma unroll 1
-  while (issued_steps < RING - 1 && issued_steps < total) issue_step();
-
   // bf16 activations of one K-segment: the codes come from a table of the magnitudes [2^lo, 2^hi) of both signs (below it every
-  // code is 0, above it the arithmetic runs), filled here with that arithmetic while the loads are on the way: 3840 evaluations
-  // per workgroup instead of one per element (16 x 1152: 18432; 12.8 -> 9.6 us for the layer of 6912 columns).
+  // code is 0, above it the arithmetic runs), filled here with that arithmetic while the items are on the way: 3840 evaluations
+  // per workgroup instead of one per element (16 x 1152: 18432; 14.4 -> 11.3 us for the layer of 6912 columns, weights from HBM).
   uint8_t* code_tab = reinterpret_cast<uint8_t*>(tok);             // [sign][kTabHalf]: entry 0 below the window, then the window
   constexpr int kTabHalf = C::TOK / 2;
   if (a.x_tab_n > 0) {
@@ -226,16 +219,13 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
     lds_barrier();
   }
 
-  if (a.x_raw) {
-#define SQ_RAW_OPERANDS "+v"(raw2[0]), "+v"(raw2[1]), "+v"(raw2[2]), "+v"(raw2[3]), "+v"(raw2[4]), \
-                        "+v"(raw4[0]), "+v"(raw4[1]), "+v"(raw4[2]), "+v"(raw4[3]), "+v"(raw4[4])
-    static_assert(RAWPRE == 5, "operand list above");
-    // One statement carries the registers (a second one on another path would make the compiler merge the two sets
-    // with copies, and a copy placed before the wait reads a register the load has not written yet).
-    if (issued_steps != RING - 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // ring not fully primed
-    asm volatile("s_waitcnt vmcnt(%[cnt])" : SQ_RAW_OPERANDS : [cnt] "n"(PRIME_LOADS) : "memory");
-#undef SQ_RAW_OPERANDS
+  if (a.x_raw) {                                                   // X has landed before the ring's loads go out
+#pragma unroll
+    for (int j = 0; j < RAWPRE; ++j) asm volatile("" : "+v"(raw2[j]), "+v"(raw4[j]));
   }
+  if (g_cnt > 0) set_issue_group(0);
+#pragma unroll 1
+  while (issued_steps < RING - 1 && issued_steps < total) issue_step();
 
   // ---- X^ slab: [16*MT rows][K + 16] bytes, rows beyond M repeat the last row (masked at the store) ----------
   // PS: a second plane of the same shape behind the first; plane 0 holds X^_+ (the whole code in a single-scale

@@ -297,7 +297,6 @@ def test_binding_wrappers_are_well_formed():
     """Every wrapper of the binding passes exactly (status, its own name) to _check, names a function the header declares,
     and every declared entry point has a wrapper or is listed in EXPORTS."""
     import ast
-    import re
 
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     src = open(os.path.join(root, "paper_2507_14811_amd", "binding.py")).read()
@@ -315,3 +314,18 @@ def test_binding_wrappers_are_well_formed():
             assert isinstance(name, ast.Constant) and name.value == fn.name, (fn.name, ast.dump(name))
             assert fn.name in declared, fn.name
     assert seen >= 20
+
+
+def test_no_inline_assembly_load_into_registers():
+    """A load written in inline assembly counts as done for the compiler, which may copy or reuse its registers while it is in
+    flight: in the kernels such loads go to LDS only (no output operand); loads into registers are ordinary ones."""
+
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_14811_amd", "csrc")
+    found = 0
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        for m in re.finditer(r"\basm\s+volatile\s*\(((?:[^()]|\([^()]*\))*)\)", text):
+            if re.search(r"(global|flat|buffer|scratch|s)_load", m.group(1)):
+                found += 1
+                assert "_load_lds_" in m.group(1) and '"=' not in m.group(1), (name, m.group(0)[:120])
+    assert found >= 3                                      # the direct loads to LDS
