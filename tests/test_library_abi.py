@@ -319,12 +319,11 @@ def test_binding_wrappers_are_well_formed():
 def test_no_inline_assembly_load_into_registers():
     """A load written in inline assembly counts as done for the compiler, which may copy or reuse its registers while it is in
     flight: in the kernels such loads go to LDS only (no output operand); loads into registers are ordinary ones."""
-
     csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_14811_amd", "csrc")
     found = 0
     for name in sorted(os.listdir(csrc)):
         text = open(os.path.join(csrc, name)).read()
-        for m in re.finditer(r"\basm\s+volatile\s*\(((?:[^()]|\([^()]*\))*)\)", text):
+        for m in re.finditer(r"\basm\s+volatile\s*\((.*?)\);", text, re.S):
             if re.search(r"(global|flat|buffer|scratch|s)_load", m.group(1)):
                 found += 1
                 assert "_load_lds_" in m.group(1) and '"=' not in m.group(1), (name, m.group(0)[:120])
