@@ -216,7 +216,7 @@ def measure(name, steps, warmup, rotate_quant=True, hot_only=False):
     quant()
     torch.cuda.synchronize()
 
-    ms_calib = ms_quant_fused = ms_quant_fused_lut = ms_quant_dyn = ms_gemm_dyn = ms_calib_pct = ms_wblock = None
+    ms_calib = ms_quant_fused = ms_quant_dyn = ms_gemm_dyn = ms_calib_pct = ms_wblock = None
     if not hot_only:
         # calibration-side kernels on the same tensors: min/max steps (one read of the activations) and the
         # block-granular weight quantizer
@@ -231,10 +231,6 @@ def measure(name, steps, warmup, rotate_quant=True, hot_only=False):
         sq.sq_quantize_act_fused(layer, s["x"], codes, xq_f)
         torch.cuda.synchronize()
         ms_quant_fused = float(np.median(_time_events(lambda: sq.sq_quantize_act_fused(layer, s["x"], codes, xq_f), 20)))
-        fws = torch.empty((sq.sq_quantize_act_fused_workspace_bytes(layer),), dtype=torch.uint8, device="cuda:0")
-        sq.sq_quantize_act_fused(layer, s["x"], codes, xq_f, workspace=fws)
-        torch.cuda.synchronize()
-        ms_quant_fused_lut = float(np.median(_time_events(lambda: sq.sq_quantize_act_fused(layer, s["x"], codes, xq_f, workspace=fws), 20)))
         del xq_f
         # dynamic per-token activation steps (the 4-bit settings' activation rule) on the same layer: quantizer that also
         # writes every row's steps, and the GEMM that reads them in its flushes (8-bit weights)
@@ -297,7 +293,7 @@ def measure(name, steps, warmup, rotate_quant=True, hot_only=False):
         gemm_tops=w.int8_ops / (ms_gemm * 1e-3) / 1e12, step_tops=w.int8_ops / (ms_step * 1e-3) / 1e12,
         ms_gemm_b2b=ms_gemm_b2b, gemm_tops_b2b=w.int8_ops / (ms_gemm_b2b * 1e-3) / 1e12,
         gemm_bytes=gbytes, gemm_gbs=gbytes / (ms_gemm * 1e-3) / 1e9, gemm_gbs_b2b=gbytes / (ms_gemm_b2b * 1e-3) / 1e9,
-        ms_gemm_hbm=ms_gemm_hbm, ms_gemm_hbm_stream=ms_gemm_hbm_stream, ms_quant_stream=ms_quant_stream, weight_sets=nsets, ms_quant_fused=ms_quant_fused, ms_quant_fused_lut=ms_quant_fused_lut, ms_quant_dyn=ms_quant_dyn, ms_gemm_dyn=ms_gemm_dyn, ms_calibrate=ms_calib, ms_calibrate_percentile=ms_calib_pct, ms_quantize_weight_block=ms_wblock,
+        ms_gemm_hbm=ms_gemm_hbm, ms_gemm_hbm_stream=ms_gemm_hbm_stream, ms_quant_stream=ms_quant_stream, weight_sets=nsets, ms_quant_fused=ms_quant_fused, ms_quant_dyn=ms_quant_dyn, ms_gemm_dyn=ms_gemm_dyn, ms_calibrate=ms_calib, ms_calibrate_percentile=ms_calib_pct, ms_quantize_weight_block=ms_wblock,
         calib_gbs=None if ms_calib is None else (w.M * w.K * (2 if w.x_dtype == "bf16" else 4)) / (ms_calib * 1e-3) / 1e9,
         gemm_gbs_hbm=(gbytes / (ms_gemm_hbm * 1e-3) / 1e9) if ms_gemm_hbm else None,
         quant_bytes=qbytes, quant_gbs=qbytes / (ms_quant * 1e-3) / 1e9, quant_rotation=nrot,
@@ -627,9 +623,6 @@ def measure_fp8(names=("cfg5", "cfg4", "cfg2")):
         if name == names[0]:
             acts = [sq.SQ_ACT_GELU if d else sq.SQ_ACT_NONE for d in w.dual]
             t_qf = _gpu_side_ms([lambda: sq.sq_quantize_act_fp8_fused(layer, s["x"], acts, xq)], launches=30)
-            lut_ws = torch.empty((sq.sq_quantize_act_fused_workspace_bytes(layer),), dtype=torch.uint8, device=dev)
-            t_qt = _gpu_side_ms([lambda: sq.sq_quantize_act_fp8_fused(layer, s["x"], acts, xq, lut_ws)], launches=30)   # the same route: one launch
-            r["ms_quantize_act_fp8_fused_gelu_by_code_table"] = round(t_qt, 5)
             quant()                                               # restore the codes of the plain quantizer
             r["ms_quantize_act_fp8_fused_gelu"] = round(t_qf, 5)
             codes = xq.view(-1)[: 16 << 20]
@@ -878,11 +871,10 @@ def main():
                          "bytes": head["quant_bytes"], "traffic": MEASURED_TRAFFIC_QUANT.get(args.config)},
         "quantize_act_fused": {"bound": "hbm", "activation": "GELU (tanh form) on the dual K-segments",
                                "path": "code table filled and read in LDS (bf16 input, one launch)",
-                               "ms_per_call": round(head["ms_quant_fused_lut"], 5),
-                               "achieved": round(head["quant_bytes"] / (head["ms_quant_fused_lut"] * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS,
-                               "unit": "GB/s", "frac": round(head["quant_bytes"] / (head["ms_quant_fused_lut"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                               "bytes": head["quant_bytes"],
-                               "ms_per_call_without_workspace": round(head["ms_quant_fused"], 5)},
+                               "ms_per_call": round(head["ms_quant_fused"], 5),
+                               "achieved": round(head["quant_bytes"] / (head["ms_quant_fused"] * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS,
+                               "unit": "GB/s", "frac": round(head["quant_bytes"] / (head["ms_quant_fused"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+                               "bytes": head["quant_bytes"]},
         "quantize_act_geglu": geglu,
         "dynamic_token_steps": {"workload": head["name"], "ms_quantize_act_dynamic": None if head["ms_quant_dyn"] is None else round(head["ms_quant_dyn"], 5),
                                 "ms_seglinear_dynamic": None if head["ms_gemm_dyn"] is None else round(head["ms_gemm_dyn"], 5),

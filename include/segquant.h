@@ -202,10 +202,11 @@ sq_status sq_quantize_act(const sq_layer* layer, const void* x, sq_dtype x_dt, i
  *   h    dev, [M][K] of h_dt (pre-activation)                in
  *   act  host, int32 [S], SQ_ACT_* per K-segment             in
  *   xq   dev, int8 [M][K], polarity-merged codes             out
- *   workspace  dev or NULL; where given, at least sq_quantize_act_fused_workspace_bytes(layer) bytes, 16-byte aligned.  It is
- *        checked and otherwise unused: large bf16 inputs with 16-aligned K-segments are served by a table  bf16 pattern ->
- *        code  that every workgroup fills on chip with the arithmetic above (same codes, HBM-bound instead of ALU-bound),
- *        small ones, fp32 input and unaligned segments by the arithmetic per element.
+ *   workspace  dev or NULL; where given, at least sq_quantize_act_fused_workspace_bytes(layer) bytes, 16-byte aligned.  Kept for
+ *        callers that pass one: it is checked and otherwise unused, NULL does the same.  Large bf16 inputs with 16-aligned
+ *        K-segments are served by a table  bf16 pattern -> code  that every workgroup fills on chip with the arithmetic above
+ *        (same codes, HBM-bound instead of ALU-bound), small ones, fp32 input, unaligned segments and steps whose table would be
+ *        too wide for the size of the matrix by the arithmetic per element.
  * SQ_ERR_INVALID_ARG for an unknown activation code or a workspace that is too small or misaligned; otherwise as
  * sq_quantize_act.
  */

@@ -268,8 +268,9 @@ __device__ __forceinline__ void flush_histogram(const unsigned int (*h)[256][COP
 // The two digits of a bf16 pattern, counted on the pattern itself: sign and exponent are its top nine bits, so the first
 // pass is one bit-field extract, one address and one LDS atomic per value (the general take() is 15 instructions, as much
 // time as the atomics: 58 us a pass on 4608 x 15360 against 23 us for the first pass, a read at 6.1 TB/s, and 30 for the second
-// this way), the second one compares them with the two prefixes and counts the mantissa.  Digit 0 is counted along (the select kernel does not look
-// at it).  Patterns above infinity (NaN) take the general route, which ignores them.
+// this way), the second one compares them with the two prefixes and counts the mantissa.  Digit 0 is counted along (the select
+// kernel does not look at it).  A chunk with a pattern above infinity (NaN: inputs must be finite) takes the general route, which
+// passes it over in a polarity-split segment and counts it under its magnitude in a one-step segment.
 typedef unsigned short v2us __attribute__((ext_vector_type(2)));
 template <bool FIRST, bool DUAL, int COPIES>
 __device__ __forceinline__ void count_bf16(const Chunk<true>& c, const DigitCounter<COPIES>& dc, unsigned int* own,

@@ -172,7 +172,7 @@ def test_quantize_act_fused(oracle, case, spread):
     want = (rp.astype(np.int16) + rn.astype(np.int16)).astype(np.int8)
     bad = np.argwhere(got != want)
     assert bad.size == 0, (len(bad), bad[:5], h[tuple(bad[0])], got[tuple(bad[0])], want[tuple(bad[0])])
-    # with a workspace (bf16 inputs with aligned segments go through the code tables): the same codes
+    # with a workspace (checked, otherwise unused): the same codes
     ws = torch.full((sq.sq_quantize_act_fused_workspace_bytes(layer),), 0x33, dtype=torch.uint8, device=g.DEV)
     xq_t = torch.full((M, K), 99, dtype=torch.int8, device=g.DEV)
     sq.sq_quantize_act_fused(layer, hd, case["act"], xq_t, workspace=ws)
@@ -280,7 +280,7 @@ def test_quantize_act_fused_exhaustive_bf16_and_dense_f32(oracle, act):
         layer = sq.Layer(M, K, 4, [0, K], [0, 4], [1], sp, sn)
         xq = torch.empty((M, K), dtype=torch.int8, device=g.DEV)
         ws = torch.empty((sq.sq_quantize_act_fused_workspace_bytes(layer),), dtype=torch.uint8, device=g.DEV) if dt == "bf16" else None
-        sq.sq_quantize_act_fused(layer, hd, [act], xq, workspace=ws)     # bf16: by table; fp32: arithmetic per element
+        sq.sq_quantize_act_fused(layer, hd, [act], xq, workspace=ws)     # too small for the code table: arithmetic per element
         torch.cuda.synchronize()
         rp, rn = oracle.quantize_act_fused(h, [0, K], [1], [act], sp, sn)
         want = (rp.astype(np.int16) + rn.astype(np.int16)).astype(np.int8)
@@ -1104,7 +1104,7 @@ def test_quantize_act_fp8_fused(oracle, case):
     r_xp, r_xn = oracle.quantize_act_fp8_fused(w.x, w.kseg_off, w.dual, case["act"], w.s_pos, w.s_neg)
     xp, xn = _split_fp8(w, xq.cpu().numpy())
     assert np.array_equal(xp, _plus_zero(r_xp)) and np.array_equal(xn, _plus_zero(r_xn))
-    # with a workspace (bf16 inputs: code tables in LDS): the same codes
+    # with a workspace (checked, otherwise unused): the same codes
     ws = torch.full((sq.sq_quantize_act_fused_workspace_bytes(gl.layer),), 0xA5, dtype=torch.uint8, device=g.DEV)
     xq_t = torch.full_like(xq, 0x7F)
     sq.sq_quantize_act_fp8_fused(gl.layer, gl.x, case["act"], xq_t, ws)
@@ -1392,7 +1392,8 @@ def test_headline_config_calibration_and_fused_quantizer(oracle):
     """The entry points beyond the hot path, at the headline layer's full size (cfg5: 4608 x 15360 bf16, a plain
     K-segment and a dual one), in the launch configuration the benchmark times: min/max steps against the oracle,
     percentile thresholds through the counting definition of a quantile (valid at any size), and the fused
-    GELU + quantizer (table path and per-element path) against the oracle on sampled token rows."""
+    GELU + quantizer by the code table against the arithmetic per element (row slices too small for the table) on every element and
+    against the oracle on sampled token rows."""
     import torch
 
     g = _gpu()
@@ -1432,11 +1433,16 @@ def test_headline_config_calibration_and_fused_quantizer(oracle):
     lay = sq.Layer(M, K, w.N, w.kseg_off, w.nseg_off, w.dual, sp, sn)
     rp, rn = oracle.quantize_act_fused(h[rows], w.kseg_off, w.dual, act, sp, sn)
     want = (rp.astype(np.int16) + rn.astype(np.int16)).astype(np.int8)
-    fws = torch.empty((sq.sq_quantize_act_fused_workspace_bytes(lay),), dtype=torch.uint8, device=g.DEV)
+    fws = torch.empty((sq.sq_quantize_act_fused_workspace_bytes(lay),), dtype=torch.uint8, device=g.DEV)   # checked, not used
     xq_t = torch.empty((M, K), dtype=torch.int8, device=g.DEV)
     xq_e = torch.empty((M, K), dtype=torch.int8, device=g.DEV)
     sq.sq_quantize_act_fused(lay, hd, act, xq_t, workspace=fws)
-    sq.sq_quantize_act_fused(lay, hd, act, xq_e)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    step = 8192 * cus // K - 1                                       # below 8192 elements per compute unit
+    for r0 in range(0, M, step):
+        r1 = min(r0 + step, M)
+        part = sq.Layer(r1 - r0, K, w.N, w.kseg_off, w.nseg_off, w.dual, sp, sn)
+        sq.sq_quantize_act_fused(part, hd[r0:r1], act, xq_e[r0:r1])
     torch.cuda.synchronize()
     assert torch.equal(xq_t, xq_e)                                   # the two device paths agree everywhere
     assert np.array_equal(xq_t.cpu().numpy()[rows], want)            # and with the oracle on the sampled rows
@@ -1576,9 +1582,9 @@ def test_quantize_act_dynamic_rows(oracle, M, loads, dt):
     assert np.array_equal(tok.cpu().numpy().view(np.uint32), np.stack([sp, sn]).view(np.uint32))
 
 
-# One round of small tiles (64 x 64, 64 x 128 where that is more than 256 of them, then 128 x 64), four waves splitting K: the
-# edges of the tiles, 1, 2, ring - 1, ring, ring + 1 and more stages of 128 bytes of K (the ring holds 9 or 6), odd and even
-# numbers of them, single and dual K-segments in either order, ragged and unaligned columns.
+# Layers around the K-splitting tiles' lines as the library dispatches them (which kernel serves depends on the compute units and on
+# the K-segments; every tile, forced, below): edges of the tiles, odd and even numbers of stages, single and dual K-segments in
+# either order, ragged and unaligned columns.
 KSPLIT = [
     dict(M=33, K=128, N=1, kseg=[0, 128], dual=[1], dt="f32"),
     dict(M=64, K=256, N=384, kseg=[0, 128, 256], dual=[1, 1], dt="f32"),
@@ -1598,7 +1604,7 @@ KSPLIT = [
 
 @pytest.mark.parametrize("case", KSPLIT, ids=lambda c: "%dx%dx%d_S%d" % (c["M"], c["K"], c["N"], len(c["dual"])))
 def test_seglinear_ksplit(oracle, case):
-    """The K-splitting tiles against the oracle: sums bit-exact, outputs within the fp32 tolerance, per-token steps too."""
+    """Against the oracle, as dispatched: sums bit-exact, outputs within the fp32 tolerance, per-token steps too."""
     import torch
 
     g = _gpu()
