@@ -835,11 +835,14 @@ __global__ __launch_bounds__(256) void quantize_act_geglu_kernel(const void* __r
 // workgroup with activate(), i.e. the very bits the arithmetic path produces) sit in LDS, and a gate costs one ds_read_b32
 // instead of the ~35-instruction sequence.  An item with a gate outside the window (tiny, huge, non-finite: seen on the
 // packed extremes of its magnitudes) goes through the sequence, in a block of its own so that the common path stays free of
-// it.  HBM-bound, 5 bytes per output: 4096 x 5120 20.9 us (5.0 TB/s).  Each by itself: window test on packed extremes instead of
-// per element 24.7 -> 23.5 us, items of eight instead of sixteen (which left 2.5 rounds to a thread) 23.5 -> 21.4, the next
-// item's loads ahead 21.4 -> 20.9.  With the 4096 x 5120 x 1280 product behind it in a long run, where the chip's power budget is
-// shared, 79.9 -> 79.6 us on one card and 78.0 -> 75.4 on another.  Persistent workgroups (two per CU) so that filling the table
-// is a small part of their work.
+// it.  HBM-bound, 5 bytes per output: 4096 x 5120 21.4 us (4.9 TB/s).  Each by itself: window test on packed extremes instead of
+// per element 24.7 -> 23.5 us, items of eight instead of sixteen (which left 2.5 rounds to a thread) 23.5 -> 21.4.  With the layer's
+// product behind it, calls in a row, what counts is the sum: 4096 x 5120 x 1280 78.0 -> 74.0 us, 798 x 11264 x 2816 74.0 -> 71.4,
+// 1136 x 8704 x 2176 64.6 -> 62.2, 995 x 11776 x 2944 83.6 -> 82.3.  Requesting the first item's loads under the fill of the table and
+// every next one's ahead takes the quantizer to 20.9 us, but those sums to 77.5, 77.1, 66.2 and 86.5 on most cards (72.5, 70.7,
+// 61.8 and 81.8 on the quickest); ahead in the loop alone, or with one workgroup per CU, is between the two: loads in the loop's
+// order are never behind the sixteen-output form.  Persistent workgroups (two per CU) so that
+// filling the table is a small part of their work.
 constexpr int kGegluExpLo = 113, kGegluExps = 17;        // biased exponents 113 ... 129: 2^-14 <= |gate| < 2^3
 constexpr int kGegluThreads = 1024;
 __global__ __launch_bounds__(kGegluThreads, 8) void quantize_act_geglu_tab_kernel(const uint16_t* __restrict__ h,
@@ -849,31 +852,25 @@ __global__ __launch_bounds__(kGegluThreads, 8) void quantize_act_geglu_tab_kerne
   typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
   constexpr uint32_t LOW = kGegluExpLo << 7, N = kGegluExps * 128;  // window of gate magnitudes, per sign
   __shared__ float gelu_tab[2 * N];
-  // items of eight outputs: one 16-byte load of values and one of gates, the next item's under the arithmetic of this one
+  // items of eight outputs: one 16-byte load of values and one of gates
   const uint32_t per_row = (uint32_t)K >> 3, nitem = (uint32_t)M * per_row;        // M * K < 2^31 (checked by the host)
   const uint32_t stride = gridDim.x * (uint32_t)kGegluThreads, dr = stride / per_row, dc = stride - dr * per_row;
   uint32_t c = blockIdx.x * (uint32_t)kGegluThreads + threadIdx.x, m = c / per_row, cc = c - m * per_row;
-  v4i nv = (v4i)(0), ng = (v4i)(0);
-  auto fetch = [&]() __attribute__((always_inline)) {
-    const uint16_t* p = h + (size_t)m * 2 * (size_t)K + 8 * cc;
-    nv = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
-    ng = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p + K));
-  };
-  if (c < nitem) fetch();                                           // under the fill of the table
   for (int i = threadIdx.x; i < (int)(2 * N); i += kGegluThreads) {
     const uint32_t sign = (uint32_t)i / N, bits = (sign << 15) | (LOW + (uint32_t)i - sign * N);
     gelu_tab[i] = activate(SQ_ACT_GELU, __uint_as_float(bits << 16));
   }
   __syncthreads();
   while (c < nitem) {
-    const v4i cv = nv, cg = ng;
     const int col = (int)(8 * cc);
+    const uint16_t* p = h + (size_t)m * 2 * (size_t)K + col;
+    const v4i cv = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
+    const v4i cg = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p + K));
     int8_t* to = xq + (size_t)m * (size_t)K + col;
     c += stride;
     m += dr;
     cc += dc;
     if (cc >= per_row) { cc -= per_row; ++m; }
-    if (c < nitem) fetch();
     float sp = tb.s_pos[0], sn = tb.s_neg[0], ip = tb.inv_pos[0], in = tb.inv_neg[0];
     bool dual = tb.dual[0] != 0;
     for (int s = 1; s < tb.S; ++s) {
