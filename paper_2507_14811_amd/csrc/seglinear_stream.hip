@@ -192,36 +192,37 @@ __global__ __launch_bounds__(stream_waves(MT) * 64) void seglinear_stream_kernel
   v4i raw4[RAWPRE];                                                // fp32 items: 16 bytes
 #pragma unroll
   for (int j = 0; j < RAWPRE; ++j) {
-    const int c = threadIdx.x + j * NT;
     raw2[j] = 0;
     raw4[j] = (v4i)(0);
-    if (c < nitem) {
-      if (a.x_raw_bf16) raw2[j] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const uint16_t*>(a.x_raw) + (size_t)c * 4);
-      else raw4[j] = *reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(a.x_raw) + (size_t)c * 4);
-    }
   }
-
   // bf16 activations of one K-segment: the codes come from a table of the magnitudes [2^lo, 2^hi) of both signs (below it every
   // code is 0, above it the arithmetic runs), filled here with that arithmetic while the items are on the way: 3840 evaluations
   // per workgroup instead of one per element (16 x 1152: 18432; 14.4 -> 11.3 us for the layer of 6912 columns, weights from HBM).
   uint8_t* code_tab = reinterpret_cast<uint8_t*>(tok);             // [sign][kTabHalf]: entry 0 below the window, then the window
   constexpr int kTabHalf = C::TOK / 2;
-  if (a.x_tab_n > 0) {
-    const float sp = tb.s_pos[0], sn = tb.s_neg[0], ip = tb.inv_pos[0], in = tb.inv_neg[0];
-    const bool dl = tb.dual[0] != 0;
-    for (int i = threadIdx.x; i < 2 * (a.x_tab_n + 1); i += NT) {
-      const int sgn = i & 1, e = i >> 1;
-      const float av = activate(tb.act[0], __uint_as_float((uint32_t)(a.x_tab_low - 1 + e) << 16 | (uint32_t)sgn << 31));
-      const bool ng = dl && (av < 0.0f);
-      const int code = clip_code(round_quotient(av, ng ? sn : sp, ng ? in : ip));
-      code_tab[sgn * kTabHalf + e] = e == 0 ? (uint8_t)0 : (uint8_t)code;
-    }
-    lds_barrier();
-  }
-
-  if (a.x_raw) {                                                   // X has landed before the ring's loads go out
+  if (__builtin_expect(a.x_raw != nullptr, 0)) {                   // (out of line: codes, the usual input, go on to the ring at once)
 #pragma unroll
-    for (int j = 0; j < RAWPRE; ++j) asm volatile("" : "+v"(raw2[j]), "+v"(raw4[j]));
+    for (int j = 0; j < RAWPRE; ++j) {
+      const int c = threadIdx.x + j * NT;
+      if (c < nitem) {
+        if (a.x_raw_bf16) raw2[j] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const uint16_t*>(a.x_raw) + (size_t)c * 4);
+        else raw4[j] = *reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(a.x_raw) + (size_t)c * 4);
+      }
+    }
+    if (a.x_tab_n > 0) {
+      const float sp = tb.s_pos[0], sn = tb.s_neg[0], ip = tb.inv_pos[0], in = tb.inv_neg[0];
+      const bool dl = tb.dual[0] != 0;
+      for (int i = threadIdx.x; i < 2 * (a.x_tab_n + 1); i += NT) {
+        const int sgn = i & 1, e = i >> 1;
+        const float av = activate(tb.act[0], __uint_as_float((uint32_t)(a.x_tab_low - 1 + e) << 16 | (uint32_t)sgn << 31));
+        const bool ng = dl && (av < 0.0f);
+        const int code = clip_code(round_quotient(av, ng ? sn : sp, ng ? in : ip));
+        code_tab[sgn * kTabHalf + e] = e == 0 ? (uint8_t)0 : (uint8_t)code;
+      }
+      lds_barrier();
+    }
+#pragma unroll
+    for (int j = 0; j < RAWPRE; ++j) asm volatile("" : "+v"(raw2[j]), "+v"(raw4[j]));   // X has landed before the ring's loads go out
   }
   if (g_cnt > 0) set_issue_group(0);
 #pragma unroll 1
