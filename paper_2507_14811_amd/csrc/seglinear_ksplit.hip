@@ -446,9 +446,11 @@ bool ksplit_supported(const GemmArgs& a, const GemmTable& tb) {
 // and made this kernel the slower one on all but one of 16 layers (1296 x 8192 x 2048: 61 against 55 us).  A K-segment costs a
 // start, a drain and an exchange (0.3 - 0.5 us on the tiles with 64 columns, 2 us on 64 x 128), which its stages of 128 columns have
 // to earn back: about 0.2 us each where both polarity paths run, 0.07 where one does (64 x 128: 0.09 and 0.02).  2145 layers of
-// 1 - 8 equal segments of 128 - 12288 columns, 33 - 20000 rows, every mix of paths: of the 1040 that the lines below take none was
-// slower than on the tile kernel by more than 1.5 %, the median took 0.82 of its time; of all with one round of tiles, those of
+// 1 - 8 equal segments of 128 - 12288 columns, 33 - 20000 rows, every mix of paths: of the 1039 that the lines below take none was
+// slower than on the tile kernel by more than 1.5 %, the median took 0.81 of its time; of all with one round of tiles, those of
 // many short segments took up to 1.8 times as long (1024 x 1024 x 1920, eight segments: 21.1 us on the tile kernel, 36.8 here).
+// One segment on 64 x 128 tiles, ten shapes: 2048 columns of one path took 0.95 - 0.81 of the tile kernel's time, 1536 of them
+// 1.03 - 0.87; 2304 of two paths 0.97 - 0.81, 2048 of them 1.03 - 0.89, 1536 of them up to 1.25.
 int ksplit_pick(const GemmArgs& a, const GemmTable& tb) {
   if (!ksplit_supported(a, tb)) return -1;
   int tile = 0;
@@ -459,7 +461,7 @@ int ksplit_pick(const GemmArgs& a, const GemmTable& tb) {
   for (int s = 0; s < S; ++s) (tb.dual[s] ? both : one) += (tb.kseg_off[s + 1] - tb.kseg_off[s]) >> 7;
   bool earns;
   if (tile == 1) {
-    earns = both > 0 ? 6 * both + one >= 128 * S + 16 : S == 1 && one >= 24;
+    earns = S == 1 ? both >= 18 || one >= 16 : both > 0 && 6 * both + one >= 128 * S + 16;
   } else if (both == 0) {
     earns = tile == 2 ? S <= 2 : (S <= 3 || one >= 24 * S);
   } else if (one == 0) {

@@ -1599,6 +1599,9 @@ KSPLIT = [
     dict(M=1089, K=896, N=996, kseg=[0, 896], dual=[0], dt="f32"),
     dict(M=9000, K=384, N=130, kseg=[0, 384], dual=[1], dt="bf16"),
     dict(M=8999, K=640, N=127, kseg=[0, 128, 640], dual=[0, 0], dt="f32"),
+    dict(M=1090, K=1920, N=1010, kseg=[0, 1920], dual=[0], dt="bf16"),
+    dict(M=1090, K=2048, N=1010, kseg=[0, 2048], dual=[0], dt="bf16"),
+    dict(M=1090, K=2304, N=1010, kseg=[0, 2304], dual=[1], dt="f32"),
 ]
 
 
