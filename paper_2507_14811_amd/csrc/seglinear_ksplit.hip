@@ -25,12 +25,6 @@ namespace sq {
 
 typedef float v8f __attribute__((ext_vector_type(8)));
 
-// X^_- of four packed codes: the negative bytes, the others 0.  v_perm_b32 selectors 8 .. 11 replicate the sign of a 16-bit
-// half, so the signs of the odd bytes come from x and those of the even bytes from x << 8.
-__device__ __forceinline__ int negative_codes(const int x) {
-  return x & (int)__builtin_amdgcn_perm((unsigned)x << 8, (unsigned)x, 0x090B080Au);
-}
-
 constexpr int kKsplitSegments = 8;
 struct KsplitTable {                       // the segment table of at most eight K-segments: a few cache lines of arguments
   int S;

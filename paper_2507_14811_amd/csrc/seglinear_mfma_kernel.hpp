@@ -107,6 +107,12 @@ __device__ __forceinline__ void split_polarity(const int x, int& pos, int& neg) 
   pos = x ^ neg;
 }
 
+// X^_- of four packed codes: the bytes with the sign bit set, the others 0.  v_perm_b32 selectors 8 .. 11 replicate the sign of
+// a 16-bit half, so the signs of the odd bytes come from x and those of the even bytes from x << 8.
+__device__ __forceinline__ int negative_codes(const int x) {
+  return x & (int)__builtin_amdgcn_perm((unsigned)x << 8, (unsigned)x, 0x090B080Au);
+}
+
 template <int SK> __device__ __forceinline__ int row_swizzle(int row) {
   return SK == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3);
 }
@@ -124,6 +130,14 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   constexpr int FW = C::FW, CH = FW / 4;      // dwords / 16-byte chunks of a lane's operand
   using vfrag = std::conditional_t<FP8, v8i, v4i>;
   constexpr bool FSUM = MULTI && !SHARE;      // a separate fp32 running-sum register set
+  // Polarity separation of a dword: X^_- in three VALU instructions (negative_codes), X^_+ = X^ ^ X^_- in one more.  WHOLE: the
+  // one more is left out, the first accumulator set takes X^ W^ and the flush forms X^_+ W^ = X^ W^ - X^_- W^, exactly (integers).
+  // The separation is what the k-steps of the smaller wave tiles have no free issue slots for; per 128-byte stage, no power limit
+  // (zero codes), with five instructions / as now: 128x192 0.943 / 0.790 us, 128x128 0.727 / 0.591, 64x192 0.557 / 0.488.  The
+  // 64x128 wave tile has the slots (1.036 / 1.015 with four, 0.963 with three) but runs at the power limit, where an operand with
+  // all its negative codes costs more than an instruction: 4608 x (3072 + 12288) x 3072 349 us with five, 343 with four, 354 with
+  // three.
+  constexpr bool WHOLE = DUAL && !FP8 && C::IM * C::JN < 8;
   constexpr int IM = C::IM, JN = C::JN, GA = C::GA, GB = C::GB, STAGE = C::STAGE, RPL = C::RPL, SUB = C::SUB;
   constexpr int KSH = SK == 128 ? 7 : 6;
   constexpr int LT = C::LT, NSLOT = C::NSLOT;
@@ -305,14 +319,19 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
       for (int j = 0; j < JN; ++j) bfr[set][j] = *reinterpret_cast<const v4i*>(fragB + j * (32 * SK) + fo);
     }
   };
-  // polarity separation of a fetched X^ fragment set: afr <- X^_+ codes, nfr <- X^_- codes
+  // afr <- X^_+ codes (WHOLE: X^ stays), nfr <- X^_- codes
+  auto separate = [&](const int x, int& pos, int& neg) __attribute__((always_inline)) {
+    neg = negative_codes(x);
+    pos = WHOLE ? x : x ^ neg;
+    asm volatile("" : "+v"(neg), "+v"(pos));                 // done here: left alone, the compiler sinks it to the MFMAs of the next k-step
+  };
   auto split_frags = [&](const int set) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
       for (int d = 0; d < FW; ++d) {
         int pos, neg;
-        split_polarity(afr[set][i][d], pos, neg);
+        separate(afr[set][i][d], pos, neg);
         afr[set][i][d] = pos;
         nfr[set][DUAL ? i : 0][d] = neg;
       }
@@ -325,7 +344,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   // barriers between slots:
   //   * LDS reads are spread over the MFMA stream, X^ fragments first (a burst of reads stalls MFMA issue:
   //     measured 80 % of the MFMA rate with six reads in front of sixteen MFMAs, 94 % with one read per two);
-  //   * the separation's VALU work (5 instructions per dword) follows once its fragment had time to arrive,
+  //   * the separation's VALU work (3 or 4 instructions per dword) follows once its fragment had time to arrive,
   //     a dword or two per MFMA, which the matrix pipe (8 issue slots per MFMA) absorbs;
   //   * the direct loads of the group go into the slots that carry neither an LDS read nor separation work.
   auto kstep = [&](auto dl_tag, auto pf_tag, auto grp_tag, const int cur, const int fo_next) __attribute__((always_inline)) {
@@ -385,7 +404,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
           const int w = (q - QV0) * DPS + t;                 // dword index: fragment w / FW, element w % FW
           if (w < ND) {
             int pos, neg;
-            split_polarity(afr[nxt][w / FW][w % FW], pos, neg);
+            separate(afr[nxt][w / FW][w % FW], pos, neg);
             afr[nxt][w / FW][w % FW] = pos;
             nfr[nxt][DUAL ? w / FW : 0][w % FW] = neg;
           }
@@ -610,6 +629,12 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
     }
   };
 
+  // sum of the X^_+ path in element v of block (i, j); sep: this segment's accn holds X^_- W^ (or zeros)
+  auto pos_sum = [&](const int i, const int j, const int v, const bool sep) __attribute__((always_inline)) {
+    if (WHOLE && sep) return accp[i][j][v] - accn[DUAL ? i : 0][DUAL ? j : 0][v];
+    return accp[i][j][v];
+  };
+
   // debug entry point: raw int32 sums of segment ks, acc_neg = 0 where the segment ran one path
   auto store_debug = [&](auto full_tag, const int ks, const bool has_neg) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full_tag)::value;
@@ -628,7 +653,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
             v4i p, q;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              p[r] = accp[i][j][4 * g + r];
+              p[r] = pos_sum(i, j, 4 * g + r, has_neg);
               q[r] = has_neg ? accn[DUAL ? i : 0][DUAL ? j : 0][4 * g + r] : 0;
             }
             if (FULL || (avec && n + 3 < a.N)) {
@@ -675,9 +700,10 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
             if (SHARE) {
               const int old = accn[DUAL ? i : 0][DUAL ? j : 0][v];
               const float prev = first ? cneg * acc_value<FP8>(old) : __int_as_float(old);
-              accn[DUAL ? i : 0][DUAL ? j : 0][v] = __float_as_int(prev + cpos * acc_value<FP8>(accp[i][j][v]));
+              const int ps = pos_sum(i, j, v, first);
+              accn[DUAL ? i : 0][DUAL ? j : 0][v] = __float_as_int(prev + cpos * acc_value<FP8>(ps));
             } else {
-              float t = cpos * acc_value<FP8>(accp[i][j][v]);
+              float t = cpos * acc_value<FP8>(pos_sum(i, j, v, true));
               if (DUAL) t += cneg * acc_value<FP8>(accn[DUAL ? i : 0][DUAL ? j : 0][v]);
               fsum[FSUM ? i : 0][FSUM ? j : 0][v] += t;
             }
@@ -732,7 +758,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
         float t[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          float u = (cw[v] * spr[i]) * acc_value<FP8>(accp[i][j][v]);
+          float u = (cw[v] * spr[i]) * acc_value<FP8>(pos_sum(i, j, v, !SHARE));
           if (SHARE) u += __int_as_float(accn[DUAL ? i : 0][DUAL ? j : 0][v]);   // running sum (never the first segment)
           else if (DUAL) u += (cw[v] * snr[i]) * acc_value<FP8>(accn[DUAL ? i : 0][DUAL ? j : 0][v]);
           if (FSUM) u += fsum[FSUM ? i : 0][FSUM ? j : 0][v];
