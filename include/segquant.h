@@ -462,6 +462,9 @@ int sq_version(void);
  *   key "force_path":   -1 = automatic, 0 = generic kernel, 1 = MFMA tile kernel, 2 = skinny kernel,
  *                       3 = skinny weight-stream kernel, 4 = K-splitting tiles (sq_seglinear, its raw-sum form and
  *                       sq_seglinear_dynamic; "gemm_variant" 0 / 1 / 2: tiles of 64 x 64, 64 x 128, 128 x 64; -1: 64 x 64)
+ *                       5 = tiles taken in turn (one K-segment without a polarity split, K a multiple of 128 from 512;
+ *                       sq_seglinear, sq_seglinear_dynamic, sq_seglinear_fp8; "gemm_variant" 0 (not fp8) / 1 / 2: tiles of
+ *                       128 x 256, 128 x 192, 128 x 128; -1: 128 x 192)
  * Returns SQ_ERR_INVALID_ARG for an unknown key or value.  Not thread-safe against running calls.
  */
 sq_status sq_tuning_set(const char* key, int value);

@@ -8,7 +8,7 @@
 namespace {
 
 int g_gemm_variant = -1;   // sq_tuning_set("gemm_variant", v)
-int g_force_path = -1;     // sq_tuning_set("force_path", p): 0 generic, 1 MFMA tiles, 2 skinny, 3 skinny weight stream, 4 K-splitting tiles
+int g_force_path = -1;     // sq_tuning_set("force_path", p): 0 generic, 1 MFMA tiles, 2 skinny, 3 skinny weight stream, 4 K-splitting tiles, 5 tiles in turn
 
 bool offsets_ok(int n, int cnt, const int32_t* off) {
   if (cnt < 1 || cnt > SQ_MAX_SEGMENTS || off == nullptr) return false;
@@ -75,6 +75,11 @@ void fill_gemm_table(const sq_layer* L, sq::GemmTable& tb) {
   if (L->seg_scale) std::memcpy(tb.seg_scale, L->seg_scale, sizeof(float) * L->S * L->T);
 }
 
+// sq_tuning_set("force_path", 5): the tile that "gemm_variant" names (automatic: 128 x 192), -1 where it cannot run
+int forced_pair_tile(const sq::GemmArgs& a, const sq::GemmTable& tb, sq::OutMode mode, bool fp8) {
+  const int tile = g_gemm_variant < 0 ? 1 : g_gemm_variant;
+  return sq::pair_supported(a, tb, mode, tile, fp8) ? tile : -1;
+}
 // sq_tuning_set("force_path", 4): the tile that "gemm_variant" names (automatic: 64 x 64), -1 where it cannot run
 int forced_ksplit_tile(const sq::GemmArgs& a, const sq::GemmTable& tb) {
   const int tile = g_gemm_variant < 0 ? 0 : g_gemm_variant;
@@ -104,20 +109,25 @@ sq_status run_gemm(const sq_layer* L, const int8_t* xq, const int8_t* wq,
   if (path == 1 && !sq::mfma_supported(a, tb)) return SQ_ERR_UNSUPPORTED;
   int ktile = path == 4 ? forced_ksplit_tile(a, tb) : -1;
   if (path == 4 && ktile < 0) return SQ_ERR_UNSUPPORTED;
+  int ptile = path == 5 ? forced_pair_tile(a, tb, mode, false) : -1;
+  if (path == 5 && ptile < 0) return SQ_ERR_UNSUPPORTED;
   if (path < 0) {
     // up to two 16-row tiles of tokens: the weight-stream kernel (measured 5.9 TB/s on wide layers); more rows: the
-    // K-splitting tiles where ksplit_pick() finds them the faster ones, else the tile kernel; the skinny kernel serves the
-    // layers of up to 64 rows that neither takes
+    // K-splitting tiles where ksplit_pick() finds them the faster ones, the tiles taken in turn where pair_pick() does, else the
+    // tile kernel; the skinny kernel serves the layers of up to 64 rows that none of them takes
     if (a.M > 32 && g_gemm_variant < 0) ktile = sq::ksplit_pick(a, tb);
     if (a.M <= 32 && sq::stream_supported(a, tb)) path = 3;
     else if (ktile >= 0) path = 4;
+    else if (g_gemm_variant < 0 && (ptile = sq::pair_pick(a, tb, mode, false)) >= 0) path = 5;
     else if (a.M <= 64 && a.M > 32 && sq::mfma_supported(a, tb)) path = 1;
     else if (sq::skinny_supported(a, tb)) path = 2;
     else if (sq::mfma_supported(a, tb)) path = 1;
     else path = 0;
   }
   hipError_t e;
-  if (path == 4) {
+  if (path == 5) {
+    e = sq::launch_seglinear_pair(a, tb, mode, ptile, false, st);
+  } else if (path == 4) {
     e = sq::launch_seglinear_ksplit(a, tb, mode, ktile, st);
   } else if (path == 3) {
     e = sq::launch_seglinear_stream(a, tb, mode, sq::device_cus(), st);
@@ -171,8 +181,14 @@ sq_status run_gemm_dynamic(const sq_layer* L, const int8_t* xq, const float* tok
   if (w_bits == 8 && g_force_path == 4) ktile = forced_ksplit_tile(a, tb);
   else if (w_bits == 8 && g_force_path < 0 && g_gemm_variant < 0 && !stream_ok) ktile = sq::ksplit_pick(a, tb);
   if (g_force_path == 4 && ktile < 0) return SQ_ERR_UNSUPPORTED;
+  int ptile = -1;
+  if (w_bits == 8 && g_force_path == 5) ptile = forced_pair_tile(a, tb, mode, false);
+  else if (w_bits == 8 && g_force_path < 0 && g_gemm_variant < 0 && !stream_ok && ktile < 0) ptile = sq::pair_pick(a, tb, mode, false);
+  if (g_force_path == 5 && ptile < 0) return SQ_ERR_UNSUPPORTED;
   hipError_t e;
-  if (g_force_path != 0 && g_force_path != 1 && g_force_path != 4 && stream_ok) {
+  if (ptile >= 0) {
+    e = sq::launch_seglinear_pair(a, tb, mode, ptile, false, st);
+  } else if (g_force_path != 0 && g_force_path != 1 && g_force_path != 4 && stream_ok) {
     e = w_bits == 4 ? sq::launch_seglinear_stream_w4(a, tb, mode, sq::device_cus(), st)
                     : sq::launch_seglinear_stream(a, tb, mode, sq::device_cus(), st);
   } else if (ktile >= 0) {
@@ -523,8 +539,13 @@ sq_status sq_seglinear_fp8(const sq_layer* layer, const uint8_t* xq, const uint8
   const bool stream_ok = sq::stream_supported(a, tb);
   if (g_force_path == 3 && !stream_ok) return SQ_ERR_UNSUPPORTED;
   hipError_t e;
+  int ptile = g_force_path == 5 ? forced_pair_tile(a, tb, mode, true) : -1;
+  if (g_force_path == 5 && ptile < 0) return SQ_ERR_UNSUPPORTED;
+  if (g_force_path < 0 && g_gemm_variant < 0) ptile = sq::pair_pick(a, tb, mode, true);
   if (g_force_path == 0) {
     e = sq::launch_seglinear_fp8(a, tb, mode, hs);
+  } else if (ptile >= 0) {
+    e = sq::launch_seglinear_pair(a, tb, mode, ptile, true, hs);
   } else if (g_force_path == 3 || (g_force_path < 0 && a.M <= 32 && stream_ok)) {
     e = sq::launch_seglinear_stream_fp8(a, tb, mode, sq::device_cus(), hs);
   } else {
@@ -824,7 +845,7 @@ sq_status sq_tuning_set(const char* key, int value) {
     return SQ_OK;
   }
   if (std::strcmp(key, "force_path") == 0) {
-    if (value < -1 || value > 4) return SQ_ERR_INVALID_ARG;
+    if (value < -1 || value > 5) return SQ_ERR_INVALID_ARG;
     g_force_path = value;
     return SQ_OK;
   }

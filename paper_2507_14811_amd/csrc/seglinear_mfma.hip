@@ -113,13 +113,13 @@ static const float kEffFp8Dual[kNumMfmaVariants] = {0.96f, 0.80f, 0.0f, 0.69f, 0
 static bool fp8_variant_ok(int v, bool dual, bool multi, bool share, int kalign) {
   return kalign == 128 && variant_ok(v, dual, multi, share, kalign, false) && kMfmaVariantHasFp8[v];
 }
-int mfma_fp8_pick_variant(const GemmArgs& a, const GemmTable& tb) {
+static int fp8_pick(const GemmArgs& a, const GemmTable& tb, float& best_score) {
   bool dual, multi, share;
   layer_flags(tb, dual, multi, share);
   const int cus = device_cus();
   const float* eff = dual ? kEffFp8Dual : kEffFp8Single;
   int best = -1;
-  float best_score = -1.0f;
+  best_score = -1.0f;
   for (int v = 0; v < kNumMfmaVariants; ++v) {
     if (!fp8_variant_ok(v, dual, multi, share, k_alignment(a, tb))) continue;
     const MfmaVariantInfo i = variant_info(v);
@@ -130,6 +130,15 @@ int mfma_fp8_pick_variant(const GemmArgs& a, const GemmTable& tb) {
     if (score > best_score) { best_score = score; best = v; }
   }
   return best;
+}
+int mfma_fp8_pick_variant(const GemmArgs& a, const GemmTable& tb) {
+  float score;
+  return fp8_pick(a, tb, score);
+}
+float mfma_fp8_pick_score(const GemmArgs& a, const GemmTable& tb) {
+  float score;
+  fp8_pick(a, tb, score);
+  return score;
 }
 
 static hipError_t launch_tiles(GemmArgs a, const GemmTable& tb_in, OutMode mode, int variant, bool fp8, hipStream_t st);

@@ -91,6 +91,7 @@ int mfma_pick_variant(const GemmArgs& a, const GemmTable& tb, OutMode mode);
 hipError_t launch_seglinear_mfma(GemmArgs a, const GemmTable& tb, OutMode mode, int variant, hipStream_t st);
 // the same tile kernel on fp8 (E4M3) codes: K and every K-segment boundary % 128 == 0, static steps
 int mfma_fp8_pick_variant(const GemmArgs& a, const GemmTable& tb);
+float mfma_fp8_pick_score(const GemmArgs& a, const GemmTable& tb);   // occupancy of the rounds times efficiency of its choice
 hipError_t launch_seglinear_mfma_fp8(GemmArgs a, const GemmTable& tb, OutMode mode, int variant, hipStream_t st);
 
 // seglinear_ksplit.hip : layers with few output tiles, the waves of a workgroup split K.  K and K-segment boundaries
@@ -100,6 +101,13 @@ hipError_t launch_seglinear_mfma_fp8(GemmArgs a, const GemmTable& tb, OutMode mo
 bool ksplit_supported(const GemmArgs& a, const GemmTable& tb);
 int ksplit_pick(const GemmArgs& a, const GemmTable& tb);
 hipError_t launch_seglinear_ksplit(GemmArgs a, const GemmTable& tb, OutMode mode, int tile, hipStream_t st);
+
+// seglinear_pair.hip : layers of one K-segment without a polarity split, large enough for the compute units to take tiles in
+// turn.  K % 128 == 0, K >= 512, no seg_scale; int8 (static or per-token steps) and fp8 (static steps).
+// pair_pick: its tile (0: 128 x 256, int8 only, 1: 128 x 192, 2: 128 x 128), or -1 where the tile kernel serves.
+bool pair_supported(const GemmArgs& a, const GemmTable& tb, OutMode mode, int tile, bool fp8);
+int pair_pick(const GemmArgs& a, const GemmTable& tb, OutMode mode, bool fp8);
+hipError_t launch_seglinear_pair(const GemmArgs& a, const GemmTable& tb, OutMode mode, int tile, bool fp8, hipStream_t st);
 
 // seglinear_skinny.hip : M <= 64, weight-streaming kernel.  Same alignment needs as the MFMA kernel.
 bool skinny_supported(const GemmArgs& a, const GemmTable& tb);

@@ -1688,6 +1688,90 @@ def test_seglinear_ksplit_forced_elsewhere_is_refused():
         sq.sq_tuning_set("force_path", -1)
 
 
+# Tiles taken in turn by two groups of waves, every tile width forced: one stored by its group alone, one beside each group's next
+# (2 and 3 tiles per compute unit), K loops of 4, 5, 9 and 12 stages (three, two and one blocks stored per stage), ragged and odd edges
+# (16-, 8- and 2-byte row pieces of bf16).
+PAIR_CASES = [(1, 512, 1), (130, 640, 201), (257, 1536, 520), (1500, 1152, 3100), (2200, 512, 4104), (2177, 640, 4236)]
+
+
+@pytest.mark.parametrize("shape", PAIR_CASES, ids=lambda c: "%dx%dx%d" % c)
+def test_seglinear_pair_tiles(oracle, shape):
+    import torch
+
+    g = _gpu()
+    M, K, N = shape
+    w = wl.random_layer(M, K, N, [0, K], [0, N], [0], seed=M + K + N, x_dtype="bf16", act="normal", with_bias=N % 8 != 0)
+    gl = g.GpuLayer(w)
+    gl.quantize_weight()
+    gl.quantize_act()
+    r = oracle.seglinear(w.x, w.w, w.kseg_off, w.nseg_off, w.dual, w.s_pos, w.s_neg, None, w.bias, None)
+    tok = torch.full((2, M, 1), float("nan"), dtype=torch.float32, device=g.DEV)
+    xqd = torch.full((M, K), 99, dtype=torch.int8, device=g.DEV)
+    sq.sq_quantize_act_dynamic(gl.layer, gl.x, xqd, tok)
+    rd = oracle.seglinear_dynamic(w.x, w.w, w.kseg_off, w.nseg_off, w.dual, None, w.bias, wbits=8)
+    l8 = sq.Layer(M, K, N, w.kseg_off, w.nseg_off, w.dual, w.s_pos * np.float32(127.0 / 448.0), w.s_neg)
+    wq8 = torch.full((N, K), 0x7F, dtype=torch.uint8, device=g.DEV)
+    xq8 = torch.full((M, K), 0x7F, dtype=torch.uint8, device=g.DEV)
+    ws8 = torch.full((1, N), float("nan"), dtype=torch.float32, device=g.DEV)
+    sq.sq_quantize_weight_fp8(l8, gl.wt, wq8, ws8)
+    sq.sq_quantize_act_fp8(l8, gl.x, xq8)
+    xp8, xn8 = _split_fp8(w, xq8.cpu().numpy())
+    ref8, mag8 = oracle.seglinear_fp8(xp8, xn8, wq8.cpu().numpy(), w.kseg_off, w.nseg_off, w.dual, l8.s_pos, l8.s_neg, ws8.cpu().numpy(),
+                                      None, w.bias)
+    sq.sq_tuning_set("force_path", 5)
+    for tile in (0, 1, 2):
+        sq.sq_tuning_set("gemm_variant", tile)
+        for dt in (torch.float32, torch.bfloat16):
+            for what, ref, call in (("static", r.y32, lambda y: sq.sq_seglinear(gl.layer, gl.xq, gl.wq, gl.wscale, gl.bias, y)),
+                                    ("token", rd.y32, lambda y: sq.sq_seglinear_dynamic(gl.layer, xqd, tok, gl.wq, 8, gl.wscale, gl.bias, y))):
+                y = torch.full((M + 1, N), float("nan"), dtype=dt, device=g.DEV)       # one row more: nothing is stored beyond M
+                call(y[:M])
+                torch.cuda.synchronize()
+                assert bool(torch.isnan(y[M]).all()), (what, tile, dt)
+                tol = RTOL * float(np.abs(ref).max())
+                if dt == torch.float32:
+                    assert float(np.abs(y[:M].cpu().numpy().astype(np.float64) - ref).max()) <= tol, (what, tile)
+                else:
+                    g.check_bf16_against(g.bf16_tensor_bits(y[:M].contiguous()), ref, wl.f32_to_bf16_bits(ref), tol)
+            if tile > 0:
+                y = torch.full((M, N), float("nan"), dtype=dt, device=g.DEV)
+                sq.sq_seglinear_fp8(l8, xq8, wq8, ws8, gl.bias, y)
+                got = y.float().cpu().numpy().astype(np.float64)
+                tol = _fp8_tol(K, mag8, ref8, "bf16" if dt == torch.bfloat16 else "f32")
+                assert not np.isnan(got).any() and (np.abs(got - ref8) <= tol).all(), ("fp8", tile, dt)
+
+
+def test_seglinear_pair_forced_elsewhere_is_refused():
+    """A polarity-split layer, two K-segments, K below four stages, seg_scale, raw sums, fp8 on the widest tile: no fallback."""
+    import torch
+
+    g = _gpu()
+    for K, kseg, dual, scale in ((512, [0, 512], [1], None), (1024, [0, 512, 1024], [0, 0], None), (384, [0, 384], [0], None),
+                                 (512, [0, 512], [0], [1.5])):
+        S = len(kseg) - 1
+        layer = sq.Layer(80, K, 64, kseg, [0, 64], dual, [0.1] * S, [0.1] * S, scale)
+        q, wq = torch.zeros((80, K), dtype=torch.int8, device=g.DEV), torch.zeros((64, K), dtype=torch.int8, device=g.DEV)
+        ws, y = torch.ones((S, 64), device=g.DEV), torch.zeros((80, 64), device=g.DEV)
+        tok = torch.ones((2, 80, S), device=g.DEV)
+        acc = torch.zeros((S, 80, 64), dtype=torch.int32, device=g.DEV)
+        sq.sq_seglinear(layer, q, wq, ws, None, y)
+        sq.sq_tuning_set("force_path", 5)
+        for call in (lambda: sq.sq_seglinear(layer, q, wq, ws, None, y), lambda: sq.sq_seglinear_dynamic(layer, q, tok, wq, 8, ws, None, y),
+                     lambda: sq.sq_seglinear_fp8(layer, q.view(torch.uint8), wq.view(torch.uint8), ws, None, y)):
+            with pytest.raises(sq.SqError):
+                call()
+        sq.sq_tuning_set("force_path", -1)
+    layer = sq.Layer(80, 512, 64, [0, 512], [0, 64], [0], [0.1], [0.1])
+    q, wq = torch.zeros((80, 512), dtype=torch.int8, device=g.DEV), torch.zeros((64, 512), dtype=torch.int8, device=g.DEV)
+    acc, ws, y = torch.zeros((1, 80, 64), dtype=torch.int32, device=g.DEV), torch.ones((1, 64), device=g.DEV), torch.zeros((80, 64), device=g.DEV)
+    sq.sq_tuning_set("force_path", 5)
+    sq.sq_tuning_set("gemm_variant", 0)
+    for call in (lambda: sq.sq_seglinear_debug_acc(layer, q, wq, acc, acc),
+                 lambda: sq.sq_seglinear_fp8(layer, q.view(torch.uint8), wq.view(torch.uint8), ws, None, y)):
+        with pytest.raises(sq.SqError):
+            call()
+
+
 @pytest.mark.parametrize("case", DYNCASES)
 def test_seglinear_dynamic(oracle, case):
     """Per-token steps: codes and steps bit-exact against the oracle, outputs within the fp32 tolerance, for 8-bit and
