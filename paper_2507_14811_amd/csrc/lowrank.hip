@@ -19,15 +19,6 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int kLrRowsPerWg = 256;     // down projection: 4 waves x 64 token rows
 constexpr int kLrMaxSplit = 32;
-constexpr int kLrUpCols = 128;        // up projection: output columns per wave (32 token rows)
-// Outputs from which the up projection fetches ahead (52 MB of y_q): beyond that the GEMM's y_q is no longer near, and what
-// counts is bytes in flight and keeping y_q, read once, out of the caches; below it the loads are short and the wave per SIMD
-// that the second block's registers cost is worth more.  Per-token GEMM and branch together, three sets of buffers in turn, bf16
-// output, form without / with fetching ahead: rank 64 2048 x 1152 x 3456 (28 MB) 50.4 / 52.3 us, 4096 x 1024 x 3072 (50 MB) 65.0 /
-// 67.4, 1500 x 3072 x 9216 (55 MB) 107.7 / 100.6, 4096 x 1536 x 4608 (75 MB) 108.2 / 99.7, 8500 x 1536 x 4608 (157 MB) 203.7 /
-// 187.7; rank 32 61.1 / 62.9 at 50 MB, 101.6 / 94.4 at 55 MB.  The call alone, 9000 x 512 x 1536: 32.8 / 36.3 us.
-constexpr long long kLrAheadOutputs = 13000000;
-
 int lowrank_splits(int M, int K, int cus) {
   const int row_blocks = (M + kLrRowsPerWg - 1) / kLrRowsPerWg;
   int s = (2 * cus + row_blocks - 1) / row_blocks;          // about two workgroups per compute unit
@@ -288,117 +279,147 @@ __global__ __launch_bounds__(256) void lowrank_sum_kernel(const float* __restric
   reinterpret_cast<v4f*>(tsum)[i] = s;
 }
 
-// Up projection and addition.  A wave owns 32 token rows and kLrUpCols output columns: its T fragment stays in registers
-// as three bf16 terms per value (hi = bf16(t), mid = bf16(t - hi), lo = bf16(t - hi - mid): the differences are exact, so
-// hi + mid + lo reproduces t to 2^-25 of its magnitude), Lu rows (bf16) are the other operand, one 32 x 32 block of
-// outputs at a time, three v_mfma_f32_32x32x16_bf16 per 16 features (fp32 accumulation; 12 matrix instructions per
-// block for rank 64 where the fp32 instruction v_mfma_f32_32x32x2_f32 needs 32 of twice the length).  The matrix
-// instruction pairs lane half h of both operands, so half h takes the features [h R/2, (h + 1) R/2) of T and Lu: every lane
-// reads one contiguous run of each.  T is the "A" operand: a half-wave then holds 32 consecutive columns of one row.
-template <bool YBF16, int R, bool AHEAD>
+// KH consecutive features of T, split exactly into three bf16 terms (hi + mid + lo carries the 24-bit mantissa; the last term is
+// rounded at 2^-25 of the value), eight features per matrix instruction
+template <int KH>
+__device__ __forceinline__ void split_t(const float* src, v8bf (&thi)[KH / 8], v8bf (&tmid)[KH / 8], v8bf (&tlo)[KH / 8]) {
+#pragma unroll
+  for (int c = 0; c < KH / 8; ++c) {
+    const v4f a = *reinterpret_cast<const v4f*>(src + 8 * c), b = *reinterpret_cast<const v4f*>(src + 8 * c + 4);
+    const float t[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    v4i ph, pm, pl;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t hb = f32x2_to_bf16x2(t[2 * i], t[2 * i + 1]);
+      const float r0 = t[2 * i] - __uint_as_float(hb << 16), r1 = t[2 * i + 1] - __uint_as_float(hb & 0xFFFF0000u);
+      const uint32_t mbits = f32x2_to_bf16x2(r0, r1);
+      const float q0 = r0 - __uint_as_float(mbits << 16), q1 = r1 - __uint_as_float(mbits & 0xFFFF0000u);
+      ph[i] = (int)hb;
+      pm[i] = (int)mbits;
+      pl[i] = (int)f32x2_to_bf16x2(q0, q1);
+    }
+    thi[c] = __builtin_bit_cast(v8bf, ph);
+    tmid[c] = __builtin_bit_cast(v8bf, pm);
+    tlo[c] = __builtin_bit_cast(v8bf, pl);
+  }
+}
+
+// Up projection and addition.  A wave owns 32 token rows: its T fragment stays in registers as three bf16 terms per value, Lu rows
+// (bf16) are the other operand, one 32 x 32 block of outputs at a time, three v_mfma_f32_32x32x16_bf16 per 16 features (fp32
+// accumulation; 12 matrix instructions per block for rank 64 where the fp32 instruction v_mfma_f32_32x32x2_f32 needs 32 of twice
+// the length).  The matrix instruction pairs lane half h of both operands, so half h takes the features [h R/2, (h + 1) R/2) of T
+// and Lu.  T is the "A" operand: a half-wave then holds 32 consecutive columns of one row.
+// What bounds it is memory: y_q is read and y written once (235 MB at 8500 x 1536 x 4608, 46 us at the rate of a large copy).
+//   * A workgroup owns 128 token rows and kLrStrip columns, whose Lu rows it stages in LDS once by direct loads of whole lines; a
+//     wave that fetches them itself touches 32 lines per load instruction and fetches them four times as often.
+//   * y_q of the next block is requested ahead of the matrix instructions of the current one, except at rank 32 and less than 11 M
+//     outputs, where the registers cost a wave per SIMD (6266 x 512 x 1536 48.1 us, without 46.0), and past the caches from 13 M outputs on
+//     where rows are whole lines (8500 x 1536 x 4608 153.4 us; 6987 x 1920 x 5418 241 past them, 231 through them).
+//   * Where y_q and y together fill half to all of the 256 MB Infinity Cache, y is stored past it as well: ordinary stores displace y_q
+//     that has not been read yet.  4-bit layer with the branch (quantizer to y), stores past the cache / ordinary / waves that fetch
+//     Lu themselves: 8500 x 1536 x 4608 (235 MB) 148.8 / 154.1 / 160.2 us, 2749 x 2816 x 8448 (139 MB) 126.6 / 127.1 / 133.0, but
+//     2236 x 1792 x 5376 (72 MB) 67.3 / 65.1 / 72.6 and 4298 x 4096 x 12288 (317 MB) 306.3 / 301.5 / 303.6.
+// Measured and not taken: 16-byte accesses (a load covers 64 bytes of 16 rows instead of 128 of two; 170 - 179 us), strips of 256
+// columns (152.3).
+constexpr int kLrStrip = 128;
+constexpr long long kLrAhead = 11000000, kLrReadPast = 13000000, kLrPastFrom = 20000000, kLrPastTo = 44000000;   // outputs
+enum LrMode { LR_SHORT, LR_AHEAD, LR_READ_PAST, LR_PAST };           // each with what the ones before it have
+template <bool YBF16, int R, LrMode MODE>
 __global__ __launch_bounds__(256) void lowrank_up_kernel(const float* __restrict__ tsum, const uint16_t* __restrict__ lu,
                                                          const float* y_in, void* y_out, int M, int N) {
-  constexpr int KH = R / 2;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int h = lane >> 5;
-  const int m = blockIdx.y * 32 + (lane & 31);
-  const int n_begin = (blockIdx.x * 4 + wave) * kLrUpCols;
-  if (n_begin >= N) return;
-  const int n_end = (n_begin + kLrUpCols) < N ? (n_begin + kLrUpCols) : N;
-  // this lane's KH features of T, split exactly into three bf16 terms (hi + mid + lo carries the 24-bit mantissa; the
-  // last term is rounded at 2^-25 of the value), eight features per matrix instruction
+  constexpr int KH = R / 2, RB = R * 2;                            // features of a lane half, bytes of a Lu row
+  constexpr int SW = RB == 128 ? 7 : 3;
+  __shared__ __attribute__((aligned(1024))) char smem[kLrStrip * RB];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = lane >> 5, frow = lane & 31;
+  const int n0 = blockIdx.x * kLrStrip;
+  const int ncols = (N - n0) < kLrStrip ? (N - n0) : kLrStrip;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)smem);
+  constexpr int RPI = 1024 / RB, CPR = RB / 16;
+#pragma unroll
+  for (int g = 0; g < kLrStrip / RPI / 4; ++g) {
+    const int rt = (wave * (kLrStrip / RPI / 4) + g) * RPI + lane / CPR;
+    const int r = rt < ncols ? rt : ncols - 1;                     // beyond N: re-read the last row, masked at the store
+    const int slot = (lane % CPR) ^ ((RB == 128 ? rt >> 1 : rt >> 2) & SW);
+    lr_glds16(lu, (uint32_t)(n0 + r) * (uint32_t)RB + (uint32_t)(slot << 4), __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(wave * (kLrStrip / RPI / 4) + g) * 1024u));
+  }
+  const int mb = blockIdx.y * 128 + wave * 32;
   v8bf thi[KH / 8], tmid[KH / 8], tlo[KH / 8];
   {
-    const float* src = tsum + (size_t)(m < M ? m : M - 1) * R + KH * h;
-#pragma unroll
-    for (int c = 0; c < KH / 8; ++c) {
-      const v4f a = *reinterpret_cast<const v4f*>(src + 8 * c), b = *reinterpret_cast<const v4f*>(src + 8 * c + 4);
-      const float t[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-      v4i ph, pm, pl;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t hb = f32x2_to_bf16x2(t[2 * i], t[2 * i + 1]);
-        const float r0 = t[2 * i] - __uint_as_float(hb << 16), r1 = t[2 * i + 1] - __uint_as_float(hb & 0xFFFF0000u);
-        const uint32_t mbits = f32x2_to_bf16x2(r0, r1);
-        const float q0 = r0 - __uint_as_float(mbits << 16), q1 = r1 - __uint_as_float(mbits & 0xFFFF0000u);
-        ph[i] = (int)hb;
-        pm[i] = (int)mbits;
-        pl[i] = (int)f32x2_to_bf16x2(q0, q1);
-      }
-      thi[c] = __builtin_bit_cast(v8bf, ph);
-      tmid[c] = __builtin_bit_cast(v8bf, pm);
-      tlo[c] = __builtin_bit_cast(v8bf, pl);
-    }
+    const int m = mb + frow;
+    split_t<KH>(tsum + (size_t)(m < M ? m : M - 1) * R + KH * h, thi, tmid, tlo);
   }
-  const int mb = blockIdx.y * 32;
   const bool pair_ok = (N % 2 == 0) && (reinterpret_cast<uintptr_t>(y_out) % 4 == 0);     // two bf16 columns per store
-  // AHEAD: y_q and the Lu rows of a block column are requested one block column ahead of their use, so that every wave keeps two
-  // blocks' loads in flight and the stores of one run under the loads of the next, at 215 instead of 140 vector registers (rank
-  // 64; two waves per SIMD instead of three); y_q is then read past the caches (8500 x 1536 x 4608: 72 -> 66 us, 235 MB of y_q
-  // and y; 256 columns per wave instead of 128 69 us).
-  struct Block { v8bf lf[KH / 8]; float yq[16]; };
-  auto load_block = [&](const int nb) __attribute__((always_inline)) {
-    Block b;
-    const int n = nb + (lane & 31);
-    const int na = n < N ? n : N - 1;                            // beyond N: re-read the last row, masked at the store
-    const uint16_t* lsrc = lu + (size_t)na * R + KH * h;
-#pragma unroll
-    for (int c = 0; c < KH / 8; ++c) b.lf[c] = *reinterpret_cast<const v8bf*>(lsrc + 8 * c);
-    // Element v of the block in lane l: token row mb + 8 (v >> 2) + 4 (l >> 5) + (v & 3), output column nb + (l & 31): the 32
-    // lanes of a half-wave hold 32 consecutive columns of one row, so every access covers whole 128-byte (fp32) or 64-byte
-    // (bf16) row pieces.  AHEAD: rows beyond M re-read the last one.
+  auto store = [](auto* p, const auto v) __attribute__((always_inline)) {
+    if (MODE == LR_PAST) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  };
+  // element v of a block in lane l: token row mb + 8 (v >> 2) + 4 (l >> 5) + (v & 3), output column nb + (l & 31): every access covers
+  // whole 128-byte (fp32) or 64-byte (bf16) row pieces.  Rows and columns beyond the matrix re-read the last ones.
+  struct Yq { float q[16]; };
+  auto load_yq = [&](const int nb) __attribute__((always_inline)) {
+    Yq t;
+    const int n = nb + frow, na = n < N ? n : N - 1;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int mv = mb + 8 * (v >> 2) + 4 * h + (v & 3);
-      if (AHEAD) b.yq[v] = y_in != nullptr ? __builtin_nontemporal_load(y_in + (size_t)(mv < M ? mv : M - 1) * N + na) : 0.0f;
-      else b.yq[v] = (y_in != nullptr && n < N && mv < M) ? y_in[(size_t)mv * N + n] : 0.0f;
+      const float* src = y_in + (size_t)(mv < M ? mv : M - 1) * N + na;
+      t.q[v] = y_in == nullptr ? 0.0f : MODE >= LR_READ_PAST ? __builtin_nontemporal_load(src) : *src;
     }
-    return b;
+    return t;
   };
-  Block next;
-  if (AHEAD) next = load_block(n_begin);
+  Yq next;
+  if (MODE >= LR_AHEAD) next = load_yq(n0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // Lu has landed
+  __syncthreads();
+  if (mb >= M) return;
 #pragma unroll 1
-  for (int nb = n_begin; nb < n_end; nb += 32) {
-    Block cur;
-    if (AHEAD) {
+  for (int nb = 0; nb < ncols; nb += 32) {
+    Yq cur;
+    if (MODE >= LR_AHEAD) {
       cur = next;
-      if (nb + 32 < n_end) next = load_block(nb + 32);
+      if (nb + 32 < ncols) next = load_yq(n0 + nb + 32);
     } else {
-      cur = load_block(nb);
+      cur = load_yq(n0 + nb);
     }
-    const v8bf* lf = cur.lf;
-    const float* yq = cur.yq;
-    const int n = nb + (lane & 31);
-    const bool n_ok = n < N;
     v16f acc = (v16f)(0.0f);
+    v8bf lf[KH / 8];
+#pragma unroll
+    for (int c = 0; c < KH / 8; ++c) {
+      const int chunk = (KH / 8) * h + c, r = nb + frow;
+      lf[c] = *reinterpret_cast<const v8bf*>(smem + r * RB + ((chunk ^ ((RB == 128 ? r >> 1 : r >> 2) & SW)) << 4));
+    }
 #pragma unroll
     for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tlo[c], lf[c], acc, 0, 0, 0);
 #pragma unroll
     for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tmid[c], lf[c], acc, 0, 0, 0);
 #pragma unroll
     for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(thi[c], lf[c], acc, 0, 0, 0);
-    if (YBF16 && pair_ok && nb + 32 <= N) {
+    const int n = n0 + nb + frow;
+    const bool n_ok = n < N;
+    if (YBF16 && pair_ok) {
       // bf16: neighbouring lanes exchange one value of every row pair, so that a lane stores two adjacent columns (4 bytes):
       // even lanes the row of element 2 u, odd lanes the row of element 2 u + 1
       const bool odd = (lane & 1) != 0;
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const float o0 = yq[2 * u] + acc[2 * u], o1 = yq[2 * u + 1] + acc[2 * u + 1];
+        const float o0 = cur.q[2 * u] + acc[2 * u], o1 = cur.q[2 * u + 1] + acc[2 * u + 1];
         const float send = odd ? o0 : o1;
         const float recv = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0xB1, 0xF, 0xF, false));   // lane ^ 1
         const int v = 2 * u + (odd ? 1 : 0);
         const int mv = mb + 8 * (v >> 2) + 4 * h + (v & 3);
         const uint32_t pk = odd ? f32x2_to_bf16x2(recv, o1) : f32x2_to_bf16x2(o0, recv);
-        if (mv < M) *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(y_out) + (size_t)mv * N + (n & ~1)) = pk;
+        if (n_ok && mv < M) store(reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(y_out) + (size_t)mv * N + (n & ~1)), pk);
       }
     } else {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int mv = mb + 8 * (v >> 2) + 4 * h + (v & 3);
-        const float o = yq[v] + acc[v];
+        const float o = cur.q[v] + acc[v];
         if (n_ok && mv < M) {
           if (YBF16) reinterpret_cast<uint16_t*>(y_out)[(size_t)mv * N + n] = f32_to_bf16(o);
-          else reinterpret_cast<float*>(y_out)[(size_t)mv * N + n] = o;
+          else store(reinterpret_cast<float*>(y_out) + (size_t)mv * N + n, o);
         }
       }
     }
@@ -435,14 +456,19 @@ hipError_t launch_lowrank_add(const void* x, bool x_is_bf16, const uint16_t* ld,
     hipLaunchKernelGGL(lowrank_sum_kernel, dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st, workspace, nsplit, nvec, dst);
     tsum = dst;
   }
-  dim3 gu((N + 4 * kLrUpCols - 1) / (4 * kLrUpCols), (M + 31) / 32);
-  const bool ahead = (long long)M * N >= kLrAheadOutputs;
+  const dim3 gu((N + kLrStrip - 1) / kLrStrip, (M + 127) / 128);
+  const long long outputs = (long long)M * N;
+  const bool lines = N % 32 == 0;                                    // rows begin on whole lines of y_q and 64-byte pieces of bf16 y
+#define SQ_UPM(B, R, MODE) hipLaunchKernelGGL((lowrank_up_kernel<B, R, MODE>), gu, dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
 #define SQ_UP(B, R) \
-  if (ahead) hipLaunchKernelGGL((lowrank_up_kernel<B, R, true>), gu, dim3(256), 0, st, tsum, lu, y_in, y_out, M, N); \
-  else hipLaunchKernelGGL((lowrank_up_kernel<B, R, false>), gu, dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
+  if (lines && outputs >= kLrPastFrom && outputs < kLrPastTo) SQ_UPM(B, R, LR_PAST); \
+  else if (lines && outputs >= kLrReadPast) SQ_UPM(B, R, LR_READ_PAST); \
+  else if (R == 64 || outputs >= kLrAhead) SQ_UPM(B, R, LR_AHEAD); \
+  else SQ_UPM(B, R, LR_SHORT)
   if (rank == 64) { if (y_is_bf16) { SQ_UP(true, 64); } else { SQ_UP(false, 64); } }
   else            { if (y_is_bf16) { SQ_UP(true, 32); } else { SQ_UP(false, 32); } }
 #undef SQ_UP
+#undef SQ_UPM
   return hipGetLastError();
 }
 

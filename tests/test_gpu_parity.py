@@ -933,6 +933,14 @@ def test_lowrank_add_large(M, N, rank, yq):
         assert torch.equal(y1, want)
 
 
+@pytest.mark.parametrize("rank", [64, 32])
+@pytest.mark.parametrize("M,N", [(6300, 3200), (3300, 3400), (6301, 7008)])
+def test_lowrank_up_sizes(M, N, rank):
+    """The other sizes at which the up projection changes its way through the caches: 20 M outputs (y stored past them), 11 M (y_q
+    through them, a block column ahead) and 44 M, with a ragged row block and a last strip of 104 and 96 columns."""
+    test_lowrank_add_large(M, N, rank, True)
+
+
 @pytest.mark.parametrize("M", [16, 300])
 def test_w4_layer_with_lowrank_branch(oracle, M):
     """The 4-bit setting end to end: W = Lu Ld + R (numpy's SVD, rank 64), R through the 4-bit weight quantizer and the
