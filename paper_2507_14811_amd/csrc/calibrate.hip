@@ -15,6 +15,8 @@ __global__ void calib_init_kernel(float* __restrict__ amax, int n) {
   if (i < n) amax[i] = 0.0f;
 }
 
+__device__ __forceinline__ float step_of(float a) { return (a == 0.0f) ? 1.0f : a / kQmax; }   // the neutral step where the maximum is 0
+
 // ---- the aligned pass over a batch --------------------------------------------------------------------------------------
 // One workgroup of 1024 threads per compute unit, dealt to the K-segments in proportion to their width; a workgroup walks
 // the 8-element chunks of its segment with a constant stride, kPassUnroll chunks per thread in flight (64 KB of bf16 per
@@ -159,13 +161,10 @@ __global__ __launch_bounds__(256) void calib_amax_kernel(const void* __restrict_
   combine_maxima<4>(mp, mn, amax, ks, tb.S);
 }
 
-// steps[ks] = s_+ , steps[S + ks] = s_- : amax / 127, the neutral step 1.0 where the maximum is 0
+// steps[ks] = s_+ , steps[S + ks] = s_-
 __global__ void calib_steps_kernel(const float* __restrict__ amax, float* __restrict__ steps, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    const float a = amax[i];
-    steps[i] = (a == 0.0f) ? 1.0f : a / kQmax;
-  }
+  if (i < n) steps[i] = step_of(amax[i]);
 }
 
 static bool pass_aligned(const void* x, int K, const ActTable& tb) {
@@ -197,19 +196,24 @@ hipError_t launch_calibrate_act(const void* x, bool x_is_bf16, int M, int K, con
 // and polarity the threshold is the nearest-rank quantile of max(x,0), max(-x,0) or |x| over the batch, zeros
 // included.  The values are >= 0, so their fp32 bit patterns order like unsigned integers and the exact order
 // statistic comes from a radix select on those bits, most significant digit first: a histogram pass over the
-// activations per digit (one pass per 8 bits: two for bf16 inputs, four for fp32), each followed by a tiny kernel
-// that walks the 256 bins from the top, picks the bin holding the wanted rank and narrows the search to it.
-// Digit 0 is never counted (it would make the zeros of the other polarity one hot bin): its count is the rest of
-// the bucket.
+// activations per digit (one pass per 8 bits: two for bf16 inputs, four for fp32), after which the bin of the 256 that
+// holds the wanted rank is searched from the top and the search narrowed to it.  Digit 0 is never counted (it would make
+// the zeros of the other polarity one hot bin): its count is the rest of the bucket.
+// Aligned bf16 batches need one pass as a rule: a sample of the segment says about where the order statistic lies, and a
+// pass counts the 254 bit patterns around that place (a factor of two to either side) one by one, with everything above in one
+// more bin.  Where the rank falls outside, the two digit passes follow; else they return at once.  4608 x 15360 (142 MB),
+// p = 0.9999, kernels: 6.3 us sample, 27.1 window pass, 4.8 search, 2 x 4.8 passes with nothing to do, against 4.8 clearing,
+// 23 + 30 digit passes, 2 x 4.8 searches; with both weight formats and the min/max calibration 183.2 -> 163.2 us.
 // ------------------------------------------------------------------------------------------------------------
 struct PctState {                                 // the caller's workspace
-  unsigned int hist[SQ_MAX_SEGMENTS][2][256];     // [ks][polarity][digit], zero between passes
+  unsigned int hist[SQ_MAX_SEGMENTS][2][256];     // [ks][polarity][digit], zero between passes; digit 0 is no count: [ks][0][0]
+                                                  // counts the workgroups that have finished the segment's pass, [ks][1][0]
+                                                  // is set where the window pass has met NaN
   unsigned int rank[SQ_MAX_SEGMENTS][2];          // wanted rank from the top (1 = largest) inside the bucket
-  unsigned int bucket[SQ_MAX_SEGMENTS][2];        // elements that share the prefix found so far
-  unsigned int prefix[SQ_MAX_SEGMENTS][2];        // magnitude bits found so far
+  unsigned int open[SQ_MAX_SEGMENTS][2];          // 0: the threshold is found
+  unsigned int prefix[SQ_MAX_SEGMENTS][2];        // magnitude bits found so far; window pass: bf16 pattern of its bin 0
 };
-struct PctRanks {                                 // per K-segment: elements of a batch, rank from the top
-  unsigned int n[SQ_MAX_SEGMENTS];
+struct PctRanks {                                 // per K-segment: rank from the top in the batch
   unsigned int r[SQ_MAX_SEGMENTS];
 };
 
@@ -220,14 +224,70 @@ constexpr int kPctStreamCopies = 32;    // 64 KB: one workgroup per compute unit
 
 size_t calibrate_workspace_bytes() { return sizeof(PctState); }
 
-__global__ void pct_init_kernel(PctState* __restrict__ st, const PctRanks rk, int S) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < S * 2 * 256) (&st->hist[0][0][0])[i] = 0u;
-  if (i < S * 2) {
-    const int ks = i >> 1, pol = i & 1;
-    st->rank[ks][pol] = rk.r[ks];
-    st->bucket[ks][pol] = rk.n[ks];
-    st->prefix[ks][pol] = 0u;
+// True in the workgroup that is the last of n to arrive at a counter that was 0 before the launch.  Called by one thread after the
+// workgroup's atomics have completed (each wave waits for its own, then the workgroup's barrier); what other workgroups
+// added by agent-scope atomics before they arrived can then be read with agent-scope loads.
+__device__ __forceinline__ bool arrive_last(unsigned int* counter, unsigned int n) {
+  return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == n;
+}
+// One workgroup of 1024 threads per K-segment clears its state.  SAMPLE (aligned bf16): it also reads up to kPctSample chunks,
+// spread evenly over the segment with a jitter inside each share (a plain stride could walk one column of every row), and
+// centres the window on the sample's order statistic, found to half a binade.  1024 chunks = 8192 values: more of them cost
+// more (a compute unit's histogram atomics) than the place gains by.
+constexpr unsigned kPctSample = 1024;
+constexpr unsigned kPctWindowHalf = 127, kPctBaseMax = 0x7F00;
+template <bool SAMPLE>
+__global__ __launch_bounds__(kPassThreads) void pct_init_kernel(const void* __restrict__ x, int M, int K, const ActTable tb,
+                                                                PctState* __restrict__ st, const PctRanks rk) {
+  const int ks = blockIdx.x, t = threadIdx.x;
+  if (t < 512) (&st->hist[ks][0][0])[t] = 0u;
+  if (t < 2) {
+    st->rank[ks][t] = rk.r[ks];
+    st->open[ks][t] = 1u;
+    st->prefix[ks][t] = 0u;
+  }
+  if constexpr (SAMPLE) {
+    constexpr int COPIES = 4;
+    __shared__ unsigned int h[2][512][COPIES];                // bins of half a binade: pattern >> 6
+    __shared__ unsigned int wave_sum[16];
+    for (int i = t; i < 2 * 512 * COPIES; i += kPassThreads) (&h[0][0][0])[i] = 0u;
+    __syncthreads();
+    const bool dual = tb.dual[ks] != 0;
+    const int k0 = tb.kseg_off[ks];
+    const unsigned cpr = (unsigned)(tb.kseg_off[ks + 1] - k0) >> 3, total = (unsigned)M * cpr;
+    const unsigned ns = total < kPctSample ? total : kPctSample;
+    const unsigned share = total / ns;
+    for (unsigned j = t; j < ns; j += kPassThreads) {
+      const unsigned first = (unsigned)((unsigned long long)j * total / ns);
+      const unsigned item = first + ((j * 2654435761u) >> 8) % share;
+      const unsigned r = item / cpr, c = item - r * cpr;
+      const v4i raw = *reinterpret_cast<const v4i*>(reinterpret_cast<const uint16_t*>(x) + (size_t)r * K + k0 + c * 8);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const unsigned u = ((unsigned)raw[i >> 1] >> (i & 1 ? 16 : 0)) & 0xFFFFu;
+        atomicAdd(&h[dual ? u >> 15 : 0][(u & 0x7FFFu) >> 6][t & (COPIES - 1)], 1u);
+      }
+    }
+    __syncthreads();
+    // thread (polarity, d): elements of the bins d .. 511, by a scan from the top inside each wave and over the eight waves
+    const int pol = t >> 9, d = 511 - (t & 511), lane = t & 63, wave = t >> 6;
+    unsigned own = 0u;
+    for (int k = 0; k < COPIES; ++k) own += h[pol][d][k];
+    own = d != 0 ? own : 0u;
+    unsigned suf = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const unsigned up = (unsigned)__shfl_up((int)suf, off, 64);
+      suf += lane >= off ? up : 0u;
+    }
+    if (lane == 63) wave_sum[wave] = suf;
+    __syncthreads();
+    for (int w = pol * 8; w < wave; ++w) suf += wave_sum[w];
+    const unsigned want = (unsigned)((unsigned long long)rk.r[ks] * ns / total), rs = want < 1u ? 1u : want;
+    if (d != 0 && suf - own < rs && rs <= suf) {              // no thread: the rank is among the smallest, the window starts at 0
+      const int base = (d << 6) + 32 - (int)kPctWindowHalf;
+      st->prefix[ks][pol] = base < 0 ? 0u : base > (int)kPctBaseMax ? kPctBaseMax : (unsigned)base;
+    }
   }
 }
 
@@ -261,7 +321,63 @@ __device__ __forceinline__ void flush_histogram(const unsigned int (*h)[256][COP
     const int pol = i >> 8, d = i & 255;
     unsigned int c = 0u;
     for (int k = 0; k < COPIES; ++k) c += h[pol][d][(k + i) % COPIES];   // neighbouring bins start on different banks
-    if (c != 0u) atomicAdd(&st->hist[ks][pol][d], c);
+    if (d != 0 && c != 0u) atomicAdd(&st->hist[ks][pol][d], c);
+  }
+}
+
+// The search after a pass, by one workgroup of at least 512 threads: thread (polarity, d) holds bin d; suffix sums of the 256 bins
+// from the top (a log-step scan in LDS); the bin d >= 1 whose suffix sum first reaches the wanted rank holds it, else it lies in
+// the uncounted digit 0.  The bucket is narrowed to that bin and the histogram cleared for the next pass.  When the
+// threshold is found (the prefix after the last digit, or the pattern base + d of a window; its bins 0 and 255 are open ends,
+// except that below base 0 there are only zeros) it is folded into the running maxima and the steps are written (amax,
+// steps: [2][S], as the min/max calibration).
+enum PctPass { PCT_DIGIT, PCT_LAST_DIGIT, PCT_WINDOW };
+__device__ __forceinline__ void pct_select(PctState* st, int ks, int S, int shift, PctPass pass, int accumulate, float* amax, float* steps,
+                                           unsigned int (*suf)[256]) {
+  const int pol = (threadIdx.x >> 8) & 1, d = threadIdx.x & 255;
+  const bool in = threadIdx.x < 512;
+  unsigned int own = 0u;
+  bool nan = false;
+  if (in) {
+    if (d != 0) own = __hip_atomic_load(&st->hist[ks][pol][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    nan = __hip_atomic_load(&st->hist[ks][1][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+  }
+  __syncthreads();
+  if (in) {
+    st->hist[ks][pol][d] = 0u;                               // digit 0: the counter of finished workgroups
+    suf[pol][d] = own;
+  }
+  __syncthreads();
+  for (int off = 1; off < 256; off <<= 1) {                  // suf[d] = sum of bins d .. 255
+    const unsigned int add = in && d + off < 256 ? suf[pol][d + off] : 0u;
+    __syncthreads();
+    if (in) suf[pol][d] += add;
+    __syncthreads();
+  }
+  const bool open = in && st->open[ks][pol] != 0u;
+  const unsigned int r = st->rank[ks][pol], pre = st->prefix[ks][pol];
+  const unsigned int above = d < 255 ? suf[pol][d + 1] : 0u; // elements in bins above d
+  const unsigned int total = suf[pol][1];                    // all counted elements (bins 1 .. 255)
+  // exactly one thread holds the rank: bin d >= 1 with above < r <= above + own, or d == 0 when r > total
+  const bool mine = d >= 1 ? (above < r && r <= above + own) : (r > total);
+  __syncthreads();                                           // every thread has read the state before it changes
+  if (open && mine) {
+    bool found = pass == PCT_LAST_DIGIT;
+    unsigned int bits = pre | ((unsigned int)d << shift);
+    if (pass == PCT_WINDOW) {
+      found = !nan && (d == 0 ? pre == 0u : d < 255);
+      bits = found ? (pre + (unsigned int)d) << 16 : 0u;
+    } else {
+      st->rank[ks][pol] = r - (d >= 1 ? above : total);
+    }
+    st->prefix[ks][pol] = bits;
+    if (found) {
+      const int i = pol * S + ks;
+      const float a = __builtin_fmaxf(accumulate ? amax[i] : 0.0f, __uint_as_float(bits));
+      st->open[ks][pol] = 0u;
+      amax[i] = a;
+      steps[i] = step_of(a);
+    }
   }
 }
 
@@ -295,34 +411,97 @@ __device__ __forceinline__ void count_bf16(const Chunk<true>& c, const DigitCoun
   }
 }
 
-template <bool BF16>
+// The window pass: bf16 patterns base .. base + 255 one bin each, in packed 16-bit arithmetic (two values per instruction).  With
+// two polarities a pattern's distance above its own base (saturated: 0 below it) is 0 on the side of the other sign, whose
+// patterns lie below sign bit + base once the sign bit is where the side's own patterns have it; the difference of the two,
+// clamped to -255 .. 255, names the bin.  Bin 0 is counted along (in its own bank per lane class, which is cheaper than a
+// branch).  top collects the largest magnitude pattern for the test for NaN behind the pass.
+template <bool DUAL, int COPIES>
+__device__ __forceinline__ void count_window(const Chunk<true>& c, char* lds, const v2us at, const v2us base_p, const v2us base_n, v2us& top) {
+  typedef short v2s __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t u = (uint32_t)c.raw[0][i];
+    const v2us mag = __builtin_bit_cast(v2us, u & 0x7FFF7FFFu);
+    v2s d;
+    if (DUAL) {
+      top = __builtin_elementwise_max(top, mag);
+      d = __builtin_bit_cast(v2s, __builtin_elementwise_sub_sat(__builtin_bit_cast(v2us, u ^ 0x80008000u), base_p) -
+                                      __builtin_elementwise_sub_sat(__builtin_bit_cast(v2us, u), base_n));
+      d = __builtin_elementwise_max(d, (v2s)(short)-255);
+    } else {
+      d = __builtin_bit_cast(v2s, __builtin_elementwise_sub_sat(mag, base_p));
+    }
+    d = __builtin_elementwise_min(d, (v2s)(short)255);
+    const uint32_t to = __builtin_bit_cast(uint32_t, __builtin_bit_cast(v2us, d) * (unsigned short)(COPIES * 4) + at);   // byte offsets
+    atomicAdd(reinterpret_cast<unsigned int*>(lds + (to & 0xFFFFu)), 1u);
+    atomicAdd(reinterpret_cast<unsigned int*>(lds + (to >> 16)), 1u);
+  }
+}
+
+// One pass over the batch.  WINDOW: the pass around the sampled place.  The search behind a pass is a kernel of its own (4.8 us in a
+// trace, about half of it in a stream of launches) except behind the digit passes of bf16 batches, which as a rule have
+// nothing to do: there the last workgroup of a K-segment searches, so that they are two launches that return at once and not four.
+// Where the pass runs that costs more (the arrivals' fences and the search: 8 us behind the window pass).
+template <bool BF16, bool WINDOW>
 __global__ __launch_bounds__(kPassThreads) void pct_hist_stream_kernel(const void* __restrict__ x, int M, int K, const ActTable tb,
                                                                        const PassPlan plan, PctState* __restrict__ st, int shift,
-                                                                       unsigned int dmask, unsigned int himask) {
+                                                                       unsigned int dmask, unsigned int himask, PctPass pass,
+                                                                       int accumulate, float* __restrict__ amax, float* __restrict__ steps) {
   const int b = blockIdx.x;
   int ks = 0;
   for (int s = 1; s < tb.S; ++s)
     if (b >= plan.first[s]) ks = s;
+  if ((st->open[ks][0] | st->open[ks][1]) == 0u) return;     // written by an earlier launch, the same for all of the segment
   const int k0 = tb.kseg_off[ks], L = tb.kseg_off[ks + 1] - k0;
+  const unsigned nwg = (unsigned)(plan.first[ks + 1] - plan.first[ks]);
+  const bool dual = tb.dual[ks] != 0;
   __shared__ unsigned int h[2][256][kPctStreamCopies];
+  __shared__ unsigned int suf[2][256];
+  __shared__ bool last;
   for (int i = threadIdx.x; i < 2 * 256 * kPctStreamCopies; i += kPassThreads) (&h[0][0][0])[i] = 0u;
-  const DigitCounter<kPctStreamCopies> dc{h, st->prefix[ks][0], st->prefix[ks][1], dmask, himask, shift,
-                                          (int)threadIdx.x & (kPctStreamCopies - 1), tb.dual[ks] != 0};
   __syncthreads();
-  auto walk = [&](auto&& visit) { walk_segment<BF16>(x, M, K, k0, L, b - plan.first[ks], plan.first[ks + 1] - plan.first[ks], visit); };
-  if constexpr (BF16) {
-    unsigned int* own = &h[0][0][dc.copy];
-    const unsigned int key_p = dc.pre_p >> 23, key_n = 0x100u | (dc.pre_n >> 23);
-    const bool first = himask == 0u;
-    if (first && dc.dual) walk([&](const Chunk<BF16>& c) { count_bf16<true, true>(c, dc, own, key_p, key_n); });
-    else if (first) walk([&](const Chunk<BF16>& c) { count_bf16<true, false>(c, dc, own, key_p, key_n); });
-    else if (dc.dual) walk([&](const Chunk<BF16>& c) { count_bf16<false, true>(c, dc, own, key_p, key_n); });
-    else walk([&](const Chunk<BF16>& c) { count_bf16<false, false>(c, dc, own, key_p, key_n); });
+  auto walk = [&](auto&& visit) { walk_segment<BF16>(x, M, K, k0, L, b - plan.first[ks], (int)nwg, visit); };
+  unsigned int* own = &h[0][0][threadIdx.x & (kPctStreamCopies - 1)];
+  if constexpr (WINDOW) {
+    static_assert(sizeof(h) <= 65536, "16-bit byte offsets");
+    char* lds = reinterpret_cast<char*>(&h[0][0][0]);
+    const v2us at = (v2us)(unsigned short)((255 * kPctStreamCopies + ((int)threadIdx.x & (kPctStreamCopies - 1))) * 4);
+    const v2us bp = (v2us)(unsigned short)((dual ? 0x8000u : 0u) + st->prefix[ks][0]), bn = (v2us)(unsigned short)(0x8000u + st->prefix[ks][1]);
+    v2us top = (v2us)(0);
+    if (dual) walk([&](const Chunk<true>& c) { count_window<true, kPctStreamCopies>(c, lds, at, bp, bn, top); });
+    else walk([&](const Chunk<true>& c) { count_window<false, kPctStreamCopies>(c, lds, at, bp, bn, top); });
+    // NaN counts in neither polarity: the digit passes sort it out, for which this pass must not find the rank
+    if (top[0] > 0x7F80 || top[1] > 0x7F80) atomicOr(&st->hist[ks][1][0], 1u);
+    __syncthreads();
+    if (threadIdx.x < 512) {
+      const int pol = threadIdx.x >> 8, d = threadIdx.x & 255, bin = 255 + (pol ? -d : d);
+      unsigned int n = 0u;
+      for (int k = 0; k < kPctStreamCopies; ++k) n += (&h[0][0][0])[bin * kPctStreamCopies + ((k + bin) & (kPctStreamCopies - 1))];
+      if (d != 0 && n != 0u) atomicAdd(&st->hist[ks][pol][d], n);
+    }
   } else {
-    walk([&](const Chunk<BF16>& c) { for_each_value<BF16>(c, [&](float v) { dc.take(v); }); });
+    const DigitCounter<kPctStreamCopies> dc{h, st->prefix[ks][0], st->prefix[ks][1], dmask, himask, shift,
+                                            (int)threadIdx.x & (kPctStreamCopies - 1), dual};
+    if constexpr (BF16) {
+      const unsigned int key_p = dc.pre_p >> 23, key_n = 0x100u | (dc.pre_n >> 23);
+      const bool first = himask == 0u;
+      if (first && dual) walk([&](const Chunk<BF16>& c) { count_bf16<true, true>(c, dc, own, key_p, key_n); });
+      else if (first) walk([&](const Chunk<BF16>& c) { count_bf16<true, false>(c, dc, own, key_p, key_n); });
+      else if (dual) walk([&](const Chunk<BF16>& c) { count_bf16<false, true>(c, dc, own, key_p, key_n); });
+      else walk([&](const Chunk<BF16>& c) { count_bf16<false, false>(c, dc, own, key_p, key_n); });
+    } else {
+      walk([&](const Chunk<BF16>& c) { for_each_value<BF16>(c, [&](float v) { dc.take(v); }); });
+    }
+    __syncthreads();
+    flush_histogram<kPctStreamCopies, kPassThreads>(h, st, ks);
   }
+  if (WINDOW || !BF16) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this wave's counts are in
   __syncthreads();
-  flush_histogram<kPctStreamCopies, kPassThreads>(h, st, ks);
+  if (threadIdx.x == 0) last = arrive_last(&st->hist[ks][0][0], nwg);
+  __syncthreads();
+  if (last) pct_select(st, ks, tb.S, shift, pass, accumulate, amax, steps, suf);
 }
 
 // Unaligned rows or segments.  grid: (row blocks, K-segments).
@@ -348,47 +527,10 @@ __global__ __launch_bounds__(256) void pct_hist_kernel(const void* __restrict__ 
   flush_histogram<kPctCopies, 256>(h, st, ks);
 }
 
-// One 256-thread workgroup per (K-segment, polarity): suffix sums of the 256 bins from the top (a log-step scan in
-// LDS); the bin d >= 1 whose suffix sum first reaches the wanted rank holds it, else it lies in the uncounted digit 0.
-// The bucket is narrowed to that bin and the histogram cleared for the next pass.  After the last digit the prefix is
-// the threshold: fold it into the running maxima and write the steps (amax, steps: [2][S], as the min/max calibration).
-__global__ __launch_bounds__(256) void pct_select_kernel(PctState* __restrict__ st, int S, int shift, int last, int accumulate,
+__global__ __launch_bounds__(512) void pct_select_kernel(PctState* __restrict__ st, int S, int shift, PctPass pass, int accumulate,
                                                          float* __restrict__ amax, float* __restrict__ steps) {
-  const int i = blockIdx.x;                                  // grid: 2 S
-  const int pol = i / S, ks = i - pol * S;
-  const int d = threadIdx.x;
-  unsigned int* h = st->hist[ks][pol];
-  __shared__ unsigned int suf[256];
-  const unsigned int own = d >= 1 ? h[d] : 0u;               // digit 0 is not counted
-  h[d] = 0u;
-  suf[d] = own;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {                  // suf[d] = sum of bins d .. 255
-    const unsigned int add = d + off < 256 ? suf[d + off] : 0u;
-    __syncthreads();
-    suf[d] += add;
-    __syncthreads();
-  }
-  const unsigned int r = st->rank[ks][pol], bucket = st->bucket[ks][pol], pre = st->prefix[ks][pol];
-  const unsigned int above = d < 255 ? suf[d + 1] : 0u;      // elements in bins above d
-  const unsigned int total = suf[1];                         // all counted elements (bins 1 .. 255)
-  __syncthreads();
-  // exactly one thread holds the rank: bin d >= 1 with above < r <= above + own, or d == 0 when r > total
-  const bool mine = d >= 1 ? (above < r && r <= above + own) : (r > total);
-  if (mine) {
-    const unsigned int taken = d >= 1 ? above : total;
-    const unsigned int npre = pre | ((unsigned int)d << shift);
-    st->rank[ks][pol] = r - taken;
-    st->bucket[ks][pol] = d >= 1 ? own : bucket - total;
-    st->prefix[ks][pol] = npre;
-    if (last) {
-      const float t = __uint_as_float(npre);
-      float a = accumulate ? amax[i] : 0.0f;
-      a = __builtin_fmaxf(a, t);
-      amax[i] = a;
-      steps[i] = (a == 0.0f) ? 1.0f : a / kQmax;
-    }
-  }
+  __shared__ unsigned int suf[2][256];
+  pct_select(st, blockIdx.x, S, shift, pass, accumulate, amax, steps, suf);
 }
 
 hipError_t launch_calibrate_act_percentile(const void* x, bool x_is_bf16, int M, int K, const ActTable& tb, double p,
@@ -399,14 +541,20 @@ hipError_t launch_calibrate_act_percentile(const void* x, bool x_is_bf16, int M,
     const long long n = (long long)M * (tb.kseg_off[s + 1] - tb.kseg_off[s]);
     long long k = (long long)std::ceil(p * (double)n);      // nearest rank, in IEEE double
     k = k < 1 ? 1 : (k > n ? n : k);
-    rk.n[s] = (unsigned int)n;
     rk.r[s] = (unsigned int)(n - k + 1);                    // k-th smallest = (n - k + 1)-th largest
   }
-  const int nclear = tb.S * 2 * 256;
-  hipLaunchKernelGGL(pct_init_kernel, dim3((nclear + 255) / 256), dim3(256), 0, st, ws, rk, tb.S);
   const bool vec = pass_aligned(x, K, tb);
   const PassPlan plan = pass_plan(M, tb, K, device_cus());
   const dim3 grid((M + kCalibRows - 1) / kCalibRows, tb.S);
+  const int acc = accumulate ? 1 : 0;
+  if (vec && x_is_bf16) {
+    hipLaunchKernelGGL((pct_init_kernel<true>), dim3(tb.S), dim3(kPassThreads), 0, st, x, M, K, tb, ws, rk);
+    hipLaunchKernelGGL((pct_hist_stream_kernel<true, true>), dim3(plan.first[tb.S]), dim3(kPassThreads), 0, st, x, M, K, tb, plan, ws,
+                       0, 0u, 0u, PCT_WINDOW, acc, amax, steps);
+    hipLaunchKernelGGL(pct_select_kernel, dim3(tb.S), dim3(512), 0, st, ws, tb.S, 0, PCT_WINDOW, acc, amax, steps);
+  } else {
+    hipLaunchKernelGGL((pct_init_kernel<false>), dim3(tb.S), dim3(kPassThreads), 0, st, x, M, K, tb, ws, rk);
+  }
   // digits of the magnitude bits, most significant first; a bf16 value has nothing below bit 16
   static const int kShift[4] = {23, 15, 7, 0};
   static const unsigned int kMask[4] = {0xFFu, 0xFFu, 0xFFu, 0x7Fu};
@@ -416,14 +564,17 @@ hipError_t launch_calibrate_act_percentile(const void* x, bool x_is_bf16, int M,
     unsigned int dmask = kMask[ps];
     if (x_is_bf16 && ps == 1) { shift = 16; dmask = 0x7Fu; }
     const unsigned int himask = 0x7FFFFFFFu & ~((dmask << shift) | ((1u << shift) - 1u));
+    const PctPass pass = ps == npass - 1 ? PCT_LAST_DIGIT : PCT_DIGIT;
 #define SQ_PCT(B) \
-  if (vec) hipLaunchKernelGGL((pct_hist_stream_kernel<B>), dim3(plan.first[tb.S]), dim3(kPassThreads), 0, st, x, M, K, tb, plan, ws, shift, dmask, himask); \
-  else hipLaunchKernelGGL((pct_hist_kernel<B>), grid, dim3(256), 0, st, x, M, K, tb, ws, shift, dmask, himask)
+  if (vec) \
+    hipLaunchKernelGGL((pct_hist_stream_kernel<B, false>), dim3(plan.first[tb.S]), dim3(kPassThreads), 0, st, x, M, K, tb, plan, ws, shift, \
+                       dmask, himask, pass, acc, amax, steps); \
+  else \
+    hipLaunchKernelGGL((pct_hist_kernel<B>), grid, dim3(256), 0, st, x, M, K, tb, ws, shift, dmask, himask)
     if (x_is_bf16) { SQ_PCT(true); }
     else           { SQ_PCT(false); }
 #undef SQ_PCT
-    hipLaunchKernelGGL(pct_select_kernel, dim3(2 * tb.S), dim3(256), 0, st, ws, tb.S, shift,
-                       ps == npass - 1 ? 1 : 0, accumulate ? 1 : 0, amax, steps);
+    if (!vec || !x_is_bf16) hipLaunchKernelGGL(pct_select_kernel, dim3(tb.S), dim3(512), 0, st, ws, tb.S, shift, pass, acc, amax, steps);
   }
   return hipGetLastError();
 }

@@ -684,6 +684,51 @@ def test_calibration_pass_shares(oracle, shape, dt):
         assert np.array_equal(amax.cpu().numpy(), np.stack([r[2], r[3]])), p
 
 
+@pytest.mark.parametrize("kind", ["tail", "two_scales", "constant", "zeros", "tiny", "huge", "nan"])
+@pytest.mark.parametrize("shape", [(1, [0, 8]), (700, [0, 64, 512]), (2049, [0, 8, 256])], ids=lambda s: "%dx%d" % (s[0], s[1][-1]))
+def test_percentile_window(oracle, shape, kind):
+    """Aligned bf16 batches count a window of bit patterns around a sampled place first: order statistics inside it, on its first
+    and last patterns, above and below it (values that the sample hardly meets, two scales with the rank between them), at 0 and at
+    the largest finite pattern; NaN is passed over in polarity-split segments.  Bit-exact against the oracle's sort."""
+    import torch
+
+    g = _gpu()
+    M, kseg = shape
+    K, S = kseg[-1], len(kseg) - 1
+    rng = np.random.default_rng(M * K + len(kind))
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    if kind == "tail":                                   # about one value in 40000, far above: the sample of 8192 may miss them
+        x[rng.random((M, K)) < 2.5e-5] *= 1e6
+        x[M // 2, K - 1] = -3e7
+    elif kind == "two_scales":
+        x *= np.where(rng.random((M, K)) < 0.5, 1e-9, 1e3).astype(np.float32)
+    elif kind == "constant":
+        x[:] = np.where(x < 0, -2.0, 0.5)
+    elif kind == "zeros":
+        x[:] = 0.0
+    elif kind == "tiny":
+        x *= np.float32(2.0 ** -131)                     # bf16 denormals
+    elif kind == "huge":
+        x *= np.float32(4e37)
+    x = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(x))
+    xd = torch.from_numpy(x).to(g.DEV).to(torch.bfloat16)
+    xo = x
+    dual = [(s + 1) % 2 for s in range(S)]
+    if kind == "nan":                                    # the last dual segment only; a zero counts as little there
+        xo = x.copy()
+        bits = xd.view(torch.int16)
+        for m, k, b in ((0, 1, 0x7FC0), (M - 1, 0, -0x40), (M // 2, 7, 0x7F81)):
+            bits[m, k], xo[m, k] = b, 0.0
+    layer = sq.Layer(M, K, 16, kseg, [0, 16], dual)
+    amax, steps = (torch.full((2, S), float("nan"), dtype=torch.float32, device=g.DEV) for _ in range(2))
+    ws = torch.full((sq.sq_calibrate_workspace_bytes(),), 0x5A, dtype=torch.uint8, device=g.DEV)
+    for p in (0.9999, 0.99, 0.75, 0.5, 0.25, 1e-4, 1.0):
+        sq.sq_calibrate_act_percentile(layer, xd, p, amax, steps, ws)
+        r = oracle.calibrate_act_percentile(xo, np.asarray(kseg, np.int32), np.asarray(dual, np.uint8), p)
+        assert np.array_equal(amax.cpu().numpy(), np.stack([r[2], r[3]])), p
+        assert np.array_equal(steps.cpu().numpy(), np.stack([r[0], r[1]])), p
+
+
 @pytest.mark.parametrize("w_dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,kseg", [(2051, [0, 1152]), (2051, [0, 2048]), (1030, [0, 2176, 4352]), (2051, [0, 4096]), (3001, [0, 256]), (3001, [0, 384]),
                                     (517, [0, 512]), (70, [0, 2176] + [2176 + 128 * i for i in range(1, 9)]), (300, [0, 128, 256, 384, 8448])],
