@@ -138,26 +138,38 @@ __global__ __launch_bounds__(256) void lowrank_down_kernel(const void* __restric
   }
 }
 
-// The same product for bf16 activations with K % 64 == 0, staged through LDS: a workgroup owns 256 token rows, a stage is
-// 64 features (128 bytes) of those rows and of the rank rows of Ld, fetched with direct global->LDS loads whose lanes
-// cover whole 128-byte row pieces (eight rows per instruction), three stages in a ring (two in flight while one is
-// multiplied), one barrier per stage.  The 16-byte chunks of a row are XOR-swizzled with (row >> 1) & 7, which makes the
-// fragment reads (lane -> row lane % 32, chunk 2 h + lane / 32) free of bank conflicts.  Every Ld byte is fetched once
-// per workgroup instead of once per wave, and every load instruction moves whole cache lines.
-constexpr int kLdsRows = 256, kLdsStages = 3;
-
+// The same product for bf16 activations with K % 64 == 0, staged through LDS: a workgroup owns RB = 1, 2 or 4 blocks of 32
+// token rows, a stage is 64 features (128 bytes) of those rows and of the rank rows of Ld, fetched with direct global->LDS loads whose
+// lanes cover whole 128-byte row pieces (eight rows per instruction) into a ring of NS stages, one barrier per stage.  The four
+// waves of a row block take one 16-feature step of every stage each and add their sums through LDS at the end, in a fixed
+// order.  The 16-byte chunks of a row are XOR-swizzled with (row >> 1) & 7, which makes the fragment reads (lane -> row lane % 32,
+// chunk 2 wave + lane / 32) free of bank conflicts.
+// What bounds it is latency: a compute unit moves its ring's bytes once per trip to memory (2.5 us with the chip loaded), so
+// the ring takes the whole LDS.  Few rows per workgroup fill the chip with whole rows of X: K is not cut over workgroups, and
+// no partial T goes through memory, where a slice of K would be short.
 __device__ __forceinline__ void lr_glds16(const void* sbase, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr) : "memory");
 }
 
-template <int JB>
-__global__ __launch_bounds__(256) void lowrank_down_lds_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ ld,
+template <int I, int LT>
+__device__ __forceinline__ void lr_wait_stages(int left) {      // until at most `left` (<= I) later stages are outstanding
+  if constexpr (I == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    if (left >= I) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(I * LT) : "memory");
+    else lr_wait_stages<I - 1, LT>(left);
+  }
+}
+
+template <int JB, int RB, int NS>
+__global__ __launch_bounds__(RB * 256) void lowrank_down_lds_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ ld,
                                                                float* __restrict__ tpart, int M, int K, int nsplit) {
   constexpr int R = JB * 32;
-  constexpr int STAGE = (kLdsRows + R) * 128;
-  constexpr int GX = kLdsRows / 8 / 4, GL = R / 8 / 4;          // direct loads per wave and stage (8 rows each)
-  constexpr int LT = GX + GL;
-  __shared__ __attribute__((aligned(1024))) char smem[kLdsStages * STAGE];
+  constexpr int ROWS = RB * 32, STAGE = (ROWS + R) * 128;
+  // direct loads per wave and stage (8 rows each): one of X and GL of Ld, these by the first LW waves only
+  constexpr int GL = R / 8 / (4 * RB) > 0 ? R / 8 / (4 * RB) : 1, LW = R / 8 / GL;
+  static_assert(LW <= 4 * RB, "pieces of Ld");
+  __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // this workgroup's run of 64-feature stages: the K / 64 stages are dealt evenly over the nsplit slices
@@ -165,26 +177,22 @@ __global__ __launch_bounds__(256) void lowrank_down_lds_kernel(const uint16_t* _
   const int b = blockIdx.y;
   const int st_begin = b * per + (b < rem ? b : rem);
   const int nst = per + (b < rem ? 1 : 0);
-  const int m0 = blockIdx.x * kLdsRows;
+  const int m0 = blockIdx.x * ROWS;
 
   // direct loads: lane -> (row lane / 8 of the instruction's eight rows, slot lane % 8 holding chunk slot ^ swizzle(row))
   const int lrow = lane >> 3, lslot = lane & 7;
-  uint32_t voffX[GX], voffL[GL];
+  auto offset = [&](const int rt, const int row) __attribute__((always_inline)) {
+    return ((uint32_t)row * (uint32_t)K) * 2u + (uint32_t)((lslot ^ ((rt >> 1) & 7)) << 4);
+  };
+  const int rx = wave * 8 + lrow;
+  const uint32_t voffX = offset(rx, m0 + rx < M ? m0 + rx : M - 1);        // rows beyond M re-read the last row, masked at the store
+  const bool with_ld = LW == 4 * RB || wave < LW;
+  uint32_t voffL[GL];
 #pragma unroll
-  for (int g = 0; g < GX; ++g) {
-    const int rt = (wave * GX + g) * 8 + lrow;
-    int r = m0 + rt;
-    r = r < M ? r : M - 1;                                    // rows beyond M re-read the last row, masked at the store
-    voffX[g] = ((uint32_t)r * (uint32_t)K) * 2u + (uint32_t)((lslot ^ ((rt >> 1) & 7)) << 4);
-  }
-#pragma unroll
-  for (int g = 0; g < GL; ++g) {
-    const int rt = (wave * GL + g) * 8 + lrow;
-    voffL[g] = ((uint32_t)rt * (uint32_t)K) * 2u + (uint32_t)((lslot ^ ((rt >> 1) & 7)) << 4);
-  }
+  for (int g = 0; g < GL; ++g) voffL[g] = offset((wave * GL + g) * 8 + lrow, (wave * GL + g) * 8 + lrow);
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)smem);
-  const uint32_t ldsX = lds0 + (uint32_t)(wave * GX) * 1024u;
-  const uint32_t ldsL = lds0 + (uint32_t)kLdsRows * 128u + (uint32_t)(wave * GL) * 1024u;
+  const uint32_t ldsX = lds0 + (uint32_t)wave * 1024u;
+  const uint32_t ldsL = lds0 + (uint32_t)ROWS * 128u + (uint32_t)(wave * GL) * 1024u;
   auto issue_stage = [&](const int s) __attribute__((always_inline)) {       // s: stage index inside this slice
     const size_t kbyte = (size_t)(st_begin + s) * 128;
     // uniform base addresses in scalar registers (the halves go through unsigned 32-bit values: readfirstlane returns a
@@ -197,73 +205,95 @@ __global__ __launch_bounds__(256) void lowrank_down_lds_kernel(const uint16_t* _
     };
     const void* px = uniform_ptr(x, kbyte);
     const void* pl = uniform_ptr(ld, kbyte);
-    const uint32_t so = __builtin_amdgcn_readfirstlane((uint32_t)(s % kLdsStages) * (uint32_t)STAGE);
+    const uint32_t so = __builtin_amdgcn_readfirstlane((uint32_t)(s % NS) * (uint32_t)STAGE);
+    lr_glds16(px, voffX, __builtin_amdgcn_readfirstlane(ldsX + so));
+    if (with_ld)
 #pragma unroll
-    for (int g = 0; g < GX; ++g) lr_glds16(px, voffX[g], ldsX + so + (uint32_t)g * 1024u);
-#pragma unroll
-    for (int g = 0; g < GL; ++g) lr_glds16(pl, voffL[g], ldsL + so + (uint32_t)g * 1024u);
+      for (int g = 0; g < GL; ++g) lr_glds16(pl, voffL[g], __builtin_amdgcn_readfirstlane(ldsL + so + (uint32_t)g * 1024u));
   };
 
-  // fragments: row lane % 32 of a 32-row block, chunk 2 h + lane / 32 of k-step h
-  const int frow = lane & 31, fhi = lane >> 5, fsw = (frow >> 1) & 7;
-  int foff[4];
+  // fragments: row lane % 32 of a 32-row block, chunk 2 kw + lane / 32
+  const int kw = wave & 3, rb = wave >> 2;
+  const int frow = lane & 31, fhi = lane >> 5;
+  const int foff = frow * 128 + (((2 * kw + fhi) ^ ((frow >> 1) & 7)) << 4);
+  v16f acc[JB];
 #pragma unroll
-  for (int h = 0; h < 4; ++h) foff[h] = frow * 128 + (((2 * h + fhi) ^ fsw) << 4);
-  const char* fragX = smem + (wave * 64) * 128;
-  const char* fragL = smem + kLdsRows * 128;
-  v16f acc[2][JB];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int jb = 0; jb < JB; ++jb) acc[i][jb] = (v16f)(0.0f);
+  for (int jb = 0; jb < JB; ++jb) acc[jb] = (v16f)(0.0f);
 
 #pragma unroll 1
-  for (int s = 0; s < kLdsStages - 1 && s < nst; ++s) issue_stage(s);
+  for (int s = 0; s < NS - 1 && s < nst; ++s) issue_stage(s);
 #pragma unroll 1
   for (int s = 0; s < nst; ++s) {
-    // stage s has landed in this wave's view (loads return in order): all but the loads of the later stages issued so far
-    if (s + kLdsStages - 1 <= nst) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kLdsStages - 2) * LT) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // stage s has landed in this wave's view (loads return in order)
+    if (with_ld) lr_wait_stages<NS - 2, 1 + GL>(nst - 1 - s);
+    else lr_wait_stages<NS - 2, 1>(nst - 1 - s);
     __syncthreads();                                          // ... and in every wave's; the buffer of stage s - 1 is free
-    if (s + kLdsStages - 1 < nst) issue_stage(s + kLdsStages - 1);
-    const int so = (s % kLdsStages) * STAGE;
+    if (s + NS - 1 < nst) issue_stage(s + NS - 1);
+    const char* frag = smem + (s % NS) * STAGE + foff;
+    const v8bf xa = *reinterpret_cast<const v8bf*>(frag + rb * (32 * 128));
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      v8bf xa[2], lb[JB];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) xa[i] = *reinterpret_cast<const v8bf*>(fragX + so + i * (32 * 128) + foff[h]);
-#pragma unroll
-      for (int jb = 0; jb < JB; ++jb) lb[jb] = *reinterpret_cast<const v8bf*>(fragL + so + jb * (32 * 128) + foff[h]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb) acc[i][jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lb[jb], xa[i], acc[i][jb], 0, 0, 0);
+    for (int jb = 0; jb < JB; ++jb) {
+      const v8bf lb = *reinterpret_cast<const v8bf*>(frag + (ROWS + jb * 32) * 128);
+      acc[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lb, xa, acc[jb], 0, 0, 0);
     }
   }
-  // element v of block (i, jb) in lane l: row m0 + 64 wave + 32 i + (l & 31), column j = 32 jb + 8 (v >> 2) + 4 (l >> 5) + (v & 3)
+  // element v of block jb in lane l: row m0 + 32 rb + (l & 31), column j = 32 jb + 8 (v >> 2) + 4 (l >> 5) + (v & 3).  Run q = 4 jb +
+  // (v >> 2) of four columns is added up by wave q / JB of the row block, in the order of the waves.
+  static_assert(4 * RB * 4 * JB * 1024 <= NS * STAGE, "the sums of all waves");
+  __syncthreads();                                            // the ring has been read
+  char* sums = smem + rb * (16 * JB * 1024) + lane * 16;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int m = m0 + wave * 64 + i * 32 + frow;
-    if (m >= M) continue;
-    float* out = tpart + ((size_t)blockIdx.y * M + m) * R;
+  for (int q = 0; q < 4 * JB; ++q) {
+    const v16f& t = acc[q >> 2];
+    const int v = 4 * (q & 3);
+    *reinterpret_cast<v4f*>(sums + (kw * 4 * JB + q) * 1024) = (v4f){t[v], t[v + 1], t[v + 2], t[v + 3]};
+  }
+  __syncthreads();
+  const int m = m0 + rb * 32 + frow;
+  if (m >= M) return;
+  float* out = tpart + ((size_t)blockIdx.y * M + m) * R;
 #pragma unroll
-    for (int jb = 0; jb < JB; ++jb)
+  for (int i = 0; i < JB; ++i) {
+    const int q = kw * JB + i;
+    v4f sum = *reinterpret_cast<const v4f*>(sums + q * 1024);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const v4f o = {acc[i][jb][4 * g], acc[i][jb][4 * g + 1], acc[i][jb][4 * g + 2], acc[i][jb][4 * g + 3]};
-        *reinterpret_cast<v4f*>(out + jb * 32 + 8 * g + 4 * fhi) = o;
-      }
+    for (int w = 1; w < 4; ++w) sum += *reinterpret_cast<const v4f*>(sums + (w * 4 * JB + q) * 1024);
+    *reinterpret_cast<v4f*>(out + 8 * q + 4 * fhi) = sum;
   }
 }
 
-// slices of the LDS-staged kernel: one workgroup per compute unit, at least four stages (256 features) per slice
-static int lowrank_lds_splits(int M, int K, int cus) {
-  const int row_blocks = (M + kLdsRows - 1) / kLdsRows;
-  int s = cus / row_blocks;
-  const int max_by_k = (K >> 6) / 4;
-  s = s < max_by_k ? s : max_by_k;
-  s = s < kLrMaxSplit ? s : kLrMaxSplit;
-  return s < 1 ? 1 : s;
+// Row blocks per workgroup and slices of K: the choice that moves the fewest bytes into a compute unit.  The launch of the sum costs
+// what moves in 2 - 3 us (144 KB), and a byte of partial T, written and read back by all at once, as much as ten of a ring.  8500 x
+// 1536, rank 64: 256 rows and seven slices took 10.6 + 5.3 us for the sum, two row blocks and no slices take 13.1.  Whole call with
+// N = 128, 160 sizes of 1 - 16384 rows and K of 512 - 16384, against 256 rows and a workgroup per compute unit always: 4096 x 1536
+// 17.9 -> 15.5 us, 256 x 3072 16.0 -> 14.2, 64 x 8192 20.3 -> 16.5, 6000 x 3072 22.2 -> 19.7; 8500 x 4096 27.9 -> 28.4 is the worst.
+struct DownPlan { int rb, slices; };
+constexpr int kLdsSliceStages = 8, kLdsRing = 144 * 1024;
+static DownPlan lowrank_lds_plan(int M, int K, int rank, int cus) {
+  DownPlan best{1, 1};
+  long long least = -1;
+  const int nst = K >> 6;
+  for (int rb = 1; rb <= 4; rb *= 2) {
+    const int blocks = (M + 32 * rb - 1) / (32 * rb);
+    int most = cus / blocks;                                     // slices of at least eight stages, a workgroup per compute unit
+    most = most < nst / kLdsSliceStages ? most : nst / kLdsSliceStages;
+    most = most < kLrMaxSplit ? most : kLrMaxSplit;
+    for (int pass = 0; pass < 2; ++pass) {
+      const int s = pass == 0 || most < 1 ? 1 : most;
+      const long long rounds = (blocks * s + cus - 1) / cus;
+      const long long cost = rounds * ((nst + s - 1) / s) * ((32 * rb + rank) * 128) + (s > 1 ? 144 * 1024 + 40ll * s * M * rank / cus : 0);
+      if (least < 0 || cost < least) { least = cost; best = {rb, s}; }
+    }
+  }
+  return best;
+}
+template <int JB>
+static void launch_down_lds(const uint16_t* x, const uint16_t* ld, float* tpart, int M, int K, DownPlan p, hipStream_t st) {
+#define SQ_DOWN(RB) hipLaunchKernelGGL((lowrank_down_lds_kernel<JB, RB, (kLdsRing / ((32 * RB + 32 * JB) * 128) < 12 ? kLdsRing / ((32 * RB + 32 * JB) * 128) : 12)>), dim3((M + 32 * RB - 1) / (32 * RB), p.slices), dim3(RB * 256), 0, st, x, ld, tpart, M, K, p.slices)
+  if (p.rb == 1) SQ_DOWN(1);
+  else if (p.rb == 2) SQ_DOWN(2);
+  else SQ_DOWN(4);
+#undef SQ_DOWN
 }
 static bool lowrank_lds_usable(const void* x, bool x_is_bf16, const uint16_t* ld, int M, int K) {
   return x_is_bf16 && K % 64 == 0 && K >= 64 && (size_t)M * K * 2 < 0x7FFFFFFFull && (size_t)64 * K * 2 < 0x7FFFFFFFull &&
@@ -427,7 +457,7 @@ __global__ __launch_bounds__(256) void lowrank_up_kernel(const float* __restrict
 }
 
 size_t lowrank_workspace_bytes(int M, int K, int rank, int cus) {
-  const int a = lowrank_splits(M, K, cus), b = lowrank_lds_splits(M, K, cus);    // whichever down projection runs
+  const int a = lowrank_splits(M, K, cus), b = lowrank_lds_plan(M, K, rank, cus).slices;    // whichever down projection runs
   return (size_t)((a > b ? a : b) + 1) * M * rank * sizeof(float);               // the slices' partial T, then their sum
 }
 
@@ -435,10 +465,10 @@ hipError_t launch_lowrank_add(const void* x, bool x_is_bf16, const uint16_t* ld,
                               void* y_out, bool y_is_bf16, int M, int K, int N, float* workspace, int cus, hipStream_t st) {
   int nsplit;
   if (lowrank_lds_usable(x, x_is_bf16, ld, M, K)) {
-    nsplit = lowrank_lds_splits(M, K, cus);
-    dim3 gd((M + kLdsRows - 1) / kLdsRows, nsplit);
-    if (rank == 64) hipLaunchKernelGGL(lowrank_down_lds_kernel<2>, gd, dim3(256), 0, st, reinterpret_cast<const uint16_t*>(x), ld, workspace, M, K, nsplit);
-    else hipLaunchKernelGGL(lowrank_down_lds_kernel<1>, gd, dim3(256), 0, st, reinterpret_cast<const uint16_t*>(x), ld, workspace, M, K, nsplit);
+    const DownPlan p = lowrank_lds_plan(M, K, rank, cus);
+    nsplit = p.slices;
+    if (rank == 64) launch_down_lds<2>(reinterpret_cast<const uint16_t*>(x), ld, workspace, M, K, p, st);
+    else launch_down_lds<1>(reinterpret_cast<const uint16_t*>(x), ld, workspace, M, K, p, st);
   } else {
     nsplit = lowrank_splits(M, K, cus);
     int slice = (K + nsplit - 1) / nsplit;

@@ -944,6 +944,14 @@ def test_lowrank_add(oracle, case):
         assert torch.equal(y1, y2)
 
 
+@pytest.mark.parametrize("M,K,rank", [(1, 64, 32), (33, 1600, 64), (33, 832, 32), (8225, 192, 64), (8225, 896, 32), (16417, 64, 32), (16417, 192, 64),
+                                      (6001, 4096, 64), (4100, 8256, 32)])
+def test_lowrank_down_plans(oracle, M, K, rank):
+    """The down projection's choices: one row block of 32 and two, where 32 rows per compute unit are no longer enough, four with and
+    without slices of K; fewer stages than the ring, as many and more, stages dealt unevenly, a last row block of one row."""
+    test_lowrank_add(oracle, dict(M=M, K=K, N=40, rank=rank, x_dtype="bf16", yq=True))
+
+
 @pytest.mark.parametrize("rank,yq", [(64, True), (32, True), (64, False)])
 @pytest.mark.parametrize("M,N", [(201, 65002), (203, 64999), (4130, 3200)])
 def test_lowrank_add_large(M, N, rank, yq):
