@@ -352,8 +352,11 @@ static void launch_weight_pass(const void* w, bool w_is_bf16, int8_t* wq, float*
 // Weight quantize of aligned rows (8-bit codes, or 4-bit codes in the packed order of quantize_weight_w4_kernel): TPI threads
 // own one (output channel, K-segment) and keep it in registers between the maximum and the codes, so W is read once, by up
 // to NCH independent 16-byte loads per thread.  The code is round_quotient()'s, bit-identical to the division (one in a few
-// thousand elements divides).  HBM-bound: 3072 x 15360 fp32, two K-segments (189 MB in): 8 bit 83 -> 51 us (4.6 TB/s), 4 bit
-// 108 -> 45 us (4.7 TB/s) against the one-wave-per-row kernels that read the row twice and divide every element.
+// thousand elements divides).  HBM-bound: 3072 x 15360 fp32, two K-segments (189 MB in): 8 bit 44 us (5.3 TB/s), 4 bit 42
+// (5.0 TB/s), against 83 and 108 of the one-wave-per-row kernels that read the row twice and divide every element.  A workgroup
+// is short, so the chain in front of its loads counts: the grid's second dimension is the K-segment (no division, the segment's
+// bounds by scalar loads), and loads beyond the segment repeat its last elements where a test on each kept two of them apart
+// from the rest and put a wait between them (8 bit 50, 4 bit 45 us; 4096 x 20480 83 -> 75, bf16 3072 x 15360 38 -> 30).
 // ------------------------------------------------------------------------------------------------
 template <bool BF16, int BITS, int TPI, int NCH>
 __global__ __launch_bounds__(256) void quantize_weight_row_kernel(const void* __restrict__ w, uint8_t* __restrict__ out,
@@ -362,9 +365,15 @@ __global__ __launch_bounds__(256) void quantize_weight_row_kernel(const void* __
   constexpr int PS = 64 / CE;                      // 4 bit: pairs of loads (64 columns apart) per 128-code step
   const int rows = BITS == 4 ? (N + 15) & ~15 : N;
   const int t = threadIdx.x % TPI;
-  const long item = (long)blockIdx.x * (256 / TPI) + threadIdx.x / TPI;
-  if (item >= (long)rows * tb.S) return;           // a whole wave (TPI 64) or workgroup leaves together
-  const int n = (int)(item / tb.S), ks = (int)(item - (long)n * tb.S);
+  unsigned block = blockIdx.x;
+  // 4 bit, wide fp32 rows: the 16 rows that share the packed lines go to one XCD (workgroup ids go round the eight; 3072 x 15360 43.6
+  // -> 42.2 us, 4096 x 20480 73.4 -> 70.8; 12288 x 3072 31.0 / 31.9, bf16 2048 x 10240 15.4 / 15.8)
+  if (BITS == 4 && !BF16 && NCH >= 8) {
+    constexpr unsigned G = 16 * TPI / 256;         // workgroups of such a group
+    if (block < gridDim.x / (8 * G) * (8 * G)) block = block / (8 * G) * (8 * G) + block % 8 * G + block / 8 % G;
+  }
+  const int n = block * (256 / TPI) + __builtin_amdgcn_readfirstlane(threadIdx.x / TPI), ks = blockIdx.y;
+  if (n >= rows) return;                           // a whole wave (TPI 64) or workgroup leaves together
   const int k0 = tb.off[ks], L = tb.off[ks + 1] - k0;
   auto column = [&](const int l) __attribute__((always_inline)) {   // first column, inside the segment, of load l
     if (BITS == 8) return (t + TPI * l) * CE;
@@ -388,11 +397,10 @@ __global__ __launch_bounds__(256) void quantize_weight_row_kernel(const void* __
   const size_t row = (size_t)n * K + k0;
   v4i raw[NCH];
 #pragma unroll
-  for (int l = 0; l < NCH; ++l) {
-    raw[l] = (v4i)(0);
-    if (column(l) < L)
-      raw[l] = BF16 ? __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const uint16_t*>(w) + row + column(l)))
-                    : __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(w) + row + column(l)));
+  for (int l = 0; l < NCH; ++l) {                  // beyond the segment: its last elements again, which no maximum minds
+    const int c = column(l) < L ? column(l) : L - CE;
+    raw[l] = BF16 ? __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const uint16_t*>(w) + row + c))
+                  : __builtin_nontemporal_load(reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(w) + row + c));
   }
   auto value = [&](const int l, const int i) __attribute__((always_inline)) {
     if (!BF16) return __int_as_float(raw[l][i & 3]);
@@ -458,8 +466,9 @@ static bool launch_weight_rows(const void* w, bool w_is_bf16, uint8_t* out, floa
   const int shortest = w_is_bf16 ? (BITS == 8 ? 257 : 385) : (BITS == 8 ? 1 : 129);
   if (!ok || longest > 256 * 16 * ce || longest < shortest) return false;
   if (longest > 64 * 4 * ce && (BITS == 8 ? 4ll : 6ll) * K < (long long)tb.S * longest) return false;
-  const long items = (long)(BITS == 4 ? (N + 15) & ~15 : N) * tb.S;
-#define SQ_ROWS(B, T, C) hipLaunchKernelGGL((quantize_weight_row_kernel<B, BITS, T, C>), dim3((unsigned)((items + 256 / T - 1) / (256 / T))), dim3(256), 0, st, w, out, wscale, N, K, tb)
+  const int rows = BITS == 4 ? (N + 15) & ~15 : N;
+  const long items = (long)rows * tb.S;
+#define SQ_ROWS(B, T, C) hipLaunchKernelGGL((quantize_weight_row_kernel<B, BITS, T, C>), dim3((unsigned)((rows + 256 / T - 1) / (256 / T)), tb.S), dim3(256), 0, st, w, out, wscale, N, K, tb)
 #define SQ_PICK(B) \
   if (longest <= 64 * 4 * ce) SQ_ROWS(B, 64, 4); \
   else if (longest <= 64 * 8 * ce && items >= 2048) SQ_ROWS(B, 64, 8); \
