@@ -465,6 +465,8 @@ int sq_version(void);
  *                       5 = tiles taken in turn (one K-segment without a polarity split, K a multiple of 128 from 512;
  *                       sq_seglinear, sq_seglinear_dynamic, sq_seglinear_fp8; "gemm_variant" 0 (not fp8) / 1 / 2: tiles of
  *                       128 x 256, 128 x 192, 128 x 128; -1: 128 x 192)
+ *                       6 = a wave per 32 x 32 outputs (at most two K-segments, boundaries multiples of 128; sq_seglinear,
+ *                       sq_seglinear_dynamic)
  * Returns SQ_ERR_INVALID_ARG for an unknown key or value.  Not thread-safe against running calls.
  */
 sq_status sq_tuning_set(const char* key, int value);

@@ -8,7 +8,7 @@
 namespace {
 
 int g_gemm_variant = -1;   // sq_tuning_set("gemm_variant", v)
-int g_force_path = -1;     // sq_tuning_set("force_path", p): 0 generic, 1 MFMA tiles, 2 skinny, 3 skinny weight stream, 4 K-splitting tiles, 5 tiles in turn
+int g_force_path = -1;     // sq_tuning_set("force_path", p): 0 generic, 1 MFMA tiles, 2 skinny, 3 skinny weight stream, 4 K-splitting tiles, 5 tiles in turn, 6 direct
 
 bool offsets_ok(int n, int cnt, const int32_t* off) {
   if (cnt < 1 || cnt > SQ_MAX_SEGMENTS || off == nullptr) return false;
@@ -111,12 +111,15 @@ sq_status run_gemm(const sq_layer* L, const int8_t* xq, const int8_t* wq,
   if (path == 4 && ktile < 0) return SQ_ERR_UNSUPPORTED;
   int ptile = path == 5 ? forced_pair_tile(a, tb, mode, false) : -1;
   if (path == 5 && ptile < 0) return SQ_ERR_UNSUPPORTED;
+  if (path == 6 && !sq::direct_supported(a, tb, mode)) return SQ_ERR_UNSUPPORTED;
   if (path < 0) {
-    // up to two 16-row tiles of tokens: the weight-stream kernel (measured 5.9 TB/s on wide layers); more rows: the
+    // up to two 16-row tiles of tokens: the weight-stream kernel (measured 5.9 TB/s on wide layers); more rows: a wave per 32 x 32
+    // outputs where direct_pick() finds a layer small enough for it, the
     // K-splitting tiles where ksplit_pick() finds them the faster ones, the tiles taken in turn where pair_pick() does, else the
     // tile kernel; the skinny kernel serves the layers of up to 64 rows that none of them takes
     if (a.M > 32 && g_gemm_variant < 0) ktile = sq::ksplit_pick(a, tb);
     if (a.M <= 32 && sq::stream_supported(a, tb)) path = 3;
+    else if (g_gemm_variant < 0 && sq::direct_pick(a, tb, mode)) path = 6;
     else if (ktile >= 0) path = 4;
     else if (g_gemm_variant < 0 && (ptile = sq::pair_pick(a, tb, mode, false)) >= 0) path = 5;
     else if (a.M <= 64 && a.M > 32 && sq::mfma_supported(a, tb)) path = 1;
@@ -125,7 +128,9 @@ sq_status run_gemm(const sq_layer* L, const int8_t* xq, const int8_t* wq,
     else path = 0;
   }
   hipError_t e;
-  if (path == 5) {
+  if (path == 6) {
+    e = sq::launch_seglinear_direct(a, tb, mode, st);
+  } else if (path == 5) {
     e = sq::launch_seglinear_pair(a, tb, mode, ptile, false, st);
   } else if (path == 4) {
     e = sq::launch_seglinear_ksplit(a, tb, mode, ktile, st);
@@ -185,8 +190,13 @@ sq_status run_gemm_dynamic(const sq_layer* L, const int8_t* xq, const float* tok
   if (w_bits == 8 && g_force_path == 5) ptile = forced_pair_tile(a, tb, mode, false);
   else if (w_bits == 8 && g_force_path < 0 && g_gemm_variant < 0 && !stream_ok && ktile < 0) ptile = sq::pair_pick(a, tb, mode, false);
   if (g_force_path == 5 && ptile < 0) return SQ_ERR_UNSUPPORTED;
+  const bool direct = w_bits == 8 && (g_force_path == 6 ? sq::direct_supported(a, tb, mode)
+                                                        : g_force_path < 0 && g_gemm_variant < 0 && !stream_ok && sq::direct_pick(a, tb, mode));
+  if (g_force_path == 6 && !direct) return SQ_ERR_UNSUPPORTED;
   hipError_t e;
-  if (ptile >= 0) {
+  if (direct) {
+    e = sq::launch_seglinear_direct(a, tb, mode, st);
+  } else if (ptile >= 0) {
     e = sq::launch_seglinear_pair(a, tb, mode, ptile, false, st);
   } else if (g_force_path != 0 && g_force_path != 1 && g_force_path != 4 && stream_ok) {
     e = w_bits == 4 ? sq::launch_seglinear_stream_w4(a, tb, mode, sq::device_cus(), st)
@@ -845,7 +855,7 @@ sq_status sq_tuning_set(const char* key, int value) {
     return SQ_OK;
   }
   if (std::strcmp(key, "force_path") == 0) {
-    if (value < -1 || value > 5) return SQ_ERR_INVALID_ARG;
+    if (value < -1 || value > 6) return SQ_ERR_INVALID_ARG;
     g_force_path = value;
     return SQ_OK;
   }

@@ -102,6 +102,12 @@ bool ksplit_supported(const GemmArgs& a, const GemmTable& tb);
 int ksplit_pick(const GemmArgs& a, const GemmTable& tb);
 hipError_t launch_seglinear_ksplit(GemmArgs a, const GemmTable& tb, OutMode mode, int tile, hipStream_t st);
 
+// seglinear_direct.hip : small layers, a wave per 32 x 32 outputs.  K and K-segment boundaries % 128 == 0, at most two K-segments, no
+// seg_scale, no raw sums.
+bool direct_supported(const GemmArgs& a, const GemmTable& tb, OutMode mode);
+bool direct_pick(const GemmArgs& a, const GemmTable& tb, OutMode mode);
+hipError_t launch_seglinear_direct(const GemmArgs& a, const GemmTable& tb, OutMode mode, hipStream_t st);
+
 // seglinear_pair.hip : layers of one K-segment without a polarity split, large enough for the compute units to take tiles in
 // turn.  K % 128 == 0, K >= 512, no seg_scale; int8 (static or per-token steps) and fp8 (static steps).
 // pair_pick: its tile (0: 128 x 256, int8 only, 1: 128 x 192, 2: 128 x 128), or -1 where the tile kernel serves.

@@ -1749,6 +1749,64 @@ def test_seglinear_ksplit_forced_elsewhere_is_refused():
         sq.sq_tuning_set("force_path", -1)
 
 
+# A wave per 32 x 32 outputs, forced and chosen: fewer stages of 128 columns than the ring of four, as many, more; a K-segment that ends
+# inside the ring and at its end; both kinds of segment in either order; one row and one column, ragged and odd edges.
+DIRECT_CASES = [
+    dict(M=1, N=1, seg=[128], dual=[1]),
+    dict(M=33, N=384, seg=[128, 128], dual=[1, 1]),
+    dict(M=64, N=100, seg=[384, 128], dual=[0, 1]),
+    dict(M=95, N=33, seg=[512, 512], dual=[1, 0]),
+    dict(M=40, N=66, seg=[640], dual=[0]),
+    dict(M=257, N=511, seg=[128, 1024], dual=[0, 0]),
+    dict(M=37, N=260, seg=[1152, 640], dual=[1, 1]),
+    dict(M=130, N=1000, seg=[2048], dual=[1]),
+]
+
+
+@pytest.mark.parametrize("case", DIRECT_CASES, ids=lambda c: "%dx%dx%d_S%d" % (c["M"], sum(c["seg"]), c["N"], len(c["seg"])))
+def test_seglinear_direct(oracle, case):
+    import torch
+
+    g = _gpu()
+    M, N, K = case["M"], case["N"], sum(case["seg"])
+    w = wl.random_layer(M, K, N, [0] + list(np.cumsum(case["seg"])), [0, N], case["dual"], seed=M + K + N, x_dtype="bf16", act="gelu",
+                        with_bias=N % 2 == 0)
+    r = oracle.seglinear(w.x, w.w, w.kseg_off, w.nseg_off, w.dual, w.s_pos, w.s_neg, None, w.bias)
+    rd = oracle.seglinear_dynamic(w.x, w.w, w.kseg_off, w.nseg_off, w.dual, None, w.bias, wbits=8)
+    tol = RTOL * float(np.abs(r.y32).max())
+    gl = g.GpuLayer(w)
+    gl.quantize_weight()
+    tok = torch.full((2, M, w.S), float("nan"), dtype=torch.float32, device=g.DEV)
+    for path in (6, -1):
+        gl.quantize_act()
+        sq.sq_tuning_set("force_path", path)
+        assert float(np.abs(gl.seglinear("f32").astype(np.float64) - r.y32.astype(np.float64)).max()) <= tol
+        g.check_bf16_against(gl.seglinear("bf16"), r.y32, wl.f32_to_bf16_bits(r.y32), tol)
+        sq.sq_quantize_act_dynamic(gl.layer, gl.x, gl.xq, tok)
+        y = torch.full((M, N), float("nan"), dtype=torch.float32, device=g.DEV)
+        sq.sq_seglinear_dynamic(gl.layer, gl.xq, tok, gl.wq, 8, gl.wscale, gl.bias, y)
+        assert float(np.abs(y.cpu().numpy().astype(np.float64) - rd.y32.astype(np.float64)).max()) <= RTOL * float(np.abs(rd.y32).max())
+
+
+def test_seglinear_direct_forced_elsewhere_is_refused():
+    """Three K-segments, a 64-aligned segment, seg_scale, raw sums: the forced call must not fall back to another kernel."""
+    import torch
+
+    g = _gpu()
+    for K, kseg, scale in ((384, [0, 128, 256, 384], None), (256, [0, 64, 256], None), (256, [0, 256], [1.5])):
+        S = len(kseg) - 1
+        layer = sq.Layer(64, K, 64, kseg, [0, 64], [0] * S, [0.1] * S, [0.1] * S, scale)
+        q = torch.zeros((64, K), dtype=torch.int8, device=g.DEV)
+        ws, y = torch.ones((S, 64), device=g.DEV), torch.zeros((64, 64), device=g.DEV)
+        sq.sq_tuning_set("force_path", 6)
+        with pytest.raises(sq.SqError):
+            sq.sq_seglinear(layer, q, q, ws, None, y)
+        acc = torch.zeros((2, S, 64, 64), dtype=torch.int32, device=g.DEV)
+        with pytest.raises(sq.SqError):
+            sq.sq_seglinear_debug_acc(layer, q, q, acc[0], acc[1])
+        sq.sq_tuning_set("force_path", -1)
+
+
 # Tiles taken in turn by two groups of waves, every tile width forced: one stored by its group alone, one beside each group's next
 # (2 and 3 tiles per compute unit), K loops of 4, 5, 9 and 12 stages (three, two and one blocks stored per stage), ragged and odd edges
 # (16-, 8- and 2-byte row pieces of bf16).
