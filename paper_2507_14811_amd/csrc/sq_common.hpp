@@ -109,11 +109,12 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return (uint16_t)(f32
 // round-half-to-even.  v * (1/s) is within 2^-14.4 of the correctly rounded quotient whenever the
 // quotient matters (|q| <= 256, beyond that both clip), so the cheap product decides unless it lands
 // within 2^-13 of a tie; only then (or when inv is NaN/Inf) the true division is evaluated.
+constexpr float kTieDistance = 0.4998779296875f;
 __device__ __forceinline__ float round_quotient(float v, float s, float inv) {
   float q0 = v * inv;
   float r = __builtin_rintf(q0);
   float t = q0 - r;
-  if (!(__builtin_fabsf(t) < 0.4998779296875f)) r = __builtin_rintf(v / s);
+  if (!(__builtin_fabsf(t) < kTieDistance)) r = __builtin_rintf(v / s);
   return r;
 }
 
