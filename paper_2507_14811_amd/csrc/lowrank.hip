@@ -367,12 +367,13 @@ __global__ __launch_bounds__(256) void lowrank_up_kernel(const float* __restrict
   const int ncols = (N - n0) < kLrStrip ? (N - n0) : kLrStrip;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)smem);
   constexpr int RPI = 1024 / RB, CPR = RB / 16;
+  const uint16_t* strip = lu + (size_t)n0 * R;                     // Lu may exceed 4 GiB: 32-bit offsets only inside the strip
 #pragma unroll
   for (int g = 0; g < kLrStrip / RPI / 4; ++g) {
     const int rt = (wave * (kLrStrip / RPI / 4) + g) * RPI + lane / CPR;
     const int r = rt < ncols ? rt : ncols - 1;                     // beyond N: re-read the last row, masked at the store
     const int slot = (lane % CPR) ^ ((RB == 128 ? rt >> 1 : rt >> 2) & SW);
-    lr_glds16(lu, (uint32_t)(n0 + r) * (uint32_t)RB + (uint32_t)(slot << 4), __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(wave * (kLrStrip / RPI / 4) + g) * 1024u));
+    lr_glds16(strip, (uint32_t)(r * RB + (slot << 4)), __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(wave * (kLrStrip / RPI / 4) + g) * 1024u));
   }
   const int mb = blockIdx.y * 128 + wave * 32;
   v8bf thi[KH / 8], tmid[KH / 8], tlo[KH / 8];

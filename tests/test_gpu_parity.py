@@ -994,6 +994,31 @@ def test_lowrank_up_sizes(M, N, rank):
     test_lowrank_add_large(M, N, rank, True)
 
 
+@pytest.mark.parametrize("rank,N", [(64, (1 << 25) + 200), (32, (1 << 26) + 200)])
+def test_lowrank_up_beyond_4gib(rank, N):
+    """Lu of more than 4 GiB: the last columns, whose byte offsets need 33 bits, bit for bit those of a call on these columns alone
+    (the same T, and the matrix instruction adds up the rank's features in one order)."""
+    import torch
+
+    g = _gpu()
+    M, K, tail = 2, 16, 328                               # the tail begins on a strip of 128 columns
+    assert (N - tail) % 128 == 0 and N * rank * 2 > 1 << 32
+    gen = torch.Generator(device=g.DEV)
+    gen.manual_seed(rank)
+    x, ld = (torch.randn(s, generator=gen, device=g.DEV).to(torch.bfloat16) for s in ((M, K), (rank, K)))
+    lu = torch.randn((N, rank), dtype=torch.bfloat16, generator=gen, device=g.DEV)
+
+    def call(rows):
+        n = rows.shape[0]
+        layer = sq.Layer(M, K, n, [0, K], [0, n], [0])
+        ws = torch.empty((sq.sq_lowrank_workspace_bytes(layer, rank),), dtype=torch.uint8, device=g.DEV)
+        y = torch.full((M, n), float("nan"), dtype=torch.float32, device=g.DEV)
+        sq.sq_lowrank_add(layer, x, ld, rows, None, y, ws)
+        return y
+
+    assert torch.equal(call(lu)[:, N - tail:], call(lu[N - tail:]))
+
+
 @pytest.mark.parametrize("M", [16, 300])
 def test_w4_layer_with_lowrank_branch(oracle, M):
     """The 4-bit setting end to end: W = Lu Ld + R (numpy's SVD, rank 64), R through the 4-bit weight quantizer and the
