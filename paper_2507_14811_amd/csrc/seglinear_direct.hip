@@ -158,12 +158,26 @@ bool direct_supported(const GemmArgs& a, const GemmTable& tb, OutMode mode) {
 // waves per compute unit 14.0 -> 11.6 (128 x 2048 x 4096), 17.8 / 18.8 at 4096 columns; at four they share the loads' path (256 x 256
 // x 4096: 7.7 / 9.1).  One K-segment: two paths 5.1 -> 4.1 at 512 columns, 8.9 -> 7.8 at 2048, 11.7 / 12.3 at 4096; one path 3.9 / 3.9
 // at 256, 4.3 -> 3.9 at 384, 6.4 -> 5.6 at 1536, 7.2 / 7.1 at 2048.
+// Up to 32 rows come here where the slab of the weight-stream kernel is too small for them (17 - 32 rows from 2560 columns, 1 - 16
+// from 5120).  With per-token steps the K-splitting kernel would run: 1.06 - 2.2 times as fast here (125 layers).  With static steps it
+// is the skinny kernel, whose four waves split K: of 58 layers of 16 rows and fewer most are slower here (0.82 - 1.1, median 0.94), so
+// they stay there.  17 - 32 rows, 400 layers: beyond 4096 outputs 1.6 - 1.9 times as fast (24 x 6272 x 8192 31.6 -> 17.9 us), without
+// a split segment 1.0 - 1.16; below, where at least half of the columns run two paths, 0.99 - 1.19 up to 4096 columns or 1024 outputs
+// and 0.93 - 1.14 (median 1.0) beyond both; 0.84 - 1.2 (median 1.01) where less than half do.
 bool direct_pick(const GemmArgs& a, const GemmTable& tb, OutMode mode) {
   if (!direct_supported(a, tb, mode)) return false;
   const long long waves = (long long)((a.M + 31) / 32) * ((a.N + 31) / 32);
   const int cus = device_cus();
   bool dual = false;
-  for (int s = 0; s < tb.S; ++s) dual = dual || tb.dual[s] != 0;
+  int split = 0;                                                    // columns of two paths
+  for (int s = 0; s < tb.S; ++s) {
+    if (!tb.dual[s]) continue;
+    dual = true;
+    split += tb.kseg_off[s + 1] - tb.kseg_off[s];
+  }
+  if (a.M <= 32 && a.tok_steps == nullptr &&
+      (a.M <= 16 || (a.N <= 4096 && (2 * split < a.K || (a.K > 4096 && a.N > 1024)))))
+    return false;
   if (tb.S == 2) return a.K <= 2048 ? waves <= 2 * cus : waves <= cus && a.K <= (dual ? 8192 : 4096);
   return waves <= cus && (dual ? a.K <= 2048 : a.K >= 384 && a.K <= 1536);
 }

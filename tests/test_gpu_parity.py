@@ -1813,6 +1813,32 @@ def test_seglinear_direct(oracle, case):
         assert float(np.abs(y.cpu().numpy().astype(np.float64) - rd.y32.astype(np.float64)).max()) <= RTOL * float(np.abs(rd.y32).max())
 
 
+@pytest.mark.parametrize("M,N,seg,dual", [(8, 512, [1024, 4096], [1, 1]), (16, 8192, [2560, 2560], [0, 1]), (24, 2048, [3072, 3072], [1, 1]),
+                                          (32, 1000, [2048, 512], [0, 1]), (17, 512, [1280, 1408], [0, 0])])
+def test_few_rows_beyond_the_stream(M, N, seg, dual):
+    """Layers of up to 32 rows that the weight-stream kernel refuses for their columns and where a wave per 32 x 32 outputs is the
+    slower one: the automatic choice is the skinny kernel, bit for bit (the two round the sums of the K-segments differently)."""
+    import torch
+
+    g = _gpu()
+    K = sum(seg)
+    gen = torch.Generator(device=g.DEV)
+    gen.manual_seed(K + N)
+    xq, wq = (torch.randint(-127, 128, s, generator=gen, device=g.DEV, dtype=torch.int8) for s in ((M, K), (N, K)))
+    ws, bias = (torch.rand(s, generator=gen, device=g.DEV) for s in ((2, N), (N,)))
+    layer = sq.Layer(M, K, N, [0, seg[0], K], [0, N], dual, [0.013, 0.021], [0.007, 0.003])
+    y = {}
+    for path in (-1, 2, 6):
+        sq.sq_tuning_set("force_path", path)
+        y[path] = torch.full((M, N), float("nan"), device=g.DEV)
+        sq.sq_seglinear(layer, xq, wq, ws, bias, y[path])
+    sq.sq_tuning_set("force_path", 3)
+    with pytest.raises(sq.SqError):
+        sq.sq_seglinear(layer, xq, wq, ws, bias, y[-1])
+    assert not torch.equal(y[2], y[6])
+    assert torch.equal(y[-1], y[2])
+
+
 def test_seglinear_direct_forced_elsewhere_is_refused():
     """Three K-segments, a 64-aligned segment, seg_scale, raw sums: the forced call must not fall back to another kernel."""
     import torch
