@@ -684,7 +684,7 @@ def test_calibration_pass_shares(oracle, shape, dt):
         assert np.array_equal(amax.cpu().numpy(), np.stack([r[2], r[3]])), p
 
 
-@pytest.mark.parametrize("kind", ["tail", "two_scales", "constant", "zeros", "tiny", "huge", "nan"])
+@pytest.mark.parametrize("kind", ["tail", "two_scales", "constant", "zeros", "tiny", "huge", "nan", "cauchy", "strong"])
 @pytest.mark.parametrize("shape", [(1, [0, 8]), (700, [0, 64, 512]), (2049, [0, 8, 256])], ids=lambda s: "%dx%d" % (s[0], s[1][-1]))
 def test_percentile_window(oracle, shape, kind):
     """Aligned bf16 batches count a window of bit patterns around a sampled place first: order statistics inside it, on its first
@@ -710,6 +710,10 @@ def test_percentile_window(oracle, shape, kind):
         x *= np.float32(2.0 ** -131)                     # bf16 denormals
     elif kind == "huge":
         x *= np.float32(4e37)
+    elif kind == "cauchy":                               # a tail without an end: segments that go without the window
+        x /= np.where(x == 0, 1, rng.standard_normal((M, K))).astype(np.float32)
+    elif kind == "strong":                               # the first segment only, the others keep theirs
+        x[:, :kseg[1] // 8] *= 100
     x = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(x))
     xd = torch.from_numpy(x).to(g.DEV).to(torch.bfloat16)
     xo = x
@@ -1909,6 +1913,51 @@ def test_seglinear_pair_tiles(oracle, shape):
                 got = y.float().cpu().numpy().astype(np.float64)
                 tol = _fp8_tol(K, mag8, ref8, "bf16" if dt == torch.bfloat16 else "f32")
                 assert not np.isnan(got).any() and (np.abs(got - ref8) <= tol).all(), ("fp8", tile, dt)
+
+
+@pytest.mark.parametrize("M,K,N", [(4100, 512, 10250), (4229, 640, 9480)])
+def test_seglinear_pair_many_tiles(M, K, N):
+    """Five to eleven tiles per workgroup of every width, so that both groups of waves come back to their K loop twice and more, with
+    their next tile's constants in place of the last one's; panels of six row tiles and of eight; ragged rows, whole and odd columns.
+    Against a device product in 64 bits, with the tolerances of the other tests."""
+    import torch
+
+    g = _gpu()
+    gen = torch.Generator(device=g.DEV)
+    gen.manual_seed(N)
+
+    def rand(*shape):
+        return torch.rand(shape, generator=gen, device=g.DEV)
+
+    xq, wq = (torch.randint(-127, 128, s, generator=gen, device=g.DEV, dtype=torch.int8) for s in ((M, K), (N, K)))
+    x8, w8 = ((torch.randn(s, generator=gen, device=g.DEV) * 60).clamp(-448, 448).to(torch.float8_e4m3fn) for s in ((M, K), (N, K)))
+    ws, bias, tok = rand(1, N) + 0.5, rand(N) * 100 - 50, rand(2, M, 1) + 0.5
+    s_pos = np.float32(0.0131)
+    layer = sq.Layer(M, K, N, [0, K], [0, N], [0], [s_pos], [s_pos])
+    acc, acc8 = (a.double() @ b.double().t().contiguous() for a, b in ((xq, wq), (x8.float(), w8.float())))
+    mag8 = x8.float().abs().double() @ w8.float().abs().double().t().contiguous()
+    scale = ws.double() * float(s_pos)
+    refs = {"static": acc * scale + bias.double(), "token": acc * ws.double() * tok[0].double() + bias.double(),
+            "fp8": acc8 * scale + bias.double()}
+    tol8 = (mag8 * scale + bias.double().abs()).cpu().numpy()
+    sq.sq_tuning_set("force_path", 5)
+    for tile in (0, 1, 2):
+        sq.sq_tuning_set("gemm_variant", tile)
+        for dt in (torch.float32, torch.bfloat16):
+            for what, call in (("static", lambda y: sq.sq_seglinear(layer, xq, wq, ws, bias, y)),
+                               ("token", lambda y: sq.sq_seglinear_dynamic(layer, xq, tok, wq, 8, ws, bias, y)),
+                               ("fp8", lambda y: sq.sq_seglinear_fp8(layer, x8.view(torch.uint8), w8.view(torch.uint8), ws, bias, y))):
+                if what == "fp8" and tile == 0:
+                    continue
+                y = torch.full((M, N), float("nan"), dtype=dt, device=g.DEV)
+                call(y)
+                ref = refs[what]
+                if what == "fp8":
+                    err = (y.double() - ref).abs().cpu().numpy()
+                    assert (err <= _fp8_tol(K, tol8, ref.cpu().numpy(), "bf16" if dt == torch.bfloat16 else "f32")).all(), (tile, dt)
+                else:
+                    bound = RTOL * ref.abs().max() + (y.double().abs() * 2.0 ** -8 if dt == torch.bfloat16 else 0.0)
+                    assert bool(((y.double() - ref).abs() <= bound).all()), (what, tile, dt)
 
 
 def test_seglinear_pair_forced_elsewhere_is_refused():
