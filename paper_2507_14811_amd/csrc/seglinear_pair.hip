@@ -401,15 +401,16 @@ bool pair_supported(const GemmArgs& a, const GemmTable& tb, OutMode mode, int ti
 // shortest time rounds * (stages + start of a tile), both in units of a 128 x 256 stage: fitted to 300 layers (256 - 9000 rows, K 512 -
 // 16384, 0.8 % off the best tile in the mean).  int8: from three quarters of the compute units' worth of 128 x 256 tiles; below
 // that a compute unit has no second tile to overlap with and the smaller tiles of the other kernels win or lose by up to 1.3.
-// 223 such layers (bf16 and fp32 output, static and per-token steps, N whole and odd): 1.18 times as fast as the tile kernel in
-// the mean, the slowest 0.98.  E4M3: the tile kernel has 256 x 256 tiles, with half the operand bytes per product; where they fill
-// the rounds and K is long they are as quick (2818 x 4096 x 16384 183 us there, 190 here; 4608 x 3072 x 12288 167 and 149), so
-// the fill of the rounds is compared with the tile kernel's score (mfma_fp8_pick_score, 1 = full rounds of 256 x 256): of 162
-// layers two became slower by more than 2 % (3074 x 1024 x 4096 0.92), the others taken are 1.12 times as fast.
+// 420 such layers (65 - 9000 rows, bf16 and fp32 output, static and per-token steps, N whole and odd): 1.21 times as fast as the tile
+// kernel in the mean, the slowest 0.997.  E4M3: the tile kernel has 256 x 256 tiles, with half the operand bytes per product; where
+// they fill the rounds and K is long they are as quick (2818 x 4096 x 16384 183 us there, 190 here; 4608 x 3072 x 12288 167 and 149),
+// so the fill of the rounds, weighted by the length of the K loop, is compared with the tile kernel's score (mfma_fp8_pick_score, 1 =
+// full rounds of 256 x 256).  1600 layers (65 - 9000 rows, K 512 - 16384, N 384 - 16384): the 1393 taken are 1.21 times as fast in the
+// mean, four of them slower by more than 2 % (6016 x 1408 x 15872 0.93, 8878 x 768 x 704 16.0 us there, 17.0 here).
 int pair_pick(const GemmArgs& a, const GemmTable& tb, OutMode mode, bool fp8) {
   if (a.M <= 64 || !pair_supported(a, tb, mode, 1, fp8)) return -1;
   static const float kStage[3] = {1.0f, 0.84f, 0.61f}, kStart[3] = {2.1f, 1.2f, 1.06f};
-  static const float kStageFp8[3] = {1.0f, 0.76f, 0.62f}, kStartFp8[3] = {0.0f, 1.2f, 1.0f};
+  static const float kStageFp8[3] = {1.0f, 0.76f, 0.62f}, kStartFp8[3] = {0.0f, 1.6f, 0.7f};
   const long cus = device_cus(), nk = a.K >> 7;
   auto tiles = [&](int bn) { return (long)((a.M + 127) / 128) * ((a.N + bn - 1) / bn); };
   if (4 * tiles(256) < 3 * cus) return -1;
