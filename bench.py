@@ -885,8 +885,9 @@ def main():
                           "unit": "GB/s", "frac": round(head["calib_gbs"] / HBM_PEAK_GBS, 4),
                           "note": "three launches (init, max-reduce, steps); cfg5's activations fit the Infinity Cache"},
         "calibrate_act_percentile": {"p": 0.9999, "ms_per_call": round(head["ms_calibrate_percentile"], 5),
-                                     "note": "exact radix select: one histogram pass over the activations per 8 bits "
-                                             "(two for bf16 input), each followed by a bin-select kernel"},
+                                     "note": "exact order statistic: a sample places a window of 254 bf16 patterns, one pass counts them "
+                                             "one by one, a kernel searches; two digit passes follow, which return at once unless the "
+                                             "rank lies outside the window (then a radix select by 8 bits each)"},
         "other_workloads": others,
         "grouped_skinny": grouped,
         "w4_skinny": w4,

@@ -113,10 +113,10 @@ sq_status run_gemm(const sq_layer* L, const int8_t* xq, const int8_t* wq,
   if (path == 5 && ptile < 0) return SQ_ERR_UNSUPPORTED;
   if (path == 6 && !sq::direct_supported(a, tb, mode)) return SQ_ERR_UNSUPPORTED;
   if (path < 0) {
-    // up to two 16-row tiles of tokens: the weight-stream kernel (measured 5.9 TB/s on wide layers); more rows: a wave per 32 x 32
-    // outputs where direct_pick() finds a layer small enough for it, the
-    // K-splitting tiles where ksplit_pick() finds them the faster ones, the tiles taken in turn where pair_pick() does, else the
-    // tile kernel; the skinny kernel serves the layers of up to 64 rows that none of them takes
+    // up to two 16-row tiles of tokens: the weight-stream kernel (measured 5.9 TB/s on wide layers); more rows, or more columns than
+    // its slab holds: a wave per 32 x 32 outputs where direct_pick() finds a layer small enough for it, the K-splitting tiles where
+    // ksplit_pick() finds them the faster ones, the tiles taken in turn where pair_pick() does, else the tile kernel; the skinny
+    // kernel serves the layers of up to 64 rows that none of them takes
     if (a.M > 32 && g_gemm_variant < 0) ktile = sq::ksplit_pick(a, tb);
     if (a.M <= 32 && sq::stream_supported(a, tb)) path = 3;
     else if (g_gemm_variant < 0 && sq::direct_pick(a, tb, mode)) path = 6;
@@ -158,9 +158,9 @@ bool w4_layout_ok(const sq_layer* L) {
   return true;
 }
 
-// Dynamic per-token steps: the weight-stream kernel (M <= 64, at most 8 K-segments: its step table is 4 KiB of LDS), the
-// K-splitting tiles or the MFMA tile kernel (8-bit weights, its alignment rules) or the one-thread-per-output kernel (any shape, 4-bit weights at
-// large M).
+// Dynamic per-token steps: the weight-stream kernel (M <= 64, at most 8 K-segments: its step table is 4 KiB of LDS); with 8-bit
+// weights a wave per 32 x 32 outputs, the K-splitting tiles, the tiles taken in turn or the MFMA tile kernel, by the rules of
+// run_gemm(); or the one-thread-per-output kernel (any shape, 4-bit weights at large M).
 sq_status run_gemm_dynamic(const sq_layer* L, const int8_t* xq, const float* tok_steps, const void* wq, int w_bits,
                            const float* wscale, const float* bias, void* y, sq::OutMode mode, void* stream) {
   if (w_bits == 4 && !w4_layout_ok(L)) return SQ_ERR_UNSUPPORTED;
@@ -544,8 +544,9 @@ sq_status sq_seglinear_fp8(const sq_layer* layer, const uint8_t* xq, const uint8
   if (!sq::fp8_gemm_supported(a, tb)) return SQ_ERR_UNSUPPORTED;
   const sq::OutMode mode = y_dt == SQ_BF16 ? sq::OUT_BF16 : sq::OUT_F32;
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
-  // up to two 16-row tiles of tokens: the weight-stream kernel; otherwise the pipelined tile kernel shared with the int8
-  // path.  force_path 0: the plain tile kernel of fp8.hip, 1: the pipelined tile kernel, 3: the weight-stream kernel
+  // up to two 16-row tiles of tokens: the weight-stream kernel; otherwise the tiles taken in turn where pair_pick() finds them the
+  // faster ones, else the pipelined tile kernel, both shared with the int8 path.  force_path 0: the plain tile kernel of fp8.hip,
+  // 1: the pipelined tile kernel, 3: the weight-stream kernel, 5: the tiles taken in turn
   const bool stream_ok = sq::stream_supported(a, tb);
   if (g_force_path == 3 && !stream_ok) return SQ_ERR_UNSUPPORTED;
   hipError_t e;

@@ -202,8 +202,15 @@ hipError_t launch_calibrate_act(const void* x, bool x_is_bf16, int M, int K, con
 // Aligned bf16 batches need one pass as a rule: a sample of the segment says about where the order statistic lies, and a
 // pass counts the 254 bit patterns around that place (a factor of two to either side) one by one, with everything above in one
 // more bin.  Where the rank falls outside, the two digit passes follow; else they return at once.  4608 x 15360 (142 MB),
-// p = 0.9999, kernels: 6.3 us sample, 27.1 window pass, 4.8 search, 2 x 4.8 passes with nothing to do, against 4.8 clearing,
+// p = 0.9999, kernels: 5.4 us sample, 26.6 window pass, 4.8 search, 2 x 4.8 passes with nothing to do, against 4.8 clearing,
 // 23 + 30 digit passes, 2 x 4.8 searches; with both weight formats and the min/max calibration 183.2 -> 163.2 us.
+// The call alone, digit passes only / window / window missed: 4608 x 15360 61 / 37 / 90 - 95 us, 1024 x 4608 20 - 24 / 19 / 35 - 43,
+// 256 x 1152 15.5 / 14.7 / 20 - 26.  Normal values, GELU outputs and a channel in a hundred ten times as strong are found for p from
+// 0.9 to 0.9999, the first two also beyond.  Missed are: NaN in a polarity-split segment; tails without a scale from p = 0.9999 on
+// (Cauchy, lognormal of sigma 2, a channel in a thousand a hundred times as strong), p = 1 of strong channels and of Student's t with
+// three degrees; in a polarity-split segment a p that is the share of the other sign's values, at which the quantile is next to the
+// zeros (p = 0.5 of symmetric values).  A test of the sample's spread that sends such segments on the digit passes at once took 76 -
+// 81 us and 31 - 36 there, as the searches behind passes with work cost more, and sent Cauchy at p = 0.999 there too (37 / 19 now).
 // ------------------------------------------------------------------------------------------------------------
 struct PctState {                                 // the caller's workspace
   unsigned int hist[SQ_MAX_SEGMENTS][2][256];     // [ks][polarity][digit], zero between passes; digit 0 is no count: [ks][0][0]

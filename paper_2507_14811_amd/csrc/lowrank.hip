@@ -4,10 +4,11 @@
 //   y[m][n] = y_q[m][n] + sum_j T[m][j] Lu[n][j],    T[m][j] = sum_k X[m][k] Ld[j][k]        (Ld [r][K], Lu [N][r]).
 // Three kernels:
 //   * down projection T = X Ld^T on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation): one pass over
-//     X, HBM-bound (2 bytes per activation).  The K range is cut into slices so that the launch fills the chip; every
-//     slice writes its own fp32 partial T (no atomics: the sum order is fixed).  bf16 activations with K % 64 == 0 are
-//     staged through LDS by direct loads of whole 128-byte row pieces; everything else is read straight into fragments.
-//   * the slices summed in ascending order (fp32).
+//     X, HBM-bound (2 bytes per activation).  bf16 activations with K % 64 == 0 are staged through LDS by direct loads of whole
+//     128-byte row pieces, few rows per workgroup, with all of K as a rule; everything else is read straight into fragments.
+//     Where there are too few rows to fill the chip K is cut into slices, each of which writes its own fp32 partial T (no
+//     atomics: the sum order is fixed).
+//   * the slices, if any, summed in ascending order (fp32).
 //   * up projection and add: T times Lu^T on the bf16 matrix cores with every fp32 T value split exactly into three bf16
 //     terms (T is not rounded to 16 bit), added to y_q before the single rounding to the output type: one read of y_q,
 //     one write of y, both in whole row pieces.
@@ -348,7 +349,11 @@ __device__ __forceinline__ void split_t(const float* src, v8bf (&thi)[KH / 8], v
 //   * Where y_q and y together fill half to all of the 256 MB Infinity Cache, y is stored past it as well: ordinary stores displace y_q
 //     that has not been read yet.  4-bit layer with the branch (quantizer to y), stores past the cache / ordinary / waves that fetch
 //     Lu themselves: 8500 x 1536 x 4608 (235 MB) 148.8 / 154.1 / 160.2 us, 2749 x 2816 x 8448 (139 MB) 126.6 / 127.1 / 133.0, but
-//     2236 x 1792 x 5376 (72 MB) 67.3 / 65.1 / 72.6 and 4298 x 4096 x 12288 (317 MB) 306.3 / 301.5 / 303.6.
+//     2236 x 1792 x 5376 (72 MB) 67.3 / 65.1 / 72.6 and 4298 x 4096 x 12288 (317 MB) 306.3 / 301.5 / 303.6.  The lines are in
+//     outputs because fp32 y gains in the same range, at a third more bytes: product and branch, y past the cache / only y_q / neither,
+//     bf16 27.6 M outputs 104.8 / 107.9 / 115.2 us, 39.2 M (rank 32) 139.5 / 151.2 / 167.0; fp32 27.6 M 112.7 / 115.9 / 120.1, 39.2 M
+//     145.9 / 170.0 / 177.6; at 13.2 M and 52.8 M all three within 2 % (fp32 58.1 / 57.7 / 57.8, 314 / 316 / 320).  Without y_q fp32 y
+//     gains from 15 M on (33.0 M 47.2 / 53.4), bf16 y 2 - 3 %.
 // Measured and not taken: 16-byte accesses (a load covers 64 bytes of 16 rows instead of 128 of two; 170 - 179 us), strips of 256
 // columns (152.3).
 constexpr int kLrStrip = 128;

@@ -5,9 +5,10 @@
 // split needs one accumulator set, half of the registers, so here two groups of four waves share a compute unit and take its tiles
 // in turn: one group runs the K loop of its tile while the other one stores its last tile, a 32 x 32 block or a few between two
 // barriers.  Both groups pass the same barriers, one per 128-byte stage.
-//   * The group in its K loop fetches (direct global->LDS loads, ring of three stages across all tiles): its waits never count
-//     the stores of a finished tile that are still on their way.  Shared between the groups instead, the loads waited behind
-//     stores (4608 x 3072 x 12288 with bf16 output 154 -> 147 us, 8500 x 1536 x 4608 59 -> 56, zero codes).
+//   * The group in its K loop fetches (direct global->LDS loads, ring of three stages across all tiles), so its loads do not wait
+//     behind the stores of the other group.  Its own stores have the rest of that group's K loop and two stages of its next one
+//     until a wait counts them: little with K = 512, where they take three of the four stages.  Shared between the groups instead,
+//     the loads waited behind stores (4608 x 3072 x 12288 with bf16 output 154 -> 147 us, 8500 x 1536 x 4608 59 -> 56, zero codes).
 //   * wscale, bias and token steps of a tile come by direct loads into LDS at the start of its K loop, so the store code has no
 //     memory latency of its own.
 //   * A store instruction covers 64 consecutive bytes of 16 rows (lane swaps), not 32 of 32.
