@@ -433,13 +433,14 @@ int pair_pick(const GemmArgs& a, const GemmTable& tb, OutMode mode, bool fp8) {
 
 // Row tiles of a panel.  Each XCD walks an eighth of the tile list; where the list has about two, four or eight panels, the XCDs begin
 // theirs at the same columns and fetch the same lines of W at the same time, with all or half of the others: 8518 x 1664 x 14912 in
-// E4M3 (67 row tiles) 275 us with panels of eight, 208 with six, 3751 x 1408 x 12864 (30) 113 and 88.  Of 220 layers 46 change: 16
-// become faster by more than 3 %, one slower by 2 %.  Where an XCD's L2 holds W panels of six gain nothing (11 layers, 0.97 - 1.06).
+// E4M3 (67 row tiles) 275 us with panels of eight, 208 with six, 3751 x 1408 x 12864 (30) 113 and 88.  Of 220 layers 38 change: 16
+// become faster by more than 3 %, one slower by 2 %.  Up to 8 MB of W, which the XCDs' L2s hold all of or half, panels of six gain
+// nothing (19 layers, 0.97 - 1.06 times the time; 8500 x 1536 x 4608 with its quantizer 76.9 / 77.5 us).
 static int panel_rows(const GemmArgs& a) {
   bool same_columns = false;
   for (int panels = 2; panels <= 8; panels *= 2)
     same_columns = same_columns || (10 * a.tiles_m >= 72 * panels && 9 * a.tiles_m <= 80 * panels);
-  const int rows = same_columns && (long long)a.N * a.K > (4 << 20) ? 6 : 8;
+  const int rows = same_columns && (long long)a.N * a.K > (8 << 20) ? 6 : 8;
   return a.tiles_m < rows ? a.tiles_m : rows;
 }
 
