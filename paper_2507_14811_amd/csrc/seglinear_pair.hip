@@ -431,11 +431,12 @@ int pair_pick(const GemmArgs& a, const GemmTable& tb, OutMode mode, bool fp8) {
   return best;
 }
 
-// Row tiles of a panel.  Each XCD walks an eighth of the tile list; where the list has about two, four or eight panels, the XCDs begin
-// theirs at the same columns and fetch the same lines of W at the same time, with all or half of the others: 8518 x 1664 x 14912 in
-// E4M3 (67 row tiles) 275 us with panels of eight, 208 with six, 3751 x 1408 x 12864 (30) 113 and 88.  Of 220 layers 38 change: 16
-// become faster by more than 3 %, one slower by 2 %.  Up to 8 MB of W, which the XCDs' L2s hold all of or half, panels of six gain
-// nothing (19 layers, 0.97 - 1.06 times the time; 8500 x 1536 x 4608 with its quantizer 76.9 / 77.5 us).
+// Row tiles of a panel.  Each XCD walks an eighth of the tile list; where the list has about two, four or eight panels, all XCDs or every
+// second one begin theirs at the same columns, and go on reading the same lines of W and writing the same columns of y at the same
+// time, which costs most where y is most of the traffic.  E4M3, panels of eight / six: 8518 x 1664 x 14912 (67 row tiles) 275 / 208 us;
+// fp32 output, K = 1408, N = 15936, 10 - 72 row tiles: eight 1.26 - 1.53 times the best width from 58 to 69 and 1.21 at 32, six 1.0 - 1.03
+// there; K = 2048 or 3072 with bf16 output: at most 1.04.  Of 220 layers 38 change: 16 become faster by more than 3 %, one slower by 2 %.
+// Up to 8 MB of W panels of six gain nothing (19 layers, 0.97 - 1.06 times the time; 8500 x 1536 x 4608 with its quantizer 76.9 / 77.5 us).
 static int panel_rows(const GemmArgs& a) {
   bool same_columns = false;
   for (int panels = 2; panels <= 8; panels *= 2)
