@@ -14,6 +14,8 @@
 //     one write of y, both in whole row pieces.
 #include "sq_kernels.hpp"
 
+#include <type_traits>
+
 namespace sq {
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -313,10 +315,10 @@ __global__ __launch_bounds__(256) void lowrank_sum_kernel(const float* __restric
 // KH consecutive features of T, split exactly into three bf16 terms (hi + mid + lo carries the 24-bit mantissa; the last term is
 // rounded at 2^-25 of the value), eight features per matrix instruction
 template <int KH>
-__device__ __forceinline__ void split_t(const float* src, v8bf (&thi)[KH / 8], v8bf (&tmid)[KH / 8], v8bf (&tlo)[KH / 8]) {
+__device__ __forceinline__ void split_t(const v4f (&src)[KH / 4], v8bf (&thi)[KH / 8], v8bf (&tmid)[KH / 8], v8bf (&tlo)[KH / 8]) {
 #pragma unroll
   for (int c = 0; c < KH / 8; ++c) {
-    const v4f a = *reinterpret_cast<const v4f*>(src + 8 * c), b = *reinterpret_cast<const v4f*>(src + 8 * c + 4);
+    const v4f a = src[2 * c], b = src[2 * c + 1];
     const float t[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
     v4i ph, pm, pl;
 #pragma unroll
@@ -339,126 +341,136 @@ __device__ __forceinline__ void split_t(const float* src, v8bf (&thi)[KH / 8], v
 // (bf16) are the other operand, one 32 x 32 block of outputs at a time, three v_mfma_f32_32x32x16_bf16 per 16 features (fp32
 // accumulation; 12 matrix instructions per block for rank 64 where the fp32 instruction v_mfma_f32_32x32x2_f32 needs 32 of twice
 // the length).  The matrix instruction pairs lane half h of both operands, so half h takes the features [h R/2, (h + 1) R/2) of T
-// and Lu.  T is the "A" operand: a half-wave then holds 32 consecutive columns of one row.
+// and Lu.  T is the "A" operand: a lane holds one column of 16 rows.
 // What bounds it is memory: y_q is read and y written once (235 MB at 8500 x 1536 x 4608, 46 us at the rate of a large copy).
-//   * A workgroup owns 128 token rows and kLrStrip columns, whose Lu rows it stages in LDS once by direct loads of whole lines; a
-//     wave that fetches them itself touches 32 lines per load instruction and fetches them four times as often.
-//   * y_q of the next block is requested ahead of the matrix instructions of the current one, except at rank 32 and less than 11 M
-//     outputs, where the registers cost a wave per SIMD (6266 x 512 x 1536 48.1 us, without 46.0), and past the caches from 13 M outputs on
-//     where rows are whole lines (8500 x 1536 x 4608 153.4 us; 6987 x 1920 x 5418 241 past them, 231 through them).
-//   * Where y_q and y together fill half to all of the 256 MB Infinity Cache, y is stored past it as well: ordinary stores displace y_q
-//     that has not been read yet.  4-bit layer with the branch (quantizer to y), stores past the cache / ordinary / waves that fetch
-//     Lu themselves: 8500 x 1536 x 4608 (235 MB) 148.8 / 154.1 / 160.2 us, 2749 x 2816 x 8448 (139 MB) 126.6 / 127.1 / 133.0, but
-//     2236 x 1792 x 5376 (72 MB) 67.3 / 65.1 / 72.6 and 4298 x 4096 x 12288 (317 MB) 306.3 / 301.5 / 303.6.  The lines are in
-//     outputs because fp32 y gains in the same range, at a third more bytes: product and branch, y past the cache / only y_q / neither,
-//     bf16 27.6 M outputs 104.8 / 107.9 / 115.2 us, 39.2 M (rank 32) 139.5 / 151.2 / 167.0; fp32 27.6 M 112.7 / 115.9 / 120.1, 39.2 M
-//     145.9 / 170.0 / 177.6; at 13.2 M and 52.8 M all three within 2 % (fp32 58.1 / 57.7 / 57.8, 314 / 316 / 320).  Without y_q fp32 y
-//     gains from 15 M on (33.0 M 47.2 / 53.4), bf16 y 2 - 3 %.
-// Measured and not taken: 16-byte accesses (a load covers 64 bytes of 16 rows instead of 128 of two; 170 - 179 us), strips of 256
-// columns (152.3).
-constexpr int kLrStrip = 128;
-constexpr long long kLrAhead = 11000000, kLrReadPast = 13000000, kLrPastFrom = 20000000, kLrPastTo = 44000000;   // outputs
-enum LrMode { LR_SHORT, LR_AHEAD, LR_READ_PAST, LR_PAST };           // each with what the ones before it have
-template <bool YBF16, int R, LrMode MODE>
-__global__ __launch_bounds__(256) void lowrank_up_kernel(const float* __restrict__ tsum, const uint16_t* __restrict__ lu,
-                                                         const float* y_in, void* y_out, int M, int N) {
+//   * A lane holds CPL = 4 (or 2) neighbouring columns, one in each of CPL blocks: place 32 j + f of the staged strip holds Lu row
+//     CPL f + j, so the order costs nothing.  A load of y_q then covers 512 (256) consecutive bytes of two rows, a store 256 (128)
+//     bytes of bf16 y; with a block of 32 neighbouring columns at a time they were 128 and 64, and twice to four times as many.
+//   * All loads of a wave (its share of Lu, T, y_q) go out before anything waits; the T values are split meanwhile.
+//   * Row blocks run from the last to the first: the product has written the last rows of y_q last, and they are still in the Infinity
+//     Cache, while the first ones of a large y_q would be displaced before they are read.
+//   * y_q is read, and y written from kLrPastFrom outputs on, past the caches where rows are whole lines.
+// 4-bit layer with the branch (quantizer to y), 32 columns at a time / here with rows upwards / as it is: 8500 x 1536 x 4608 145 / 140 /
+// 134.5 us, 2749 x 2816 x 8448 122 / 123 / 116.5, 8191 x 896 x 2688 81 / 81.5 / 77, 7000 x 3072 x 9216 313 / 290 / 290, 6987 x 1920 x
+// 5418 225 / 211 / 209 (rows of odd length, through the caches: past them 3 - 7 % slower).
+// Not taken: three waves per SIMD at CPL = 4 (the registers spill: 163 us), CPL = 2 throughout (290 -> 302 at 7000 x 3072 x 9216).
+constexpr long long kLrPastFrom = 10000000;                          // outputs
+enum LrMode { LR_PLAIN, LR_READ_PAST, LR_PAST };                     // each with what the ones before it have
+template <bool YBF16, int R, int CPL, LrMode MODE>
+__global__ __launch_bounds__(256, CPL == 4 ? 2 : 3) void lowrank_up_kernel(const float* __restrict__ tsum, const uint16_t* __restrict__ lu,
+                                                                           const float* y_in, void* y_out, int M, int N) {
+  constexpr int STRIP = 32 * CPL;                                  // columns of a workgroup, CPL per lane
   constexpr int KH = R / 2, RB = R * 2;                            // features of a lane half, bytes of a Lu row
   constexpr int SW = RB == 128 ? 7 : 3;
-  __shared__ __attribute__((aligned(1024))) char smem[kLrStrip * RB];
+  __shared__ __attribute__((aligned(1024))) char smem[STRIP * RB];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = lane >> 5, frow = lane & 31;
-  const int n0 = blockIdx.x * kLrStrip;
-  const int ncols = (N - n0) < kLrStrip ? (N - n0) : kLrStrip;
+  const int n0 = blockIdx.x * STRIP;
+  const int ncols = (N - n0) < STRIP ? (N - n0) : STRIP;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)smem);
   constexpr int RPI = 1024 / RB, CPR = RB / 16;
   const uint16_t* strip = lu + (size_t)n0 * R;                     // Lu may exceed 4 GiB: 32-bit offsets only inside the strip
 #pragma unroll
-  for (int g = 0; g < kLrStrip / RPI / 4; ++g) {
-    const int rt = (wave * (kLrStrip / RPI / 4) + g) * RPI + lane / CPR;
-    const int r = rt < ncols ? rt : ncols - 1;                     // beyond N: re-read the last row, masked at the store
+  for (int g = 0; g < STRIP / RPI / 4; ++g) {
+    const int rt = (wave * (STRIP / RPI / 4) + g) * RPI + lane / CPR;   // place 32 j + f holds Lu row CPL f + j
+    const int col = CPL * (rt & 31) + (rt >> 5);
+    const int r = col < ncols ? col : ncols - 1;                   // beyond N: re-read the last row, masked at the store
     const int slot = (lane % CPR) ^ ((RB == 128 ? rt >> 1 : rt >> 2) & SW);
-    lr_glds16(strip, (uint32_t)(r * RB + (slot << 4)), __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(wave * (kLrStrip / RPI / 4) + g) * 1024u));
+    lr_glds16(strip, (uint32_t)(r * RB + (slot << 4)), __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(wave * (STRIP / RPI / 4) + g) * 1024u));
   }
-  const int mb = blockIdx.y * 128 + wave * 32;
-  v8bf thi[KH / 8], tmid[KH / 8], tlo[KH / 8];
-  {
-    const int m = mb + frow;
-    split_t<KH>(tsum + (size_t)(m < M ? m : M - 1) * R + KH * h, thi, tmid, tlo);
-  }
-  const bool pair_ok = (N % 2 == 0) && (reinterpret_cast<uintptr_t>(y_out) % 4 == 0);     // two bf16 columns per store
-  auto store = [](auto* p, const auto v) __attribute__((always_inline)) {
-    if (MODE == LR_PAST) __builtin_nontemporal_store(v, p);
-    else *p = v;
-  };
-  // element v of a block in lane l: token row mb + 8 (v >> 2) + 4 (l >> 5) + (v & 3), output column nb + (l & 31): every access covers
-  // whole 128-byte (fp32) or 64-byte (bf16) row pieces.  Rows and columns beyond the matrix re-read the last ones.
-  struct Yq { float q[16]; };
-  auto load_yq = [&](const int nb) __attribute__((always_inline)) {
-    Yq t;
-    const int n = nb + frow, na = n < N ? n : N - 1;
+  const int mb = (int)(gridDim.y - 1 - blockIdx.y) * 128 + wave * 32;
+  // Element v of block j in lane l: token row mb + 8 (v >> 2) + 4 (l >> 5) + (v & 3), output column n0 + CPL (l & 31) + j.  FULL: the
+  // wave's rows and the strip lie inside the matrix (addresses are then a scalar per row and one offset per lane); else rows beyond
+  // it re-read the last one.
+  const int nl = n0 + CPL * frow;
+  auto strip_of = [&](auto full_tag, auto yq_tag) __attribute__((always_inline)) {
+    constexpr bool FULL = decltype(full_tag)::value, YQ = decltype(yq_tag)::value;
+    typedef float vf __attribute__((ext_vector_type(CPL)));
+    typedef float vfu __attribute__((ext_vector_type(CPL), aligned(4)));   // rows of any N: 4-byte (bf16: 2-byte) alignment
+    typedef int viu __attribute__((ext_vector_type(CPL / 2), aligned(2)));
+    const uint32_t here = (uint32_t)(4 * h) * (uint32_t)N + (uint32_t)(CPL * frow);   // FULL: 32 N < 2^31
+    auto first_of = [&](const int v) __attribute__((always_inline)) { return (size_t)(mb + 8 * (v >> 2) + (v & 3)) * N + n0; };
+    v4f t[KH / 4];
+    {
+      const int m = mb + frow;
+      const v4f* src = reinterpret_cast<const v4f*>(tsum + (size_t)(FULL || m < M ? m : M - 1) * R + KH * h);
+#pragma unroll
+      for (int c = 0; c < KH / 4; ++c) t[c] = src[c];
+    }
+    asm volatile("" ::: "memory");                                 // T is requested ahead of y_q
+    vf q[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      q[v] = (vf)(0.0f);
+      if (YQ && FULL) {
+        const vfu* s4 = reinterpret_cast<const vfu*>(reinterpret_cast<const char*>(y_in + first_of(v)) + here * 4u);
+        q[v] = MODE >= LR_READ_PAST ? __builtin_nontemporal_load(s4) : *s4;
+      } else if (YQ) {
+        const int mv = mb + 8 * (v >> 2) + 4 * h + (v & 3);
+        const float* src = y_in + (size_t)(mv < M ? mv : M - 1) * N;
+#pragma unroll
+        for (int j = 0; j < CPL; ++j) q[v][j] = src[nl + j < N ? nl + j : N - 1];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);                             // all loads are out
+    v8bf thi[KH / 8], tmid[KH / 8], tlo[KH / 8];
+    split_t<KH>(t, thi, tmid, tlo);
+    // Lu has landed: the sixteen loads of y_q are younger
+    if (FULL && YQ) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (!FULL && mb >= M) return;
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+      v16f acc = (v16f)(0.0f);
+      v8bf lf[KH / 8];
+#pragma unroll
+      for (int c = 0; c < KH / 8; ++c) {
+        const int chunk = (KH / 8) * h + c, r = 32 * j + frow;
+        lf[c] = *reinterpret_cast<const v8bf*>(smem + r * RB + ((chunk ^ ((RB == 128 ? r >> 1 : r >> 2) & SW)) << 4));
+      }
+#pragma unroll
+      for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tlo[c], lf[c], acc, 0, 0, 0);
+#pragma unroll
+      for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tmid[c], lf[c], acc, 0, 0, 0);
+#pragma unroll
+      for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(thi[c], lf[c], acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) q[v][j] += acc[v];
+      __builtin_amdgcn_sched_barrier(0);                           // one block's sums at a time
+    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int mv = mb + 8 * (v >> 2) + 4 * h + (v & 3);
-      const float* src = y_in + (size_t)(mv < M ? mv : M - 1) * N + na;
-      t.q[v] = y_in == nullptr ? 0.0f : MODE >= LR_READ_PAST ? __builtin_nontemporal_load(src) : *src;
+      viu p;
+#pragma unroll
+      for (int j = 0; j < CPL; j += 2) p[j / 2] = (int)f32x2_to_bf16x2(q[v][j], q[v][j + 1]);
+      if constexpr (FULL && YBF16) {
+        viu* y = reinterpret_cast<viu*>(reinterpret_cast<char*>(reinterpret_cast<uint16_t*>(y_out) + first_of(v)) + here * 2u);
+        if (MODE == LR_PAST) __builtin_nontemporal_store(p, y);
+        else *y = p;
+      } else if constexpr (FULL) {
+        vfu* y = reinterpret_cast<vfu*>(reinterpret_cast<char*>(reinterpret_cast<float*>(y_out) + first_of(v)) + here * 4u);
+        const vfu t = q[v];
+        if (MODE == LR_PAST) __builtin_nontemporal_store(t, y);
+        else *y = t;
+      } else if (mv < M) {
+#pragma unroll
+        for (int j = 0; j < CPL; ++j)
+          if (nl + j < N) {
+            if (YBF16) reinterpret_cast<uint16_t*>(y_out)[(size_t)mv * N + nl + j] = (uint16_t)((uint32_t)p[j >> 1] >> (16 * (j & 1)));
+            else reinterpret_cast<float*>(y_out)[(size_t)mv * N + nl + j] = q[v][j];
+          }
+      }
     }
-    return t;
   };
-  Yq next;
-  if (MODE >= LR_AHEAD) next = load_yq(n0);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // Lu has landed
-  __syncthreads();
-  if (mb >= M) return;
-#pragma unroll 1
-  for (int nb = 0; nb < ncols; nb += 32) {
-    Yq cur;
-    if (MODE >= LR_AHEAD) {
-      cur = next;
-      if (nb + 32 < ncols) next = load_yq(n0 + nb + 32);
-    } else {
-      cur = load_yq(n0 + nb);
-    }
-    v16f acc = (v16f)(0.0f);
-    v8bf lf[KH / 8];
-#pragma unroll
-    for (int c = 0; c < KH / 8; ++c) {
-      const int chunk = (KH / 8) * h + c, r = nb + frow;
-      lf[c] = *reinterpret_cast<const v8bf*>(smem + r * RB + ((chunk ^ ((RB == 128 ? r >> 1 : r >> 2) & SW)) << 4));
-    }
-#pragma unroll
-    for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tlo[c], lf[c], acc, 0, 0, 0);
-#pragma unroll
-    for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tmid[c], lf[c], acc, 0, 0, 0);
-#pragma unroll
-    for (int c = 0; c < KH / 8; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(thi[c], lf[c], acc, 0, 0, 0);
-    const int n = n0 + nb + frow;
-    const bool n_ok = n < N;
-    if (YBF16 && pair_ok) {
-      // bf16: neighbouring lanes exchange one value of every row pair, so that a lane stores two adjacent columns (4 bytes):
-      // even lanes the row of element 2 u, odd lanes the row of element 2 u + 1
-      const bool odd = (lane & 1) != 0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float o0 = cur.q[2 * u] + acc[2 * u], o1 = cur.q[2 * u + 1] + acc[2 * u + 1];
-        const float send = odd ? o0 : o1;
-        const float recv = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0xB1, 0xF, 0xF, false));   // lane ^ 1
-        const int v = 2 * u + (odd ? 1 : 0);
-        const int mv = mb + 8 * (v >> 2) + 4 * h + (v & 3);
-        const uint32_t pk = odd ? f32x2_to_bf16x2(recv, o1) : f32x2_to_bf16x2(o0, recv);
-        if (n_ok && mv < M) store(reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(y_out) + (size_t)mv * N + (n & ~1)), pk);
-      }
-    } else {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int mv = mb + 8 * (v >> 2) + 4 * h + (v & 3);
-        const float o = cur.q[v] + acc[v];
-        if (n_ok && mv < M) {
-          if (YBF16) reinterpret_cast<uint16_t*>(y_out)[(size_t)mv * N + n] = f32_to_bf16(o);
-          else store(reinterpret_cast<float*>(y_out) + (size_t)mv * N + n, o);
-        }
-      }
-    }
+  if (ncols == STRIP && mb + 32 <= M) {
+    if (y_in != nullptr) strip_of(std::true_type{}, std::true_type{});
+    else strip_of(std::true_type{}, std::false_type{});
+  } else {
+    if (y_in != nullptr) strip_of(std::false_type{}, std::true_type{});
+    else strip_of(std::false_type{}, std::false_type{});
   }
 }
 
@@ -492,18 +504,21 @@ hipError_t launch_lowrank_add(const void* x, bool x_is_bf16, const uint16_t* ld,
     hipLaunchKernelGGL(lowrank_sum_kernel, dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st, workspace, nsplit, nvec, dst);
     tsum = dst;
   }
-  const dim3 gu((N + kLrStrip - 1) / kLrStrip, (M + 127) / 128);
-  const long long outputs = (long long)M * N;
   const bool lines = N % 32 == 0;                                    // rows begin on whole lines of y_q and 64-byte pieces of bf16 y
-#define SQ_UPM(B, R, MODE) hipLaunchKernelGGL((lowrank_up_kernel<B, R, MODE>), gu, dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
-#define SQ_UP(B, R) \
-  if (lines && outputs >= kLrPastFrom && outputs < kLrPastTo) SQ_UPM(B, R, LR_PAST); \
-  else if (lines && outputs >= kLrReadPast) SQ_UPM(B, R, LR_READ_PAST); \
-  else if (R == 64 || outputs >= kLrAhead) SQ_UPM(B, R, LR_AHEAD); \
-  else SQ_UPM(B, R, LR_SHORT)
-  if (rank == 64) { if (y_is_bf16) { SQ_UP(true, 64); } else { SQ_UP(false, 64); } }
-  else            { if (y_is_bf16) { SQ_UP(true, 32); } else { SQ_UP(false, 32); } }
+  // Four columns per lane where their 128 x 128 blocks fill the compute units (two workgroups each); below, half as wide strips spread
+  // over more of them: 1500 x 1024 x 3072 39.2 -> 37.5 us, 700 x 1024 x 3072 33.0 -> 31.3, 400 x 3072 x 9216 53.5 -> 51.9.
+  const int rows = (M + 127) / 128;
+  const bool wide = (long long)rows * ((N + 127) / 128) >= 2ll * cus;
+#define SQ_UPM(B, R, C, MODE) hipLaunchKernelGGL((lowrank_up_kernel<B, R, C, MODE>), dim3((N + 32 * C - 1) / (32 * C), rows), dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
+#define SQ_UPC(B, R, C) \
+  if (lines && (long long)M * N >= kLrPastFrom) SQ_UPM(B, R, C, LR_PAST); \
+  else if (lines) SQ_UPM(B, R, C, LR_READ_PAST); \
+  else SQ_UPM(B, R, C, LR_PLAIN)
+#define SQ_UP(B, R) if (wide) { SQ_UPC(B, R, 4); } else { SQ_UPC(B, R, 2); }
+  if (rank == 64) { if (y_is_bf16) { SQ_UP(true, 64) } else { SQ_UP(false, 64) } }
+  else            { if (y_is_bf16) { SQ_UP(true, 32) } else { SQ_UP(false, 32) } }
 #undef SQ_UP
+#undef SQ_UPC
 #undef SQ_UPM
   return hipGetLastError();
 }

@@ -990,6 +990,15 @@ def test_lowrank_add_large(M, N, rank, yq):
         assert torch.equal(y1, want)
 
 
+@pytest.mark.parametrize("yq", [True, False])
+@pytest.mark.parametrize("M,N,rank", [(1, 1, 64), (31, 2, 32), (33, 63, 64), (127, 65, 32), (129, 127, 64), (160, 129, 32), (130, 191, 64),
+                                      (257, 32801, 32), (8323, 1021, 64), (16290, 514, 32)])
+def test_lowrank_up_edges(oracle, M, N, rank, yq):
+    """Ends of a wave's rows and of a strip, two (fewest rows) and four columns per lane (the last three sizes), the last lane's columns in
+    part beyond the matrix, rows of y at odd addresses."""
+    test_lowrank_add(oracle, dict(M=M, K=64, N=N, rank=rank, x_dtype="bf16", yq=yq))
+
+
 @pytest.mark.parametrize("rank", [64, 32])
 @pytest.mark.parametrize("M,N", [(6300, 3200), (3300, 3400), (6301, 7008)])
 def test_lowrank_up_sizes(M, N, rank):
