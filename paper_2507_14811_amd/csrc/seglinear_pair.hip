@@ -3,7 +3,7 @@
 // The kernel of seglinear_mfma_kernel.hpp has one wave per SIMD: while it scales, converts and stores a tile the matrix cores
 // idle (a fifth of the time at K = 1536), and the loads of its next K loop complete behind the stores.  A layer without a polarity
 // split needs one accumulator set, half of the registers, so here two groups of four waves share a compute unit and take its tiles
-// in turn: one group runs the K loop of its tile while the other one stores its last tile, a 32 x 32 block or a few between two
+// in turn: one group runs the K loop of its tile while the other one stores its last tile, a few rows of each 32 x 32 block between two
 // barriers.  Both groups pass the same barriers, one per 128-byte stage.
 //   * The group in its K loop fetches (direct global->LDS loads, ring of three stages across all tiles), so its loads do not wait
 //     behind the stores of the other group.  Its own stores have the rest of that group's K loop and two stages of its next one
@@ -11,7 +11,13 @@
 //     the loads waited behind stores (4608 x 3072 x 12288 with bf16 output 154 -> 147 us, 8500 x 1536 x 4608 59 -> 56, zero codes).
 //   * wscale, bias and token steps of a tile come by direct loads into LDS at the start of its K loop, so the store code has no
 //     memory latency of its own.
-//   * A store instruction covers 64 consecutive bytes of 16 rows (lane swaps), not 32 of 32.
+//   * X^ rows are the MFMA "A" operand (the other way round than in the tile kernel), and W^ rows lie in a stage in the order that gives a
+//     lane BN / 64 neighbouring columns of a row: it stores what it holds, one row piece of 32 lanes x BN / 64 columns beside the next,
+//     at any alignment, and has one scale and bias per column instead of sixteen per block.  A 32 x 32
+//     block at a time (64 bytes of 16 rows an instruction, behind lane swaps; odd N value by value) / this way, with the quantizer: 8500 x
+//     1536 x 4608 bf16 67.6 / 65.8 us, fp32 output 103.5 / 97.5, N = 4607 121.6 / 75.0; 5500 x 896 x 2688 29.6 / 24.3; E4M3 4608 x 3072 x
+//     12288 168.8 / 162.0, 4608 x 4096 x 16384 288.8 / 276.8.  Measured and not taken: of three columns two beside each other and one
+//     32 further on (stores of 4 bytes a lane, lines shared between waves: 43 -> 58 us for 3000 x 2048 x 6144).
 // Measured, tile kernel / here: 8500 x 1536 x 4608 bf16 74 / 64.6 us, fp32 output with token steps 93 / 74.7, E4M3 72 / 64.4;
 // 4608 x 3072 x 12288 bf16 172 / 152, E4M3 167 / 149; 4733 x 896 x 3018 60 / 42.  What bounds it is the power of real codes (zero
 // codes: 50 us for 8500 x 1536 x 4608), then 0.62 us per stage of a 128 x 256 tile (MFMAs 0.43, LDS reads and direct loads 0.48).
@@ -34,6 +40,10 @@ struct PairCfg {
   static constexpr int CONST = (BN + BN + BM) * 4;                 // wscale, bias, token steps of a group's tile
   static constexpr int LDS = NS * STAGE + 2 * CONST;
   static_assert(BM % 32 == 0 && BN % 64 == 0 && LDS <= 160 * 1024, "tile");
+  // The tile's column in place 32 (JN wn + j) + f of a stage's W^ rows: lane f of a wave holds JN neighbouring ones, one per block
+  static __device__ __forceinline__ int column(int place) {
+    return place / (32 * JN) * (32 * JN) + JN * (place & 31) + (place >> 5) % JN;
+  }
 };
 
 template <int BN, bool TOK, bool FP8, bool BF>
@@ -89,8 +99,8 @@ __global__ __launch_bounds__(512, 2) void seglinear_pair_kernel(const GemmArgs a
     }
 #pragma unroll
     for (int g = 0; g < GB; ++g) {
-      const int rt = (w4 * GB + g) * 8 + lrow;
-      voffB[g] = (uint32_t)(rt < nlast ? rt : nlast) * (uint32_t)a.K + (uint32_t)((lslot ^ row_swizzle<128>(rt)) << 4);
+      const int rt = (w4 * GB + g) * 8 + lrow, col = C::column(rt);
+      voffB[g] = (uint32_t)(col < nlast ? col : nlast) * (uint32_t)a.K + (uint32_t)((lslot ^ row_swizzle<128>(rt)) << 4);
     }
   };
   auto issue_load = [&](const int e) __attribute__((always_inline)) {       // e is a compile-time constant after unrolling
@@ -146,9 +156,9 @@ __global__ __launch_bounds__(512, 2) void seglinear_pair_kernel(const GemmArgs a
       const int i = q / JN, j = q % JN;
       if constexpr (FP8) {
         acc[i][j] = __builtin_bit_cast(v16i, __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-            bfr[cur][j], afr[cur][i], __builtin_bit_cast(v16f, acc[i][j]), 0, 0, 0, 0, 0, 0));
+            afr[cur][i], bfr[cur][j], __builtin_bit_cast(v16f, acc[i][j]), 0, 0, 0, 0, 0, 0));
       } else {
-        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bfr[cur][j], afr[cur][i], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(afr[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
       if (PF) {
@@ -205,90 +215,80 @@ __global__ __launch_bounds__(512, 2) void seglinear_pair_kernel(const GemmArgs a
     }
   };
 
-  // ---- one 32x32 block: scale, add the bias, store -------------------------------------------------------------------------------
-  // Element v of block (i, j) in lane l: row l % 32, column 8 (v >> 2) + 4 (l >> 5) + (v & 3).  v_permlane32_swap (bf16) and
-  // v_permlane16_swap exchange runs between the lanes of a row and of the row 16 below, so that a store instruction covers 64
-  // consecutive bytes of 16 rows instead of 32 bytes of 32 rows.
-  float cw[16], bs[16];
-  auto block_constants = [&](const int j) __attribute__((always_inline)) {
-    const float* p = cst + (wn * JN + j) * 32 + 4 * fhi;
+  // ---- a run of four rows: scale, add the bias, store ---------------------------------------------------------------------------
+  // Element v of block (i, j) in lane l: row 8 (v >> 2) + 4 (l >> 5) + (v & 3), and column f = l % 32 of the block's places.  Stored as
+  // it lies: JN neighbouring columns of a row per lane, so that a store instruction covers JN x 32 consecutive columns of two rows.
+  // bf16: neighbouring lanes exchange a row of every two, for twice as many columns of a row per lane.
+  float cw[JN], bs[JN];
+  auto tile_constants = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const v4f w = *reinterpret_cast<const v4f*>(p + 8 * g);
-      const v4f b = *reinterpret_cast<const v4f*>(p + BN + 8 * g);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        cw[4 * g + r] = TOK ? w[r] : w[r] * s_pos;
-        bs[4 * g + r] = has_bias ? b[r] : 0.0f;
-      }
+    for (int j = 0; j < JN; ++j) {
+      const int col = C::column((wn * JN + j) * 32 + frow);
+      cw[j] = TOK ? cst[col] : cst[col] * s_pos;
+      bs[j] = has_bias ? cst[BN + col] : 0.0f;
     }
   };
-  const bool rows16 = (a.N % (BF ? 8 : 4)) == 0 && reinterpret_cast<uintptr_t>(a.y) % 16 == 0;   // 16-byte row pieces
-  const bool rows8 = a.N % 4 == 0 && reinterpret_cast<uintptr_t>(a.y) % 8 == 0;
-  auto store_block = [&](auto full_tag, const int i, const int j) __attribute__((always_inline)) {
+  auto store_run = [&](auto full_tag, const int i, const int g) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full_tag)::value;
-    const float sp = TOK ? cst[2 * BN + (wm * IM + i) * 32 + frow] : 1.0f;
-    uint32_t d[16];
+    const int row = (wm * IM + i) * 32 + 8 * g + 4 * fhi;
+    const int m = m0 + row, n = n0 + 32 * JN * wn + JN * frow;
+    v4f sp = (v4f)(1.0f);
+    if (TOK) sp = *reinterpret_cast<const v4f*>(cst + 2 * BN + row);
+    float d[4][JN];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) d[v] = __float_as_uint((TOK ? cw[v] * sp : cw[v]) * acc_value<FP8>(acc[i][j][v]) + bs[v]);
-    const int mb = m0 + (wm * IM + i) * 32 + (lane & 15);          // rows mb and mb + 16
-    const int nb = n0 + (wn * JN + j) * 32;
-    if (BF) {
-      v4i o[2];
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const uint32_t a0 = f32x2_to_bf16x2(__uint_as_float(d[8 * p + 0]), __uint_as_float(d[8 * p + 1]));
-        const uint32_t a1 = f32x2_to_bf16x2(__uint_as_float(d[8 * p + 2]), __uint_as_float(d[8 * p + 3]));
-        const uint32_t b0 = f32x2_to_bf16x2(__uint_as_float(d[8 * p + 4]), __uint_as_float(d[8 * p + 5]));
-        const uint32_t b1 = f32x2_to_bf16x2(__uint_as_float(d[8 * p + 6]), __uint_as_float(d[8 * p + 7]));
-        const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
-        const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-        o[p] = (v4i){(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]};
-      }
+      for (int j = 0; j < JN; ++j) d[r][j] = (TOK ? cw[j] * sp[r] : cw[j]) * acc_value<FP8>(acc[i][j][4 * g + r]) + bs[j];
+    if constexpr (BF) {
+      typedef int vst __attribute__((ext_vector_type(JN), aligned(2)));   // rows of any N
+      const bool odd = (lane & 1) != 0;
+      auto swap = [](const int v) __attribute__((always_inline)) { return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false); };   // lane ^ 1
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const auto s = __builtin_amdgcn_permlane16_swap((uint32_t)o[0][k], (uint32_t)o[1][k], false, false);
-        o[0][k] = (int)s[0];
-        o[1][k] = (int)s[1];
-      }
-      const int n = nb + 16 * ((lane >> 4) & 1) + 8 * fhi;
-      uint16_t* y = reinterpret_cast<uint16_t*>(a.y);
+      for (int r = 0; r < 4; r += 2) {
+        const int mm = m + r + (odd ? 1 : 0), nn = n - (odd ? JN : 0);    // this lane's row, and 2 JN columns of it
+        vst o;
+        if constexpr (JN == 3) {
+          float t[6];
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const int m = mb + 16 * p;
-        if (FULL || (rows16 && m < a.M && n + 7 < a.N)) {
-          *reinterpret_cast<v4i*>(y + (size_t)m * a.N + n) = o[p];
-        } else if (rows8 && m < a.M && n + 7 < a.N) {
-          *reinterpret_cast<v2i*>(y + (size_t)m * a.N + n) = (v2i){o[p][0], o[p][1]};
-          *reinterpret_cast<v2i*>(y + (size_t)m * a.N + n + 4) = (v2i){o[p][2], o[p][3]};
-        } else if (m < a.M) {
+          for (int j = 0; j < 3; ++j) {
+            const float got = __int_as_float(swap(__float_as_int(odd ? d[r][j] : d[r + 1][j])));
+            t[j] = odd ? got : d[r][j];
+            t[3 + j] = odd ? d[r + 1][j] : got;
+          }
 #pragma unroll
-          for (int k = 0; k < 8; ++k)
-            if (n + k < a.N) y[(size_t)m * a.N + n + k] = (uint16_t)((uint32_t)o[p][k >> 1] >> (16 * (k & 1)));
+          for (int k = 0; k < 3; ++k) o[k] = (int)f32x2_to_bf16x2(t[2 * k], t[2 * k + 1]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < JN / 2; ++k) {
+            const int p0 = (int)f32x2_to_bf16x2(d[r][2 * k], d[r][2 * k + 1]), p1 = (int)f32x2_to_bf16x2(d[r + 1][2 * k], d[r + 1][2 * k + 1]);
+            const int got = swap(odd ? p0 : p1);
+            o[k] = odd ? got : p0;
+            o[JN / 2 + k] = odd ? p1 : got;
+          }
+        }
+        uint16_t* to = reinterpret_cast<uint16_t*>(a.y) + (size_t)mm * a.N + nn;
+        if (FULL || (mm < a.M && nn + 2 * JN <= a.N)) {
+          *reinterpret_cast<vst*>(to) = o;
+        } else if (mm < a.M) {
+#pragma unroll
+          for (int k = 0; k < 2 * JN; ++k)
+            if (nn + k < a.N) to[k] = (uint16_t)((uint32_t)o[k >> 1] >> (16 * (k & 1)));
         }
       }
     } else {
-      float* y = reinterpret_cast<float*>(a.y);
+      typedef float vst __attribute__((ext_vector_type(JN), aligned(4)));
 #pragma unroll
-      for (int g = 0; g < 2; ++g) {                                // column runs 16 g ..
-        v4f o[2];
+      for (int r = 0; r < 4; ++r) {
+        float* to = reinterpret_cast<float*>(a.y) + (size_t)(m + r) * a.N + n;
+        if (FULL || (m + r < a.M && n + JN <= a.N)) {
+          vst t;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const auto s = __builtin_amdgcn_permlane16_swap(d[8 * g + k], d[8 * g + 4 + k], false, false);
-          o[0][k] = __uint_as_float(s[0]);
-          o[1][k] = __uint_as_float(s[1]);
-        }
-        const int n = nb + 16 * g + 8 * ((lane >> 4) & 1) + 4 * fhi;
+          for (int j = 0; j < JN; ++j) t[j] = d[r][j];
+          *reinterpret_cast<vst*>(to) = t;
+        } else if (m + r < a.M) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          const int m = mb + 16 * p;
-          if (FULL || (rows16 && m < a.M && n + 3 < a.N)) {
-            *reinterpret_cast<v4f*>(y + (size_t)m * a.N + n) = o[p];
-          } else if (m < a.M) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-              if (n + k < a.N) y[(size_t)m * a.N + n + k] = o[p][k];
-          }
+          for (int j = 0; j < JN; ++j)
+            if (n + j < a.N) to[j] = d[r][j];
         }
       }
     }
@@ -311,7 +311,8 @@ __global__ __launch_bounds__(512, 2) void seglinear_pair_kernel(const GemmArgs a
 #pragma unroll 1
     for (int i = 0; i < nk; ++i) barrier();
   }
-  const int per_slot = (NB + nk - 2) / (nk - 1);                   // blocks to store between two barriers
+  constexpr int NRUN = 4 * IM;                                     // runs of a tile to store
+  const int per_slot = (NRUN + nk - 2) / (nk - 1);                 // of them between two barriers
 #pragma unroll 1
   for (int t = group; t < ntile; t += 2) {
     m0 = om0;
@@ -367,11 +368,11 @@ __global__ __launch_bounds__(512, 2) void seglinear_pair_kernel(const GemmArgs a
       tile_origin(t + 3, nm0, nn0);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    block_constants(0);
-    const bool full = rows16 && m0 + BM <= a.M && n0 + BN <= a.N;
+    tile_constants();
+    const bool full = m0 + BM <= a.M && n0 + BN <= a.N;
     int slots = 1, left = 0;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
+    for (int b = 0; b < NRUN; ++b) {
       if (left == 0) {
         left = per_slot;
         if (beside) {
@@ -380,9 +381,8 @@ __global__ __launch_bounds__(512, 2) void seglinear_pair_kernel(const GemmArgs a
         }
       }
       --left;
-      if (full) store_block(std::true_type{}, b % IM, b / IM);
-      else store_block(std::false_type{}, b % IM, b / IM);
-      if (b % IM == IM - 1 && b + 1 < NB) block_constants((b + 1) / IM);
+      if (full) store_run(std::true_type{}, b >> 2, b & 3);
+      else store_run(std::false_type{}, b >> 2, b & 3);
     }
     if (beside) {
       set_fetch(om0, on0, 2);

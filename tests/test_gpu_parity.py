@@ -1969,6 +1969,33 @@ def test_seglinear_pair_many_tiles(M, K, N):
                     assert bool(((y.double() - ref).abs() <= bound).all()), (what, tile, dt)
 
 
+@pytest.mark.parametrize("N", [1021, 1022, 1023, 1154])
+def test_seglinear_pair_rows_at_any_address(N):
+    """Row pieces of four, three and two columns per lane that begin at odd addresses (odd N, y itself at an odd element) and that the
+    last column cuts: every element against a device product in 64 bits, nothing written in front of y or behind it."""
+    import torch
+
+    g = _gpu()
+    M, K = 260, 640
+    gen = torch.Generator(device=g.DEV)
+    gen.manual_seed(N)
+    xq, wq = (torch.randint(-127, 128, s, generator=gen, device=g.DEV, dtype=torch.int8) for s in ((M, K), (N, K)))
+    ws, bias = torch.rand((1, N), generator=gen, device=g.DEV) + 0.5, torch.rand(N, generator=gen, device=g.DEV) * 100 - 50
+    s_pos = np.float32(0.0131)
+    layer = sq.Layer(M, K, N, [0, K], [0, N], [0], [s_pos], [s_pos])
+    ref = (xq.double() @ wq.double().t().contiguous()) * (ws.double() * float(s_pos)) + bias.double()
+    sq.sq_tuning_set("force_path", 5)
+    for tile in (0, 1, 2):
+        sq.sq_tuning_set("gemm_variant", tile)
+        for dt in (torch.float32, torch.bfloat16):
+            buf = torch.full((M * N + 3,), float("nan"), dtype=dt, device=g.DEV)
+            y = buf[1:1 + M * N].view(M, N)
+            sq.sq_seglinear(layer, xq, wq, ws, bias, y)
+            assert bool(torch.isnan(buf[[0, -2, -1]]).all())
+            bound = RTOL * ref.abs().max() + (y.double().abs() * 2.0 ** -8 if dt == torch.bfloat16 else 0.0)
+            assert bool(((y.double() - ref).abs() <= bound).all()), (tile, dt)
+
+
 def test_seglinear_pair_forced_elsewhere_is_refused():
     """A polarity-split layer, two K-segments, K below four stages, seg_scale, raw sums, fp8 on the widest tile: no fallback."""
     import torch
