@@ -117,6 +117,15 @@ template <int SK> __device__ __forceinline__ int row_swizzle(int row) {
   return SK == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3);
 }
 
+// Column of a place in a tile: columns are stored in pieces of eight, and a piece that would pass the last column is shifted back
+// to the last eight.  Lanes then compute columns that others have as well, and store the same bits; so do the rows beyond M, which
+// repeat the last one: no store of a ragged tile needs a mask.  N < 8: the last column is repeated.
+__device__ __forceinline__ int piece_of(const int n, const int N) { return N < 8 || n < N - 8 ? n : N - 8; }   // n: a piece's first column
+__device__ __forceinline__ int column_of(const int first, const int place, const int N) {
+  const int in = place & 7, n = piece_of(first + place - in, N) + in;
+  return n < N ? n : N - 1;
+}
+
 // TOK: dynamic per-token activation steps (App. B, 4-bit settings): the flushes take s_+ / s_- of every lane's own token
 // rows from a.tok_steps [2][M][S] instead of the layer's static steps.
 // FP8: the codes are OCP E4M3 bytes and the products run on v_mfma_f32_32x32x64_f8f6f4 (no block scales)
@@ -182,14 +191,13 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
     for (int g = 0; g < GA; ++g) {
       const int rt = (wave * GA + g) * RPL + lrow;            // row inside the tile
       int r = im0 + rt;
-      r = r < a.M ? r : a.M - 1;                              // ragged tail: re-read the last row, masked at the store
+      r = r < a.M ? r : a.M - 1;                              // ragged tail: the last row again
       voffA[g] = (uint32_t)r * (uint32_t)a.K + (uint32_t)((lslot ^ row_swizzle<SK>(rt)) << 4);
     }
 #pragma unroll
     for (int g = 0; g < GB; ++g) {
       const int rt = (wave * GB + g) * RPL + lrow;
-      int r = in0 + rt;
-      r = r < a.N ? r : a.N - 1;
+      const int r = column_of(in0, rt, a.N);
       voffB[g] = (uint32_t)r * (uint32_t)a.K + (uint32_t)((lslot ^ row_swizzle<SK>(rt)) << 4);
     }
   };
@@ -540,43 +548,57 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   //   row    m = m0 + wm*TM + i*32 + (l & 31)
   //   column n = n0 + wn*TN + j*32 + 8*(v >> 2) + 4*(l >> 5) + (v & 3):
   // a lane owns four runs of four consecutive output columns of one row, which it scales with per-column
-  // constants fetched 16 bytes at a time and stores directly as 16-byte (fp32, int32) or 8-byte (bf16)
-  // pieces; the pieces of the two lane halves and the four runs fill a row's cache lines back to back.
+  // constants fetched 16 bytes at a time and stores directly as 16-byte pieces; the pieces of the two lane halves and the four runs
+  // fill a row's cache lines back to back.
   int mrow = 0, ncol = 0;                                  // of the tile being computed (set_compute_tile)
+  int wcol = 0;                                            // the wave's first column
   bool full_tile = false;
   const bool vec4 = (a.N % 4) == 0;                        // rows of Y / wscale / bias keep 16-byte alignment
   const bool ptr16 = ((reinterpret_cast<uintptr_t>(a.y) | reinterpret_cast<uintptr_t>(a.wscale) |
                        reinterpret_cast<uintptr_t>(a.bias) | reinterpret_cast<uintptr_t>(a.acc_pos) |
                        reinterpret_cast<uintptr_t>(a.acc_neg)) % 16 == 0);
-  // FULL: the tile lies inside the matrix and every row piece is 16-byte aligned, so the flush code runs
-  // without bounds checks or scalar fallbacks (one uniform branch picks the instantiation).
+  // FULL: the tile lies inside the matrix and every row piece is 16-byte aligned.  Else the pieces of column_of() are fetched and stored
+  // at whatever address they have (one uniform branch picks the instantiation).  Either way the flush code runs without masks:
+  // masked, and value by value where N is no multiple of four, ragged tiles took 2500 x 8192 x 2011 99 us instead of 87, 3000 x
+  // (1024 + 4096) x 1093 57 instead of 47.5, 4096 x 5120 x 1280 (with its quantizer) 71 instead of 68.
   auto set_compute_tile = [&](const int it) __attribute__((always_inline)) {
     int m0, n0;
     tile_origin(it, m0, n0);
     mrow = m0 + wm * C::TM + (lane & 31);
-    ncol = n0 + wn * C::TN + 4 * (lane >> 5);
+    wcol = n0 + wn * C::TN;
+    ncol = wcol + 4 * (lane >> 5);
     full_tile = vec4 && ptr16 && m0 + BM <= a.M && n0 + BN <= a.N;
   };
 
-  // per-column constants of block column j in K-segment ks: cw[v] = seg_scale * wscale (0 outside N).  fetch_cw only
+  typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+  // A value that the compiler cannot trace: addresses of ragged tiles are then worked out where they are used.  Shared between the
+  // blocks of a tile they stay in registers across its flush, which spills.
+  auto untraced = [](int v) __attribute__((always_inline)) {
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  // a per-column array's values at the sixteen columns of this lane in block column j
+  auto fetch_columns = [&](auto full_tag, auto narrow_tag, const float* p, const int j, float (&c)[16]) __attribute__((always_inline)) {
+    constexpr bool FULL = decltype(full_tag)::value, NARROW = decltype(narrow_tag)::value;
+    if (FULL || !NARROW) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        v4f w4;
+        if (FULL) w4 = *reinterpret_cast<const v4f*>(p + (ncol + j * 32 + 8 * g));
+        else w4 = *reinterpret_cast<const v4fu*>(p + (piece_of(wcol + j * 32 + 8 * g, a.N) + untraced(4 * fhi)));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c[4 * g + r] = w4[r];
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) c[v] = p[column_of(wcol, j * 32 + 8 * (v >> 2) + untraced(4 * fhi) + (v & 3), a.N)];
+    }
+  };
+  // per-column constants of block column j in K-segment ks: cw[v] = seg_scale * wscale.  fetch_cw only
   // issues the loads of wscale, scale_cw applies the multiplier: the flush code fetches block column j + 1 before it
   // works on block column j, so a tile pays one memory latency for its constants, not one per block column.
-  auto fetch_cw = [&](auto full_tag, const int ks, const int j, float (&cw)[16]) __attribute__((always_inline)) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    const float* ws = a.wscale + (size_t)ks * a.N;
-    const bool wvec = FULL || (vec4 && (reinterpret_cast<uintptr_t>(ws) % 16 == 0));
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int n = ncol + j * 32 + 8 * g;
-      if (FULL || (wvec && n + 3 < a.N)) {
-        const v4f w4 = *reinterpret_cast<const v4f*>(ws + n);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) cw[4 * g + r] = w4[r];
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) cw[4 * g + r] = (n + r < a.N) ? ws[n + r] : 0.0f;
-      }
-    }
+  auto fetch_cw = [&](auto full_tag, auto narrow_tag, const int ks, const int j, float (&cw)[16]) __attribute__((always_inline)) {
+    fetch_columns(full_tag, narrow_tag, a.wscale + (size_t)ks * a.N, j, cw);
   };
   auto scale_cw = [&](const int ks, const int j, float (&cw)[16]) __attribute__((always_inline)) {
     if (tb.has_seg_scale) {                                // multiplier of block (ks, N-segment of the column)
@@ -589,27 +611,23 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
         const int off = tb.nseg_off[t];
         const float st = tb.seg_scale[ks * tb.T + t];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sg[v] = (ncol + j * 32 + 8 * (v >> 2) + (v & 3) >= off) ? st : sg[v];
+        for (int g = 0; g < 4; ++g) {
+          const int n = piece_of(wcol + j * 32 + 8 * g, a.N) + untraced(4 * fhi);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sg[4 * g + r] = n >= off - r ? st : sg[4 * g + r];
+        }
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) cw[v] *= sg[v];
     }
   };
 
-  auto fetch_bias = [&](auto full_tag, const int j, float (&bs)[16]) __attribute__((always_inline)) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    const bool bvec = FULL || (vec4 && (reinterpret_cast<uintptr_t>(a.bias) % 16 == 0));
+  auto fetch_bias = [&](auto full_tag, auto narrow_tag, const int j, float (&bs)[16]) __attribute__((always_inline)) {
+    if (a.bias) {
+      fetch_columns(full_tag, narrow_tag, a.bias, j, bs);
+    } else {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int n = ncol + j * 32 + 8 * g;
-      if (a.bias && bvec && (FULL || n + 3 < a.N)) {
-        const v4f b4 = *reinterpret_cast<const v4f*>(a.bias + n);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bs[4 * g + r] = b4[r];
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bs[4 * g + r] = (a.bias && n + r < a.N) ? a.bias[n + r] : 0.0f;
-      }
+      for (int v = 0; v < 16; ++v) bs[v] = 0.0f;
     }
   };
 
@@ -619,7 +637,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
     for (int i = 0; i < IM; ++i) {
       if (TOK) {
         int m = mrow + i * 32;
-        m = m < a.M ? m : a.M - 1;                       // rows beyond M are masked at the store
+        m = m < a.M ? m : a.M - 1;                       // rows beyond M repeat the last one
         spr[i] = a.tok_steps[(size_t)m * tb.S + ks];
         snr[i] = dl ? a.tok_steps[((size_t)a.M + m) * tb.S + ks] : 0.0f;
       } else {
@@ -636,35 +654,20 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   };
 
   // debug entry point: raw int32 sums of segment ks, acc_neg = 0 where the segment ran one path
-  auto store_debug = [&](auto full_tag, const int ks, const bool has_neg) __attribute__((always_inline)) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    const bool avec = FULL || (vec4 && ((reinterpret_cast<uintptr_t>(a.acc_pos) | reinterpret_cast<uintptr_t>(a.acc_neg)) % 16 == 0));
+  auto store_debug = [&](const int ks, const bool has_neg) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
       for (int j = 0; j < JN; ++j) {
-        const int m = mrow + i * 32;
         pin_block(i, j);
+        const int m = mrow + i * 32, half = untraced(fhi);
+        const uint32_t row = ((uint32_t)ks * (uint32_t)a.M + (uint32_t)untraced(m < a.M ? m : a.M - 1)) * (uint32_t)a.N;   // S*M*N < 2^31 is checked by the host
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int n = ncol + j * 32 + 8 * g;
-          if (FULL || m < a.M) {
-            const size_t o = ((size_t)ks * a.M + m) * a.N + n;     // S*M*N < 2^31 is checked by the host
-            v4i p, q;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              p[r] = pos_sum(i, j, 4 * g + r, has_neg);
-              q[r] = has_neg ? accn[DUAL ? i : 0][DUAL ? j : 0][4 * g + r] : 0;
-            }
-            if (FULL || (avec && n + 3 < a.N)) {
-              *reinterpret_cast<v4i*>(a.acc_pos + o) = p;
-              *reinterpret_cast<v4i*>(a.acc_neg + o) = q;
-            } else {
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if (n + r < a.N) { a.acc_pos[o + r] = p[r]; a.acc_neg[o + r] = q[r]; }
-            }
-          }
+        for (int v = 0; v < 16; ++v) {
+          const int n = piece_of(wcol + j * 32 + 8 * (v >> 2), a.N) + 4 * half + (v & 3);
+          const uint32_t o = row + (uint32_t)(n < a.N ? n : a.N - 1);
+          a.acc_pos[o] = pos_sum(i, j, v, has_neg);
+          a.acc_neg[o] = has_neg ? accn[DUAL ? i : 0][DUAL ? j : 0][v] : 0;
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -677,17 +680,17 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   // SHARE: the layer has exactly one dual K-segment and it is visited first.  Two int32 sets are live only
   // during that segment; at its end the X^_- set's registers are re-used for the fp32 running sum (its bits
   // are kept in accn), and every later segment accumulates in accp alone.  `first` = first visited segment.
-  auto flush_mid_impl = [&](auto full_tag, const int ks, const bool dl, const bool first) __attribute__((always_inline)) {
+  auto flush_mid_impl = [&](auto full_tag, auto narrow_tag, const int ks, const bool dl, const bool first) __attribute__((always_inline)) {
     if (mode == OUT_DEBUG_ACC) {
-      store_debug(full_tag, ks, DUAL && dl && (!SHARE || first));
+      store_debug(ks, DUAL && dl && (!SHARE || first));
     } else if (SHARE || FSUM) {
       float spr[IM], snr[IM];
       row_steps(ks, dl, spr, snr);
       float cwb[2][16];
-      fetch_cw(full_tag, ks, 0, cwb[0]);
+      fetch_cw(full_tag, narrow_tag, ks, 0, cwb[0]);
 #pragma unroll
       for (int j = 0; j < JN; ++j) {
-        if (j + 1 < JN) fetch_cw(full_tag, ks, j + 1, cwb[(j + 1) & 1]);
+        if (j + 1 < JN) fetch_cw(full_tag, narrow_tag, ks, j + 1, cwb[(j + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);               // the next block column's loads are out, nothing else moves up
         float (&cw)[16] = cwb[j & 1];
         scale_cw(ks, j, cw);
@@ -724,28 +727,27 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
       }
   };
   auto flush_mid = [&](const int ks, const bool dl, const bool first) __attribute__((always_inline)) {
-    if (full_tile) flush_mid_impl(std::true_type{}, ks, dl, first);
-    else flush_mid_impl(std::false_type{}, ks, dl, first);
+    if (full_tile) flush_mid_impl(std::true_type{}, std::false_type{}, ks, dl, first);
+    else flush_mid_impl(std::false_type{}, std::true_type{}, ks, dl, first);   // column by column, for any N
   };
 
   // ---- last K-segment: dequantize, add bias, store ----------------------------------------------------
   // bf16 output of an interior tile: the two halves of the wave (lanes l and l + 32 hold the same row, column
   // runs 4 apart) exchange every second run with v_permlane32_swap, so that each lane ends up with eight
   // consecutive columns and stores 16 bytes.
-  auto flush_last_impl = [&](auto full_tag, auto bf16_tag, const int ks, const bool dl) __attribute__((always_inline)) {
+  auto flush_last_impl = [&](auto full_tag, auto bf16_tag, auto narrow_tag, const int ks, const bool dl) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full_tag)::value;
-    constexpr bool BF = decltype(bf16_tag)::value;
+    constexpr bool BF = decltype(bf16_tag)::value, NARROW = decltype(narrow_tag)::value;
     float spr[IM], snr[IM];
     row_steps(ks, dl, spr, snr);
-    const bool yvec = FULL || (vec4 && (reinterpret_cast<uintptr_t>(a.y) % 16 == 0));
     float cwb[2][16], bsb[2][16];
-    fetch_cw(full_tag, ks, 0, cwb[0]);
-    fetch_bias(full_tag, 0, bsb[0]);
+    fetch_cw(full_tag, narrow_tag, ks, 0, cwb[0]);
+    fetch_bias(full_tag, narrow_tag, 0, bsb[0]);
 #pragma unroll
     for (int j = 0; j < JN; ++j) {
       if (j + 1 < JN) {
-        fetch_cw(full_tag, ks, j + 1, cwb[(j + 1) & 1]);
-        fetch_bias(full_tag, j + 1, bsb[(j + 1) & 1]);
+        fetch_cw(full_tag, narrow_tag, ks, j + 1, cwb[(j + 1) & 1]);
+        fetch_bias(full_tag, narrow_tag, j + 1, bsb[(j + 1) & 1]);
       }
       __builtin_amdgcn_sched_barrier(0);                 // the next block column's loads are out, nothing else moves up
       float (&cw)[16] = cwb[j & 1];
@@ -764,7 +766,18 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
           if (FSUM) u += fsum[FSUM ? i : 0][FSUM ? j : 0][v];
           t[v] = u + bs[v];
         }
-        if (FULL && BF) {
+        // FULL: whole pieces at their places; else pieces of column_of(), in rows up to the last one
+        const size_t row = FULL ? (size_t)m * a.N : (size_t)(uint32_t)untraced(m < a.M ? m : a.M - 1) * a.N;
+        const int half = FULL ? fhi : untraced(fhi);
+        if (NARROW) {                                        // N < 8: value by value
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const size_t o = row + column_of(wcol, j * 32 + 8 * (v >> 2) + 4 * half + (v & 3), a.N);
+            if (BF) reinterpret_cast<uint16_t*>(a.y)[o] = f32_to_bf16(t[v]);
+            else reinterpret_cast<float*>(a.y)[o] = t[v];
+          }
+        } else if (BF) {
+          typedef int v4iu __attribute__((ext_vector_type(4), aligned(2)));
 #pragma unroll
           for (int p = 0; p < 2; ++p) {
             const uint32_t a0 = f32x2_to_bf16x2(t[8 * p + 0], t[8 * p + 1]), a1 = f32x2_to_bf16x2(t[8 * p + 2], t[8 * p + 3]);
@@ -772,35 +785,17 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
             // lanes 32..63 of the first operand <-> lanes 0..31 of the second
             const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
             const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-            const v4i o4 = {(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]};
-            const size_t o = (size_t)m * a.N + (ncol + j * 32 + 16 * p + 4 * (lane >> 5));
-            *reinterpret_cast<v4i*>(reinterpret_cast<uint16_t*>(a.y) + o) = o4;
+            const v4iu o4 = {(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]};
+            const int n = FULL ? ncol + j * 32 + 16 * p + 4 * (lane >> 5) : piece_of(wcol + j * 32 + 16 * p + 8 * half, a.N);
+            *reinterpret_cast<v4iu*>(reinterpret_cast<uint16_t*>(a.y) + row + n) = o4;
           }
         } else {
+          typedef float v4fy __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            const int n = ncol + j * 32 + 8 * g;
-            if (FULL || m < a.M) {
-              const size_t o = (size_t)m * a.N + n;
-              if (FULL || (yvec && n + 3 < a.N)) {
-                if (!BF) {
-                  const v4f o4 = {t[4 * g], t[4 * g + 1], t[4 * g + 2], t[4 * g + 3]};
-                  *reinterpret_cast<v4f*>(reinterpret_cast<float*>(a.y) + o) = o4;
-                } else {
-                  v2i o2;
-                  o2[0] = (int)f32x2_to_bf16x2(t[4 * g], t[4 * g + 1]);
-                  o2[1] = (int)f32x2_to_bf16x2(t[4 * g + 2], t[4 * g + 3]);
-                  *reinterpret_cast<v2i*>(reinterpret_cast<uint16_t*>(a.y) + o) = o2;
-                }
-              } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  if (n + r < a.N) {
-                    if (!BF) reinterpret_cast<float*>(a.y)[o + r] = t[4 * g + r];
-                    else reinterpret_cast<uint16_t*>(a.y)[o + r] = f32_to_bf16(t[4 * g + r]);
-                  }
-              }
-            }
+            const v4fy o4 = {t[4 * g], t[4 * g + 1], t[4 * g + 2], t[4 * g + 3]};
+            const int n = FULL ? ncol + j * 32 + 8 * g : piece_of(wcol + j * 32 + 8 * g, a.N) + 4 * half;
+            *reinterpret_cast<v4fy*>(reinterpret_cast<float*>(a.y) + row + n) = o4;
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -809,14 +804,15 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   };
   auto flush_last = [&](const int ks, const bool dl, const bool first) __attribute__((always_inline)) {
     if (mode == OUT_DEBUG_ACC) {
-      if (full_tile) store_debug(std::true_type{}, ks, DUAL && dl && (!SHARE || first));
-      else store_debug(std::false_type{}, ks, DUAL && dl && (!SHARE || first));
+      store_debug(ks, DUAL && dl && (!SHARE || first));
     } else if (mode == OUT_BF16) {
-      if (full_tile) flush_last_impl(std::true_type{}, std::true_type{}, ks, dl);
-      else flush_last_impl(std::false_type{}, std::true_type{}, ks, dl);
+      if (full_tile) flush_last_impl(std::true_type{}, std::true_type{}, std::false_type{}, ks, dl);
+      else if (a.N >= 8) flush_last_impl(std::false_type{}, std::true_type{}, std::false_type{}, ks, dl);
+      else flush_last_impl(std::false_type{}, std::true_type{}, std::true_type{}, ks, dl);
     } else {
-      if (full_tile) flush_last_impl(std::true_type{}, std::false_type{}, ks, dl);
-      else flush_last_impl(std::false_type{}, std::false_type{}, ks, dl);
+      if (full_tile) flush_last_impl(std::true_type{}, std::false_type{}, std::false_type{}, ks, dl);
+      else if (a.N >= 8) flush_last_impl(std::false_type{}, std::false_type{}, std::false_type{}, ks, dl);
+      else flush_last_impl(std::false_type{}, std::false_type{}, std::true_type{}, ks, dl);
     }
   };
 

@@ -1996,6 +1996,57 @@ def test_seglinear_pair_rows_at_any_address(N):
             assert bool(((y.double() - ref).abs() <= bound).all()), (tile, dt)
 
 
+@pytest.mark.parametrize("N", [1, 7, 8, 9, 137, 261, 1027])
+@pytest.mark.parametrize("dual,scale", [((1,), False), ((0, 1), True), ((1, 1), False), ((0, 0), True)])
+def test_seglinear_mfma_ragged_tiles(N, dual, scale):
+    """Every tile of the tile kernel where it passes the last row and column: pieces of eight columns shifted back (fewer than eight
+    columns: value by value), rows of y at odd addresses, steps and multipliers of the columns they are shifted to, the raw sums.
+    Every element against a device product in 64 bits, nothing written in front of y or behind it."""
+    import torch
+
+    g = _gpu()
+    M, L, S = 203, 256, len(dual)
+    K = L * S
+    gen = torch.Generator(device=g.DEV)
+    gen.manual_seed(N + S)
+    xq, wq = (torch.randint(-127, 128, s, generator=gen, device=g.DEV, dtype=torch.int8) for s in ((M, K), (N, K)))
+    ws, bias = torch.rand((S, N), generator=gen, device=g.DEV) + 0.5, torch.rand(N, generator=gen, device=g.DEV) * 100 - 50
+    nseg = [0, N // 3, N] if scale and N >= 3 else [0, N]
+    mult = np.linspace(0.5, 2.0, S * (len(nseg) - 1)).astype(np.float32) if scale else None
+    sp, sn = [0.0131, 0.0072][:S], [0.0019, 0.0043][:S]
+    layer = sq.Layer(M, K, N, list(range(0, K + 1, L)), nseg, dual, sp, sn, mult)
+    ref, accs = bias.double().repeat(M, 1), []
+    for s in range(S):
+        x, w = xq[:, s * L:(s + 1) * L].double(), wq[:, s * L:(s + 1) * L].double().t().contiguous()
+        parts = (x.clamp(min=0) @ w, x.clamp(max=0) @ w) if dual[s] else (x @ w, torch.zeros_like(ref))
+        accs.append(parts)
+        c = ws[s].double()
+        if scale:
+            c = c * torch.from_numpy(np.repeat(mult.reshape(S, -1)[s], np.diff(nseg))).to(g.DEV).double()
+        ref += c * (float(np.float32(sp[s])) * parts[0] + float(np.float32(sn[s])) * parts[1])
+    sq.sq_tuning_set("force_path", 1)
+    ran = 0
+    for tile in range(9):
+        sq.sq_tuning_set("gemm_variant", tile)
+        for dt in (torch.float32, torch.bfloat16):
+            buf = torch.full((M * N + 3,), float("nan"), dtype=dt, device=g.DEV)
+            y = buf[1:1 + M * N].view(M, N)
+            try:
+                sq.sq_seglinear(layer, xq, wq, ws, bias, y)
+            except sq.SqError:                                # a tile without registers for this kind of layer
+                break
+            ran += 1
+            assert bool(torch.isnan(buf[[0, -2, -1]]).all())
+            bound = RTOL * ref.abs().max() + (y.double().abs() * 2.0 ** -8 if dt == torch.bfloat16 else 0.0)
+            assert bool(((y.double() - ref).abs() <= bound).all()), (tile, dt)
+        else:
+            acc = torch.full((2, S, M, N), 7, dtype=torch.int32, device=g.DEV)
+            sq.sq_seglinear_debug_acc(layer, xq, wq, acc[0], acc[1])
+            for s in range(S):
+                assert torch.equal(acc[0, s].double(), accs[s][0]) and torch.equal(acc[1, s].double(), accs[s][1]), (tile, s)
+    assert ran >= 8
+
+
 def test_seglinear_pair_forced_elsewhere_is_refused():
     """A polarity-split layer, two K-segments, K below four stages, seg_scale, raw sums, fp8 on the widest tile: no fallback."""
     import torch
