@@ -1996,10 +1996,8 @@ def test_seglinear_pair_rows_at_any_address(N):
             assert bool(((y.double() - ref).abs() <= bound).all()), (tile, dt)
 
 
-@pytest.mark.parametrize("N", [1, 7, 8, 9, 137, 261, 1027])
-@pytest.mark.parametrize("dual,scale", [((1,), False), ((0, 1), True), ((1, 1), False), ((0, 0), True)])
-def test_seglinear_mfma_ragged_tiles(N, dual, scale):
-    """Every tile of the tile kernel where it passes the last row and column: pieces of eight columns shifted back (fewer than eight
+def _ragged_tiles(path, tiles, N, dual, scale):
+    """Every tile of a kernel where it passes the last row and column: pieces of eight columns shifted back (fewer than eight
     columns: value by value), rows of y at odd addresses, steps and multipliers of the columns they are shifted to, the raw sums.
     Every element against a device product in 64 bits, nothing written in front of y or behind it."""
     import torch
@@ -2024,9 +2022,9 @@ def test_seglinear_mfma_ragged_tiles(N, dual, scale):
         if scale:
             c = c * torch.from_numpy(np.repeat(mult.reshape(S, -1)[s], np.diff(nseg))).to(g.DEV).double()
         ref += c * (float(np.float32(sp[s])) * parts[0] + float(np.float32(sn[s])) * parts[1])
-    sq.sq_tuning_set("force_path", 1)
+    sq.sq_tuning_set("force_path", path)
     ran = 0
-    for tile in range(9):
+    for tile in range(tiles):
         sq.sq_tuning_set("gemm_variant", tile)
         for dt in (torch.float32, torch.bfloat16):
             buf = torch.full((M * N + 3,), float("nan"), dtype=dt, device=g.DEV)
@@ -2044,7 +2042,20 @@ def test_seglinear_mfma_ragged_tiles(N, dual, scale):
             sq.sq_seglinear_debug_acc(layer, xq, wq, acc[0], acc[1])
             for s in range(S):
                 assert torch.equal(acc[0, s].double(), accs[s][0]) and torch.equal(acc[1, s].double(), accs[s][1]), (tile, s)
-    assert ran >= 8
+    return ran
+
+
+@pytest.mark.parametrize("N", [1, 7, 8, 9, 137, 261, 1027])
+@pytest.mark.parametrize("dual,scale", [((1,), False), ((0, 1), True), ((1, 1), False), ((0, 0), True)])
+def test_seglinear_mfma_ragged_tiles(N, dual, scale):
+    assert _ragged_tiles(1, 9, N, dual, scale) >= 8
+
+
+@pytest.mark.parametrize("N", [1, 7, 8, 9, 137, 261, 1027])
+@pytest.mark.parametrize("dual", [(0,), (1,), (0, 1)])
+def test_seglinear_ksplit_ragged_tiles(N, dual):
+    """The K-splitting tiles share the pieces of eight columns."""
+    assert _ragged_tiles(4, 3, N, dual, False) == 6
 
 
 def test_seglinear_pair_forced_elsewhere_is_refused():
