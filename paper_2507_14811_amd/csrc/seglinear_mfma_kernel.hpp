@@ -249,12 +249,13 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
     return reinterpret_cast<const int8_t*>(((uint64_t)hi << 32) | lo);
   };
-  auto issue_begin = [&]() __attribute__((always_inline)) {
+  auto issue_begin_at = [&](const int offset) __attribute__((always_inline)) {   // offset of the stage's buffer in the ring
     const int k0 = ik << KSH;
-    iso = __builtin_amdgcn_readfirstlane((uint32_t)(ikt % NSTAGE) * (uint32_t)STAGE);
+    iso = __builtin_amdgcn_readfirstlane((uint32_t)offset);
     ipA = uniform_ptr(a.xq + k0);
     ipB = uniform_ptr(a.wq + k0);
   };
+  auto issue_begin = [&]() __attribute__((always_inline)) { issue_begin_at((ikt % NSTAGE) * STAGE); };
   auto issue_slot = [&](const int e) __attribute__((always_inline)) {          // e is a compile-time constant after unrolling
     if (e < GA) glds16(ipA, voffA[e < GA ? e : 0], ldsA + iso + (uint32_t)e * 1024u);
     else glds16(ipB, voffB[e >= GA ? e - GA : 0], ldsB + iso + (uint32_t)(e - GA) * 1024u);
@@ -456,9 +457,8 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   // the way.  Iterations that still refill and those at the very end of K that do not are separate plain
   // loops, so that the accumulators flow through one MFMA block per loop and stay in accumulation registers.
   int kt = 0;
-  auto tail_steps = [&](auto dl_tag, auto more_tag, const int s) __attribute__((always_inline)) {   // k-steps 0 .. SUB-2 of stage s
+  auto tail_steps = [&](auto dl_tag, auto more_tag, const int so) __attribute__((always_inline)) {   // k-steps 0 .. SUB-2 of the stage at so
     constexpr bool MORE = decltype(more_tag)::value;
-    const int so = stage_off(s);
 #pragma unroll
     for (int h = 0; h + 1 < SUB; ++h) {
       if (h == 0) kstep(dl_tag, std::true_type{}, std::integral_constant<int, MORE ? 1 : -1>{}, 0, so + foff[1]);
@@ -487,11 +487,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
     if (kt > 0 && ikt < nkt) {
       issue_begin();
       issue_group(0);
-      tail_steps(dl_tag, std::true_type{}, kt);
+      tail_steps(dl_tag, std::true_type{}, stage_off(kt));
       issue_end();
       issue_next_tile_if_done();
     } else {
-      tail_steps(dl_tag, std::false_type{}, kt);
+      tail_steps(dl_tag, std::false_type{}, stage_off(kt));
     }
     int b = kt;
     const int b_more_end = (kt_end - 1) < (nkt - NSTAGE) ? (kt_end - 1) : (nkt - NSTAGE);
@@ -500,13 +500,19 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
       // one run of the loop issues one stage per iteration and stays inside the tile being fetched
       const int left = (iit + 1) * nkt_tile - ikt;
       const int stop = (b + left) < b_more_end ? (b + left) : b_more_end;
+      // Here the stages up to b + NSTAGE - 1 have been requested, and stage b + NSTAGE goes into the buffer of stage b: the wait is a
+      // constant and the buffers' offsets follow each other.  Counted and compared at run time, with a division by NSTAGE per buffer,
+      // a stage had some 25 scalar instructions and branches more: 4608 x (3072 + 12288) x 3072 343 -> 335.5 us with its quantizer, 2048 x
+      // 4608 x 1152 34.2 -> 33.3, 2048 x (2304 + 2304) x 1152 36.2 -> 34.5.
+      int at = stage_off(b);
 #pragma unroll 1
       for (; b < stop; ++b) {
-        wait_landed(b + 1);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NSTAGE - 2) * LT) : "memory");
         __syncthreads();
-        issue_begin();
-        kstep(dl_tag, std::true_type{}, std::integral_constant<int, 0>{}, LASTSET, stage_off(b + 1) + foff[0]);
-        tail_steps(dl_tag, std::true_type{}, b + 1);
+        issue_begin_at(at);
+        at = at == (NSTAGE - 1) * STAGE ? 0 : at + STAGE;
+        kstep(dl_tag, std::true_type{}, std::integral_constant<int, 0>{}, LASTSET, at + foff[0]);
+        tail_steps(dl_tag, std::true_type{}, at);
         issue_end();
       }
       issue_next_tile_if_done();
@@ -516,7 +522,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
       wait_landed(b + 1);
       __syncthreads();
       kstep(dl_tag, std::true_type{}, std::integral_constant<int, -1>{}, LASTSET, stage_off(b + 1) + foff[0]);
-      tail_steps(dl_tag, std::false_type{}, b + 1);
+      tail_steps(dl_tag, std::false_type{}, stage_off(b + 1));
     }
     kstep(dl_tag, std::false_type{}, std::integral_constant<int, -1>{}, LASTSET, 0);
     kt = kt_end;
