@@ -401,7 +401,13 @@ __global__ __launch_bounds__(256) void quantize_weight_row_kernel(const void* __
     constexpr unsigned G = 16 * TPI / 256;         // workgroups of such a group
     if (block < gridDim.x / (8 * G) * (8 * G)) block = block / (8 * G) * (8 * G) + block % 8 * G + block / 8 % G;
   }
-  const int n = block * (256 / TPI) + __builtin_amdgcn_readfirstlane(threadIdx.x / TPI), ks = blockIdx.y;
+  // 4 bit, long fp32 rows: from the last row to the first.  Both formats are often made of one weight, the 8-bit codes first, and the end
+  // of it may still be in the Infinity Cache (3072 x 15360, both behind the two calibrations of 4608 rows 153.1 -> 150.2 us; shorter
+  // rows gained nothing.  The 8-bit pass reading through that cache: 149, but 47 instead of 44 us by itself).
+  constexpr bool BACK = BITS == 4 && !BF16 && NCH >= 16;
+  if (BACK) block = gridDim.x - 1 - block;
+  const int n = block * (256 / TPI) + __builtin_amdgcn_readfirstlane(threadIdx.x / TPI);
+  const int ks = BACK ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
   if (n >= rows) return;                           // a whole wave (TPI 64) or workgroup leaves together
   const int k0 = tb.off[ks], L = tb.off[ks + 1] - k0;
   auto column = [&](const int l) __attribute__((always_inline)) {   // first column, inside the segment, of load l
