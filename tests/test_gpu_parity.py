@@ -959,7 +959,7 @@ def test_lowrank_down_plans(oracle, M, K, rank):
 @pytest.mark.parametrize("rank,yq", [(64, True), (32, True), (64, False)])
 @pytest.mark.parametrize("M,N", [(201, 65002), (203, 64999), (4130, 3200)])
 def test_lowrank_add_large(M, N, rank, yq):
-    """From 13 M outputs the up projection fetches y_q and Lu one block column ahead: ragged rows, ragged and odd columns, bit for bit
+    """From 10 M outputs the up projection stores y past the caches: ragged rows, ragged and odd columns, bit for bit
     the result of the same rows in calls below that size (K = 256: one K slice in all of them, so the same T)."""
     import torch
 
@@ -1002,8 +1002,8 @@ def test_lowrank_up_edges(oracle, M, N, rank, yq):
 @pytest.mark.parametrize("rank", [64, 32])
 @pytest.mark.parametrize("M,N", [(6300, 3200), (3300, 3400), (6301, 7008)])
 def test_lowrank_up_sizes(M, N, rank):
-    """The other sizes at which the up projection changes its way through the caches: 20 M outputs (y stored past them), 11 M (y_q
-    through them, a block column ahead) and 44 M, with a ragged row block and a last strip of 104 and 96 columns."""
+    """More large sizes of the up projection, past the caches and through them, with a ragged row block and a last strip of 104 and 96
+    columns."""
     test_lowrank_add_large(M, N, rank, True)
 
 
