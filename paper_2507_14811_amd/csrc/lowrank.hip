@@ -346,7 +346,10 @@ __device__ __forceinline__ void split_t(const v4f (&src)[KH / 4], v8bf (&thi)[KH
 //   * A lane holds CPL = 4 (or 2) neighbouring columns, one in each of CPL blocks: place 32 j + f of the staged strip holds Lu row
 //     CPL f + j, so the order costs nothing.  A load of y_q then covers 512 (256) consecutive bytes of two rows, a store 256 (128)
 //     bytes of bf16 y; with a block of 32 neighbouring columns at a time they were 128 and 64, and twice to four times as many.
-//   * All loads of a wave (its share of Lu, T, y_q) go out before anything waits; the T values are split meanwhile.
+//   * All loads of a wave (its share of Lu, T, y_q) go out before anything waits; the T values are split meanwhile.  Whether there is a
+//     y_q is a template argument: as a branch in the kernel, both sides began with T, and the compiler waited for it in front of the
+//     branch (and kept 36 registers more, 16 bytes of them in scratch memory at CPL = 2).  Timed in turn the two orders are alike, other
+//     waves fill the gap: 8500 x 1536 x 4608 134.1 -> 133.2 us, 1500 x 1024 x 3072 39.0 -> 38.1, 2749 x 2816 x 8448 117.9 -> 118.2.
 //   * Row blocks run from the last to the first: the product has written the last rows of y_q last, and they are still in the Infinity
 //     Cache, while the first ones of a large y_q would be displaced before they are read.
 //   * y_q is read, and y written from kLrPastFrom outputs on, past the caches where rows are whole lines.
@@ -356,7 +359,7 @@ __device__ __forceinline__ void split_t(const v4f (&src)[KH / 4], v8bf (&thi)[KH
 // Not taken: three waves per SIMD at CPL = 4 (the registers spill: 163 us), CPL = 2 throughout (290 -> 302 at 7000 x 3072 x 9216).
 constexpr long long kLrPastFrom = 10000000;                          // outputs
 enum LrMode { LR_PLAIN, LR_READ_PAST, LR_PAST };                     // each with what the ones before it have
-template <bool YBF16, int R, int CPL, LrMode MODE>
+template <bool YBF16, int R, int CPL, LrMode MODE, bool YQ>
 __global__ __launch_bounds__(256, CPL == 4 ? 2 : 3) void lowrank_up_kernel(const float* __restrict__ tsum, const uint16_t* __restrict__ lu,
                                                                            const float* y_in, void* y_out, int M, int N) {
   constexpr int STRIP = 32 * CPL;                                  // columns of a workgroup, CPL per lane
@@ -384,8 +387,8 @@ __global__ __launch_bounds__(256, CPL == 4 ? 2 : 3) void lowrank_up_kernel(const
   // wave's rows and the strip lie inside the matrix (addresses are then a scalar per row and one offset per lane); else rows beyond
   // it re-read the last one.
   const int nl = n0 + CPL * frow;
-  auto strip_of = [&](auto full_tag, auto yq_tag) __attribute__((always_inline)) {
-    constexpr bool FULL = decltype(full_tag)::value, YQ = decltype(yq_tag)::value;
+  auto strip_of = [&](auto full_tag) __attribute__((always_inline)) {
+    constexpr bool FULL = decltype(full_tag)::value;
     typedef float vf __attribute__((ext_vector_type(CPL)));
     typedef float vfu __attribute__((ext_vector_type(CPL), aligned(4)));   // rows of any N: 4-byte (bf16: 2-byte) alignment
     typedef int viu __attribute__((ext_vector_type(CPL / 2), aligned(2)));
@@ -465,13 +468,8 @@ __global__ __launch_bounds__(256, CPL == 4 ? 2 : 3) void lowrank_up_kernel(const
       }
     }
   };
-  if (ncols == STRIP && mb + 32 <= M) {
-    if (y_in != nullptr) strip_of(std::true_type{}, std::true_type{});
-    else strip_of(std::true_type{}, std::false_type{});
-  } else {
-    if (y_in != nullptr) strip_of(std::false_type{}, std::true_type{});
-    else strip_of(std::false_type{}, std::false_type{});
-  }
+  if (ncols == STRIP && mb + 32 <= M) strip_of(std::true_type{});
+  else strip_of(std::false_type{});
 }
 
 size_t lowrank_workspace_bytes(int M, int K, int rank, int cus) {
@@ -509,17 +507,19 @@ hipError_t launch_lowrank_add(const void* x, bool x_is_bf16, const uint16_t* ld,
   // over more of them: 1500 x 1024 x 3072 39.2 -> 37.5 us, 700 x 1024 x 3072 33.0 -> 31.3, 400 x 3072 x 9216 53.5 -> 51.9.
   const int rows = (M + 127) / 128;
   const bool wide = (long long)rows * ((N + 127) / 128) >= 2ll * cus;
-#define SQ_UPM(B, R, C, MODE) hipLaunchKernelGGL((lowrank_up_kernel<B, R, C, MODE>), dim3((N + 32 * C - 1) / (32 * C), rows), dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
+#define SQ_UPY(B, R, C, MODE, YQ) hipLaunchKernelGGL((lowrank_up_kernel<B, R, C, MODE, YQ>), dim3((N + 32 * C - 1) / (32 * C), rows), dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
+#define SQ_UPM(B, R, C, MODE) if (y_in != nullptr) { SQ_UPY(B, R, C, MODE, true); } else { SQ_UPY(B, R, C, MODE, false); }
 #define SQ_UPC(B, R, C) \
-  if (lines && (long long)M * N >= kLrPastFrom) SQ_UPM(B, R, C, LR_PAST); \
-  else if (lines) SQ_UPM(B, R, C, LR_READ_PAST); \
-  else SQ_UPM(B, R, C, LR_PLAIN)
-#define SQ_UP(B, R) if (wide) { SQ_UPC(B, R, 4); } else { SQ_UPC(B, R, 2); }
+  if (lines && (long long)M * N >= kLrPastFrom) { SQ_UPM(B, R, C, LR_PAST) } \
+  else if (lines) { SQ_UPM(B, R, C, LR_READ_PAST) } \
+  else { SQ_UPM(B, R, C, LR_PLAIN) }
+#define SQ_UP(B, R) if (wide) { SQ_UPC(B, R, 4) } else { SQ_UPC(B, R, 2) }
   if (rank == 64) { if (y_is_bf16) { SQ_UP(true, 64) } else { SQ_UP(false, 64) } }
   else            { if (y_is_bf16) { SQ_UP(true, 32) } else { SQ_UP(false, 32) } }
 #undef SQ_UP
 #undef SQ_UPC
 #undef SQ_UPM
+#undef SQ_UPY
   return hipGetLastError();
 }
 

@@ -1,0 +1,61 @@
+"""Properties of the compiled kernels that no result shows: the gfx950 code inside the built library is disassembled (no GPU needed)."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """name -> list of (mnemonic, operands), of all kernels whose mangled name contains one of the words asked for"""
+    from paper_2507_14811_amd import binding, build
+
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    if not os.path.exists(binding.LIB_PATH):
+        build.build_library(verbose=False)
+    d = tmp_path_factory.mktemp("code")
+    shutil.copy(binding.LIB_PATH, d / "l.so")
+    subprocess.run([OBJDUMP, "--offloading", "l.so"], cwd=d, check=True, stdout=subprocess.DEVNULL)
+    objects = sorted(d.glob("l.so.*gfx950*"))
+    assert objects
+
+    def select(*words):
+        out = {}
+        for o in objects:
+            if not any(w.encode() in o.read_bytes() for w in words):
+                continue
+            text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(o)], check=True, stdout=subprocess.PIPE, text=True).stdout
+            for m in re.finditer(r"^[0-9a-f]+ <(_Z\w+)>:\n(.*?)(?=^\s*$|\Z)", text, re.S | re.M):
+                if any(w in m.group(1) for w in words):
+                    out[m.group(1)] = [tuple((line.split("//")[0].split(None, 1) + [""])[:2]) for line in m.group(2).splitlines() if line.strip()]
+        return out
+
+    return select
+
+
+def test_up_projection_requests_all_before_it_waits(kernels):
+    """With y_q: the wave's share of Lu, its T values and sixteen pieces of y_q are requested in this order before the first wait, and nothing up to the
+    barrier waits for y_q (the wait for Lu counts on exactly sixteen younger loads)."""
+    seen = 0
+    for name, code in kernels("lowrank_up_kernel").items():
+        rank, cpl, mode, yq = map(int, re.search(r"Lb[01]ELi(\d+)ELi(\d)ELNS_6LrModeE(\d)ELb([01])E", name).groups())
+        first = max(i for i, (op, _) in enumerate(code) if op == "global_load_lds_dwordx4") + 1
+        loads, waits = [], []
+        for op, args in code[first:]:
+            if op == "s_barrier":
+                break
+            if op.startswith("global_load"):
+                loads.append((op, len(waits)))
+            if op == "s_waitcnt" and "vmcnt" in args:
+                waits.append(int(re.search(r"vmcnt\((\d+)\)", args).group(1)))
+        assert [n for _, n in loads] == [0] * len(loads), (name, "a load behind a wait")
+        assert [op for op, _ in loads[:rank // 8]] == ["global_load_dwordx4"] * (rank // 8), name
+        assert [op for op, _ in loads[rank // 8:]] == ["global_load_dwordx%d" % cpl] * (16 if yq else 0), name
+        assert min(waits) == (16 if yq else 0), (name, waits)
+        seen += yq
+    assert seen >= 8
