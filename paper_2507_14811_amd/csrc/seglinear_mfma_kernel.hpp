@@ -659,8 +659,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
     return accp[i][j][v];
   };
 
-  // debug entry point: raw int32 sums of segment ks, acc_neg = 0 where the segment ran one path
+  // debug entry point: raw int32 sums of segment ks, acc_neg = 0 where the segment ran one path.  Four columns of a row per store
+  // (N < 8: value by value): a store of single values touches 32 rows for four bytes each and took 8500 x 1536 x 4608 245 us instead
+  // of 129, 1000 x 1028 with eight K-segments of 128 84 instead of 33.
   auto store_debug = [&](const int ks, const bool has_neg) __attribute__((always_inline)) {
+    typedef int v4iu __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
@@ -669,13 +672,25 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
         const int m = mrow + i * 32, half = untraced(fhi);
         const uint32_t row = ((uint32_t)ks * (uint32_t)a.M + (uint32_t)untraced(m < a.M ? m : a.M - 1)) * (uint32_t)a.N;   // S*M*N < 2^31 is checked by the host
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int n = piece_of(wcol + j * 32 + 8 * (v >> 2), a.N) + 4 * half + (v & 3);
-          const uint32_t o = row + (uint32_t)(n < a.N ? n : a.N - 1);
-          a.acc_pos[o] = pos_sum(i, j, v, has_neg);
-          a.acc_neg[o] = has_neg ? accn[DUAL ? i : 0][DUAL ? j : 0][v] : 0;
+        for (int g = 0; g < 4; ++g) {
+          const int n = piece_of(wcol + j * 32 + 8 * g, a.N) + 4 * half;
+          auto store = [&](int32_t* sums, const v4iu t) __attribute__((always_inline)) {
+            if (a.N >= 8) {
+              *reinterpret_cast<v4iu*>(sums + (row + (uint32_t)n)) = t;
+            } else {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) sums[row + (uint32_t)(n + r < a.N ? n + r : a.N - 1)] = t[r];
+            }
+          };
+          v4iu t;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) t[r] = pos_sum(i, j, 4 * g + r, has_neg);
+          store(a.acc_pos, t);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) t[r] = has_neg ? accn[DUAL ? i : 0][DUAL ? j : 0][4 * g + r] : 0;
+          store(a.acc_neg, t);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
       }
     // stores share the vector-memory counter with the direct loads but complete out of order with them:
     // drain everything so that the load accounting of the K loop stays valid

@@ -11,7 +11,7 @@ OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """name -> list of (mnemonic, operands), of all kernels whose mangled name contains one of the words asked for"""
+    """name -> list of (mnemonic, operands), of all kernels whose mangled name matches the pattern asked for"""
     from paper_2507_14811_amd import binding, build
 
     if not os.path.exists(OBJDUMP):
@@ -24,15 +24,17 @@ def kernels(tmp_path_factory):
     objects = sorted(d.glob("l.so.*gfx950*"))
     assert objects
 
-    def select(*words):
+    def select(pattern):
         out = {}
         for o in objects:
-            if not any(w.encode() in o.read_bytes() for w in words):
+            names = [n for n in subprocess.run([OBJDUMP, "-t", str(o)], check=True, stdout=subprocess.PIPE, text=True).stdout.split()
+                     if re.search(pattern, n) and "." not in n]
+            if not names:
                 continue
-            text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(o)], check=True, stdout=subprocess.PIPE, text=True).stdout
+            text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--disassemble-symbols=" + ",".join(names), str(o)], check=True,
+                                  stdout=subprocess.PIPE, text=True).stdout
             for m in re.finditer(r"^[0-9a-f]+ <(_Z\w+)>:\n(.*?)(?=^\s*$|\Z)", text, re.S | re.M):
-                if any(w in m.group(1) for w in words):
-                    out[m.group(1)] = [tuple((line.split("//")[0].split(None, 1) + [""])[:2]) for line in m.group(2).splitlines() if line.strip()]
+                out[m.group(1)] = [tuple((line.split("//")[0].split(None, 1) + [""])[:2]) for line in m.group(2).splitlines() if line.strip()]
         return out
 
     return select
@@ -59,3 +61,15 @@ def test_up_projection_requests_all_before_it_waits(kernels):
         assert min(waits) == (16 if yq else 0), (name, waits)
         seen += yq
     assert seen >= 8
+
+
+def test_raw_sums_are_stored_sixteen_bytes_at_a_time(kernels):
+    """Tile kernel, one K-segment: per 32 x 32 block four 16-byte stores of fp32 and two of bf16 results, whole tiles and ragged ones, and twice four
+    of the raw sums."""
+    seen = 0
+    for name, code in kernels(r"seglinear_mfma_kernelI(Li\d+E){7}Lb[01]ELb0E").items():
+        bm, bn, wm, wn = map(int, re.search(r"kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", name).groups())
+        blocks = (bm // wm // 32) * (bn // wn // 32)
+        assert sum(op == "global_store_dwordx4" for op, _ in code) >= 20 * blocks, name
+        seen += 1
+    assert seen >= 17                                      # nine tiles, eight of them with a polarity split
