@@ -507,19 +507,26 @@ hipError_t launch_lowrank_add(const void* x, bool x_is_bf16, const uint16_t* ld,
   // over more of them: 1500 x 1024 x 3072 39.2 -> 37.5 us, 700 x 1024 x 3072 33.0 -> 31.3, 400 x 3072 x 9216 53.5 -> 51.9.
   const int rows = (M + 127) / 128;
   const bool wide = (long long)rows * ((N + 127) / 128) >= 2ll * cus;
-#define SQ_UPY(B, R, C, MODE, YQ) hipLaunchKernelGGL((lowrank_up_kernel<B, R, C, MODE, YQ>), dim3((N + 32 * C - 1) / (32 * C), rows), dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
-#define SQ_UPM(B, R, C, MODE) if (y_in != nullptr) { SQ_UPY(B, R, C, MODE, true); } else { SQ_UPY(B, R, C, MODE, false); }
-#define SQ_UPC(B, R, C) \
-  if (lines && (long long)M * N >= kLrPastFrom) { SQ_UPM(B, R, C, LR_PAST) } \
-  else if (lines) { SQ_UPM(B, R, C, LR_READ_PAST) } \
-  else { SQ_UPM(B, R, C, LR_PLAIN) }
-#define SQ_UP(B, R) if (wide) { SQ_UPC(B, R, 4) } else { SQ_UPC(B, R, 2) }
+  // Narrow strips have less than 2 cus x 128 x 128 = 8.4 M outputs, so kLrPastFrom concerns the wide ones only; without a y_q there is
+  // nothing to read past the caches.
+  const bool past = lines && (long long)M * N >= kLrPastFrom;
+#define SQ_UPM(B, R, C, MODE, YQ) hipLaunchKernelGGL((lowrank_up_kernel<B, R, C, MODE, YQ>), dim3((N + 32 * C - 1) / (32 * C), rows), dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
+#define SQ_UP(B, R) \
+  if (y_in != nullptr) { \
+    if (wide && past) SQ_UPM(B, R, 4, LR_PAST, true); \
+    else if (wide && lines) SQ_UPM(B, R, 4, LR_READ_PAST, true); \
+    else if (wide) SQ_UPM(B, R, 4, LR_PLAIN, true); \
+    else if (lines) SQ_UPM(B, R, 2, LR_READ_PAST, true); \
+    else SQ_UPM(B, R, 2, LR_PLAIN, true); \
+  } else { \
+    if (wide && past) SQ_UPM(B, R, 4, LR_PAST, false); \
+    else if (wide) SQ_UPM(B, R, 4, LR_PLAIN, false); \
+    else SQ_UPM(B, R, 2, LR_PLAIN, false); \
+  }
   if (rank == 64) { if (y_is_bf16) { SQ_UP(true, 64) } else { SQ_UP(false, 64) } }
   else            { if (y_is_bf16) { SQ_UP(true, 32) } else { SQ_UP(false, 32) } }
 #undef SQ_UP
-#undef SQ_UPC
 #undef SQ_UPM
-#undef SQ_UPY
   return hipGetLastError();
 }
 
