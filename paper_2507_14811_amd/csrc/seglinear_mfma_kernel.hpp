@@ -583,10 +583,14 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
     asm volatile("" : "+v"(v));
     return v;
   };
-  // a per-column array's values at the sixteen columns of this lane in block column j
+  // A per-column array's values at the sixteen columns of this lane in block column j.  NARROW: N may be below eight.  Between K-segments
+  // one instantiation serves all tiles that are not whole, so N decides there: always value by value, eight K-segments of 128 columns
+  // with 939 rows and 1152 columns took 24.2 us instead of 19.9, 38 x (8 x 256) x 124 30.2 instead of 26.0, 2100 x (8 x 128) x 2052 33.1 instead of
+  // 28.  Not on eight waves with a running sum next to two accumulator sets: no registers to spare, reloads in the K loop.
+  constexpr bool PIECES_MID = !(FSUM && DUAL && WM * WN == 8);
   auto fetch_columns = [&](auto full_tag, auto narrow_tag, const float* p, const int j, float (&c)[16]) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full_tag)::value, NARROW = decltype(narrow_tag)::value;
-    if (FULL || !NARROW) {
+    if (FULL || !NARROW || (PIECES_MID && a.N >= 8)) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         v4f w4;
@@ -749,7 +753,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   };
   auto flush_mid = [&](const int ks, const bool dl, const bool first) __attribute__((always_inline)) {
     if (full_tile) flush_mid_impl(std::true_type{}, std::false_type{}, ks, dl, first);
-    else flush_mid_impl(std::false_type{}, std::true_type{}, ks, dl, first);   // column by column, for any N
+    else flush_mid_impl(std::false_type{}, std::true_type{}, ks, dl, first);
   };
 
   // ---- last K-segment: dequantize, add bias, store ----------------------------------------------------

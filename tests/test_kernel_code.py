@@ -74,3 +74,17 @@ def test_raw_sums_are_stored_sixteen_bytes_at_a_time(kernels):
         assert sum(op == "global_store_dwordx4" for op, _ in code) >= 20 * blocks, name
         seen += 1
     assert seen >= 17                                      # nine tiles, eight of them with a polarity split
+
+
+def test_tile_constants_come_sixteen_bytes_at_a_time(kernels):
+    """Tile kernel, several K-segments: a block column's scales are four 16-byte loads wherever the tile lies, in the flush between K-segments (two
+    copies where one polarity-split segment shares its registers) as in the last one, which has the biases too, for fp32 and for bf16.
+    Eight waves with a running sum next to two accumulator sets alone leave the ragged tiles between K-segments to single loads."""
+    seen = 0
+    for name, code in kernels(r"seglinear_mfma_kernelILi(64ELi(128|192)E|128ELi256ELi2ELi4E)(Li\d+E)*Lb[01]ELb1ELb[01]ELb0ELb0E").items():
+        bn, wn = (int(re.findall(r"Li(\d+)E", name)[i]) for i in (1, 3))
+        dual, _, share = (f == "1" for f in re.findall(r"Lb([01])E", name)[:3])
+        mid = 16 if share else 4 if dual and wn == 4 else 8
+        assert sum(op == "global_load_dwordx4" for op, _ in code) == (32 + mid) * (bn // wn // 32), name
+        seen += 1
+    assert seen == 9
