@@ -646,8 +646,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
 #pragma unroll
     for (int i = 0; i < IM; ++i) {
       if (TOK) {
+        // Untraced, so that each flush loads its own.  A load that the compiler shares between them and that it cannot see used on every way
+        // leaves it with a register to wait for, which it did in each stage of a K loop (vmcnt(0): the ring drained): two polarity-split
+        // K-segments on 128 x 128 tiles, 2318 x (1408 + 3840) x 1280 45.6 us, 38.6 now; 6272 x (3712 + 128 + 640 + 3840) x 1024 104.6, 91.7.
         int m = mrow + i * 32;
-        m = m < a.M ? m : a.M - 1;                       // rows beyond M repeat the last one
+        m = untraced(m < a.M ? m : a.M - 1);             // rows beyond M repeat the last one
         spr[i] = a.tok_steps[(size_t)m * tb.S + ks];
         snr[i] = dl ? a.tok_steps[((size_t)a.M + m) * tb.S + ks] : 0.0f;
       } else {

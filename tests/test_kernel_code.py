@@ -88,3 +88,19 @@ def test_tile_constants_come_sixteen_bytes_at_a_time(kernels):
         assert sum(op == "global_load_dwordx4" for op, _ in code) == (32 + mid) * (bn // wn // 32), name
         seen += 1
     assert seen == 9
+
+
+def test_refilling_k_loop_waits_for_its_ring_only(kernels):
+    """Tile kernel, rings of three stages and more, per-token steps: between the barrier of a stage and the end of the loop nothing waits for a
+    vector load (a wait for one of the flush's own would drain the ring in every stage)."""
+    loops = 0
+    for name, code in kernels(r"seglinear_mfma_kernelI(Li\d+E){4}Li[34]E(Li\d+E)*(Lb[01]E){3}Lb1ELb0E").items():
+        for i, (op, _) in enumerate(code):
+            if op != "s_barrier":
+                continue
+            end = next(j for j in range(i, len(code)) if code[j][0].startswith("s_cbranch"))
+            body = code[i:end]
+            if sum(op == "global_load_lds_dwordx4" for op, _ in body) >= 6 and sum(op.startswith("v_mfma") for op, _ in body) >= 8:
+                loops += 1
+                assert not [a for op, a in body if op == "s_waitcnt" and re.search(r"vmcnt\((?!63)", a)], name
+    assert loops >= 5 * 4
