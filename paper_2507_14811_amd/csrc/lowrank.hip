@@ -352,12 +352,17 @@ __device__ __forceinline__ void split_t(const v4f (&src)[KH / 4], v8bf (&thi)[KH
 //     waves fill the gap: 8500 x 1536 x 4608 134.1 -> 133.2 us, 1500 x 1024 x 3072 39.0 -> 38.1, 2749 x 2816 x 8448 117.9 -> 118.2.
 //   * Row blocks run from the last to the first: the product has written the last rows of y_q last, and they are still in the Infinity
 //     Cache, while the first ones of a large y_q would be displaced before they are read.
-//   * y_q is read, and y written from kLrPastFrom outputs on, past the caches where rows are whole lines.
+//   * Where rows are whole lines, large calls go past the caches; what still fits in the Infinity Cache is quicker through it, and whoever
+//     reads y next pays for what does not go there.  bf16 y: y_q and y past them from 10 M outputs on (4-bit layer 5300 x 1024 x 3072 54.2 us,
+//     through them 55.2; with a quantizer reading y 67.2 / 67.9; 1100 x 3072 x 9216 72.3 / 72.3, 82.6 / 81.9).  fp32 y: y_q from 13 M on
+//     and y from 20 to 44 M (y_q written, this call, y read: 3787 x 2048 x 4032 65.9 us, y past them 69.2; 10 - 20 M 1.02 - 1.06 times as
+//     fast in the mean; beyond 44 M alike).  Below, y_q past them took 2 - 5 % longer where it had stayed there, and 0 - 1 % in a layer.  Without
+//     a y_q nothing goes past them (20 - 44 M, with a reader, fp32 1.00 - 1.08 and bf16 1.00 - 1.05 times as fast).
 // 4-bit layer with the branch (quantizer to y), 32 columns at a time / here with rows upwards / as it is: 8500 x 1536 x 4608 145 / 140 /
 // 134.5 us, 2749 x 2816 x 8448 122 / 123 / 116.5, 8191 x 896 x 2688 81 / 81.5 / 77, 7000 x 3072 x 9216 313 / 290 / 290, 6987 x 1920 x
 // 5418 225 / 211 / 209 (rows of odd length, through the caches: past them 3 - 7 % slower).
 // Not taken: three waves per SIMD at CPL = 4 (the registers spill: 163 us), CPL = 2 throughout (290 -> 302 at 7000 x 3072 x 9216).
-constexpr long long kLrPastFrom = 10000000;                          // outputs
+constexpr long long kLrPastFromBf16 = 10000000, kLrReadPast = 13000000, kLrPastFrom = 20000000, kLrPastTo = 44000000;   // outputs
 enum LrMode { LR_PLAIN, LR_READ_PAST, LR_PAST };                     // each with what the ones before it have
 template <bool YBF16, int R, int CPL, LrMode MODE, bool YQ>
 __global__ __launch_bounds__(256, CPL == 4 ? 2 : 3) void lowrank_up_kernel(const float* __restrict__ tsum, const uint16_t* __restrict__ lu,
@@ -507,21 +512,23 @@ hipError_t launch_lowrank_add(const void* x, bool x_is_bf16, const uint16_t* ld,
   // over more of them: 1500 x 1024 x 3072 39.2 -> 37.5 us, 700 x 1024 x 3072 33.0 -> 31.3, 400 x 3072 x 9216 53.5 -> 51.9.
   const int rows = (M + 127) / 128;
   const bool wide = (long long)rows * ((N + 127) / 128) >= 2ll * cus;
-  // Narrow strips have less than 2 cus x 128 x 128 = 8.4 M outputs, so kLrPastFrom concerns the wide ones only; without a y_q there is
-  // nothing to read past the caches.
-  const bool past = lines && (long long)M * N >= kLrPastFrom;
+  // Narrow strips have less than 2 cus x 128 x 128 = 8.4 M outputs, and without a y_q y goes through the caches: past them is for wide ones.
+  const long long outputs = (long long)M * N;
+  const bool y_past = lines && (y_is_bf16 ? outputs >= kLrPastFromBf16 : outputs >= kLrPastFrom && outputs < kLrPastTo);
+  const bool read_past = lines && outputs >= kLrReadPast;            // fp32 y; with bf16 y kLrPastFromBf16 is for both
 #define SQ_UPM(B, R, C, MODE, YQ) hipLaunchKernelGGL((lowrank_up_kernel<B, R, C, MODE, YQ>), dim3((N + 32 * C - 1) / (32 * C), rows), dim3(256), 0, st, tsum, lu, y_in, y_out, M, N)
 #define SQ_UP(B, R) \
-  if (y_in != nullptr) { \
-    if (wide && past) SQ_UPM(B, R, 4, LR_PAST, true); \
-    else if (wide && lines) SQ_UPM(B, R, 4, LR_READ_PAST, true); \
-    else if (wide) SQ_UPM(B, R, 4, LR_PLAIN, true); \
-    else if (lines) SQ_UPM(B, R, 2, LR_READ_PAST, true); \
-    else SQ_UPM(B, R, 2, LR_PLAIN, true); \
-  } else { \
-    if (wide && past) SQ_UPM(B, R, 4, LR_PAST, false); \
-    else if (wide) SQ_UPM(B, R, 4, LR_PLAIN, false); \
+  if (y_in == nullptr) { \
+    if (wide) SQ_UPM(B, R, 4, LR_PLAIN, false); \
     else SQ_UPM(B, R, 2, LR_PLAIN, false); \
+  } else if (!wide) { \
+    SQ_UPM(B, R, 2, LR_PLAIN, true); \
+  } else if (y_past) { \
+    SQ_UPM(B, R, 4, LR_PAST, true); \
+  } else if (read_past) { \
+    SQ_UPM(B, R, 4, (B ? LR_PLAIN : LR_READ_PAST), true); \
+  } else { \
+    SQ_UPM(B, R, 4, LR_PLAIN, true); \
   }
   if (rank == 64) { if (y_is_bf16) { SQ_UP(true, 64) } else { SQ_UP(false, 64) } }
   else            { if (y_is_bf16) { SQ_UP(true, 32) } else { SQ_UP(false, 32) } }

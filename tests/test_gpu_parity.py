@@ -960,7 +960,8 @@ def test_lowrank_down_plans(oracle, M, K, rank):
 @pytest.mark.parametrize("M,N", [(201, 65002), (203, 64999), (4130, 3200)])
 def test_lowrank_add_large(M, N, rank, yq):
     """Large up projections against the same rows in calls of half the size, bit for bit (K = 256: one K slice in all of them, so the same
-    T): ragged rows, ragged and odd columns, and (4130 x 3200) y stored past the caches on four columns per lane against two, through them."""
+    T): ragged rows, ragged and odd columns, and (4130 x 3200, 13.2 M outputs) past the caches on four columns per lane against two, through
+    them."""
     import torch
 
     g = _gpu()
@@ -994,19 +995,20 @@ def test_lowrank_add_large(M, N, rank, yq):
 @pytest.mark.parametrize("M,N,rank", [(1, 1, 64), (31, 2, 32), (33, 63, 64), (127, 65, 32), (129, 127, 64), (160, 129, 32), (130, 191, 64),
                                       (257, 32801, 32), (8323, 1021, 64), (16290, 514, 32),
                                       (33, 32, 32), (161, 544, 64), (130, 1056, 32), (32705, 160, 64), (21825, 288, 32), (3188, 3136, 64),
-                                      (3189, 3136, 64), (3189, 3136, 32)])
+                                      (3189, 3136, 64), (3189, 3136, 32), (4145, 3136, 64), (4146, 3136, 32), (6378, 3136, 64)])
 def test_lowrank_up_edges(oracle, M, N, rank, yq):
-    """Ends of a wave's rows and of a strip, the last lane's columns in part beyond the matrix.  First ten sizes: rows of y at odd addresses,
-    through the caches, two columns per lane and (the last three) four.  The others: rows of whole lines, y_q past the caches, two columns
-    per lane and (from 32705 rows on) four; y past them as well from 10 M outputs, which 3189 x 3136 has and 3188 x 3136 has not."""
+    """Ends of a wave's rows and of a strip, the last lane's columns in part beyond the matrix, with rows of y at odd addresses (first ten
+    sizes) and of whole lines; two columns per lane and (the last three of the ten, 32705 x 160 and from there on) four; past the caches bf16
+    y from 10 M outputs, y_q of fp32 y from 13 M and fp32 y from 20 M: just under and over them."""
     test_lowrank_add(oracle, dict(M=M, K=64, N=N, rank=rank, x_dtype="bf16", yq=yq))
 
 
 @pytest.mark.parametrize("rank", [64, 32])
 @pytest.mark.parametrize("M,N", [(6300, 3200), (3300, 3400), (6301, 7008), (5601, 3232)])
 def test_lowrank_up_sizes(M, N, rank):
-    """More large sizes, with a ragged row block and last strips of 104, 96 and 32 columns: y past the caches, and through them (3300 x 3400),
-    in both calls; 5601 x 3232 past them, its halves (9.05 M outputs) through them, four columns per lane in all three calls."""
+    """More large sizes, with a ragged row block and last strips of 104, 96 and 32 columns; past the caches whole call / halves, bf16 y and fp32
+    y: 6300 x 3200 (20.2 M outputs) all / all and all / nothing, 3300 x 3400 nothing, 6301 x 7008 (44.2 M) all / all and y_q / all, 5601 x 3232
+    (18.1 M) all / nothing and y_q / nothing."""
     test_lowrank_add_large(M, N, rank, True)
 
 

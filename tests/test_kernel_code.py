@@ -45,7 +45,7 @@ def test_up_projection_requests_all_before_it_waits(kernels):
     barrier waits for y_q (the wait for Lu counts on exactly sixteen younger loads)."""
     built = set()
     for name, code in kernels("lowrank_up_kernel").items():
-        rank, cpl, mode, yq = map(int, re.search(r"Lb[01]ELi(\d+)ELi(\d)ELNS_6LrModeE(\d)ELb([01])E", name).groups())
+        bf16, rank, cpl, mode, yq = map(int, re.search(r"Lb([01])ELi(\d+)ELi(\d)ELNS_6LrModeE(\d)ELb([01])E", name).groups())
         first = max(i for i, (op, _) in enumerate(code) if op == "global_load_lds_dwordx4") + 1
         loads, waits = [], []
         for op, args in code[first:]:
@@ -59,9 +59,9 @@ def test_up_projection_requests_all_before_it_waits(kernels):
         assert [op for op, _ in loads[:rank // 8]] == ["global_load_dwordx4"] * (rank // 8), name
         assert [op for op, _ in loads[rank // 8:]] == ["global_load_dwordx%d" % cpl] * (16 if yq else 0), name
         assert min(waits) == (16 if yq else 0), (name, waits)
-        built.add((cpl, mode, yq))
-    # those that the launch chooses from: y is stored past the caches on four columns per lane only, and there is no y_q to read past them without one
-    assert built == {(4, 2, 1), (4, 1, 1), (4, 0, 1), (2, 1, 1), (2, 0, 1), (4, 2, 0), (4, 0, 0), (2, 0, 0)}
+        built.add((bf16, cpl, mode, yq))
+    # those that the launch chooses from: past the caches on four columns per lane and with a y_q only, bf16 y never y_q alone
+    assert built == {(b, *k) for b in (0, 1) for k in ((4, 2, 1), (4, 0, 1), (2, 0, 1), (4, 0, 0), (2, 0, 0))} | {(0, 4, 1, 1)}
 
 
 def test_raw_sums_are_stored_sixteen_bytes_at_a_time(kernels):
