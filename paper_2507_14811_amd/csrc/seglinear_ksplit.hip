@@ -435,11 +435,13 @@ bool ksplit_supported(const GemmArgs& a, const GemmTable& tb) {
 // short for it.  A second round of tiles repeats the exposed start and exchange (3 - 7 us; the tile kernel fetches across tiles)
 // and made this kernel the slower one on all but one of 16 layers (1296 x 8192 x 2048: 61 against 55 us).  A K-segment costs a
 // start, a drain and an exchange (0.3 - 0.5 us on the tiles with 64 columns, 2 us on 64 x 128), which its stages of 128 columns have
-// to earn back: about 0.2 us each where both polarity paths run, 0.07 where one does (64 x 128: 0.09 and 0.02).  2145 layers of
-// 1 - 8 equal segments of 128 - 12288 columns, 33 - 20000 rows, every mix of paths: of the 1039 that the lines below take none was
-// slower than on the tile kernel by more than 1.5 %, the median took 0.81 of its time; of all with one round of tiles, those of
-// many short segments took up to 1.8 times as long (1024 x 1024 x 1920, eight segments: 21.1 us on the tile kernel, 36.8 here).
-// One segment on 64 x 128 tiles, ten shapes: 2048 columns of one path took 0.95 - 0.81 of the tile kernel's time, 1536 of them
+// to earn back: about 0.2 us each where both polarity paths run, 0.07 where one does (64 x 128: 0.09 and 0.02).  The lines were
+// drawn with the tile kernel as it was when none of 1039 layers taken lost more than 1.5 %.  Against the present one, 777 layers taken (1 - 8
+// segments of 128 - 12288 columns, 33 - 20000 rows, every mix of paths): one segment on 64 x 64 tiles 0.71 of its time in the median and
+// never more than 0.94; several there 0.92, 63 of 526 more than 1.02, 1.14 at the most; on 64 x 128 tiles one 0.99, several (18 layers) 1.05 - 1.25
+// (2193 x 640, four of 5248 columns, two of them with both paths: 67.3 us there, 83.8 here).  Many short segments, which are not taken, took up
+// to 2.3 times as long (522 x 2112, eight of 128: 15.5 us there, 35.4 here).
+// One segment on 64 x 128 tiles, ten shapes, when the lines were drawn: 2048 columns of one path took 0.95 - 0.81 of the tile kernel's time, 1536 of them
 // 1.03 - 0.87; 2304 of two paths 0.97 - 0.81, 2048 of them 1.03 - 0.89, 1536 of them up to 1.25.
 int ksplit_pick(const GemmArgs& a, const GemmTable& tb) {
   if (!ksplit_supported(a, tb)) return -1;

@@ -29,8 +29,8 @@
 //     (only instantiated when the layer has more than one K-segment) and cleared.  A non-dual segment
 //     issues only the MFMAs of one set.
 //   * The epilogue needs no transpose: each lane scales its runs with per-column constants fetched
-//     16 bytes at a time and stores them directly as 16-byte (fp32) or 8-byte (bf16, hardware
-//     round-to-nearest-even pack) pieces; the pieces of one row written by a wave are contiguous.
+//     16 bytes at a time and stores them as 16-byte pieces (bf16: packed by the hardware, round to nearest even, the
+//     halves of the wave exchange every second run); the pieces of one row written by a wave are contiguous.
 //   * Workgroup ids are remapped so that each XCD (ids are dealt round-robin to the 8 XCDs) works on a
 //     contiguous run of tiles, ordered in panels of group_m row-tiles so concurrently resident
 //     workgroups of an XCD share X^ and W^ tiles in that XCD's L2.
@@ -502,8 +502,8 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
       const int stop = (b + left) < b_more_end ? (b + left) : b_more_end;
       // Here the stages up to b + NSTAGE - 1 have been requested, and stage b + NSTAGE goes into the buffer of stage b: the wait is a
       // constant and the buffers' offsets follow each other.  Counted and compared at run time, with a division by NSTAGE per buffer,
-      // a stage had some 25 scalar instructions and branches more: 4608 x (3072 + 12288) x 3072 343 -> 335.5 us with its quantizer, 2048 x
-      // 4608 x 1152 34.2 -> 33.3, 2048 x (2304 + 2304) x 1152 36.2 -> 34.5.
+      // a stage had some 25 scalar instructions and branches more: 4608 x (3072 + 12288) x 3072 355 -> 345 us with its quantizer, 2048 x
+      // 4608 x 1152 35.0 -> 34.1, 4096 x (4608 + 4608) x 3072 209 -> 205.
       int at = stage_off(b);
 #pragma unroll 1
       for (; b < stop; ++b) {
@@ -565,8 +565,8 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
                        reinterpret_cast<uintptr_t>(a.acc_neg)) % 16 == 0);
   // FULL: the tile lies inside the matrix and every row piece is 16-byte aligned.  Else the pieces of column_of() are fetched and stored
   // at whatever address they have (one uniform branch picks the instantiation).  Either way the flush code runs without masks:
-  // masked, and value by value where N is no multiple of four, ragged tiles took 2500 x 8192 x 2011 99 us instead of 87, 3000 x
-  // (1024 + 4096) x 1093 57 instead of 47.5, 4096 x 5120 x 1280 (with its quantizer) 71 instead of 68.
+  // masked, and value by value where N is no multiple of four, ragged tiles took (with the quantizer) 2500 x 8192 x 2011 98 us instead of 85,
+  // 3000 x (1024 + 4096) x 1093 56 instead of 47, 4096 x 5120 x 1280 70.6 instead of 67.1.
   auto set_compute_tile = [&](const int it) __attribute__((always_inline)) {
     int m0, n0;
     tile_origin(it, m0, n0);
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) void seglinear_mfma_kernel(cons
   };
 
   // ---- last K-segment: dequantize, add bias, store ----------------------------------------------------
-  // bf16 output of an interior tile: the two halves of the wave (lanes l and l + 32 hold the same row, column
+  // bf16 output, N >= 8: the two halves of the wave (lanes l and l + 32 hold the same row, column
   // runs 4 apart) exchange every second run with v_permlane32_swap, so that each lane ends up with eight
   // consecutive columns and stores 16 bytes.
   auto flush_last_impl = [&](auto full_tag, auto bf16_tag, auto narrow_tag, const int ks, const bool dl) __attribute__((always_inline)) {

@@ -355,7 +355,7 @@ __global__ __launch_bounds__(512, 2) void seglinear_pair_kernel(const GemmArgs a
       stage_slot();
     }
     // stores, next to the other group's K loop (if it has another tile): first the next tile's first two stages, which this
-    // group has fetched, then block by block
+    // group has fetched, then run by run
     __builtin_amdgcn_s_setprio(0);
     const bool beside = t + 1 < ntile;
     if (beside) {
@@ -400,14 +400,15 @@ bool pair_supported(const GemmArgs& a, const GemmTable& tb, OutMode mode, int ti
 
 // The tile (0: 128 x 256, 1: 128 x 192, 2: 128 x 128), or -1 where the tile kernel serves.  Among the tiles the one with the
 // shortest time rounds * (stages + start of a tile), both in units of a 128 x 256 stage: fitted to 300 layers (256 - 9000 rows, K 512 -
-// 16384, 0.8 % off the best tile in the mean).  int8: from three quarters of the compute units' worth of 128 x 256 tiles; below
-// that a compute unit has no second tile to overlap with and the smaller tiles of the other kernels win or lose by up to 1.3.
-// 420 such layers (65 - 9000 rows, bf16 and fp32 output, static and per-token steps, N whole and odd): 1.21 times as fast as the tile
-// kernel in the mean, the slowest 0.997.  E4M3: the tile kernel has 256 x 256 tiles, with half the operand bytes per product; where
+// 16384), 0.7 % off the best tile in the mean of 204 others and 14 % at the most (856 x 768 x 9088).  int8: from three quarters of the
+// compute units' worth of 128 x 256 tiles; below that a compute unit has no second tile to overlap with and the smaller tiles of the other
+// kernels win or lose by up to 1.2.  Those 204 layers (65 - 9000 rows, bf16 and fp32 output, static and per-token steps): 1.14 times as fast as
+// the tile kernel in the mean with whole N, 1.23 with odd N, two slower by more than 2 % (856 x 768 x 9088 15.4 us, 14.3 there; 6018 x 1024 x
+// 896 13.3, 12.8).  E4M3: the tile kernel has 256 x 256 tiles, with half the operand bytes per product; where
 // they fill the rounds and K is long they are as quick (2818 x 4096 x 16384 183 us there, 190 here; 4608 x 3072 x 12288 167 and 149),
 // so the fill of the rounds, weighted by the length of the K loop, is compared with the tile kernel's score (mfma_fp8_pick_score, 1 =
-// full rounds of 256 x 256).  1600 layers (65 - 9000 rows, K 512 - 16384, N 384 - 16384): the 1393 taken are 1.21 times as fast in the
-// mean, four of them slower by more than 2 % (6016 x 1408 x 15872 0.93, 8878 x 768 x 704 16.0 us there, 17.0 here).
+// full rounds of 256 x 256).  900 layers (65 - 9000 rows, K 512 - 16384, N 384 - 16384): the 148 taken are 1.17 times as fast in the mean, the
+// slowest 0.98; of those not taken 121 would be faster by more than 2 %, small ones (765 x 512 x 3267 7.1 us, 9.2 there).
 int pair_pick(const GemmArgs& a, const GemmTable& tb, OutMode mode, bool fp8) {
   if (a.M <= 64 || !pair_supported(a, tb, mode, 1, fp8)) return -1;
   static const float kStage[3] = {1.0f, 0.84f, 0.61f}, kStart[3] = {2.1f, 1.2f, 1.06f};

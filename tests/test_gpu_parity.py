@@ -1877,8 +1877,8 @@ def test_seglinear_direct_forced_elsewhere_is_refused():
 
 
 # Tiles taken in turn by two groups of waves, every tile width forced: one stored by its group alone, one beside each group's next
-# (2 and 3 tiles per compute unit), K loops of 4, 5, 9 and 12 stages (three, two and one blocks stored per stage), ragged and odd edges
-# (16-, 8- and 2-byte row pieces of bf16).
+# (2 and 3 tiles per compute unit), K loops of 4, 5, 9 and 12 stages (three, two and one runs of rows stored per stage), ragged and odd edges
+# (row pieces of eight, six and four bf16 columns, cut ones value by value).
 PAIR_CASES = [(1, 512, 1), (130, 640, 201), (257, 1536, 520), (1500, 1152, 3100), (2200, 512, 4104), (2177, 640, 4236)]
 
 

@@ -104,3 +104,14 @@ def test_refilling_k_loop_waits_for_its_ring_only(kernels):
                 loops += 1
                 assert not [a for op, a in body if op == "s_waitcnt" and re.search(r"vmcnt\((?!63)", a)], name
     assert loops >= 5 * 4
+
+
+def test_three_column_pieces_are_stored_as_three(kernels):
+    """Tiles of 192 columns taken in turn: a lane's three columns (bf16: six of two rows' three) go out as twelve bytes; as the compiler's sixteen
+    they would run into the next lane's."""
+    seen = 0
+    for name, code in kernels("seglinear_pair_kernelILi192E").items():
+        stores = [op for op, _ in code if op.startswith("global_store_dword")]
+        assert "global_store_dwordx3" in stores and "global_store_dwordx4" not in stores, name
+        seen += 1
+    assert seen == 6
